@@ -243,7 +243,7 @@ void vf_destroy(vf_ctx *c) {
   (void)hipStreamSynchronize(c->stream);
   free_pipeline(c);
   vfk_free_model(c);
-  void *ps[] = {c->d_space, c->d_err,  c->d_stat, c->d_wlist, c->d_team, c->d_feat,   c->d_act[0], c->d_act[1],
+  void *ps[] = {c->d_space, c->d_err,  c->d_stat, c->d_wlist, c->d_team, c->d_pub, c->d_feat,   c->d_act[0], c->d_act[1],
                 c->d_pval,  c->d_pidx, c->d_scores, c->d_tk_val, c->d_tk_idx};
   for (void *p : ps)
     if (p) (void)hipFree(p);
@@ -542,6 +542,11 @@ int vf_beam_search(vf_ctx *c, int first, int last, vf_state *out_states, int32_t
   if (rc != VF_OK) return rc;
   rc = vfk_beam_init(c, first);
   if (rc != VF_OK) return rc;
+  if (first <= last && vfk_beam_lists(c)) {
+    rc = vfk_beam_layers(c, first, last);
+    if (rc != VF_OK) return rc;
+    first = last + 1;
+  }
   for (int i = first; i <= last; ++i) {
     rc = vfk_step_scores(c, i);
     if (rc != VF_OK) return rc;

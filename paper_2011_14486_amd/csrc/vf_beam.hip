@@ -1,0 +1,293 @@
+// Beam search on lists of valid candidates (gfx950), for the bf16 MLPs that the list scorer takes.
+//
+// Secs. 3.1 and 4.1 search with a beam guided by V.  A layer is three launches: the scores of all
+// slots' candidates (the LAYER form of k_whole: compact scores by list position and the first
+// minimum of every 64 entries), the choice of the B smallest of them (k_beam_select), and per
+// survivor its commit and the opening of its next decision (k_beam_advance).
+#include <utility>
+
+#include "vf_internal.h"
+
+namespace {
+
+#include "vf_sched_dev.h"
+
+#include "vf_score_dev.h"
+
+#include "vf_layer_dev.h"
+
+constexpr unsigned long long NO_KEY = ~0ull;
+constexpr int SEL_THREADS = 1024;
+constexpr int SEL_CAP = 2048;  // keys that the final sort takes
+
+// The smallest keys of key(0) .. key(n - 1) (NO_KEY = none, all others different), sorted, in
+// sorted[0..return value): the `want` smallest ones and possibly more, at most SEL_CAP.  A threshold
+// is bisected over the 64-bit keys until at least `want` and at most 4 * want keys lie below it
+// (the keys are all different, so there is such a threshold), and only those are sorted.
+// R: keys a thread keeps in registers (n <= 1024 R), 0 = they are evaluated again in every pass.
+// key(i) is called for i >= n too and must then only be safe to evaluate.
+template <int R, typename KEY>
+__device__ int block_select(KEY key, uint32_t n, int want, unsigned long long *sorted) {
+  __shared__ unsigned int cnt[3][3];
+  __shared__ unsigned long long range[2];
+  const int tid = threadIdx.x, lane = tid & 63;
+  unsigned long long reg[R > 0 ? R : 1];
+  __syncthreads();  // (the shared words may still be in use by a call before)
+  if (tid < 9) cnt[tid / 3][tid % 3] = 0u;
+  if (tid == 0) { range[0] = NO_KEY; range[1] = 0ull; }
+  // (no branch around a load: all of them are under way at once)
+  if (R > 0) {
+#pragma unroll
+    for (int e = 0; e < R; ++e) reg[e] = key((uint32_t)e * SEL_THREADS + tid);
+#pragma unroll
+    for (int e = 0; e < R; ++e)
+      if ((uint32_t)e * SEL_THREADS + tid >= n) reg[e] = NO_KEY;
+  }
+  auto each = [&](auto f) __attribute__((always_inline)) {
+    if (R > 0) {
+#pragma unroll
+      for (int e = 0; e < R; ++e) f(reg[e]);
+    } else {
+      for (uint32_t i0 = 0; i0 < n; i0 += SEL_THREADS) {
+        const unsigned long long k = key(i0 + tid);
+        f(i0 + tid < n ? k : NO_KEY);
+      }
+    }
+  };
+  // (counts by ballots: one scalar sum per wave, in every lane)
+  auto count_upto = [&](unsigned long long mid) __attribute__((always_inline)) {
+    unsigned int c = 0u;
+    each([&](unsigned long long k) { c += (unsigned int)__popcll(__ballot(k <= mid)); });
+    return c;
+  };
+  unsigned long long mn = NO_KEY, mx = 0ull;
+  each([&](unsigned long long k) {
+    mn = k < mn ? k : mn;
+    if (k != NO_KEY) mx = k > mx ? k : mx;
+  });
+  const unsigned int have = count_upto(NO_KEY - 1ull);
+  for (int off = 32; off > 0; off >>= 1) {
+    const unsigned long long a = __shfl_down(mn, off), b = __shfl_down(mx, off);
+    mn = a < mn ? a : mn;
+    mx = b > mx ? b : mx;
+  }
+  __syncthreads();
+  if (lane == 0 && have) {
+    atomicMin(&range[0], mn);
+    atomicMax(&range[1], mx);
+    atomicAdd(&cnt[0][0], have);
+  }
+  __syncthreads();
+  unsigned int below = cnt[0][0];  // keys <= hi
+  const unsigned int most = 4 * want < 256 ? 256u : 4 * want > SEL_CAP ? (unsigned int)SEL_CAP : 4u * want;
+  unsigned long long lo = range[0], hi = range[1];
+  // (three thresholds a round: what a round costs is the meeting of the sixteen waves)
+  for (int r = 1; below > most; ++r) {  // (the same in every thread)
+    const unsigned long long step = (hi - lo) / 4 + 1ull;  // lo + 3 step may pass hi: it then counts all
+    unsigned int c[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) c[q] = count_upto(lo + (unsigned long long)q * step);
+    unsigned int *const slot = cnt[r % 3];
+    if (lane == 0) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        if (c[q]) atomicAdd(&slot[q], c[q]);
+    }
+    if (tid < 3) cnt[(r + 1) % 3][tid] = 0u;
+    __syncthreads();
+    bool found = false;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const unsigned int got = slot[q];
+      if (!found && got >= (unsigned int)want) {
+        found = true;
+        below = got;
+        hi = lo + (unsigned long long)q * step;
+        if (q > 0) lo = lo + (unsigned long long)(q - 1) * step + 1ull;
+      }
+    }
+    if (!found) lo = lo + 2ull * step + 1ull;
+  }
+  __syncthreads();
+  if (tid == 0) cnt[0][0] = 0u;
+  int size = 128;
+  while (size < (int)below) size <<= 1;
+  for (int i = tid; i < size; i += SEL_THREADS) sorted[i] = NO_KEY;
+  __syncthreads();
+  if (below)
+    each([&](unsigned long long k) {
+      if (k <= hi && k != NO_KEY) sorted[atomicAdd(&cnt[0][0], 1u)] = k;
+    });
+  __syncthreads();
+  // bitonic sort; a wave's 64 pairs of a step of stride 64 or less lie in the same 128 keys, so
+  // that only the wider steps need the whole workgroup
+  for (int len = 2; len <= size; len <<= 1)
+    for (int stride = len >> 1; stride > 0; stride >>= 1) {
+      if (stride >= 64 && len > 128) __syncthreads();
+      if (tid < size / 2) {
+        const int a = 2 * tid - (tid & (stride - 1)), b = a + stride;
+        const unsigned long long x = sorted[a], y = sorted[b];
+        if ((x > y) == ((a & len) == 0)) { sorted[a] = y; sorted[b] = x; }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+  __syncthreads();
+  return (int)below;
+}
+
+// The survivors of a layer: the `want` smallest of all scores, ordered by (score, slot, candidate
+// id); +inf and NaN never survive.  The lists are in ascending id order, so list positions order
+// as the ids do.  No part of 64 entries outside the `want` parts with the smallest minima can hold
+// a survivor, so first those parts are chosen by their minima, then the survivors among their
+// entries: one workgroup reads the parts' minima and at most 64 * want scores instead of sorting
+// all of them (64 slots of the 100-layer network, 16384 ids each: 83 us in three launches before).
+__global__ __launch_bounds__(SEL_THREADS) void k_beam_select(const float *scores, const float *pval, const int32_t *pidx,
+                                                             const uint32_t *n_minima, int nparts, const uint32_t *list, const uint32_t *pub,
+                                                             const int32_t *space, int64_t Mpad, int want, float *sel_val,
+                                                             int32_t *sel_idx, int32_t *sel_n) {
+  __shared__ unsigned long long sorted[SEL_CAP];
+  __shared__ uint32_t parts[1024];
+  __shared__ vf_space sp;
+  const int tid = threadIdx.x;
+  for (int i = tid; i < (int)(sizeof(vf_space) / 4); i += SEL_THREADS) reinterpret_cast<int32_t *>(&sp)[i] = space[i];
+  const uint32_t nmin = n_minima[0];
+  auto part_key = [&](uint32_t i) {
+    const uint32_t at = i < nmin ? i : 0u;
+    const float v = pval[at];  // (+inf where a part has no minimum)
+    const int32_t part = pidx[at];
+    return v < __builtin_inff() ? topk_key(v, part) : NO_KEY;
+  };
+  int np = nmin <= SEL_THREADS      ? block_select<1>(part_key, nmin, want, sorted)
+           : nmin <= 4 * SEL_THREADS  ? block_select<4>(part_key, nmin, want, sorted)
+           : nmin <= 16 * SEL_THREADS ? block_select<16>(part_key, nmin, want, sorted)
+                                      : block_select<0>(part_key, nmin, want, sorted);
+  if (np > want) np = want;
+  if (tid < np) parts[tid] = (uint32_t)sorted[tid];
+  if (tid == 0 && np == 0) parts[0] = 0u;
+  __syncthreads();
+  const uint32_t nent = (uint32_t)np * 64u;
+  auto entry_key = [&](uint32_t i) {
+    const uint32_t part = parts[i < nent ? i >> 6 : 0u], slot = part / (uint32_t)nparts;
+    const uint32_t entry = (part - slot * (uint32_t)nparts) * 64u + (i & 63u);
+    const uint32_t at = slot * (uint32_t)Mpad + (entry < (uint32_t)Mpad ? entry : 0u);
+    const uint32_t count = pub[(size_t)slot * VF_PUB_WORDS + VF_PUB_COUNT];
+    const float s = scores[at];
+    return entry < count && s < __builtin_inff() ? topk_key(s, (int32_t)at) : NO_KEY;
+  };
+  int found = nent <= SEL_THREADS      ? block_select<1>(entry_key, nent, want, sorted)
+              : nent <= 4 * SEL_THREADS  ? block_select<4>(entry_key, nent, want, sorted)
+              : nent <= 16 * SEL_THREADS ? block_select<16>(entry_key, nent, want, sorted)
+                                         : block_select<0>(entry_key, nent, want, sorted);
+  if (found > want) found = want;
+  for (int r = tid; r < want; r += SEL_THREADS) {
+    const bool is = r < found;
+    const uint32_t at = is ? (uint32_t)sorted[r] : 0u, slot = at / (uint32_t)Mpad;
+    sel_val[r] = is ? topk_value(sorted[r]) : __builtin_inff();
+    sel_idx[r] = is ? (int32_t)(slot * (uint32_t)Mpad + id_of(sp, unpack_digits(list[at]))) : -1;
+  }
+  if (tid == 0) {
+    sel_n[0] = found;
+    if (found > 0) sel_n[1] = found;
+  }
+}
+
+// Survivor j of a layer: its parent's schedule is copied into slot j of the other table set, its
+// candidate becomes the decision of the layer, and (open) the next decision is opened for the
+// scorer.  The next context comes from the parent's rows in the old tables and the winner's rows in
+// LDS, so nothing waits for the copies.  A slot without a survivor is cleared; if the layer has none
+// at all the schedules end: every slot is carried over unchanged and marked dead.
+template <int RT>
+__global__ __launch_bounds__(512) void k_beam_advance(Tables t, AltTables nw, int stage, int open, uint32_t M, int64_t Mpad,
+                                                      const float *sel_val, const int32_t *sel_idx, const int32_t *sel_n,
+                                                      const uint32_t *decpack_cur, uint32_t *decpack_next, vf_fast_dev md,
+                                                      uint32_t *pub, uint32_t *list) {
+  __shared__ AdvanceShared sh;
+  const int tid = threadIdx.x, lane = tid & 63, j = blockIdx.x, S = t.S;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nsel = sel_n[0];
+  const size_t dst = (size_t)j * S;
+  int src_slot = -1;
+  int32_t cid = -1;
+  if (nsel == 0) src_slot = j;
+  else if (j < nsel) { src_slot = sel_idx[j] / (int32_t)Mpad; cid = sel_idx[j] % (int32_t)Mpad; }
+  if (cid >= 0 && tid < VF_DECPACK_DWORDS)
+    reinterpret_cast<uint32_t *>(&sh.pk)[tid] = decpack_cur[(size_t)src_slot * VF_DECPACK_DWORDS + tid];
+  {
+    const int rows = nsel == 0 ? S : stage;  // committed rows to carry over
+    const size_t src = (size_t)(src_slot < 0 ? 0 : src_slot) * S;
+    const int32_t *const cf = t.cf + src * 64, *const states = t.states + src * 16, *const cids = t.cids + src;
+    const int32_t *const prefix = t.prefix + (size_t)(src_slot < 0 ? 0 : src_slot) * (S + 1) * 2;
+    const float *const vals = t.vals + src;
+    int32_t *const ncf = nw.cf + dst * 64, *const nst = nw.states + dst * 16, *const nci = nw.cids + dst;
+    int32_t *const npre = nw.prefix + (size_t)j * (S + 1) * 2;
+    float *const nva = nw.vals + dst;
+    if (src_slot >= 0) {
+#pragma unroll 4
+      for (int i = tid; i < rows * 16; i += 512) reinterpret_cast<int4 *>(ncf)[i] = reinterpret_cast<const int4 *>(cf)[i];
+      for (int i = tid; i < rows * 4; i += 512) reinterpret_cast<int4 *>(nst)[i] = reinterpret_cast<const int4 *>(states)[i];
+      for (int i = tid; i < rows; i += 512) { nci[i] = cids[i]; nva[i] = vals[i]; }
+      // (the entries behind the layer's own are the commit's)
+      for (int i = tid; i < (S + 1) * 2; i += 512)
+        if (nsel == 0 || i < (stage + 1) * 2) npre[i] = prefix[i];
+        else if (i >= (stage + 2) * 2) npre[i] = 0;
+    } else {
+      for (int i = tid; i < (stage + 1) * 64; i += 512) ncf[i] = 0;
+      for (int i = tid; i < (stage + 1) * 16; i += 512) nst[i] = 0;
+      for (int i = tid; i <= stage; i += 512) { nci[i] = -1; nva[i] = __builtin_inff(); }
+      for (int i = tid; i < (S + 1) * 2; i += 512) npre[i] = 0;
+    }
+  }
+  if (cid >= 0) {
+    if (tid == 0) { sh.cid = cid; sh.val = sel_val[j]; }
+    Tables tn = t;
+    tn.states = nw.states; tn.cf = nw.cf; tn.prefix = nw.prefix; tn.cids = nw.cids; tn.alive = nw.alive; tn.vals = nw.vals;
+    advance_layer<RT>(sh, t, tn, src_slot, j, stage, open, M, md, pub + (size_t)j * VF_PUB_WORDS, list + (size_t)j * Mpad,
+                      decpack_next + (size_t)j * VF_DECPACK_DWORDS, tid, w, lane);
+    if (tid == 0) {
+      nw.alive[j] = sh.sums[2] ? 1 : 0;
+      if (!sh.sums[2]) t.err[0] = 1;  // cannot happen: only valid candidates have finite scores
+    }
+  } else if (tid == 0) {
+    nw.alive[j] = 0;
+    if (open) pub[(size_t)j * VF_PUB_WORDS + VF_PUB_COUNT] = 0u;
+  }
+}
+
+}  // namespace
+
+// With more than 64 tiles of 128 ids in a layer.  Below that the launches on id ranges are as fast
+// (256-512-512-1, whole search: 20 layers of 4096 ids, 2 slots 0.79 against 0.82 ms here, 4 slots 0.93
+// against 0.87, 64 slots 4.2 against 1.57; 100 layers of 16384 ids, 1 slot 4.2 either way, 8 slots 11.2
+// against 5.3, 64 slots 48.6 against 11.0).
+bool vfk_beam_lists(const vf_ctx *c) { return (c->M + 127) / 128 * c->B > 64 && vfk_layer_fits(c); }
+
+int vfk_beam_layers(vf_ctx *c, int first, int last) {
+  int rc = vfk_scores_buffer(c);
+  if (rc == VF_OK) rc = vfk_layer_open(c, first);
+  if (rc != VF_OK) return rc;
+  vf_fast_dev fd;
+  vfk_fast_dev(c, true, &fd, nullptr, nullptr);
+  uint32_t *cur = c->d_decpack, *next = c->d_decpack2;
+  for (int i = first; i <= last; ++i) {
+    int nparts = 0;
+    rc = vfk_layer_score(c, -1, c->d_scores, &nparts);
+    if (rc != VF_OK) return rc;
+    const uint32_t *list = reinterpret_cast<const uint32_t *>(c->d_wlist);
+    hipLaunchKernelGGL(k_beam_select, dim3(1), dim3(SEL_THREADS), 0, c->stream, c->d_scores, c->d_pval, c->d_pidx,
+                       (const uint32_t *)(c->d_pub + (size_t)c->B * VF_PUB_WORDS), nparts, list, c->d_pub, c->d_space, (int64_t)c->Mpad, c->B, c->d_sel_val, c->d_sel_idx, c->d_sel_n);
+    VF_HIP(c, hipGetLastError());
+    {
+      vf_prof_scope prof(c, VF_PROF_COMMIT);
+      hipLaunchKernelGGL((c->pm.fast_rt == 4 ? k_beam_advance<4> : k_beam_advance<2>), dim3((unsigned)c->B), dim3(512), 0,
+                         c->stream, tables_of(c), alt_of(c), i, (int)(i < last), (uint32_t)c->M, (int64_t)c->Mpad,
+                         c->d_sel_val, c->d_sel_idx, c->d_sel_n, cur, next, fd, c->d_pub,
+                         reinterpret_cast<uint32_t *>(c->d_wlist));
+      VF_HIP(c, hipGetLastError());
+    }
+    c->dec_stage = -1;  // (the context of the next layer is in either buffer, or not built)
+    std::swap(cur, next);
+    vfk_beam_swap(c);
+    c->n_sched = i + 1;
+  }
+  return VF_OK;
+}

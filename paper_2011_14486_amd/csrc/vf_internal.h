@@ -15,6 +15,8 @@
 #define VF_STATIC_PARTS 65536
 // size of one packed decision context (see vf_sched_dev.h)
 #define VF_DECPACK_DWORDS 428
+// size of one opened decision as it is left in memory for other workgroups (see vf_layer_dev.h)
+#define VF_PUB_WORDS 1649
 
 // Where the scorers put their per-workgroup (value, id) minima when the context's own
 // growable buffers must not be used (nullable everywhere it is taken): `cap` pairs.
@@ -129,7 +131,10 @@ struct vf_ctx {
   mutable size_t occ_smem = 0;
   mutable int occ_blocks = 0;
   unsigned int wait_rounds = 1u << 22;  // bound of the waits between workgroups that share a problem
-  int32_t *d_wlist = nullptr; size_t wlist_elems = 0;  // [B][Mpad] id lists of the whole-schedule launch
+  int32_t *d_wlist = nullptr; size_t wlist_elems = 0;  // [B][Mpad] lists of valid candidates (packed digits)
+  uint32_t *d_pub = nullptr; size_t pub_elems = 0;     // [B][VF_PUB_WORDS] opened decisions of a single layer, number of minima
+  mutable const void *layer_kern = nullptr;            // the scorer that vfk_layer_fits found to fit, and its LDS
+  mutable size_t layer_smem = 0;
 
   vf_partbuf static_parts = {nullptr, nullptr, 0};  // this device's static scratch array (vf_score_static)
 
@@ -232,6 +237,14 @@ int vfk_seq_advance(vf_ctx *c, int stage);
 int vfk_seq_advance_beam(vf_ctx *c, int stage);
 int vfk_seq_step(vf_ctx *c, int stage, float *scores, int64_t ld_scores, int noise_stage, int *nparts_out);
 int vfk_greedy_whole(vf_ctx *c, int first, int last);
+// One decision of every problem on lists of valid candidates (vf_whole.hip): open the decisions of
+// `stage` (contexts, lists, biases), then score them.  vfk_layer_score leaves the first minimum of
+// every 64 list entries in d_pval / d_pidx [B][nparts].  If asked for the scores (by list position,
+// [B][Mpad]) it leaves the minima without gaps instead, with the part they belong to and their
+// number behind the opened decisions (WholeArgs::pval).  noise_stage as elsewhere.
+bool vfk_layer_fits(const vf_ctx *c);
+int vfk_layer_open(vf_ctx *c, int stage);
+int vfk_layer_score(vf_ctx *c, int noise_stage, float *scores, int *nparts_out);
 int vfk_step_fused(vf_ctx *c, int stage, int *nparts_out);
 // Algorithm 1 over stages first..last with one launch per layer (the fused scorer also decides
 // the stage before it) and one commit at the end; VF_ESTATE if the model or space does not
@@ -243,9 +256,16 @@ int vfk_commit_from(vf_ctx *c, int stage, int nparts, const float *pval, const i
 // Scores of every candidate of `stage` for all problems into d_scores [B][Mpad]; invalid
 // candidates and padding columns get +inf.
 int vfk_step_scores(vf_ctx *c, int stage);
+// makes d_scores hold [B][Mpad]
+int vfk_scores_buffer(vf_ctx *c);
 // beam search pieces (vf_sched.hip)
 int vfk_beam_init(vf_ctx *c, int first_stage);
 int vfk_beam_select_commit(vf_ctx *c, int stage);
+// the two sets of state tables change places
+void vfk_beam_swap(vf_ctx *c);
+// whether a beam search works on lists of valid candidates, and all its layers (vf_beam.hip)
+bool vfk_beam_lists(const vf_ctx *c);
+int vfk_beam_layers(vf_ctx *c, int first, int last);
 int vfk_score_lstm(vf_ctx *c, const uint16_t *x, int64_t M, int T, float *scores, int *nparts_out,
                    const vf_partbuf *parts = nullptr);
 int vfk_argmin_groups(vf_ctx *c, int64_t M, int nparts, int parts_per_group, int ngroups,

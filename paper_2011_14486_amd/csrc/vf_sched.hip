@@ -220,11 +220,6 @@ __global__ __launch_bounds__(256) void k_commit(Tables t, int stage, int nparts,
 // B*M scores survive, ordered by (score, parent slot, candidate id); survivor j copies
 // its parent's schedule into slot j of the other table set and commits its candidate.
 
-struct AltTables {
-  int32_t *states, *cf, *prefix, *cids, *alive;
-  float *vals;
-};
-
 __device__ __forceinline__ void take_min_u(float &v, int32_t &c, float ov, int32_t oc) {
   if (oc >= 0 && (ov < v || (ov == v && (c < 0 || oc < c)))) { v = ov; c = oc; }
 }
@@ -294,19 +289,6 @@ __global__ __launch_bounds__(256) void k_topk_pass_few(const float *val_in, cons
     sel_n[0] = found;
     if (found > 0) sel_n[1] = found;
   }
-}
-
-// (value, index) as one sortable key: floats map to unsigned integers in their own order
-// (-0 counts as +0, as in a comparison), the index breaks ties.  ~0 = no entry.
-__device__ __forceinline__ unsigned long long topk_key(float v, int32_t idx) {
-  uint32_t u = __float_as_uint(v == 0.0f ? 0.0f : v);
-  u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-  return ((unsigned long long)u << 32) | (uint32_t)idx;
-}
-__device__ __forceinline__ float topk_value(unsigned long long key) {
-  uint32_t u = (uint32_t)(key >> 32);
-  u = (u & 0x80000000u) ? (u & 0x7fffffffu) : ~u;
-  return __uint_as_float(u);
 }
 
 // One selection pass: every block reduces 2048 (value, index) pairs to its k smallest,
@@ -546,13 +528,6 @@ static int beam_alloc(vf_ctx *c) {
   return VF_OK;
 }
 
-static AltTables alt_of(const vf_ctx *c) {
-  AltTables a;
-  a.states = c->d_alt_states; a.cf = c->d_alt_cf; a.prefix = c->d_alt_prefix; a.cids = c->d_alt_cids;
-  a.alive = c->d_alt_alive; a.vals = c->d_alt_vals;
-  return a;
-}
-
 int vfk_beam_init(vf_ctx *c, int first_stage) {
   (void)first_stage;
   int rc = beam_alloc(c);
@@ -564,6 +539,15 @@ int vfk_beam_init(vf_ctx *c, int first_stage) {
   VF_HIP(c, hipGetLastError());
   c->dec_stage = -1;
   return VF_OK;
+}
+
+void vfk_beam_swap(vf_ctx *c) {
+  std::swap(c->d_states, c->d_alt_states);
+  std::swap(c->d_cf, c->d_alt_cf);
+  std::swap(c->d_prefix, c->d_alt_prefix);
+  std::swap(c->d_cids, c->d_alt_cids);
+  std::swap(c->d_vals, c->d_alt_vals);
+  std::swap(c->d_alive, c->d_alt_alive);
 }
 
 // scores of the layer are in d_scores: select the survivors, commit them into the other
@@ -606,12 +590,7 @@ int vfk_beam_select_commit(vf_ctx *c, int stage) {
                        (uint32_t)c->M, (uint32_t)c->Mpad, c->d_sel_val, c->d_sel_idx, c->d_sel_n, c->d_decpack);
     VF_HIP(c, hipGetLastError());
   }
-  std::swap(c->d_states, c->d_alt_states);
-  std::swap(c->d_cf, c->d_alt_cf);
-  std::swap(c->d_prefix, c->d_alt_prefix);
-  std::swap(c->d_cids, c->d_alt_cids);
-  std::swap(c->d_vals, c->d_alt_vals);
-  std::swap(c->d_alive, c->d_alt_alive);
+  vfk_beam_swap(c);
   c->dec_stage = stage + 1 < c->S ? stage + 1 : -1;
   return VF_OK;
 }

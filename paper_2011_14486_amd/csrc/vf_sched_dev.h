@@ -698,6 +698,27 @@ __device__ __forceinline__ uint32_t stat_word(const Dec &d, int q) {
     out[(size_t)b * VF_DECPACK_DWORDS + i] = i < used ? src[i] : 0u;
 }
 
+// ---- beam search
+
+// (value, index) as one sortable key: floats map to unsigned integers in their own order
+// (-0 counts as +0, as in a comparison), the index breaks ties.  ~0 = no entry.
+[[maybe_unused]] __device__ __forceinline__ unsigned long long topk_key(float v, int32_t idx) {
+  uint32_t u = __float_as_uint(v == 0.0f ? 0.0f : v);
+  u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return ((unsigned long long)u << 32) | (uint32_t)idx;
+}
+[[maybe_unused]] __device__ __forceinline__ float topk_value(unsigned long long key) {
+  uint32_t u = (uint32_t)(key >> 32);
+  u = (u & 0x80000000u) ? (u & 0x7fffffffu) : ~u;
+  return __uint_as_float(u);
+}
+
+// The other set of state tables: the survivors of a layer are written there, then the sets swap.
+struct AltTables {
+  int32_t *states, *cf, *prefix, *cids, *alive;
+  float *vals;
+};
+
 // Table pointers of a context.
 inline Tables tables_of(const vf_ctx *c) {
   Tables t;
@@ -705,4 +726,10 @@ inline Tables tables_of(const vf_ctx *c) {
   t.states = c->d_states; t.cf = c->d_cf; t.prefix = c->d_prefix; t.cids = c->d_cids;
   t.alive = c->d_alive; t.err = c->d_err; t.vals = c->d_vals; t.S = c->S;
   return t;
+}
+inline AltTables alt_of(const vf_ctx *c) {
+  AltTables a;
+  a.states = c->d_alt_states; a.cf = c->d_alt_cf; a.prefix = c->d_alt_prefix; a.cids = c->d_alt_cids;
+  a.alive = c->d_alt_alive; a.vals = c->d_alt_vals;
+  return a;
 }

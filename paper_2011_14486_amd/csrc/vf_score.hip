@@ -1176,16 +1176,21 @@ bool vfk_can_fuse_step(const vf_ctx *c) {
          c->model.dims[0] == c->space.F;
 }
 
-int vfk_step_fused(vf_ctx *c, int stage, int *nparts_out) {
-  return score_mlp(c, nullptr, 0, c->B, c->M, c->Mpad, 1, nullptr, 0, nparts_out, stage, stage);
+static int compute_units(const vf_ctx *c) {
+  int ncu = 256;
+  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
+  return ncu;
 }
 
 // (the condition under which score_mlp takes tiles of 64 candidates for a generated step)
 static bool narrow_step(const vf_ctx *c) {
-  int maxw = 0, ncu = 256;
+  int maxw = 0;
   for (int l = 0; l < c->model.n_layers; ++l) if (c->model.dims[l] > maxw) maxw = c->model.dims[l];
-  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
-  return maxw <= 512 && c->pm.fast_rt && ((c->M + 127) / 128) * c->B * 2 <= ncu;
+  return maxw <= 512 && c->pm.fast_rt && ((c->M + 127) / 128) * c->B * 2 <= compute_units(c);
+}
+
+int vfk_step_fused(vf_ctx *c, int stage, int *nparts_out) {
+  return score_mlp(c, nullptr, 0, c->B, c->M, c->Mpad, 1, nullptr, 0, nparts_out, stage, stage);
 }
 
 bool vfk_can_chain(const vf_ctx *c) { return vfk_can_fuse_step(c) && c->M > 0 && narrow_step(c); }
@@ -1229,9 +1234,10 @@ __global__ __launch_bounds__(256) void k_mask_scores(float *scores, const int32_
 }
 }  // namespace
 
+int vfk_scores_buffer(vf_ctx *c) { return grow(c, c->d_scores, c->score_elems, (size_t)c->B * c->Mpad); }
+
 int vfk_step_scores(vf_ctx *c, int stage) {
-  const size_t want = (size_t)c->B * c->Mpad;
-  int rc = grow(c, c->d_scores, c->score_elems, want);
+  int rc = vfk_scores_buffer(c);
   if (rc != VF_OK) return rc;
   int nparts = 0;
   if (vfk_seq_model(c)) return vfk_seq_step(c, stage, c->d_scores, c->Mpad, -1, &nparts);

@@ -27,6 +27,8 @@ namespace {
 
 #include "vf_score_dev.h"
 
+#include "vf_layer_dev.h"
+
 // With fewer problems than compute units a team of `team` workgroups shares one problem:
 // every member builds the decision's context and id list for itself, member m scores
 // tiles m, m + team, ... of the list, publishes its minimum, the team meets at a counter
@@ -64,12 +66,13 @@ struct WholeArgs {
   unsigned long long *mailbox;       // [grid] the layer a helper is sent: see mail_pack
   uint32_t *pub;                     // [nprob][VF_PUB_WORDS] what an owner leaves for its helpers: the layer's
                                      // decision context, quotient tables, folded bias and candidate count
+  // one layer of every problem (LAYER): the opened decisions are in pub and list
+  float *scores;                     // nullable: V of list entry n of problem p at [p][Mpad] + n, without noise
+  float *pval;                       // the first minimum of every 64 list entries: at [problem][part], with its
+  int32_t *pidx;                     // candidate id - or, with scores, part after part over all problems, with
+  int nparts;                        // problem * nparts + part, and their number in n_minima
+  uint32_t *n_minima;
 };
-// words of an owner's published layer: DecPack, EvalTabs, first-layer bias (up to 1024 rows), count
-constexpr int VF_PUB_TABS = VF_DECPACK_DWORDS;
-constexpr int VF_PUB_BIAS = VF_PUB_TABS + (int)(sizeof(EvalTabs) / 4);
-constexpr int VF_PUB_COUNT = VF_PUB_BIAS + 1024;
-constexpr int VF_PUB_WORDS = VF_PUB_COUNT + 4;
 constexpr int VF_XIN_STRIDE = 56;  // elements between the columns of the input buffer (48 used)
 constexpr int VF_MAX_HELPERS = 3;
 constexpr int VF_POOL_SLOTS = 1024;       // more than the workgroups of a launch
@@ -84,8 +87,14 @@ __device__ __forceinline__ unsigned long long mail_pack(int unit, int stage, int
 // NC candidates per tile, RT row tiles per wave (hidden width 256 * RT), PD k-steps of
 // weight fragments in flight per wave.  stat: nullable, [0] += candidates pushed through
 // the network, [1] += valid ones (the same here: only valid ids are listed).
-// ONE: the network has a single hidden layer (otherwise two).
-template <int NC, int RT, int PD, bool ONE>
+// ONE: the network has a single hidden layer (otherwise two, with LAYER two or more).
+//
+// LAYER: one decision of every problem instead of whole schedules.  The decisions have been
+// opened (k_open_layer, k_beam_advance): their contexts and lists are in memory, as an owner
+// leaves them for its helpers.  The tiles of all problems in a row are dealt out to the workgroups
+// in equal runs, and what a workgroup leaves is the first minimum of every 64 list entries (a part)
+// and, if asked, their scores; nothing is decided here and no workgroup waits for another.
+template <int NC, int RT, int PD, bool ONE, bool LAYER = false>
 __global__ __launch_bounds__(512) void k_whole(vf_fast_dev md, int ks, int64_t M, int nprob,
                                                unsigned long long *stat, NoiseArgs na, WholeArgs wa) {
   constexpr int CT = NC / 32;
@@ -118,6 +127,42 @@ __global__ __launch_bounds__(512) void k_whole(vf_fast_dev md, int ks, int64_t M
   for (int i = tid; i < (int)md.wl_off; i += 512) auxs[i] = md.aux[i];
   for (int i = tid; i < md.dims[NH] / 2; i += 512)
     reinterpret_cast<uint32_t *>(auxs + md.wl_off)[i] = pack_bf16(md.aux[md.wl_off + 2 * i], md.aux[md.wl_off + 2 * i + 1]);
+  // LAYER: the run of tiles of this workgroup, problem by problem in order
+  int run_left = 0, run_unit = 0, run_tile = 0, run_base = 0;  // run_base: tiles of the problems before
+  if constexpr (LAYER) {
+    __shared__ int part_sum[8], run_at[2];
+    const int per = (nprob + 511) / 512, p0 = tid * per, p1 = p0 + per < nprob ? p0 + per : nprob;
+    auto tiles_of = [&](int p) { return ((int)wa.pub[(size_t)p * VF_PUB_WORDS + VF_PUB_COUNT] + NC - 1) / NC; };
+    int mine = 0;
+    for (int p = p0; p < p1; ++p) mine += tiles_of(p);
+    int upto = mine;  // inclusive sum over the wave's threads so far
+    for (int off = 1; off < 64; off <<= 1) {
+      const int o = __shfl_up(upto, off);
+      if (lane >= off) upto += o;
+    }
+    if (lane == 63) part_sum[w] = upto;
+    __syncthreads();
+    int before = upto - mine, total = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (k < w) before += part_sum[k];
+      total += part_sum[k];
+    }
+    const int t0 = (int)((int64_t)blockIdx.x * total / gridDim.x), t1 = (int)((int64_t)(blockIdx.x + 1) * total / gridDim.x);
+    if (wa.scores && blockIdx.x == 0 && tid == 0) wa.n_minima[0] = (uint32_t)(total * NWS);
+    if (t0 >= t1) return;
+    if (t0 >= before && t0 < before + mine) {
+      int p = p0;
+      for (; t0 >= before + tiles_of(p); ++p) before += tiles_of(p);
+      run_at[0] = p;
+      run_at[1] = t0 - before;
+    }
+    __syncthreads();
+    run_left = t1 - t0;
+    run_unit = run_at[0];
+    run_tile = run_at[1];
+    run_base = t0 - run_tile;
+  }
   const __amdgpu_buffer_rsrc_t ws = stream_rsrc(md.w_stream + (size_t)w * md.wave_stride);
   const __amdgpu_buffer_rsrc_t wf = stream_rsrc(md.w_full + (size_t)w * md.wave_stride_full);
   const int voff = 16 * lane;
@@ -136,7 +181,12 @@ __global__ __launch_bounds__(512) void k_whole(vf_fast_dev md, int ks, int64_t M
   int unit = (int)blockIdx.x / wa.team, stage = wa.first;
   unsigned int owner_target = 0u;  // thread 0, owner: helper arrivals the problem's layers so far sent for
   for (;;) {
-    int team = wa.team, member = (int)blockIdx.x % wa.team;
+    int team = LAYER ? 1 : wa.team, member = LAYER ? 0 : (int)blockIdx.x % wa.team;
+    if constexpr (LAYER) {
+      if (run_left <= 0) break;
+      unit = run_unit;
+      helping = true;  // (the layer is fetched as a helper fetches it)
+    } else {
     if (!helping && unit >= nprob) {
       if (!wa.helpers) break;
       helping = true;
@@ -173,113 +223,27 @@ __global__ __launch_bounds__(512) void k_whole(vf_fast_dev md, int ks, int64_t M
       if (job_stage < 0) break;  // every problem is done
       unit = job_unit; stage = job_stage; team = job_team; member = job_member;
     }
+    }
     uint32_t *const idlist = wa.list + (size_t)unit * wa.Mpad;
-    na.stage = stage;
-    __shared__ int ncand, g_npairs;
+    if (!LAYER) na.stage = stage;
+    __shared__ OpenScratch os;
     __shared__ unsigned int job_helper[VF_MAX_HELPERS];
     uint32_t *const pub = wa.pub + (size_t)unit * VF_PUB_WORDS;
-    if (helping) {
+    if (LAYER || helping) {
       // the owner has left the layer in memory before it sent the mail
       for (int i = tid; i < VF_DECPACK_DWORDS; i += 512) reinterpret_cast<uint32_t *>(&pk)[i] = pub[i];
       for (int i = tid; i < (int)(sizeof(EvalTabs) / 4); i += 512) reinterpret_cast<uint32_t *>(&tabs)[i] = pub[VF_PUB_TABS + i];
       for (int i = tid; i < md.dims[1]; i += 512) auxs[md.bias_off[0] + i] = __uint_as_float(pub[VF_PUB_BIAS + i]);
-      if (tid == 0) ncand = (int)pub[VF_PUB_COUNT];
+      if (tid == 0) os.ncand = (int)pub[VF_PUB_COUNT];
       __syncthreads();
     } else {
     build_dec(pk.d, pk.sp, wa.t, unit, stage);
-    // three small jobs side by side, on different waves: the quotient tables (waves 0, 1), the
-    // shared input rows as the first layer wants them (waves 2, 3), the split factors that fit
-    // (wave 4)
-    fill_evaltabs(tabs, pk.d, pk.sp);
-    if (tid >= 128 && tid < 128 + VF_STAT_WORDS) pk.stat[tid - 128] = stat_word(pk.d, tid - 128);
-    // Ordered list of the decision's valid ids, written down directly from the validity
-    // rules: per (compute_at, store_at) digit pair that is open - the level is offered and
-    // the hoist does not exceed it - the valid ids are the products of the split factors
-    // that fit the level's region with every loop order / vectorize / parallel choice;
-    // an inlining pair has the single id with every other digit zero.  The list holds the
-    // digits, packed, rather than the id: the evaluation works on digits, and putting an id
-    // together takes a few multiplications where taking it apart takes as many divisions.
-    __shared__ int g_pos[13], g_cat[12], g_dec[12];
-    __shared__ int g_nok[3][3], g_ok[3][3][8];
-    __shared__ float g_rcp[3][3];  // 1 / g_nok, for div_small
-    if (tid >= 256 && tid < 265) {
-      const int lvl = (tid - 256) / 3, dd = (tid - 256) % 3;
-      int cnt = 0;
-      for (int k = 0; k < pk.sp.nf[dd]; ++k)
-        if ((uint32_t)pk.sp.fac[dd][k] <= pk.d.E[lvl][dd]) g_ok[lvl][dd][cnt++] = k;
-      g_nok[lvl][dd] = cnt;
-      g_rcp[lvl][dd] = 1.0f / (float)(cnt > 0 ? cnt : 1);
-    }
-    __syncthreads();
-    const int rest_n = pk.sp.nperm * pk.sp.nvec * pk.sp.npar;
-    const float rcp_perm = 1.0f / (float)pk.sp.nperm, rcp_vec = 1.0f / (float)pk.sp.nvec;
-    if (w == 0) {
-      // lane j looks at pair j = (store_at digit, compute_at digit); the open pairs are then
-      // numbered and given their first list position in order
-      const int npairs_all = pk.sp.nsat * pk.sp.ncat;
-      int cnt = 0, cat = 0, dec = 0;
-      if (lane < npairs_all && lane < 12) {
-        const int isat = lane / pk.sp.ncat, icat = lane % pk.sp.ncat;
-        cat = pk.sp.cat[icat];
-        dec = (int)((uint32_t)icat << 24 | (uint32_t)isat << 28);
-        if (pk.d.lvl_ok[cat] != 0) {
-          if (cat == VF_INLINE) cnt = isat == 0 ? 1 : 0;
-          else if (isat <= cat) cnt = g_nok[cat][0] * g_nok[cat][1] * g_nok[cat][2] * rest_n;
-        }
-      }
-      int np = 0, pos = 0;
-#pragma unroll
-      for (int j = 0; j < 12; ++j) {
-        const int cj = __builtin_amdgcn_readlane(cnt, j);
-        if (cj == 0) continue;
-        const int catj = __builtin_amdgcn_readlane(cat, j), decj = __builtin_amdgcn_readlane(dec, j);
-        if (lane == 0) {
-          g_pos[np] = pos;
-          g_cat[np] = catj;
-          g_dec[np] = decj;
-        }
-        pos += cj;
-        ++np;
-      }
-      if (lane == 0) {
-        g_pos[np] = pos;
-        g_npairs = np;
-        ncand = pos;
-      }
-    }
-    fold_bias<RT>(wf, pk.stat, md.dims[0] == 256, w, lane,
-                  md.aux + md.bias_off[0], auxs + md.bias_off[0]);
-    __syncthreads();  // the pairs are numbered, the bias is complete
-    // (the pairs' first positions into registers: the pair of an entry is then found without
-    // a chain of dependent reads)
-    int pos_r[12];
-#pragma unroll
-    for (int j = 0; j < 12; ++j) pos_r[j] = j < g_npairs ? g_pos[j] : 0x7fffffff;
-    for (int k = tid; k < ncand; k += 512) {
-      int q = 0;
-#pragma unroll
-      for (int j = 1; j < 12; ++j) q += k >= pos_r[j] ? 1 : 0;
-      const int cat = g_cat[q];
-      uint32_t dec = (uint32_t)g_dec[q];
-      if (cat != VF_INLINE) {
-        uint32_t r = (uint32_t)(k - g_pos[q]), nxt;
-        const uint32_t nx = g_nok[cat][0], ny = g_nok[cat][1], nc = g_nok[cat][2];
-        nxt = div_small(r, nx, g_rcp[cat][0]); const uint32_t jx = r - nxt * nx; r = nxt;
-        nxt = div_small(r, ny, g_rcp[cat][1]); const uint32_t jy = r - nxt * ny; r = nxt;
-        nxt = div_small(r, nc, g_rcp[cat][2]); const uint32_t jc = r - nxt * nc; r = nxt;
-        const int ix = g_ok[cat][0][jx], iy = g_ok[cat][1][jy], ic = g_ok[cat][2][jc];
-        nxt = div_small(r, (uint32_t)pk.sp.nperm, rcp_perm); const uint32_t ip = r - nxt * (uint32_t)pk.sp.nperm; r = nxt;
-        const uint32_t par = div_small(r, (uint32_t)pk.sp.nvec, rcp_vec), vec = r - par * (uint32_t)pk.sp.nvec;
-        dec |= (uint32_t)ix | (uint32_t)iy << 4 | (uint32_t)ic << 8 | (uint32_t)ip << 12 | (uint32_t)vec << 16 |
-               (uint32_t)par << 20;
-      }
-      idlist[k] = dec;
-    }
-    if (wa.helpers) {
+    open_layer<RT>(pk, tabs, os, md, wf, tid, w, lane, auxs + md.bias_off[0], idlist);
+    if (!LAYER && wa.helpers) {
       // owner: with enough tiles, up to VF_MAX_HELPERS workgroups are taken out of the pool
       if (tid == 0) {
         int n = 0;
-        int want = (ncand + NC - 1) / NC / VF_TILES_PER_MEMBER - 1;
+        int want = (os.ncand + NC - 1) / NC / VF_TILES_PER_MEMBER - 1;
         if (want > VF_MAX_HELPERS) want = VF_MAX_HELPERS;
         for (int attempt = 0; attempt < 4 && want > 0 && n == 0; ++attempt) {
           const unsigned int taken = __hip_atomic_load(&wa.pool[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -308,16 +272,13 @@ __global__ __launch_bounds__(512) void k_whole(vf_fast_dev md, int ks, int64_t M
     }  // (not helping)
     __syncthreads();  // the id list (written by this workgroup) is complete
     if (team_failed) return;
-    if (wa.helpers && !helping) {
+    if (!LAYER && wa.helpers && !helping) {
       team = job_team;
       if (team > 1) {
         // what a helper needs of this layer goes to memory (the list is there already); the
         // helpers are sent for once all of it has arrived: every thread waits for its own
         // stores, then thread 0 sends the mail
-        for (int i = tid; i < VF_DECPACK_DWORDS; i += 512) pub[i] = reinterpret_cast<const uint32_t *>(&pk)[i];
-        for (int i = tid; i < (int)(sizeof(EvalTabs) / 4); i += 512) pub[VF_PUB_TABS + i] = reinterpret_cast<const uint32_t *>(&tabs)[i];
-        for (int i = tid; i < md.dims[1]; i += 512) pub[VF_PUB_BIAS + i] = __float_as_uint(auxs[md.bias_off[0] + i]);
-        if (tid == 0) pub[VF_PUB_COUNT] = (uint32_t)ncand;
+        publish_layer(pub, pk, tabs, auxs + md.bias_off[0], md.dims[1], os.ncand, tid);
         __threadfence();
         __syncthreads();
         if (tid == 0)
@@ -326,8 +287,10 @@ __global__ __launch_bounds__(512) void k_whole(vf_fast_dev md, int ks, int64_t M
                                __HIP_MEMORY_SCOPE_AGENT);
       }
     }
-    const int ncands = ncand;
+    const int ncands = os.ncand;
     const int ntiles = (ncands + NC - 1) / NC;
+    if (LAYER) member = run_tile;  // the first tile; the others follow one by one
+    const int t_end = LAYER && run_tile + run_left < ntiles ? run_tile + run_left : ntiles;
 
     // Thread tid evaluates the candidate of column tid % NC of the tile that starts at list
     // entry nb and stores its share of rows 16..63, normalised, as bf16 (8 rows = one 16-byte
@@ -381,10 +344,28 @@ __global__ __launch_bounds__(512) void k_whole(vf_fast_dev md, int ks, int64_t M
     unsigned int col_n = 0u;
     float pend_s = 0.0f;     // a tile's score of this thread's column that has not been scanned yet
     int32_t pend_flag = -1;  // its candidate id + 1, 0 = not a valid column, -1 = nothing pending
+    int pend_tile = 0;       // (LAYER) its tile
     auto scan_pending = [&]() __attribute__((always_inline)) {
       if (pend_flag < 0) return;
       float sv_ = pend_s;
       const int32_t colid = pend_flag - 1;
+      if constexpr (LAYER) {
+        const int entry = pend_tile * NC + tid;
+        if (wa.scores && entry < ncands) wa.scores[(size_t)unit * wa.Mpad + entry] = sv_;
+        if (na.eps != 0.0f) sv_ = add_noise(na, sv_, unit, colid);
+        const bool wins = pend_flag != 0 && sv_ < __builtin_inff();
+        float v = wins ? sv_ : __builtin_inff();
+        int32_t c = wins ? colid : -1;
+        wave_min(v, c);
+        if (lane == 0) {
+          const int part = unit * wa.nparts + pend_tile * NWS + w;
+          const int slot = wa.scores ? (run_base + pend_tile) * NWS + w : part;
+          wa.pval[slot] = v;
+          wa.pidx[slot] = wa.scores ? part : c;
+        }
+        pend_flag = -1;
+        return;
+      }
       if (pend_flag != 0) {
         if (na.eps != 0.0f) sv_ = add_noise(na, sv_, unit, colid);
         // (+inf and NaN never win: Algorithm 1 compares with a strict "<" from +inf)
@@ -426,9 +407,9 @@ __global__ __launch_bounds__(512) void k_whole(vf_fast_dev md, int ks, int64_t M
 
     // the loop starts one tile early: that round only produces the first tile's features
     int par = 1;
-    for (int t = member - team; t < ntiles; t += team, par ^= 1) {
+    for (int t = member - team; t < t_end; t += team, par ^= 1) {
       const bool real = t >= member;
-      const bool has_next = t + team < ntiles;
+      const bool has_next = t + team < t_end;
       float dot[CT];
       // ---- first layer, over the candidates' own rows in the input buffer.  (The matrix
       // loops go first on their SIMD: the other wave's vector work fills the gaps.)
@@ -457,6 +438,17 @@ __global__ __launch_bounds__(512) void k_whole(vf_fast_dev md, int ks, int64_t M
           // (nobody reads the activations of the tile before any more: barrier behind its dots)
           write_back(acc);
           __syncthreads();
+          if constexpr (LAYER) {
+            // hidden layers between the first and the last one: in place, so every wave has read
+            // the layer's input before any writes its output
+            for (int l = 1; l + 1 < NH; ++l) {
+              load_bias<RT>(bv, auxs + md.bias_off[l], w, lane);
+              contract_layer<RT, CT, PD, VF_K0_OWN % PD>(acc, bv, ring, ws, wstep, voff, false, md.dims[l] / 16, ba, 32 * ks);
+              __syncthreads();
+              write_back(acc);
+              __syncthreads();
+            }
+          }
         }
         // ---- last hidden layer and the output dots; the next tile's features.  Waves 4..7
         // produce their share of the features before the layer, waves 0..3 after it, so that
@@ -469,7 +461,7 @@ __global__ __launch_bounds__(512) void k_whole(vf_fast_dev md, int ks, int64_t M
           }
           if (!real) continue;
           floatx16 acc[RT][CT], bv[RT];
-          load_bias<RT>(bv, auxs + md.bias_off[1], w, lane);
+          load_bias<RT>(bv, auxs + md.bias_off[LAYER ? NH - 1 : 1], w, lane);
           __builtin_amdgcn_s_setprio(2);
           contract_layer<RT, CT, PD, VF_K0_OWN % PD>(acc, bv, ring, ws, wstep, voff, true, md.dims[1] / 16, ba, 32 * ks);
           __builtin_amdgcn_s_setprio(0);
@@ -493,6 +485,7 @@ __global__ __launch_bounds__(512) void k_whole(vf_fast_dev md, int ks, int64_t M
         for (int g = 0; g < 8; ++g) sacc += red[g * NC + tid];
         pend_s = sacc;
         pend_flag = okf[par * NC + tid];
+        pend_tile = t;
         col_n += (t * NC + tid < ncands ? 1u : 0u) + (pend_flag != 0 ? 0x10000u : 0u);
       }
       // no barrier here: the next tile's first layer reads the input buffer and the bias
@@ -500,6 +493,17 @@ __global__ __launch_bounds__(512) void k_whole(vf_fast_dev md, int ks, int64_t M
       // flags of the other parity behind the next tile's first one
     }
     if (w < NWS) scan_pending();
+    if constexpr (LAYER) {
+      if (stat && w < NWS && col_n) {
+        atomicAdd(&stat[0], (unsigned long long)(col_n & 0xffffu));
+        atomicAdd(&stat[1], (unsigned long long)(col_n >> 16));
+      }
+      run_base += ntiles;
+      run_left -= t_end - run_tile;
+      run_tile = 0;
+      ++run_unit;
+      continue;
+    }
 
     if (w < NWS) {
       wave_min(col_v, col_c);
@@ -581,6 +585,24 @@ __global__ __launch_bounds__(512) void k_whole(vf_fast_dev md, int ks, int64_t M
   }
 }
 
+// Opens one decision of every problem for a LAYER launch: one workgroup per problem.
+template <int RT>
+__global__ __launch_bounds__(512) void k_open_layer(vf_fast_dev md, const uint32_t *decpack, uint32_t *pub, uint32_t *list,
+                                                    int64_t Mpad, float *pval, int32_t *pidx, int nparts) {
+  __shared__ DecPack pk;
+  __shared__ EvalTabs tabs;
+  __shared__ OpenScratch os;
+  __shared__ float bias[1024];
+  const int tid = threadIdx.x, lane = tid & 63, p = blockIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (tid < VF_DECPACK_DWORDS) reinterpret_cast<uint32_t *>(&pk)[tid] = decpack[(size_t)p * VF_DECPACK_DWORDS + tid];
+  __syncthreads();
+  open_layer<RT>(pk, tabs, os, md, stream_rsrc(md.w_full + (size_t)w * md.wave_stride_full), tid, w, lane, bias,
+                 list + (size_t)p * Mpad);
+  publish_layer(pub + (size_t)p * VF_PUB_WORDS, pk, tabs, bias, md.dims[1], os.ncand, tid);
+  no_minima(pval + (size_t)p * nparts, pidx + (size_t)p * nparts, os.ncand, nparts, tid);
+}
+
 __global__ __launch_bounds__(256) void k_zero_u32(unsigned int *p, size_t n) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n) p[i] = 0u;
@@ -588,13 +610,28 @@ __global__ __launch_bounds__(256) void k_zero_u32(unsigned int *p, size_t n) {
 
 }  // namespace
 
+// Candidates per tile of a LAYER launch: 128 with 512 hidden units (64 with 1024), but 64 while a
+// decision of all problems has fewer tiles of 128 ids than half the compute units (the same line
+// as for the scorer that works on id ranges).
+static int layer_tile(const vf_ctx *c) {
+  int ncu = 256;
+  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
+  return c->pm.fast_rt == 4 || ((c->M + 127) / 128) * c->B * 2 <= ncu ? 64 : 128;
+}
+
 // Kernel and dynamic LDS bytes of a whole-schedule launch for the context's model.
 typedef void (*whole_kernel)(vf_fast_dev, int, int64_t, int, unsigned long long *, NoiseArgs, WholeArgs);
-static whole_kernel whole_launch_shape(const vf_ctx *c, vf_fast_dev *fd, int *ks, size_t *smem) {
+static whole_kernel whole_launch_shape(const vf_ctx *c, vf_fast_dev *fd, int *ks, size_t *smem, bool layer = false) {
   int NC = 0;
   vfk_fast_dev(c, true, fd, ks, &NC);
+  if (layer) NC = layer_tile(c);
   const size_t aux_words = fd->wl_off + (size_t)(fd->naux - (int)fd->wl_off + 1) / 2;  // output vector: two to a word
   *smem = (size_t)NC * *ks * 2 + (size_t)NC * VF_XIN_STRIDE * 2 + (size_t)8 * NC * 4 + (size_t)2 * NC * 4 + aux_words * 4;
+  if (layer) {
+    if (c->pm.fast_rt == 4) return fd->L == 2 ? k_whole<64, 4, 2, true, true> : k_whole<64, 4, 2, false, true>;
+    if (NC == 64) return fd->L == 2 ? k_whole<64, 2, 4, true, true> : k_whole<64, 2, 4, false, true>;
+    return fd->L == 2 ? k_whole<128, 2, 4, true, true> : k_whole<128, 2, 4, false, true>;
+  }
   if (fd->L == 2) return NC == 64 ? k_whole<64, 4, 2, true> : k_whole<128, 2, 4, true>;
   return NC == 64 ? k_whole<64, 4, 2, false> : k_whole<128, 2, 4, false>;
 }
@@ -740,5 +777,80 @@ int vfk_greedy_whole(vf_ctx *c, int first, int last) {
   c->whole_first = first;
   c->whole_last = last;
   c->whole_epoch = c->state_epoch;
+  return VF_OK;
+}
+
+bool vfk_layer_fits(const vf_ctx *c) {
+  if (!vfk_can_fuse_step(c) || c->M < 1) return false;
+  vf_fast_dev fd;
+  int ks = 0;
+  size_t smem = 0;
+  const whole_kernel kern = whole_launch_shape(c, &fd, &ks, &smem, true);
+  if (fd.k0 != VF_K0_OWN || !fd.w_full) return false;
+  if (c->layer_kern == (const void *)kern && c->layer_smem == smem) return true;
+  hipFuncAttributes attr;
+  int lds_max = 0;
+  if (hipFuncGetAttributes(&attr, (const void *)kern) != hipSuccess ||
+      hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (smem + attr.sharedSizeBytes > (size_t)lds_max) return false;
+  c->layer_kern = (const void *)kern;
+  c->layer_smem = smem;
+  return true;
+}
+
+static int layer_parts(const vf_ctx *c) { return (int)((c->M + 127) / 128) * 2; }
+
+static int grow_words(vf_ctx *c, void **p, size_t &have, size_t want) {
+  if (want <= have) return VF_OK;
+  if (*p) { VF_HIP(c, hipStreamSynchronize(c->stream)); (void)hipFree(*p); *p = nullptr; }
+  have = 0;
+  if (hipMalloc(p, want * 4) != hipSuccess) { (void)hipGetLastError(); *p = nullptr; return VF_ENOMEM; }
+  have = want;
+  return VF_OK;
+}
+
+int vfk_layer_open(vf_ctx *c, int stage) {
+  vf_fast_dev fd;
+  vfk_fast_dev(c, true, &fd, nullptr, nullptr);
+  int rc = grow_words(c, (void **)&c->d_wlist, c->wlist_elems, (size_t)c->B * c->Mpad);
+  if (rc == VF_OK) rc = grow_words(c, (void **)&c->d_pub, c->pub_elems, (size_t)c->B * VF_PUB_WORDS + 4);
+  const int nparts = layer_parts(c);
+  if (rc == VF_OK) rc = vfk_ensure_parts(c, (size_t)nparts * c->B);
+  if (rc == VF_OK) rc = vfk_prepare(c, stage);
+  if (rc != VF_OK) return rc;
+  hipLaunchKernelGGL((c->pm.fast_rt == 4 ? k_open_layer<4> : k_open_layer<2>), dim3((unsigned)c->B), dim3(512), 0, c->stream,
+                     fd, (const uint32_t *)c->d_decpack, c->d_pub, reinterpret_cast<uint32_t *>(c->d_wlist),
+                     (int64_t)c->Mpad, c->d_pval, c->d_pidx, nparts);
+  VF_HIP(c, hipGetLastError());
+  return VF_OK;
+}
+
+int vfk_layer_score(vf_ctx *c, int noise_stage, float *scores, int *nparts_out) {
+  vf_fast_dev fd;
+  int ks = 0, ncu = 256;
+  size_t smem = 0;
+  const whole_kernel kern = whole_launch_shape(c, &fd, &ks, &smem, true);
+  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
+  NoiseArgs na;
+  na.eps = noise_stage >= 0 ? c->noise_eps : 0.0f;
+  na.k0 = (uint32_t)c->noise_seed; na.k1 = (uint32_t)(c->noise_seed >> 32);
+  na.stage = noise_stage; na.first_rollout = c->noise_first;
+  WholeArgs wa = {};
+  wa.t = tables_of(c);
+  wa.list = reinterpret_cast<uint32_t *>(c->d_wlist); wa.Mpad = c->Mpad;
+  wa.pub = c->d_pub;
+  wa.scores = scores;
+  wa.pval = c->d_pval; wa.pidx = c->d_pidx;
+  wa.nparts = layer_parts(c);
+  wa.n_minima = c->d_pub + (size_t)c->B * VF_PUB_WORDS;
+  vf_prof_scope prof(c, VF_PROF_SCORE);
+  VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+  hipLaunchKernelGGL(kern, dim3((unsigned)ncu), dim3(512), smem, c->stream, fd, ks, c->M, c->B,
+                     c->profiling ? c->d_stat : (unsigned long long *)nullptr, na, wa);
+  VF_HIP(c, hipGetLastError());
+  *nparts_out = wa.nparts;
   return VF_OK;
 }

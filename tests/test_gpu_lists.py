@@ -1,0 +1,57 @@
+"""GPU: decisions on lists of valid candidates (many tiles) against the scorers on id ranges (few
+tiles) and, for the beam's selection, against the checker."""
+import numpy as np
+import pytest
+
+from paper_2011_14486_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def vf():
+    import paper_2011_14486_amd as pkg
+    return pkg.load()
+
+
+def context(vf, pipes, sp, model, w):
+    ctx = vf.vf_create(0)
+    vf.vf_set_space(ctx, sp); vf.vf_set_pipeline(ctx, pipes); vf.vf_set_model(ctx, model, w)
+    return ctx
+
+
+# the factors make the number of ids of a decision: the search works on lists from 64 tiles of 128 on
+@pytest.mark.parametrize("K,fac,const", [(2, [1, 2, 4, 8], True), (33, [1, 2, 4], True), (33, [1, 2, 4], False),
+                                         (300, [1, 4], False), (1024, [1, 4], True)])
+def test_beam_selection_on_lists(vf, ovf, K, fac, const):
+    """The survivors of the layers against the checker.  const: a network whose value is the same
+    for every state, so that all scores tie and the survivors are the first (slot, id) pairs."""
+    dims = [64, 512, 512, 1]
+    pipe = I.random_pipeline(3, 21)
+    sp = I.make_space(fac, fac, fac, I.ALL_PERMS[:2 if K > 100 else 6], 2, 2, [I.ROOT, I.L1, I.L2, I.INLINE][:1 if K > 400 else 4],
+                      2 if K < 100 else 1, 64)
+    assert (I.space_dense_count(sp) + 127) // 128 * K > 64
+    w = I.mlp_weights(dims, 5, bias_std=0.1)
+    if const:
+        w = np.zeros_like(w)
+        w[-1] = 0.75
+    model = I.model_record(I.MLP, dims, I.BF16)
+    ctx = context(vf, np.stack([pipe] * K), sp, model, w)
+    st, cids, vals, nb = (t.cpu().numpy() for t in vf.vf_beam_search(ctx))
+    vf.vf_destroy(ctx)
+    if const:
+        ref = ovf.beam(pipe, sp, K, model, w)
+        assert nb[0] == ref["n_beams"] > 0
+        assert np.array_equal(cids, ref["cids"]) and np.array_equal(vals, ref["values"])
+        return
+    assert nb[0] == K and len(set(map(tuple, cids))) == K and np.all(np.diff(vals[:, -1]) >= 0)
+    # V of every extension of the survivors' prefixes: the values agree and nothing that is clearly
+    # better than the last survivor was left out
+    kept, worst, tol = set(map(tuple, cids)), vals[:, -1].max(), 2e-2
+    scale = np.sqrt(np.mean(vals[:, -1] ** 2))
+    for pre in sorted({tuple(r[:2]) for r in cids}):
+        s, ok = ovf.decision_scores(pipe, sp, model, w, list(pre) + [0], 2)
+        for j in np.flatnonzero((cids[:, :2] == pre).all(axis=1)):
+            assert ok[cids[j, 2]] and abs(s[cids[j, 2]] - vals[j, 2]) <= tol * max(abs(s[cids[j, 2]]), scale)
+        for c in np.flatnonzero(ok & (s < worst - 2 * tol * max(abs(worst), scale))):
+            assert pre + (c,) in kept
