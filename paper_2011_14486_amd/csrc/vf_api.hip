@@ -491,7 +491,10 @@ int vf_greedy_schedule(vf_ctx *c, int first, int last, vf_state *out_states, int
     const int rc = settle_whole(c, first > 0);
     if (rc != VF_OK) return rc;
   }
-  if (first <= last && vfk_whole_team(c) >= 1) {
+  if (first <= last && vfk_layer_pays(c) && !vfk_whole_pays(c)) {
+    const int rc = vfk_greedy_layers(c, first, last);
+    if (rc != VF_OK) return rc;
+  } else if (first <= last && vfk_whole_team(c) >= 1) {
     int rc = vfk_greedy_whole(c, first, last);
     if (rc != VF_OK) return rc;
     c->n_sched = last + 1;

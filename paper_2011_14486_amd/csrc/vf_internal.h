@@ -245,6 +245,11 @@ int vfk_greedy_whole(vf_ctx *c, int first, int last);
 bool vfk_layer_fits(const vf_ctx *c);
 int vfk_layer_open(vf_ctx *c, int stage);
 int vfk_layer_score(vf_ctx *c, int noise_stage, float *scores, int *nparts_out);
+// whether lists pay for a step of this context (vf_score.hip), and Algorithm 1 over stages
+// first..last on them
+bool vfk_layer_pays(const vf_ctx *c);
+bool vfk_whole_pays(const vf_ctx *c);
+int vfk_greedy_layers(vf_ctx *c, int first, int last);
 int vfk_step_fused(vf_ctx *c, int stage, int *nparts_out);
 // Algorithm 1 over stages first..last with one launch per layer (the fused scorer also decides
 // the stage before it) and one commit at the end; VF_ESTATE if the model or space does not

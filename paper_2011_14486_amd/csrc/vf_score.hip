@@ -1189,7 +1189,22 @@ static bool narrow_step(const vf_ctx *c) {
   return maxw <= 512 && c->pm.fast_rt && ((c->M + 127) / 128) * c->B * 2 <= compute_units(c);
 }
 
+// More tiles than compute units: on lists of valid candidates (open, score) a decision costs
+// half of what it costs on id ranges, where invalid ids share the tiles and every tile takes
+// its ids apart; with a single round of tiles the second launch is what counts.
+// 256-512-512-1, 4096 ids: 16 problems 39 -> 31 us, 37: 78 -> 47, 256: 356 -> 207, but 8: 24 -> 31;
+// 256-1024-1024-1: 8 problems 61 -> 45 us, 37: 234 -> 122, but 4: 38 -> 40; 16384 ids: 8 problems 66 -> 35 us.
+bool vfk_layer_pays(const vf_ctx *c) {
+  if (!vfk_can_fuse_step(c)) return false;
+  const int NC = c->pm.fast_rt == 4 || narrow_step(c) ? 64 : 128;
+  return (c->M + NC - 1) / NC * c->B > compute_units(c) && vfk_layer_fits(c);
+}
+
 int vfk_step_fused(vf_ctx *c, int stage, int *nparts_out) {
+  if (vfk_layer_pays(c)) {
+    const int rc = vfk_layer_open(c, stage);
+    return rc != VF_OK ? rc : vfk_layer_score(c, stage, nullptr, nparts_out);
+  }
   return score_mlp(c, nullptr, 0, c->B, c->M, c->Mpad, 1, nullptr, 0, nparts_out, stage, stage);
 }
 

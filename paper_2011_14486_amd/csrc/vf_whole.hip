@@ -603,6 +603,32 @@ __global__ __launch_bounds__(512) void k_open_layer(vf_fast_dev md, const uint32
   no_minima(pval + (size_t)p * nparts, pidx + (size_t)p * nparts, os.ncand, nparts, tid);
 }
 
+// Between two LAYER launches of a greedy schedule: the decision of `stage` from the parts' minima,
+// committed, and (open) the next decision opened; one workgroup per problem.  One launch instead of
+// a commit and an opening that hands the context through memory.
+template <int RT>
+__global__ __launch_bounds__(512) void k_greedy_advance(Tables t, int stage, int open, uint32_t M, int64_t Mpad,
+                                                        vf_fast_dev md, uint32_t *decpack, uint32_t *pub, uint32_t *list,
+                                                        float *pval, int32_t *pidx, int nparts) {
+  __shared__ AdvanceShared sh;
+  const int tid = threadIdx.x, lane = tid & 63, p = blockIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint32_t *const ctx = decpack + (size_t)p * VF_DECPACK_DWORDS;
+  if (tid < VF_DECPACK_DWORDS) reinterpret_cast<uint32_t *>(&sh.pk)[tid] = ctx[tid];
+  pval += (size_t)p * nparts;
+  pidx += (size_t)p * nparts;
+  if (w == 7) {  // (the wave with the least to fetch)
+    float v = __builtin_inff();
+    int32_t c = -1;
+    for (int q = lane; q < nparts; q += 64) take_min(v, c, pval[q], pidx[q]);
+    wave_min(v, c);
+    if (lane == 0) { sh.cid = c; sh.val = v; }
+  }
+  advance_layer<RT>(sh, t, t, p, p, stage, open, M, md, pub + (size_t)p * VF_PUB_WORDS, list + (size_t)p * Mpad, ctx, tid, w,
+                    lane);
+  if (open) no_minima(pval, pidx, sh.os.ncand, nparts, tid);
+}
+
 __global__ __launch_bounds__(256) void k_zero_u32(unsigned int *p, size_t n) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n) p[i] = 0u;
@@ -693,6 +719,18 @@ int vfk_whole_team(const vf_ctx *c) {
   // decision the teams stay ahead, 2.45 against 2.6 ms)
   if (team >= 2 && (ncu - c->B * team) * 5 >= ncu && nparts >= 64) return 1;
   return team >= 2 ? team : 0;
+}
+
+// Whether whole schedules in one launch are faster than two launches per layer on lists, where
+// both can run: with a problem for most compute units but none for a second round.  The launches per
+// layer deal out the tiles of all problems evenly and wait for nobody, but pay two launches and a
+// serial opening per layer (256-512-512-1, 20 layers of 4096 ids: 64 problems 1.61 against 1.14 ms per
+// layer, 128: 2.06 / 1.75, 160: 2.52 / 2.05, 200: 2.65 / 2.46, 256: 2.95 / 2.98, 300: 4.57 / 3.46;
+// 100 layers of 16384 ids: 100 problems 13.0 / 11.6, 160: 17.1 / 16.9, 180: 18.4 / 18.6, 200: 19.7 / 20.5).
+bool vfk_whole_pays(const vf_ctx *c) {
+  int ncu = 256;
+  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
+  return c->B > ncu * 5 / 8 && c->B <= ncu && vfk_whole_team(c) >= 1;
 }
 
 // Algorithm 1 over stages first..last for every problem of the batch, one launch.
@@ -853,4 +891,24 @@ int vfk_layer_score(vf_ctx *c, int noise_stage, float *scores, int *nparts_out) 
   VF_HIP(c, hipGetLastError());
   *nparts_out = wa.nparts;
   return VF_OK;
+}
+
+// Algorithm 1 over stages first..last on lists of valid candidates, two launches per layer.
+int vfk_greedy_layers(vf_ctx *c, int first, int last) {
+  int rc = vfk_layer_open(c, first);
+  vf_fast_dev fd;
+  vfk_fast_dev(c, true, &fd, nullptr, nullptr);
+  for (int i = first; i <= last && rc == VF_OK; ++i) {
+    int nparts = 0;
+    rc = vfk_layer_score(c, i, nullptr, &nparts);
+    if (rc != VF_OK) return rc;
+    vf_prof_scope prof(c, VF_PROF_COMMIT);
+    c->dec_stage = -1;
+    hipLaunchKernelGGL((c->pm.fast_rt == 4 ? k_greedy_advance<4> : k_greedy_advance<2>), dim3((unsigned)c->B), dim3(512), 0,
+                       c->stream, tables_of(c), i, (int)(i < last), (uint32_t)c->M, (int64_t)c->Mpad, fd, c->d_decpack,
+                       c->d_pub, reinterpret_cast<uint32_t *>(c->d_wlist), c->d_pval, c->d_pidx, nparts);
+    VF_HIP(c, hipGetLastError());
+    c->n_sched = i + 1;
+  }
+  return rc;
 }

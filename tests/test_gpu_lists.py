@@ -20,6 +20,39 @@ def context(vf, pipes, sp, model, w):
     return ctx
 
 
+# (widths, problems, ids per decision): more tiles than compute units on one side, one problem with
+# one round of tiles on the other; ragged lists, one to three hidden layers, both tile shapes
+@pytest.mark.parametrize("dims", [[256, 512, 512, 1], [256, 512, 1], [256, 512, 512, 512, 1], [256, 1024, 1024, 1],
+                                  [64, 512, 512, 1]])
+def test_batch_on_lists_equals_single_problems(vf, dims):
+    """The same arithmetic candidate by candidate: ids and values of every layer are bit-identical,
+    with noise, and with problems whose schedules end early (stage 1 has no valid candidate)."""
+    B, sp = 45, I.make_space([1, 2, 4], [1, 2, 4, 8], [1, 8, 16], I.XC_INNER_PERMS, 2, 2, [I.ROOT, I.L1, I.L2, I.INLINE], 2,
+                             dims[0])
+    pipes = np.stack([I.random_pipeline(6, 70 + b) for b in range(B)])
+    w, model = I.mlp_weights(dims, 4, bias_std=0.1), I.model_record(I.MLP, dims, I.BF16)
+    many = context(vf, pipes, sp, model, w)
+    vf.vf_set_noise(many, 0.2, 9, 0)
+    vf.vf_profile_enable(many, True); vf.vf_profile_counts(many)
+    whole = [t.cpu().numpy() for t in vf.vf_greedy_schedule(many)]
+    scored, valid = vf.vf_profile_counts(many)
+    assert scored == valid > 0                     # only listed candidates were scored
+    vf.vf_profile_enable(many, False)
+    vf.vf_reset_state(many)
+    for i in range(6):
+        vf.vf_argmin_step(many, i, True)
+    steps = [t.cpu().numpy() for t in vf.vf_greedy_schedule(many, first=6)]
+    for a, b in zip(whole, steps):
+        assert np.array_equal(a, b)
+    for b in range(0, B, 4):
+        one = context(vf, pipes[b], sp, model, w)
+        vf.vf_set_noise(one, 0.2, 9, b)
+        st, cids, vals = (t.cpu().numpy()[0] for t in vf.vf_greedy_schedule(one))
+        assert np.array_equal(cids, whole[1][b]) and np.array_equal(st, whole[0][b]) and np.array_equal(vals, whole[2][b])
+        vf.vf_destroy(one)
+    vf.vf_destroy(many)
+
+
 # the factors make the number of ids of a decision: the search works on lists from 64 tiles of 128 on
 @pytest.mark.parametrize("K,fac,const", [(2, [1, 2, 4, 8], True), (33, [1, 2, 4], True), (33, [1, 2, 4], False),
                                          (300, [1, 4], False), (1024, [1, 4], True)])
