@@ -26,6 +26,16 @@ struct vf_partbuf {
   size_t cap;
 };
 
+// A small MLP packed for the kernels of vf_small.hip: per layer row tiles (nt), k-steps or groups of
+// 16 input rows (kst), offsets of its weights (16-byte units) and biases (floats).
+struct vf_small_dev {
+  const uint4 *w = nullptr;
+  const float *bias = nullptr;
+  int nw = 0, nbias = 0, L = 0, NT = 0;  // NT: row tiles of every hidden layer
+  int dims[8] = {0}, nt[8] = {0}, kst[8] = {0}, woff[8] = {0}, boff[8] = {0};
+  int wl_off = 0;  // fp32: the output vector behind the biases
+};
+
 struct vf_packed_model {
   // fp32 path: the caller's blob copied as is
   float *w_f32 = nullptr;
@@ -47,6 +57,8 @@ struct vf_packed_model {
   // the candidate.  The stream with the first layer cut to k-steps 1..3 (rows 16..63)
   uint16_t *w_stream_fold = nullptr;
   size_t wave_stride_fold = 0;
+  vf_small_dev small;              // small.w null: not small enough
+  void *small_buf = nullptr;
   // recurrent network wired to the search: [W_ih | W_hh] transposed, bf16 values as fp32, [64+H][4H]
   float *w_seqT = nullptr;
 };
@@ -222,10 +234,14 @@ void vfk_free_model(vf_ctx *c);
 // use_valid_row: row 16 of x is the validity flag (invalid -> +inf).
 // noise_stage >= 0: the context's exploration noise for that layer is added before the scan.
 // Writes scores (nullable, [nprob][ld_scores]) and the partial minima
-// (ctx->d_pval / d_pidx, [nprob][nparts], ids local to the problem).
+// (ctx->d_pval / d_pidx, [nprob][nparts], ids local to the problem), one per part_out candidates.
 int vfk_score_mlp(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob, int64_t M, int64_t ld,
                   int use_valid_row, float *scores, int64_t ld_scores, int *nparts_out, int noise_stage,
-                  const vf_partbuf *parts = nullptr);
+                  const vf_partbuf *parts = nullptr, int *part_out = nullptr);
+// The same for small models (vf_small.hip), used where pm.small.w is set.
+int vfk_pack_small(vf_ctx *c, const float *weights_dev);
+int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob, int64_t M, int64_t ld, int use_valid_row,
+                    float *scores, int64_t ld_scores, int noise_stage, const vf_partbuf *parts, int *nparts_out, int *part_out);
 // Enumerate + featurize + score + partial argmin of one stage in a single kernel (bf16
 // MLPs of uniform hidden width whose input width is the space's F).
 bool vfk_can_fuse_step(const vf_ctx *c);

@@ -107,17 +107,26 @@ __global__ __launch_bounds__(VF_PART) void k_argmin_parts(const float *scores, i
   }
 }
 
-// Final scan per group of candidates over the partial minima.
-__global__ __launch_bounds__(64) void k_argmin_groups(const float *pval, const int32_t *pidx, int nparts,
-                                                      int parts_per_group, int32_t *best_idx, float *best_val) {
-  const int g = blockIdx.x;
+// Final scan per group of candidates over the partial minima: a wave per group, or sixteen
+// where the groups have many (one group of 1563 parts: 14 us with one wave, whose reads follow each other).
+__global__ __launch_bounds__(1024) void k_argmin_groups(const float *pval, const int32_t *pidx, int nparts,
+                                                        int parts_per_group, int32_t *best_idx, float *best_val) {
+  __shared__ float sv[16];
+  __shared__ int32_t sc[16];
+  const int g = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const int lo = g * parts_per_group;
   int hi = lo + parts_per_group;
   if (hi > nparts) hi = nparts;
   float v = __builtin_inff();
   int32_t c = -1;
-  for (int p = lo + (int)threadIdx.x; p < hi; p += 64) take_min(v, c, pval[p], pidx[p]);
+  for (int p = lo + (int)threadIdx.x; p < hi; p += (int)blockDim.x) take_min(v, c, pval[p], pidx[p]);
   wave_min(v, c);
+  if (nw > 1) {
+    if (lane == 0) { sv[w] = v; sc[w] = c; }
+    __syncthreads();
+    if (threadIdx.x == 0)
+      for (int k = 1; k < nw; ++k) take_min(v, c, sv[k], sc[k]);
+  }
   if (threadIdx.x == 0) {
     if (best_idx) best_idx[g] = c;
     if (best_val) best_val[g] = v;
@@ -1039,6 +1048,7 @@ void vfk_free_model(vf_ctx *c) {
   if (c->pm.w_stream) (void)hipFree(c->pm.w_stream);
   if (c->pm.w_stream_fold) (void)hipFree(c->pm.w_stream_fold);
   if (c->pm.w_seqT) (void)hipFree(c->pm.w_seqT);
+  if (c->pm.small_buf) (void)hipFree(c->pm.small_buf);
   if (c->pm.aux) (void)hipFree(c->pm.aux);
   c->pm = vf_packed_model();
 }
@@ -1048,6 +1058,10 @@ int vfk_pack_model(vf_ctx *c, const float *wdev) {
   vf_packed_model &pm = c->pm;
   hipStream_t st = c->stream;
   auto blocks = [](size_t n) { return dim3((unsigned)((n + 255) / 256)); };
+  if (m.kind == VF_MLP) {
+    const int rc = vfk_pack_small(c, wdev);
+    if (rc != VF_OK || pm.small.w) return rc;
+  }
   if (m.kind == VF_MLP && m.dtype == VF_FP32) {
     size_t n = 0;
     for (int l = 0; l < m.n_layers; ++l) n += (size_t)m.dims[l] * m.dims[l + 1] + m.dims[l + 1];
@@ -1162,13 +1176,13 @@ int vfk_pack_model(vf_ctx *c, const float *wdev) {
 
 static int score_mlp(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob, int64_t M, int64_t ld,
                      int use_valid_row, float *scores, int64_t ld_scores, int *nparts_out, int gen_stage,
-                     int noise_stage, const vf_partbuf *parts = nullptr);
+                     int noise_stage, const vf_partbuf *parts = nullptr, int *part_out = nullptr);
 
 int vfk_score_mlp(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob, int64_t M, int64_t ld,
                   int use_valid_row, float *scores, int64_t ld_scores, int *nparts_out, int noise_stage,
-                  const vf_partbuf *parts) {
+                  const vf_partbuf *parts, int *part_out) {
   return score_mlp(c, x, prob_stride, nprob, M, ld, use_valid_row, scores, ld_scores, nparts_out, -1, noise_stage,
-                   parts);
+                   parts, part_out);
 }
 
 bool vfk_can_fuse_step(const vf_ctx *c) {
@@ -1304,7 +1318,12 @@ void vfk_fast_dev(const vf_ctx *c, bool generating, vf_fast_dev *fd, int *ks, in
 
 static int score_mlp(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob, int64_t M, int64_t ld,
                      int use_valid_row, float *scores, int64_t ld_scores, int *nparts_out, int gen_stage,
-                     int noise_stage, const vf_partbuf *parts) {
+                     int noise_stage, const vf_partbuf *parts, int *part_out) {
+  int part_here = 0;
+  if (!part_out) part_out = &part_here;
+  if (gen_stage < 0 && c->pm.small.w)
+    return vfk_score_small(c, x, prob_stride, nprob, M, ld, use_valid_row, scores, ld_scores, noise_stage, parts, nparts_out,
+                           part_out);
   NoiseArgs na;
   na.eps = noise_stage >= 0 ? c->noise_eps : 0.0f;
   na.k0 = (uint32_t)c->noise_seed; na.k1 = (uint32_t)(c->noise_seed >> 32);
@@ -1323,6 +1342,7 @@ static int score_mlp(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob
     if (rc != VF_OK) return rc;
     c->act_elems = h0 < h1 ? h0 : h1;
     const int nparts = (int)((M + VF_PART - 1) / VF_PART);
+    *part_out = VF_PART;
     rc = vfk_ensure_parts(c, (size_t)nparts * nprob);
     if (rc != VF_OK) return rc;
     const float *wp = c->pm.w_f32;
@@ -1379,6 +1399,7 @@ static int score_mlp(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob
   // contraction of a tile - most of the time a layer takes - is half as long.
   const bool narrow = !wide && gen_stage >= 0 && c->pm.fast_rt && ((M + 127) / 128) * nprob * 2 <= ncu;  // (see narrow_step)
   const int NC = (wide || narrow) ? 64 : 128;
+  *part_out = NC;
   const int nparts = (int)((M + NC - 1) / NC);
   float *pval = nullptr;
   int32_t *pidx = nullptr;
@@ -1492,7 +1513,7 @@ int vfk_score_lstm(vf_ctx *c, const uint16_t *x, int64_t M, int T, float *scores
 int vfk_argmin_groups(vf_ctx *c, int64_t M, int nparts, int parts_per_group, int ngroups, int32_t *best_idx,
                       float *best_val, const vf_partbuf *parts) {
   (void)M;
-  hipLaunchKernelGGL(k_argmin_groups, dim3((unsigned)ngroups), dim3(64), 0, c->stream,
+  hipLaunchKernelGGL(k_argmin_groups, dim3((unsigned)ngroups), dim3(parts_per_group > 256 ? 1024 : 64), 0, c->stream,
                      parts ? parts->val : c->d_pval, parts ? parts->idx : c->d_pidx, nparts,
                      parts_per_group, best_idx, best_val);
   VF_HIP(c, hipGetLastError());

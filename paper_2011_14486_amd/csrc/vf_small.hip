@@ -1,0 +1,630 @@
+// Small MLPs (hidden layers of up to 128 units) in one launch (gfx950).
+//
+// The whole network fits the LDS, so a workgroup stages the weights once and then walks over its
+// candidates; every wave takes candidates of its own through all layers and never waits for another
+// one.  Between two layers nothing moves: the accumulator of a product holds, for a lane's own column,
+// rows that the B operand of the next product wants from exactly this lane, only in another order
+// inside a k-step, and that order is free as long as the weights are packed to match
+// (pack_k_bf16, and the rows as they come for fp32).  bf16 runs on 32x32x16 products, fp32 on
+// 16x16x4 products, whose sums stay in fp32.
+//
+// 64-128-128-1 through vf_score, one launch and the scan (before: a workgroup per 128 candidates with
+// two barriers per layer and the weights out of L2 for bf16; layer after layer through memory, on the
+// vector ALU, for fp32): bf16 200,003 vectors 102 -> 32 us, a million 447 -> 83 us (3.2 TB/s of inputs);
+// fp32 192,000 vectors 286 -> 88 us, a million 1889 -> 437 us (113 TFLOP/s of the 154 that a large fp32
+// matrix product reaches).  Where the network does not fit (a hidden layer of more than 128 units:
+// the activations' registers; more than 150 KB of weights) the kernels of vf_score.hip run.
+#include "vf_internal.h"
+
+namespace {
+
+#include "vf_sched_dev.h"
+
+#include "vf_score_dev.h"
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef int32_t intx2 __attribute__((ext_vector_type(2), aligned(4)));  // 8-byte loads and stores of 4-byte aligned pairs
+typedef float floatx2 __attribute__((ext_vector_type(2), aligned(4)));
+
+constexpr int SMALL_MAX = 128;        // widest hidden layer
+constexpr int SMALL_LDS = 150 * 1024; // weights and biases
+
+// Input row (within a k-step of 16) of element e of lane half h: as they come for the first layer,
+// in the order of the accumulator's rows for the others.
+__device__ __forceinline__ int pack_k_bf16(bool first, int h, int e) { return first ? 8 * h + e : (e < 4 ? 4 * h + e : 4 + 4 * h + e); }
+
+// out[tile][kstep][lane][e] = W[tile * 32 + lane % 32][kstep * 16 + pack_k_bf16(lane / 32, e)], zeros in the padding
+__global__ __launch_bounds__(256) void k_pack_small_bf16(const float *W, int N, int K, int ntiles, int ksteps, int first,
+                                                         uint16_t *out) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= ntiles * ksteps * 512) return;
+  const int e = i & 7, lane = (i >> 3) & 63, s = (i >> 9) % ksteps, tile = (i >> 9) / ksteps;
+  const int row = tile * 32 + (lane & 31), k = s * 16 + pack_k_bf16(first != 0, lane >> 5, e);
+  out[i] = row < N && k < K ? (uint16_t)bf16_bits(W[(size_t)row * K + k]) : (uint16_t)0;
+}
+
+// out[tile][kgroup][lane][e] = W[tile * 16 + lane % 16][kgroup * 16 + 4 (lane / 16) + e], zeros in the padding
+__global__ __launch_bounds__(256) void k_pack_small_f32(const float *W, int N, int K, int ntiles, int groups, float *out) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= ntiles * groups * 256) return;
+  const int e = i & 3, lane = (i >> 2) & 63, g = (i >> 8) % groups, tile = (i >> 8) / groups;
+  const int row = tile * 16 + (lane & 15), k = g * 16 + 4 * (lane >> 4) + e;
+  out[i] = row < N && k < K ? W[(size_t)row * K + k] : 0.0f;
+}
+
+__global__ __launch_bounds__(256) void k_pad_f32(const float *src, int n, int npad, float *dst) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < npad) dst[i] = i < n ? src[i] : 0.0f;
+}
+
+// A unit is one partial minimum: `spp` sub-tiles of candidates in a row, taken by one wave.
+struct SmallArgs {
+  vf_small_dev md;
+  const int32_t *x;
+  int64_t prob_stride, M, ld;
+  int use_valid_row;
+  float *scores;      // nullable
+  int64_t ld_scores;
+  float *pval;
+  int32_t *pidx;
+  int nparts, units, spp;
+  NoiseArgs na;
+};
+
+__device__ __forceinline__ void stage_small(const SmallArgs &a, uint4 *wl, float *bl) {
+#pragma unroll 4
+  for (int i = threadIdx.x; i < a.md.nw; i += 512) wl[i] = a.md.w[i];
+  for (int i = threadIdx.x; i < a.md.nbias; i += 512) bl[i] = a.md.bias[i];
+  __syncthreads();
+}
+
+// ROWS rows of raw values of a lane: N consecutive ones of every row, the rows `ld` apart, and
+// `skip` more between row SPLIT - 1 and row SPLIT.  Whole sub-tiles take a row in one load; otherwise
+// only the `left` values that there are get loaded.  (One address at a time: the scheduler would
+// work them all out first and fill the registers with them.)
+template <int ROWS, int SPLIT, int N>
+__device__ __forceinline__ void load_raw(int32_t (&r)[ROWS][N], const int32_t *p, int64_t ld, int64_t skip, int left, bool whole) {
+  if (whole) {
+#pragma unroll
+    for (int e = 0; e < ROWS; ++e) {
+      if (N == 2) {
+        const intx2 v = *reinterpret_cast<const intx2 *>(p);
+        r[e][0] = v[0];
+        r[e][N - 1] = v[1];
+      } else {
+        r[e][0] = p[0];
+      }
+      p += e + 1 == SPLIT ? ld + skip : ld;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < ROWS; ++e) {
+#pragma unroll
+      for (int c = 0; c < N; ++c) r[e][c] = c < left ? p[c] : 0;
+      p += e + 1 == SPLIT ? ld + skip : ld;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
+// 32 * CT candidates per sub-tile, lane l has columns CT (l % 32) + 0 .. CT - 1.  The matrix products
+// of a sub-tile of 64 (64-128-128-1: 100 of them, 3200 cycles) and the conversion of its inputs cost
+// about the same; two waves per SIMD overlap one's with the other's, and the next 32 input rows are
+// always under way.
+template <int CT, int NT>
+__global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  uint4 *const wl = reinterpret_cast<uint4 *>(smem);
+  float *const bl = reinterpret_cast<float *>(wl + a.md.nw);
+  const int lane = threadIdx.x & 63, h = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  stage_small(a, wl, bl);
+  const int L = a.md.L, K0 = a.md.dims[0], chunks = K0 / 32;
+  floatx16 zero;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) zero[j] = 0.0f;
+  auto mfma = [](uint4 x, uint4 y, floatx16 z) __attribute__((always_inline)) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), z, 0, 0, 0);
+  };
+  // plus bias, rounded to bf16, ReLU on the pairs: half a row tile of the accumulator as the B operand
+  // of a k-step.  (The bias as the products' first addend would be less work, but the sums would be
+  // less exact: 4.1e-5 instead of 3.3e-5 off a 64-bit sum in the scores of 64-128-128-1.)
+  auto frag = [&](const floatx16 &v, int l, int t, int s2, int at) __attribute__((always_inline)) {
+    const float *bb = bl + a.md.boff[l] + t * 32 + 16 * s2 + 4 * (at >> 5);
+    const float4 p = *reinterpret_cast<const float4 *>(bb), q = *reinterpret_cast<const float4 *>(bb + 8);
+    uint4 b;
+    b.x = relu_bf16x2(pack_bf16(v[8 * s2 + 0] + p.x, v[8 * s2 + 1] + p.y));
+    b.y = relu_bf16x2(pack_bf16(v[8 * s2 + 2] + p.z, v[8 * s2 + 3] + p.w));
+    b.z = relu_bf16x2(pack_bf16(v[8 * s2 + 4] + q.x, v[8 * s2 + 5] + q.y));
+    b.w = relu_bf16x2(pack_bf16(v[8 * s2 + 6] + q.z, v[8 * s2 + 7] + q.w));
+    return b;
+  };
+  int32_t raw[16][CT];  // 32 input rows: per k-step eight rows of the lane half; column
+  auto fetch = [&](int p, int64_t n0, int ch) __attribute__((always_inline)) {
+    const int32_t *row = a.x + (size_t)p * a.prob_stride + n0 + (size_t)(ch * 32 + 8 * h) * a.ld;
+    const int left = (int)(a.M - n0 < 32 * CT ? a.M - n0 : 32 * CT) - CT * (lane & 31);
+    load_raw<16, 8, CT>(raw, row + CT * (lane & 31), a.ld, 8 * a.ld, left, n0 + 32 * CT <= a.M);
+  };
+  const int stride = (int)gridDim.x * 8;
+  int u = (int)blockIdx.x + (int)gridDim.x * w, sub = 0;
+  if (u >= a.units) return;
+  int p = u / a.nparts, part = u - p * a.nparts;
+  int64_t n0 = (int64_t)part * a.spp * 32 * CT;
+  fetch(p, n0, 0);
+  float v = __builtin_inff();
+  int32_t vc = -1;
+  for (;;) {
+    // the sub-tile after this one
+    int nu = u, nsub = sub + 1, np = p, npart = part;
+    int64_t nn0 = n0 + 32 * CT;
+    const bool ends = nsub >= a.spp || nn0 >= a.M;
+    if (ends) {
+      nu = u + stride;
+      nsub = 0;
+      np = nu / a.nparts;
+      npart = nu - np * a.nparts;
+      nn0 = (int64_t)npart * a.spp * 32 * CT;
+    }
+    const bool more = nu < a.units;
+    if (!more) { np = p; nn0 = n0; }
+    // (the weights and biases that a sub-tile starts with are read afresh from LDS for every one: kept
+    // across the sub-tiles they would fill the registers)
+    int at = lane;
+    asm volatile("" : "+v"(at));
+    bool ok[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) ok[c] = n0 + CT * (lane & 31) + c < a.M;
+    // ---- first layer (a network without a hidden layer has one row tile there: its output vector)
+    floatx16 acc[NT][CT];
+    const int ks0 = a.md.kst[0];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int c = 0; c < CT; ++c) acc[t][c] = zero;
+    // (a weight fragment is refilled in place behind its last product; the refill behind the last
+    // k-step reads into what follows the layer's weights and is not used)
+    const uint4 *wp = wl + at;
+    uint4 x[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) x[t] = wp[t * ks0 * 64];
+    for (int ch = 0; ch < chunks; ++ch) {
+      uint4 in[2][CT];
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+          uint4 q;
+          q.x = pack_bf16(plog2_dev(raw[8 * s + 0][c]), plog2_dev(raw[8 * s + 1][c]));
+          q.y = pack_bf16(plog2_dev(raw[8 * s + 2][c]), plog2_dev(raw[8 * s + 3][c]));
+          q.z = pack_bf16(plog2_dev(raw[8 * s + 4][c]), plog2_dev(raw[8 * s + 5][c]));
+          q.w = pack_bf16(plog2_dev(raw[8 * s + 6][c]), plog2_dev(raw[8 * s + 7][c]));
+          in[s][c] = q;
+          // row 16 is the validity flag (lane half 0; only its columns are scanned)
+          if (s == 1 && ch == 0 && a.use_valid_row) ok[c] = ok[c] && raw[8][c] != 0;
+        }
+      const bool onward = ch + 1 == chunks;  // (behind the last sub-tile of all: the same one once more)
+      fetch(onward ? np : p, onward ? nn0 : n0, onward ? 0 : ch + 1);
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        wp += 64;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+#pragma unroll
+          for (int c = 0; c < CT; ++c) acc[t][c] = mfma(x[t], in[s][c], acc[t][c]);
+          x[t] = wp[t * ks0 * 64];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+    // ---- the other hidden layers, two row tiles at a time (all of them at once would not leave
+    // registers for the input rows under way), then the output vector as a row tile with one row
+    if (L > 1) {
+      uint4 act[2 * NT][CT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+          act[2 * t][c] = frag(acc[t][c], 0, t, 0, at);
+          act[2 * t + 1][c] = frag(acc[t][c], 0, t, 1, at);
+        }
+      for (int l = 1; l < L - 1; ++l) {
+        constexpr int TH = NT < 2 ? NT : 2;
+        uint4 out[2 * NT][CT];
+#pragma unroll
+        for (int t0 = 0; t0 < NT; t0 += TH) {
+          floatx16 part[TH][CT];
+          wp = wl + a.md.woff[l] + at;
+#pragma unroll
+          for (int t = 0; t < TH; ++t)
+            if (t0 + t < NT) {
+#pragma unroll
+              for (int c = 0; c < CT; ++c) part[t][c] = zero;
+              x[t] = wp[(t0 + t) * 2 * NT * 64];
+            }
+#pragma unroll
+          for (int s = 0; s < 2 * NT; ++s)
+#pragma unroll
+            for (int t = 0; t < TH; ++t)
+              if (t0 + t < NT) {
+#pragma unroll
+                for (int c = 0; c < CT; ++c) part[t][c] = mfma(x[t], act[s][c], part[t][c]);
+                if (s + 1 < 2 * NT) x[t] = wp[((t0 + t) * 2 * NT + s + 1) * 64];
+                __builtin_amdgcn_sched_barrier(0);
+              }
+#pragma unroll
+          for (int t = 0; t < TH; ++t)
+            if (t0 + t < NT) {
+#pragma unroll
+              for (int c = 0; c < CT; ++c) {
+                out[2 * (t0 + t)][c] = frag(part[t][c], l, t0 + t, 0, at);
+                out[2 * (t0 + t) + 1][c] = frag(part[t][c], l, t0 + t, 1, at);
+              }
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 2 * NT; ++s)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) act[s][c] = out[s][c];
+      }
+      wp = wl + a.md.woff[L - 1] + at;
+#pragma unroll
+      for (int c = 0; c < CT; ++c) acc[0][c] = zero;
+#pragma unroll
+      for (int s = 0; s < 2 * NT; ++s) {
+        const uint4 y = wp[s * 64];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) acc[0][c] = mfma(y, act[s][c], acc[0][c]);
+      }
+    }
+    // ---- row 0 of the last product (element 0 of lanes 0..31) is the score
+    {
+      float s[CT];
+#pragma unroll
+      for (int c = 0; c < CT; ++c) s[c] = acc[0][c][0] + bl[a.md.boff[L - 1]];
+      const int64_t n = n0 + CT * (lane & 31);
+      if (lane < 32) {
+        if (a.scores) {
+          float *dst = a.scores + (size_t)p * a.ld_scores + n;
+          if (CT == 2 && n + 1 < a.M) {
+            *reinterpret_cast<floatx2 *>(dst) = floatx2{s[0], s[CT - 1]};
+          } else {
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+              if (n + c < a.M) dst[c] = s[c];
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+          float sc = s[c];
+          if (a.na.eps != 0.0f) sc = add_noise(a.na, sc, p, (int32_t)(n + c));
+          if (ok[c] && sc < v) { v = sc; vc = (int32_t)(n + c); }
+        }
+      }
+      if (ends) {
+        wave_min(v, vc);
+        if (lane == 0) {
+          a.pval[u] = v;
+          a.pidx[u] = vc;
+        }
+        v = __builtin_inff();
+        vc = -1;
+      }
+    }
+    if (!more) break;
+    u = nu; sub = nsub; p = np; part = npart; n0 = nn0;
+  }
+}
+
+// 16 * CT candidates per sub-tile, lane l has columns CT (l % 16) + 0 .. CT - 1 and rows 4 (l / 16) + 0..3
+// of every 16.  The output vector is a dot product on the vector ALU (a sixteenth of a row tile
+// would be used), the four lane groups' parts added at the end.
+template <int CT, int NT>
+__global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  uint4 *const wl = reinterpret_cast<uint4 *>(smem);
+  const floatx4 *const wf = reinterpret_cast<const floatx4 *>(smem);
+  float *const bl = reinterpret_cast<float *>(wl + a.md.nw);
+  const int lane = threadIdx.x & 63, q = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  stage_small(a, wl, bl);
+  const int L = a.md.L, K0 = a.md.dims[0], groups0 = a.md.kst[0], chunks = (groups0 + 1) / 2;
+  int32_t raw[8][CT];  // 32 input rows: per group of 16 four rows of the lane group; column
+  auto fetch = [&](int p, int64_t n0, int ch) __attribute__((always_inline)) {
+    const int32_t *col = a.x + (size_t)p * a.prob_stride + n0 + CT * (lane & 15);
+    const int left = (int)(a.M - n0 < 16 * CT ? a.M - n0 : 16 * CT) - CT * (lane & 15);
+    if (ch * 32 + 32 <= K0) {
+      load_raw<8, 4, CT>(raw, col + (size_t)(ch * 32 + 4 * q) * a.ld, a.ld, 12 * a.ld, left, n0 + 16 * CT <= a.M);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int r = ch * 32 + (e >> 2) * 16 + 4 * q + (e & 3);
+        // (a row past the last one has zero weights: any row will do, its values are finite)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) raw[e][c] = c < left ? col[(r < K0 ? r : 0) * a.ld + c] : 0;
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+  const int stride = (int)gridDim.x * 8;
+  int u = (int)blockIdx.x + (int)gridDim.x * w, sub = 0;
+  if (u >= a.units) return;
+  int p = u / a.nparts, part = u - p * a.nparts;
+  int64_t n0 = (int64_t)part * a.spp * 16 * CT;
+  fetch(p, n0, 0);
+  float v = __builtin_inff();
+  int32_t vc = -1;
+  for (;;) {
+    int nu = u, nsub = sub + 1, np = p, npart = part;
+    int64_t nn0 = n0 + 16 * CT;
+    const bool ends = nsub >= a.spp || nn0 >= a.M;
+    if (ends) {
+      nu = u + stride;
+      nsub = 0;
+      np = nu / a.nparts;
+      npart = nu - np * a.nparts;
+      nn0 = (int64_t)npart * a.spp * 16 * CT;
+    }
+    const bool more = nu < a.units;
+    if (!more) { np = p; nn0 = n0; }
+    // (the weights and biases that a sub-tile starts with are read afresh from LDS for every one: kept
+    // across the sub-tiles they would fill the registers)
+    int at = lane;
+    asm volatile("" : "+v"(at));
+    bool ok[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) ok[c] = n0 + CT * (lane & 15) + c < a.M;
+    floatx4 acc[NT][CT];
+    float s[CT];
+    const bool only = L == 1;  // no hidden layer: the inputs go straight into the output dot
+#pragma unroll
+    for (int c = 0; c < CT; ++c) s[c] = 0.0f;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int c = 0; c < CT; ++c) acc[t][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    // (a weight fragment is refilled in place behind its last product; the refill behind the last
+    // group reads into what follows the layer's weights and is not used)
+    constexpr int TH = NT / 2;  // fragments in flight
+    floatx4 x[TH];
+#pragma unroll
+    for (int t = 0; t < TH; ++t) x[t] = wf[(only ? 0 : t * groups0 * 64) + at];
+    for (int ch = 0; ch < chunks; ++ch) {
+      float in[2][4][CT];
+#pragma unroll
+      for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) in[g][e][c] = plog2_dev(raw[4 * g + e][c]);
+      if (ch == 0 && a.use_valid_row) {
+#pragma unroll
+        for (int c = 0; c < CT; ++c) ok[c] = ok[c] && raw[4][c] != 0;
+      }
+      const bool onward = ch + 1 == chunks;  // (behind the last sub-tile of all: the same one once more)
+      fetch(onward ? np : p, onward ? nn0 : n0, onward ? 0 : ch + 1);
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        const int kg = ch * 2 + g;
+        if (kg >= groups0) break;
+        if (only) {
+          const floatx4 y = *reinterpret_cast<const floatx4 *>(bl + a.md.wl_off + kg * 16 + 4 * (at >> 4));
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) s[c] = fmaf(y[e], in[g][e][c], s[c]);
+          continue;
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t % TH][e], in[g][e][c], acc[t][c], 0, 0, 0);
+          x[t % TH] = t < TH ? wf[((t + TH) * groups0 + kg) * 64 + at] : wf[((t - TH) * groups0 + kg + 1) * 64 + at];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+    if (!only) {
+      // a finished layer: bias, ReLU, and its rows are the next one's inputs as they lie
+      auto finish = [&](const floatx4 &v, int l, int t) __attribute__((always_inline)) {
+        const floatx4 b = *reinterpret_cast<const floatx4 *>(bl + a.md.boff[l] + t * 16 + 4 * (at >> 4));
+        floatx4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = relu_keep_nan(v[e] + b[e]);
+        return o;
+      };
+      floatx4 act[NT][CT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) act[t][c] = finish(acc[t][c], 0, t);
+      for (int l = 1; l < L - 1; ++l) {
+        // half of the row tiles at a time, as above
+        floatx4 out[NT][CT];
+        const floatx4 *wp = wf + a.md.woff[l] + at;
+#pragma unroll
+        for (int t0 = 0; t0 < NT; t0 += TH) {
+          floatx4 part[TH][CT];
+#pragma unroll
+          for (int t = 0; t < TH; ++t) {
+#pragma unroll
+            for (int c = 0; c < CT; ++c) part[t][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+            x[t] = wp[(t0 + t) * NT * 64];
+          }
+#pragma unroll
+          for (int kg = 0; kg < NT; ++kg)
+#pragma unroll
+            for (int t = 0; t < TH; ++t) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int c = 0; c < CT; ++c) part[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t][e], act[kg][c][e], part[t][c], 0, 0, 0);
+              if (kg + 1 < NT) x[t] = wp[((t0 + t) * NT + kg + 1) * 64];
+              __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+          for (int t = 0; t < TH; ++t)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) out[t0 + t][c] = finish(part[t][c], l, t0 + t);
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) act[t][c] = out[t][c];
+      }
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const floatx4 y = *reinterpret_cast<const floatx4 *>(bl + a.md.wl_off + t * 16 + 4 * (at >> 4));
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) s[c] = fmaf(y[e], act[t][c][e], s[c]);
+      }
+    }
+    const float bout = bl[a.md.boff[L - 1]];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      s[c] += __shfl_xor(s[c], 16);
+      s[c] += __shfl_xor(s[c], 32);
+      s[c] += bout;
+    }
+    const int64_t n = n0 + CT * (lane & 15);
+    if (lane < 16) {
+#pragma unroll
+      for (int c = 0; c < CT; ++c) {
+        if (a.scores && n + c < a.M) a.scores[(size_t)p * a.ld_scores + n + c] = s[c];
+        float sc = s[c];
+        if (a.na.eps != 0.0f) sc = add_noise(a.na, sc, p, (int32_t)(n + c));
+        if (ok[c] && sc < v) { v = sc; vc = (int32_t)(n + c); }
+      }
+    }
+    if (ends) {
+      wave_min(v, vc);
+      if (lane == 0) {
+        a.pval[u] = v;
+        a.pidx[u] = vc;
+      }
+      v = __builtin_inff();
+      vc = -1;
+    }
+    if (!more) break;
+    u = nu; sub = nsub; p = np; part = npart; n0 = nn0;
+  }
+}
+
+}  // namespace
+
+// Packs the model for the kernels above if it is small enough for them (pm.small.w stays null
+// otherwise).
+int vfk_pack_small(vf_ctx *c, const float *wdev) {
+  const vf_model &m = c->model;
+  vf_small_dev &d = c->pm.small;
+  d = vf_small_dev();
+  const int L = m.n_layers;
+  const bool bf16 = m.dtype == VF_BF16;
+  for (int l = 1; l < L; ++l)
+    if (m.dims[l] > SMALL_MAX) return VF_OK;
+  size_t nw = 0, nbias = 0;  // 16-byte units, floats
+  // every hidden layer gets as many row tiles as the widest one needs (fp32: an even number), the
+  // others' filled up with zeros: the kernels' loops then have no conditions
+  const int unit = bf16 ? 32 : 16;
+  int wide = 1;
+  for (int l = 1; l < L; ++l) wide = m.dims[l] > wide ? m.dims[l] : wide;
+  d.NT = (wide + 31) / 32 * (32 / unit);
+  for (int l = 0; l < L; ++l) {
+    const int K = m.dims[l], N = m.dims[l + 1];
+    d.dims[l] = K;
+    d.nt[l] = l < L - 1 ? d.NT : 1;
+    d.kst[l] = l > 0 ? d.NT * unit / 16 : (K + 15) / 16;
+    d.woff[l] = (int)nw;
+    d.boff[l] = (int)nbias;
+    if (bf16 || l < L - 1) nw += (size_t)d.nt[l] * d.kst[l] * 64;
+    nbias += (size_t)d.nt[l] * unit;
+    if ((nw + nbias) * 16 > (size_t)SMALL_LDS * 4) return VF_OK;  // (no overflow of the offsets)
+  }
+  d.wl_off = (int)nbias;
+  if (!bf16) nbias += (size_t)d.kst[L - 1] * 16;
+  if (nw * 16 + nbias * 4 > SMALL_LDS) return VF_OK;
+  d.L = L;
+  d.nw = (int)nw;
+  d.nbias = (int)nbias;
+  void *buf = nullptr;
+  VF_HIP(c, hipMalloc(&buf, nw * 16 + nbias * 4 + 16));
+  c->pm.small_buf = buf;
+  float *bias = reinterpret_cast<float *>(reinterpret_cast<uint4 *>(buf) + nw);
+  size_t off = 0;
+  for (int l = 0; l < L; ++l) {
+    const int K = m.dims[l], N = m.dims[l + 1];
+    const float *W = wdev + off, *b = W + (size_t)K * N;
+    const int n = d.nt[l] * d.kst[l] * (bf16 ? 512 : 256);
+    if (bf16)
+      hipLaunchKernelGGL(k_pack_small_bf16, dim3((n + 255) / 256), dim3(256), 0, c->stream, W, N, K, d.nt[l], d.kst[l],
+                         (int)(l == 0),
+                         reinterpret_cast<uint16_t *>(reinterpret_cast<uint4 *>(buf) + d.woff[l]));
+    else if (l < L - 1)
+      hipLaunchKernelGGL(k_pack_small_f32, dim3((n + 255) / 256), dim3(256), 0, c->stream, W, N, K, d.nt[l], d.kst[l],
+                         reinterpret_cast<float *>(reinterpret_cast<uint4 *>(buf) + d.woff[l]));
+    else
+      hipLaunchKernelGGL(k_pad_f32, dim3((d.kst[l] * 16 + 255) / 256), dim3(256), 0, c->stream, W, K, d.kst[l] * 16,
+                         bias + d.wl_off);
+    VF_HIP(c, hipGetLastError());
+    hipLaunchKernelGGL(k_pad_f32, dim3((d.nt[l] * unit + 255) / 256), dim3(256), 0, c->stream, b, N, d.nt[l] * unit,
+                       bias + d.boff[l]);
+    VF_HIP(c, hipGetLastError());
+    off += (size_t)K * N + N;
+  }
+  d.w = reinterpret_cast<const uint4 *>(buf);
+  d.bias = bias;
+  return VF_OK;
+}
+
+// Scores on the kernels above.  part_out: candidates per partial minimum, a divisor of 128.
+int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob, int64_t M, int64_t ld, int use_valid_row,
+                    float *scores, int64_t ld_scores, int noise_stage, const vf_partbuf *parts, int *nparts_out, int *part_out) {
+  const bool bf16 = c->model.dtype == VF_BF16;
+  int ncu = 256;
+  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
+  // sub-tiles of one column per lane while that leaves waves idle otherwise (two waves per SIMD)
+  const int base = bf16 ? 32 : 16;
+  const int ct = (M + base - 1) / base * nprob <= (int64_t)ncu * 8 ? 1 : 2;
+  SmallArgs a;
+  // a partial minimum per sub-tile, but 128 candidates each for very many (the buffer of
+  // vf_score_static holds 65536)
+  a.spp = (M + base * ct - 1) / (base * ct) * nprob <= 32768 ? 1 : 128 / (base * ct);
+  const int part = base * ct * a.spp;
+  a.nparts = (int)((M + part - 1) / part);
+  *nparts_out = a.nparts;
+  *part_out = part;
+  const int64_t units = (int64_t)a.nparts * nprob;
+  if (parts) {
+    if ((size_t)units > parts->cap) return VF_EINVAL;
+    a.pval = parts->val; a.pidx = parts->idx;
+  } else {
+    const int rc = vfk_ensure_parts(c, (size_t)(units > 0 ? units : 1));
+    if (rc != VF_OK) return rc;
+    a.pval = c->d_pval; a.pidx = c->d_pidx;
+  }
+  if (units == 0) return VF_OK;
+  a.md = c->pm.small;
+  a.x = x; a.prob_stride = prob_stride; a.M = M; a.ld = ld; a.use_valid_row = use_valid_row;
+  a.scores = scores; a.ld_scores = ld_scores;
+  a.units = (int)units;
+  a.na.eps = noise_stage >= 0 ? c->noise_eps : 0.0f;
+  a.na.k0 = (uint32_t)c->noise_seed; a.na.k1 = (uint32_t)(c->noise_seed >> 32);
+  a.na.stage = noise_stage; a.na.first_rollout = c->noise_first;
+  const size_t smem = (size_t)a.md.nw * 16 + (size_t)a.md.nbias * 4;
+  typedef void (*small_kernel)(SmallArgs);
+  static constexpr small_kernel kerns[2][2][4] = {
+      {{k_small_bf16<1, 1>, k_small_bf16<1, 2>, k_small_bf16<1, 3>, k_small_bf16<1, 4>},
+       {k_small_bf16<2, 1>, k_small_bf16<2, 2>, k_small_bf16<2, 3>, k_small_bf16<2, 4>}},
+      {{k_small_f32<1, 2>, k_small_f32<1, 4>, k_small_f32<1, 6>, k_small_f32<1, 8>},
+       {k_small_f32<2, 2>, k_small_f32<2, 4>, k_small_f32<2, 6>, k_small_f32<2, 8>}}};
+  const small_kernel kern = kerns[bf16 ? 0 : 1][ct - 1][a.md.NT * base / 32 - 1];
+  vf_prof_scope prof(c, VF_PROF_SCORE);
+  VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+  hipLaunchKernelGGL(kern, dim3((unsigned)(units < ncu ? units : ncu)), dim3(512), smem, c->stream, a);
+  VF_HIP(c, hipGetLastError());
+  return VF_OK;
+}

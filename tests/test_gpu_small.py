@@ -1,0 +1,74 @@
+"""GPU: small MLPs (hidden layers of up to 128 units, one launch for the whole network) against the
+CPU checker at the edges of their tiles and of their dispatch."""
+import numpy as np
+import pytest
+
+from paper_2011_14486_amd import inputs as I
+from tests.util import TOL
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def vf():
+    import paper_2011_14486_amd as pkg
+    return pkg.load()
+
+
+# (widths, dtype): no hidden layer, one, three; widths off the row tiles; input rows off a group of 16
+# and a chunk of 32; the widest that fits and (256-160-1) one that does not
+NETS = [([64, 128, 128, 1], I.FP32), ([64, 1], I.FP32), ([17, 5, 1], I.FP32), ([50, 33, 128, 7, 1], I.FP32),
+        ([128, 128, 1], I.FP32), ([64, 128, 128, 1], I.BF16), ([64, 1], I.BF16), ([32, 32, 1], I.BF16),
+        ([256, 96, 64, 32, 1], I.BF16), ([512, 64, 1], I.BF16), ([256, 160, 1], I.BF16), ([64, 160, 1], I.FP32)]
+
+
+@pytest.mark.parametrize("dims,dtype", NETS)
+def test_scores_and_minima(vf, ovf, dims, dtype):
+    """M: a single candidate, tiles and parts one short and one over, odd; more than a sub-tile per
+    wave (40001: pairs of columns, rows that start at odd addresses).  The bounds are those of the
+    tests of the same networks elsewhere (1e-5 for fp32 sums, 2e-2 for bf16), relative to the score
+    or to the RMS of many candidates' scores where that is larger: the error of a sum follows the
+    size of its terms (here about 10), so a single score that cancels to 0.007 may be 2e-5 of itself off."""
+    import torch
+    w = I.mlp_weights(dims, 3, bias_std=0.2)
+    model = I.model_record(I.MLP, dims, dtype)
+    ctx = vf.vf_create(0)
+    vf.vf_set_model(ctx, model, w)
+    x = np.floor(np.exp2(np.random.default_rng(1).random((dims[0], 40001)) * 20.0)).astype(np.int32)
+    some = np.r_[0:1500, 3000:4001, 39000:40001]
+    ref = np.full(40001, np.nan)
+    ref[some] = ovf.score_mlp(model, w, np.ascontiguousarray(x[:, some]))
+    scale = np.sqrt(np.nanmean(ref ** 2))
+    for M, ld, group in ((1, 1, 0), (15, 16, 0), (33, 33, 128), (127, 130, 128), (257, 257, 256), (4000, 4001, 768),
+                         (40001, 40001, 4096)):
+        xd = torch.from_numpy(np.ascontiguousarray(x[:, :ld])).cuda()
+        s, bi, bv = vf.vf_score(ctx, xd, M=M, group=group)
+        s, bi, bv = s.cpu().numpy(), bi.cpu().numpy(), bv.cpu().numpy()
+        keep = some[some < M]
+        err = np.abs(s[keep] - ref[keep]) / np.maximum(np.abs(ref[keep]), scale)
+        assert err.max() <= TOL[dtype], (M, ld)
+        for g, lo in enumerate(range(0, M, group or M)):
+            part = s[lo:lo + (group or M)]
+            assert bi[g] == lo + int(np.argmin(part)) and bv[g] == part.min(), (M, g)
+    vf.vf_destroy(ctx)
+
+
+@pytest.mark.parametrize("dtype", [I.FP32, I.BF16])
+def test_extreme_weights(vf, dtype):
+    """Infinite and NaN scores never win; a group without a finite score has no winner."""
+    import torch
+    dims = [64, 32, 1]
+    w = np.zeros(I.mlp_param_count(dims), np.float32)
+    W1 = w[:64 * 32].reshape(32, 64)
+    W1[0, 0], w[64 * 32 + 32:64 * 32 + 64][0] = 1.0, 1e38       # score = 1e38 * plog2(x[0]): inf from x[0] = 16 on
+    ctx = vf.vf_create(0)
+    vf.vf_set_model(ctx, I.model_record(I.MLP, dims, dtype), w)
+    x = np.full((64, 256), 1 << 20, np.int32)
+    x[0, 200] = 2
+    s, bi, bv = vf.vf_score(ctx, torch.from_numpy(x).cuda(), group=128)
+    assert bi.tolist() == [-1, 200] and torch.isinf(bv[0]) and float(bv[1]) == pytest.approx(1e38, rel=1e-2)
+    w[64 * 32 + 32] = np.nan
+    vf.vf_set_model(ctx, I.model_record(I.MLP, dims, dtype), w)
+    s, bi, bv = vf.vf_score(ctx, torch.from_numpy(x).cuda(), group=128)
+    assert torch.isnan(s).all() and bi.tolist() == [-1, -1]
+    vf.vf_destroy(ctx)
