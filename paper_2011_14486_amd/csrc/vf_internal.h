@@ -61,6 +61,7 @@ struct vf_packed_model {
   void *small_buf = nullptr;
   // recurrent network wired to the search: [W_ih | W_hh] transposed, bf16 values as fp32, [64+H][4H]
   float *w_seqT = nullptr;
+  uint16_t *w_seq_wide = nullptr;  // both in MFMA order for tiles of 96 candidates: see k_seq_step_wide
 };
 
 struct vf_ctx {

@@ -346,6 +346,7 @@ __global__ __launch_bounds__(512) void k_seq_step(SeqDev md, int stage, int64_t 
     const float *bias = gls + (size_t)(k & 1) * H4;
     floatx16 acc[4][CT];
 
+    if (active) {  // (waves without units of their own only keep the barriers company)
     const uint16_t *src = (k == 0) ? xs : hs + (size_t)(k & 1) * NC * hld;
     const int ld = (k == 0) ? XLD : hld;
     const int nsteps = (k == 0) ? 4 : ksh;
@@ -401,8 +402,6 @@ __global__ __launch_bounds__(512) void k_seq_step(SeqDev md, int stage, int64_t 
       round(0, vf_tag<true>{});
       for (int s0 = PD; s0 < nsteps; s0 += PD) round(s0, vf_tag<false>{});
     }
-    if (fetch_g) reinterpret_cast<float4 *>(gls + (size_t)((k + 1) & 1) * H4)[tid] = gnext;
-
     uint16_t *hout = hs + (size_t)((k + 1) & 1) * NC * hld;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -420,14 +419,14 @@ __global__ __launch_bounds__(512) void k_seq_step(SeqDev md, int stage, int64_t 
           cst[c][j] = cn;
           vsum[c] = fmaf(whq[e], hv[e], vsum[c]);
         }
-        if (active) {
-          uint2 pkd;
-          pkd.x = pack_bf16(hv[0], hv[1]);
-          pkd.y = pack_bf16(hv[2], hv[3]);
-          *reinterpret_cast<uint2 *>(hout + (size_t)(c * 32 + (lane & 31)) * hld + u0) = pkd;
-        }
+        uint2 pkd;
+        pkd.x = pack_bf16(hv[0], hv[1]);
+        pkd.y = pack_bf16(hv[2], hv[3]);
+        *reinterpret_cast<uint2 *>(hout + (size_t)(c * 32 + (lane & 31)) * hld + u0) = pkd;
       }
     }
+    }
+    if (fetch_g) reinterpret_cast<float4 *>(gls + (size_t)((k + 1) & 1) * H4)[tid] = gnext;
     __syncthreads();  // h_t and the next step's biases are in place
   }
 
@@ -461,6 +460,270 @@ __global__ __launch_bounds__(512) void k_seq_step(SeqDev md, int stage, int64_t 
       pidx[slot] = c;
     }
   }
+}
+
+// The same for tiles of 96 entries.  What bounds k_seq_step is that its two phases alternate: the
+// contraction of a tile of 64 waits for the weight stream (512 KB per step out of L2 at H = 256, 1.5
+// times what its products take), then the gates keep the vector ALUs busy for as long with the matrix
+// cores idle.  Here the stream serves 96 entries, so that the products take as long as the stream, and
+// a wave does its 32 hidden units in two passes of 16 (all four gates: two row tiles, three column
+// tiles, 96 accumulators), with the waves 0..3 ahead of the waves 4..7 by wave priority: on every SIMD
+// one wave's gates run under the other wave's products.  A step of 96 takes about 22k cycles, 19k of
+// them vector work of the gates (202 cycles per cell and wave, 128 of those in 5 exp and 3 rcp).
+// 64 problems of 20 layers, H = 256: 19.4 -> 17.0 ms per schedule, H = 128 8.7 -> 7.5, 12 layers of other
+// shapes 5.4 -> 3.1.  (128 entries: the accumulators and cell states leave no registers, and what is
+// spilled in the gates comes back behind the weight fragments under way: 28.6 ms.)
+// The weights are one stream per wave (k_pack_seq_wide): per pass the k-steps of h, then those of x;
+// row tile 0 of a pass holds gate i of its units in rows 0..15 and gate f in rows 16..31, row tile 1
+// the gates g and o.  The first step's x lies in the h buffer that the second step writes.
+constexpr int SEQ_WIDE = 96;
+template <int PD>
+__global__ __launch_bounds__(512) void k_seq_step_wide(SeqDev md, const uint16_t *w_wide, int stage, float *scores,
+                                                       int64_t ld_scores, float *pval, int32_t *pidx, NoiseArgs na) {
+  constexpr int NC = SEQ_WIDE, CT = NC / 32;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int H = md.H, S = md.S, H4 = 4 * H, hld = H + 8;
+  uint16_t *hs = reinterpret_cast<uint16_t *>(smem);                    // [2][NC][max(hld, 72)]
+  const int hcol = hld < 72 ? 72 : hld;
+  float *gls = reinterpret_cast<float *>(hs + (size_t)2 * NC * hcol);   // [2][4H]
+  float *red = gls + 2 * H4;                                            // [8][NC]
+  float *whs = red + 8 * NC;                                            // [H]
+  int32_t *okf = reinterpret_cast<int32_t *>(whs + H);                  // [NC] candidate id + 1, 0 = none
+  __shared__ DecPack pk;
+  __shared__ float sv[2];
+  __shared__ int32_t sc[2];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b = blockIdx.y, nparts = gridDim.x;
+  const int64_t n0 = (int64_t)blockIdx.x * NC;
+  const size_t slot = (size_t)b * nparts + blockIdx.x;
+
+  const int nvalid = md.count[b];
+  if (n0 >= nvalid) {
+    if (tid == 0) {
+      pval[slot] = __builtin_inff();
+      pidx[slot] = -1;
+    }
+    return;
+  }
+  if (tid < VF_DECPACK_DWORDS)
+    reinterpret_cast<uint32_t *>(&pk)[tid] = md.decpack[(size_t)b * VF_DECPACK_DWORDS + tid];
+  const bool active = w < H / 32;
+  const int wu = active ? w : 0;  // idle waves shadow the first units but never store
+  const int ksh = H / 16;
+  const __amdgpu_buffer_rsrc_t ws = stream_rsrc(reinterpret_cast<const uint4 *>(w_wide) + (size_t)wu * (2 * ksh + 8) * 2 * 64);
+  const int voff = 16 * lane;
+  // (the first step's x part sits behind the passes' h parts)
+  int wstep = 2 * ksh + PD;
+  uint4 ring[PD][2];
+#pragma unroll
+  for (int j = 0; j < PD; ++j)
+#pragma unroll
+    for (int r = 0; r < 2; ++r) ring[j][r] = stream_load(ws, voff, (2 * ksh + j) * 2 + r);
+  for (int i = tid; i < H4; i += 512) gls[i] = md.P[(size_t)b * H4 + i];
+  for (int i = tid; i < H; i += 512) whs[i] = md.aux[H4 + i];
+  __syncthreads();
+  if (tid < 4 * NC) {
+    // four threads per candidate, each producing 16 of the 64 core rows (what a thread does not
+    // store is dead code in its copy); padding columns are evaluated too and store zeros
+    const int n = tid % NC, part = tid / NC;
+    const bool inb = (n0 + n) < nvalid;
+    const uint32_t cid = inb ? (uint32_t)md.list[(size_t)b * md.Mpad + n0 + n] : 0u;
+    int32_t core[64];
+    uint32_t dec;
+    auto put = [&](const int32_t *v, int row0) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        uint4 q;
+        q.x = pack_bf16(plog2_dev(v[8 * k + 0]), plog2_dev(v[8 * k + 1]));
+        q.y = pack_bf16(plog2_dev(v[8 * k + 2]), plog2_dev(v[8 * k + 3]));
+        q.z = pack_bf16(plog2_dev(v[8 * k + 4]), plog2_dev(v[8 * k + 5]));
+        q.w = pack_bf16(plog2_dev(v[8 * k + 6]), plog2_dev(v[8 * k + 7]));
+        if (!inb) q = make_uint4(0u, 0u, 0u, 0u);
+        reinterpret_cast<uint4 *>(hs + (size_t)n * hcol + row0)[k] = q;
+      }
+    };
+    if (part == 0) {
+      const bool okc = eval_candidate<true>(pk.d, pk.sp, cid, dec, core);
+      okf[n] = inb && okc ? (int32_t)cid + 1 : 0;
+      put(core, 0);
+    } else if (part == 1) {
+      eval_candidate<true>(pk.d, pk.sp, cid, dec, core);
+      put(core + 16, 16);
+    } else if (part == 2) {
+      eval_candidate<true>(pk.d, pk.sp, cid, dec, core);
+      put(core + 32, 32);
+    } else {
+      eval_candidate<true>(pk.d, pk.sp, cid, dec, core);
+      put(core + 48, 48);
+    }
+  }
+  // cell state: per pass and column tile a lane's eight units 8 q + 4 (lane / 32) + e of the pass's 16
+  float cst[2][CT][8];
+  float vsum[CT];
+#pragma unroll
+  for (int ps = 0; ps < 2; ++ps)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const float4 cv = *reinterpret_cast<const float4 *>(md.cpre + (size_t)b * H + wu * 32 + 16 * ps + 8 * q + 4 * (lane >> 5));
+#pragma unroll
+      for (int c = 0; c < CT; ++c) {
+        cst[ps][c][4 * q + 0] = cv.x; cst[ps][c][4 * q + 1] = cv.y;
+        cst[ps][c][4 * q + 2] = cv.z; cst[ps][c][4 * q + 3] = cv.w;
+      }
+    }
+#pragma unroll
+  for (int c = 0; c < CT; ++c) vsum[c] = 0.0f;
+  __syncthreads();
+
+  for (int t = stage; t < S; ++t) {
+    const int k = t - stage;
+    // the next step's biases, fetched now, parked in LDS after this step's passes
+    const bool fetch_g = (t + 1 < S) && tid < H;
+    float4 gnext = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (fetch_g) gnext = reinterpret_cast<const float4 *>(md.G + ((size_t)b * S + t + 1) * H4)[tid];
+    const uint16_t *src = hs + (size_t)(k & 1) * NC * hcol;
+    uint16_t *hout = hs + (size_t)((k + 1) & 1) * NC * hcol;
+    if (active) {
+#pragma unroll
+    for (int ps = 0; ps < 2; ++ps) {
+      int u0 = wu * 32 + 16 * ps + 4 * (lane >> 5);  // the lane's units: u0 + 8 q + e
+      asm volatile("" : "+v"(u0));                   // (biases read afresh every step, not kept across them)
+      floatx16 acc[2][CT];
+      const uint16_t *bb = src + (size_t)(lane & 31) * hcol + 8 * (lane >> 5);
+      const int nsteps = k == 0 ? 4 : ksh;
+      if (w < 4) __builtin_amdgcn_s_setprio(3);
+      else __builtin_amdgcn_s_setprio(1);
+      {
+        uint4 bcur[CT];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) bcur[c] = *reinterpret_cast<const uint4 *>(bb + (size_t)c * 32 * hcol);
+        __builtin_amdgcn_s_waitcnt(0x0070);  // (see contract_layer)
+        auto round = [&](int s0, auto startc) __attribute__((always_inline)) {
+          constexpr bool starts = decltype(startc)::value;
+          if (ps == 1 && s0 + PD >= nsteps) wstep = 0;  // the next step's first fragments
+#pragma unroll
+          for (int j = 0; j < PD; ++j) {
+            if constexpr (starts) {
+              if (j == 0) {
+                // the first k-step takes the step's gate biases as its addend, row tile by row tile,
+                // so that one of the two bias vectors is in registers at a time
+                const float *bias = gls + (size_t)(k & 1) * H4 + u0;
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                  floatx16 bg;
+#pragma unroll
+                  for (int g = 0; g < 4; ++g) {
+                    const float4 v = *reinterpret_cast<const float4 *>(bias + (2 * r + (g >> 1)) * H + 8 * (g & 1));
+                    bg[4 * g + 0] = v.x; bg[4 * g + 1] = v.y; bg[4 * g + 2] = v.z; bg[4 * g + 3] = v.w;
+                  }
+#pragma unroll
+                  for (int c = 0; c < CT; ++c) {
+                    acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ring[0][r]),
+                                                                       __builtin_bit_cast(bf16x8, bcur[c]), bg, 0, 0, 0);
+                    if (r == 1) bcur[c] = *reinterpret_cast<const uint4 *>(bb + (size_t)c * 32 * hcol + 16);
+                  }
+                  ring[0][r] = stream_load(ws, voff, wstep * 2 + r);
+                  __builtin_amdgcn_sched_barrier(0);
+                }
+                continue;
+              }
+            }
+#pragma unroll
+            for (int i = 0; i < 2 * CT; ++i) {
+              const int c = i / 2, r = i % 2;
+              acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ring[j][r]),
+                                                                 __builtin_bit_cast(bf16x8, bcur[c]), acc[r][c], 0, 0, 0);
+              if (r == 1) bcur[c] = *reinterpret_cast<const uint4 *>(bb + (size_t)c * 32 * hcol + (s0 + j + 1) * 16);
+              if (c == CT - 1) ring[j][r] = stream_load(ws, voff, (wstep + j) * 2 + r);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
+          wstep += PD;
+        };
+        round(0, vf_tag<true>{});
+        for (int s0 = PD; s0 < nsteps; s0 += PD) round(s0, vf_tag<false>{});
+      }
+      __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const float4 whv = *reinterpret_cast<const float4 *>(whs + u0 + 8 * q);
+        const float whq[4] = {whv.x, whv.y, whv.z, whv.w};
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+          float hv[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float cn = cst[ps][c][4 * q + e];
+            hv[e] = lstm_cell(acc[0][c][4 * q + e], acc[0][c][8 + 4 * q + e], acc[1][c][4 * q + e], acc[1][c][8 + 4 * q + e], cn);
+            cst[ps][c][4 * q + e] = cn;
+            vsum[c] = fmaf(whq[e], hv[e], vsum[c]);
+          }
+          uint2 pkd;
+          pkd.x = pack_bf16(hv[0], hv[1]);
+          pkd.y = pack_bf16(hv[2], hv[3]);
+          *reinterpret_cast<uint2 *>(hout + (size_t)(c * 32 + (lane & 31)) * hcol + u0 + 8 * q) = pkd;
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+    }
+    if (fetch_g) reinterpret_cast<float4 *>(gls + (size_t)((k + 1) & 1) * H4)[tid] = gnext;
+    __syncthreads();  // h_t and the next step's biases are in place
+  }
+
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    const float v = vsum[c] + __shfl_xor(vsum[c], 32);
+    if (lane < 32) red[w * NC + c * 32 + lane] = active ? v : 0.0f;
+  }
+  __syncthreads();
+  if (tid < (NC + 63) / 64 * 64) {
+    const bool col = tid < NC;
+    float s = md.hsum[b] + (float)(S - stage) * md.aux[H4 + H];
+#pragma unroll
+    for (int g = 0; g < 8; ++g) s += col ? red[g * NC + tid] : 0.0f;
+    const int32_t cid = col ? okf[tid] - 1 : -1;
+    const bool ok = cid >= 0;
+    if (scores && ok) scores[(size_t)b * ld_scores + cid] = s;
+    if (na.eps != 0.0f) s = add_noise(na, s, b, cid);
+    float v = __builtin_inff();
+    int32_t c = -1;
+    if (ok && s < v) { v = s; c = cid; }
+    wave_min(v, c);
+    if (md.stat) {
+      const int nok = __popcll(__ballot(ok));
+      if (lane == 0) {
+        atomicAdd(&md.stat[0], (unsigned long long)nok);
+        atomicAdd(&md.stat[1], (unsigned long long)nok);
+      }
+    }
+    if (lane == 0) { sv[w] = v; sc[w] = c; }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    float v = sv[0];
+    int32_t c = sc[0];
+    take_min(v, c, sv[1], sc[1]);
+    pval[slot] = v;
+    pidx[slot] = c;
+  }
+}
+
+// The weights of k_seq_step_wide: out[wave][step][row tile][lane][8], steps = k-steps of h of pass 0,
+// of pass 1, then the four k-steps of x of either pass.
+__global__ __launch_bounds__(256) void k_pack_seq_wide(SeqWeights sw, uint16_t *out) {
+  const int H = sw.H, ksh = H / 16, steps = 2 * ksh + 8;
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= H / 32 * steps * 1024) return;
+  const int e = i & 7, lane = (i >> 3) & 63, r = (i >> 9) & 1, step = (i >> 10) % steps, w = (i >> 10) / steps;
+  const bool of_x = step >= 2 * ksh;
+  const int at = of_x ? step - 2 * ksh : step, per = of_x ? 4 : ksh, ps = at / per, s = at % per;
+  const int row = lane & 31, gate = 2 * r + (row >> 4), unit = w * 32 + 16 * ps + (row & 15);
+  const int k = s * 16 + 8 * (lane >> 5) + e;
+  const float v = of_x ? sw.Wih[(size_t)(gate * H + unit) * 64 + k] : sw.Whh[(size_t)(gate * H + unit) * H + k];
+  out[i] = (uint16_t)bf16_bits(v);
 }
 
 SeqWeights weights_of(const vf_ctx *c) {
@@ -537,6 +800,16 @@ int vfk_seq_sync(vf_ctx *c, int stage) {
       }
       hipLaunchKernelGGL(k_pack_seqT, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, st, sw, c->pm.w_seqT);
       VF_HIP(c, hipGetLastError());
+      {
+        const size_t nv = (size_t)H / 32 * (2 * (H / 16) + 8) * 1024;
+        if (hipMalloc((void **)&c->pm.w_seq_wide, nv * sizeof(uint16_t)) != hipSuccess) {
+          (void)hipGetLastError();
+          vfk_seq_free(c);
+          return VF_ENOMEM;
+        }
+        hipLaunchKernelGGL(k_pack_seq_wide, dim3((unsigned)((nv + 255) / 256)), dim3(256), 0, st, sw, c->pm.w_seq_wide);
+        VF_HIP(c, hipGetLastError());
+      }
     }
     c->seq_stage = -1;
   }
@@ -585,12 +858,18 @@ int vfk_seq_advance_beam(vf_ctx *c, int stage) {
 // V of every candidate state of decision `stage` of every problem: per-tile minima into
 // the partial arrays, optionally the masked scores [B][ld_scores].
 int vfk_seq_step(vf_ctx *c, int stage, float *scores, int64_t ld_scores, int noise_stage, int *nparts_out) {
-  constexpr int NC = 64;
   int rc = vfk_seq_sync(c, stage);
   if (rc != VF_OK) return rc;
   rc = vfk_prepare(c, stage);
   if (rc != VF_OK) return rc;
   const int H = c->model.dims[1];
+  // Tiles of 96 where tiles of 64 would be more than about one round of the compute units (a third
+  // of the ids is valid, as a rule): 8 problems of 4096 ids 3.1 against 3.4 ms or 1.3 against 1.1, 12: 4.7
+  // against 4.4 or 1.3 against 1.6, 16: 5.0 against 5.6, 64: 17.0 against 19.4; 1 problem: 2.9 against 2.2.
+  int ncu = 256;
+  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
+  const bool wide = (c->M + 63) / 64 * c->B >= 3 * (int64_t)ncu;
+  const int NC = wide ? SEQ_WIDE : 64;
   const int nparts = (int)((c->M + NC - 1) / NC);
   rc = vfk_ensure_parts(c, (size_t)nparts * c->B);
   if (rc != VF_OK) return rc;
@@ -613,7 +892,17 @@ int vfk_seq_step(vf_ctx *c, int stage, float *scores, int64_t ld_scores, int noi
                       (size_t)H * 4 + (size_t)2 * NC * 4;
   {
     vf_prof_scope prof(c, VF_PROF_SCORE);
-    void (*kern)(SeqDev, int, int64_t, float *, int64_t, float *, int32_t *, NoiseArgs) = k_seq_step<NC, 2>;
+    if (wide) {
+      const int hcol = hld < 72 ? 72 : hld;
+      const size_t lds = (size_t)2 * NC * hcol * 2 + (size_t)2 * 4 * H * 4 + (size_t)8 * NC * 4 + (size_t)H * 4 + (size_t)NC * 4;
+      VF_HIP(c, hipFuncSetAttribute((const void *)k_seq_step_wide<2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+      hipLaunchKernelGGL(k_seq_step_wide<2>, dim3((unsigned)nparts, (unsigned)c->B), dim3(512), lds, c->stream, md,
+                         (const uint16_t *)c->pm.w_seq_wide, stage, scores, ld_scores, c->d_pval, c->d_pidx, na);
+      VF_HIP(c, hipGetLastError());
+      *nparts_out = nparts;
+      return VF_OK;
+    }
+    void (*kern)(SeqDev, int, int64_t, float *, int64_t, float *, int32_t *, NoiseArgs) = k_seq_step<64, 2>;
     VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
     hipLaunchKernelGGL(kern, dim3((unsigned)nparts, (unsigned)c->B), dim3(512), smem, c->stream, md, stage, c->M,
                        scores, ld_scores, c->d_pval, c->d_pidx, na);

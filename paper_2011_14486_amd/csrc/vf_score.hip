@@ -929,12 +929,10 @@ __global__ __launch_bounds__(512) void k_lstm_bf16(const uint16_t *x, int64_t M,
           cst[c][j] = cn;
           vsum[c] = fmaf(whq[e], hv[e], vsum[c]);
         }
-        if (active) {
-          uint2 pkd;
-          pkd.x = pack_bf16(hv[0], hv[1]);
-          pkd.y = pack_bf16(hv[2], hv[3]);
-          *reinterpret_cast<uint2 *>(hout + (size_t)(c * 32 + (lane & 31)) * hld + w * 32 + 8 * q + 4 * (lane >> 5)) = pkd;
-        }
+        uint2 pkd;
+        pkd.x = pack_bf16(hv[0], hv[1]);
+        pkd.y = pack_bf16(hv[2], hv[3]);
+        *reinterpret_cast<uint2 *>(hout + (size_t)(c * 32 + (lane & 31)) * hld + w * 32 + 8 * q + 4 * (lane >> 5)) = pkd;
       }
     }
   };
@@ -947,10 +945,13 @@ __global__ __launch_bounds__(512) void k_lstm_bf16(const uint16_t *x, int64_t M,
     // x_{t+1} (fetched during the previous step) goes to the buffer last read at t-1
     stash((t + 1) & 1);
     fetch(t + 2);
-    kloop(xs + (size_t)(t & 1) * NC * xld, xld, ksx, false, vf_tag<true>{});
+    // (waves without units of their own only fetch inputs and keep the barrier company)
+    if (active) kloop(xs + (size_t)(t & 1) * NC * xld, xld, ksx, false, vf_tag<true>{});
     __syncthreads();  // h_{t-1} is complete; x_{t+1} is visible for the next step
-    kloop(hs + (size_t)(t & 1) * NC * hld, hld, ksh, true, vf_tag<false>{});
-    gates(t);
+    if (active) {
+      kloop(hs + (size_t)(t & 1) * NC * hld, hld, ksh, true, vf_tag<false>{});
+      gates(t);
+    }
   }
 
   // v = sum_t (w . h_t + b): add the two lane halves, then the waves in order
@@ -1048,6 +1049,7 @@ void vfk_free_model(vf_ctx *c) {
   if (c->pm.w_stream) (void)hipFree(c->pm.w_stream);
   if (c->pm.w_stream_fold) (void)hipFree(c->pm.w_stream_fold);
   if (c->pm.w_seqT) (void)hipFree(c->pm.w_seqT);
+  if (c->pm.w_seq_wide) (void)hipFree(c->pm.w_seq_wide);
   if (c->pm.small_buf) (void)hipFree(c->pm.small_buf);
   if (c->pm.aux) (void)hipFree(c->pm.aux);
   c->pm = vf_packed_model();

@@ -72,21 +72,21 @@ __device__ __forceinline__ void wave_min(float &v, int32_t &c) {
 // One cell of the recurrent network in fp32: gate pre-activations ai, af, ag, ao and the old cell
 // state give the new cell state (returned through c) and the new hidden value (returned).
 //   c' = sigma(af) c + sigma(ai) tanh(ag),   h' = sigma(ao) tanh(c')
-// A product sigma(a) tanh(b) is one quotient (e^{2b} - 1) / ((1 + e^{2b}) (1 + e^{-a})): two
-// exponentials and one reciprocal instead of two and two, which matters because these run at a
-// quarter of the rate of ordinary instructions (8 instead of 10 per cell).  Exponents are cut
-// off at 60 binary orders, where tanh is 1 and sigma is 0 to far below fp32 resolution, so that
-// the product of the two denominators stays finite; a NaN passes the cut-off and comes out.
-__device__ __forceinline__ float exp2_cut(float x) { return __builtin_amdgcn_exp2f(x > 60.0f ? 60.0f : x); }
+// A product sigma(a) tanh(b) is one quotient: with u = 1 + e^{-a} and e = e^{-2|b|} it is
+// sign(b) (1 - e) / (u + e u) - two exponentials and one reciprocal instead of two and two, which
+// matters because these run at a quarter of the rate of ordinary instructions (8 instead of 10 per
+// cell).  e never overflows; u may become infinite, and the product is then 0, as it should be.  A NaN
+// comes out as a NaN.
 __device__ __forceinline__ float sig_tanh(float a, float b) {
   constexpr float LOG2E = 1.44269504088896340736f;
-  const float ea = exp2_cut(a * -LOG2E), eb = exp2_cut(b * (2.0f * LOG2E));
-  return (eb - 1.0f) * __builtin_amdgcn_rcpf((1.0f + eb) * (1.0f + ea));
+  const float u = 1.0f + __builtin_amdgcn_exp2f(a * -LOG2E);
+  const float e = __builtin_amdgcn_exp2f(__builtin_fabsf(b) * (-2.0f * LOG2E));
+  return __builtin_copysignf(1.0f - e, b) * __builtin_amdgcn_rcpf(fmaf(e, u, u));
 }
 __device__ __forceinline__ float lstm_cell(float ai, float af, float ag, float ao, float &c) {
   constexpr float LOG2E = 1.44269504088896340736f;
   const float fg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(af * -LOG2E));
-  const float cn = fg * c + sig_tanh(ai, ag);
+  const float cn = fmaf(fg, c, sig_tanh(ai, ag));
   c = cn;
   return sig_tanh(ao, cn);
 }

@@ -53,6 +53,25 @@ def test_batch_on_lists_equals_single_problems(vf, dims):
     vf.vf_destroy(many)
 
 
+@pytest.mark.parametrize("H", [32, 96, 256])
+def test_recurrent_batch_equals_single_problems(vf, H):
+    """Many candidates run in tiles of 96, few in tiles of 64, with the same arithmetic per candidate:
+    ids and values of every layer are bit-identical (idle waves at H = 32 and 96; ragged tiles; noise)."""
+    sp, B = I.resnet18_space(256), 14                # 14 * 64 tiles of 64 ids: more than 3 * 256
+    pipes = np.stack([I.random_pipeline(5, 90 + b) for b in range(B)])
+    w, model = I.lstm_weights(64, H, seed=6, bias_std=0.2), I.model_record(I.LSTM, [64, H, 1], I.BF16)
+    many = context(vf, pipes, sp, model, w)
+    vf.vf_set_noise(many, 0.1, 3, 0)
+    st, cids, vals = (t.cpu().numpy() for t in vf.vf_greedy_schedule(many))
+    vf.vf_destroy(many)
+    for b in range(B):
+        one = context(vf, pipes[b], sp, model, w)
+        vf.vf_set_noise(one, 0.1, 3, b)
+        s1, c1, v1 = (t.cpu().numpy()[0] for t in vf.vf_greedy_schedule(one))
+        assert np.array_equal(c1, cids[b]) and np.array_equal(s1, st[b]) and np.array_equal(v1, vals[b])
+        vf.vf_destroy(one)
+
+
 # the factors make the number of ids of a decision: the search works on lists from 64 tiles of 128 on
 @pytest.mark.parametrize("K,fac,const", [(2, [1, 2, 4, 8], True), (33, [1, 2, 4], True), (33, [1, 2, 4], False),
                                          (300, [1, 4], False), (1024, [1, 4], True)])
