@@ -321,6 +321,9 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
 // would be used), the four lane groups' parts added at the end.
 template <int CT, int NT>
 __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
+  // partial sums per accumulator, even and odd groups of 16 rows apart, where the registers allow it:
+  // a sum of half as many terms is the more exact one
+  constexpr int SP = CT == 1 ? 2 : 1;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint4 *const wl = reinterpret_cast<uint4 *>(smem);
   const floatx4 *const wf = reinterpret_cast<const floatx4 *>(smem);
@@ -374,15 +377,17 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
     bool ok[CT];
 #pragma unroll
     for (int c = 0; c < CT; ++c) ok[c] = n0 + CT * (lane & 15) + c < a.M;
-    floatx4 acc[NT][CT];
+    floatx4 acc[SP][NT][CT];
     float s[CT];
     const bool only = L == 1;  // no hidden layer: the inputs go straight into the output dot
 #pragma unroll
     for (int c = 0; c < CT; ++c) s[c] = 0.0f;
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+    for (int sp = 0; sp < SP; ++sp)
 #pragma unroll
-      for (int c = 0; c < CT; ++c) acc[t][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) acc[sp][t][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
     // (a weight fragment is refilled in place behind its last product; the refill behind the last
     // group reads into what follows the layer's weights and is not used)
     constexpr int TH = NT / 2;  // fragments in flight
@@ -420,7 +425,7 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int c = 0; c < CT; ++c) acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t % TH][e], in[g][e][c], acc[t][c], 0, 0, 0);
+            for (int c = 0; c < CT; ++c) acc[g % SP][t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t % TH][e], in[g][e][c], acc[g % SP][t][c], 0, 0, 0);
           x[t % TH] = t < TH ? wf[((t + TH) * groups0 + kg) * 64 + at] : wf[((t - TH) * groups0 + kg + 1) * 64 + at];
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -428,29 +433,31 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
     }
     if (!only) {
       // a finished layer: bias, ReLU, and its rows are the next one's inputs as they lie
-      auto finish = [&](const floatx4 &v, int l, int t) __attribute__((always_inline)) {
+      auto finish = [&](const floatx4 &v0, const floatx4 &v1, int l, int t) __attribute__((always_inline)) {
         const floatx4 b = *reinterpret_cast<const floatx4 *>(bl + a.md.boff[l] + t * 16 + 4 * (at >> 4));
         floatx4 o;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = relu_keep_nan(v[e] + b[e]);
+        for (int e = 0; e < 4; ++e) o[e] = relu_keep_nan((SP > 1 ? v0[e] + v1[e] : v0[e]) + b[e]);
         return o;
       };
       floatx4 act[NT][CT];
 #pragma unroll
       for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int c = 0; c < CT; ++c) act[t][c] = finish(acc[t][c], 0, t);
+        for (int c = 0; c < CT; ++c) act[t][c] = finish(acc[0][t][c], acc[SP - 1][t][c], 0, t);
       for (int l = 1; l < L - 1; ++l) {
         // half of the row tiles at a time, as above
         floatx4 out[NT][CT];
         const floatx4 *wp = wf + a.md.woff[l] + at;
 #pragma unroll
         for (int t0 = 0; t0 < NT; t0 += TH) {
-          floatx4 part[TH][CT];
+          floatx4 part[SP][TH][CT];
 #pragma unroll
           for (int t = 0; t < TH; ++t) {
 #pragma unroll
-            for (int c = 0; c < CT; ++c) part[t][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int sp = 0; sp < SP; ++sp)
+#pragma unroll
+              for (int c = 0; c < CT; ++c) part[sp][t][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
             x[t] = wp[(t0 + t) * NT * 64];
           }
 #pragma unroll
@@ -460,14 +467,14 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
 #pragma unroll
               for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int c = 0; c < CT; ++c) part[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t][e], act[kg][c][e], part[t][c], 0, 0, 0);
+                for (int c = 0; c < CT; ++c) part[kg % SP][t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t][e], act[kg][c][e], part[kg % SP][t][c], 0, 0, 0);
               if (kg + 1 < NT) x[t] = wp[((t0 + t) * NT + kg + 1) * 64];
               __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
           for (int t = 0; t < TH; ++t)
 #pragma unroll
-            for (int c = 0; c < CT; ++c) out[t0 + t][c] = finish(part[t][c], l, t0 + t);
+            for (int c = 0; c < CT; ++c) out[t0 + t][c] = finish(part[0][t][c], part[SP - 1][t][c], l, t0 + t);
         }
 #pragma unroll
         for (int t = 0; t < NT; ++t)
