@@ -92,41 +92,42 @@ __global__ __launch_bounds__(256) void k_enumerate(Tables t, int stage, uint32_t
   }
 }
 
-// Feature-major output feat[b][F][Mpad].  A workgroup covers SPAN consecutive blocks of 256
-// candidates.  The 64 rows that differ from candidate to candidate go through LDS, 32 rows
-// of a block at a time, so that every store instruction of a wave writes a kilobyte of one
-// row (16 bytes per lane); the other rows are the same for every candidate and are written
-// over the workgroup's whole span at once.
+// Feature-major output feat[b][F][Mpad].  With 256 rows the first 192 workgroups of a problem write
+// the rows that all candidates share, one whole row each, with no more context than the row's value.
+// The others cover `span` consecutive blocks of 256 candidates each: the 64 rows that differ from
+// candidate to candidate go through LDS, 32 rows of a block at a time, so that every store
+// instruction of a wave writes a kilobyte of one row (16 bytes per lane).
+// Bound by the stores: 1 GiB (256 problems of 4096 ids) in 180 us = 6.0 TB/s, where a plain fill of as
+// much reaches 6.8 (187 us when every workgroup wrote a part of all 256 rows; 1 GiB as 64 problems of
+// 16384 ids 248 -> 194 us; four or sixteen shared rows per workgroup: 206 us).
 constexpr int VF_FEAT_SPAN = 4;
-__global__ __launch_bounds__(256) void k_featurize(Tables t, int stage, uint32_t M, uint32_t Mpad, int F,
-                                                   int32_t *feat) {
+__global__ __launch_bounds__(256) void k_featurize(Tables t, int stage, uint32_t M, uint32_t Mpad, int F, int fill,
+                                                   int span, int per, int xcds, int B, int32_t *feat) {
   __shared__ Dec d;
   __shared__ vf_space sp;
   __shared__ __attribute__((aligned(16))) int32_t tile[32][256];
-  const int b = blockIdx.y;
-  build_dec(d, sp, t, b, stage);
+  // per: workgroups per problem; xcds = 8: a problem's workgroups go to one XCD (workgroups are dealt
+  // out to the eight in turn)
+  const int q = (int)blockIdx.x / xcds, b = q / per * xcds + (int)blockIdx.x % xcds, bx = q % per;
+  if (b >= B) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   int32_t *out = feat + (size_t)b * F * Mpad;
-  const uint32_t first = blockIdx.x * (uint32_t)(256 * VF_FEAT_SPAN);
-  if (F == 256) {
-    // rows 64..255: each wave writes its rows over the whole span (first: these stores need
-    // no evaluation and are under way while the candidates are evaluated)
-    for (int r = w; r < 192; r += 4) {
-      const int32_t v = d.nb[r];
-#pragma unroll
-      for (int sb = 0; sb < VF_FEAT_SPAN; ++sb) {
-        const uint32_t col0 = first + 256u * sb + 4u * lane;
-        if (col0 >= Mpad) break;
-        int4 q;
-        q.x = col0 + 0 < M ? v : 0;
-        q.y = col0 + 1 < M ? v : 0;
-        q.z = col0 + 2 < M ? v : 0;
-        q.w = col0 + 3 < M ? v : 0;
-        *reinterpret_cast<int4 *>(out + (size_t)(64 + r) * Mpad + col0) = q;
-      }
+  if (bx < fill) {
+    const int32_t v = nb_row(t, b, stage, bx, -1);
+    int32_t *row = out + (size_t)(64 + bx) * Mpad;
+    for (uint32_t col0 = 4u * threadIdx.x; col0 < Mpad; col0 += 1024u) {
+      int4 q;
+      q.x = col0 + 0 < M ? v : 0;
+      q.y = col0 + 1 < M ? v : 0;
+      q.z = col0 + 2 < M ? v : 0;
+      q.w = col0 + 3 < M ? v : 0;
+      *reinterpret_cast<int4 *>(row + col0) = q;
     }
+    return;
   }
-  for (int sb = 0; sb < VF_FEAT_SPAN; ++sb) {
+  build_dec(d, sp, t, b, stage);
+  const uint32_t first = (uint32_t)(bx - fill) * (uint32_t)(256 * span);
+  for (int sb = 0; sb < span; ++sb) {
     const uint32_t base = first + 256u * sb;
     if (base >= Mpad) break;
     const uint32_t cid = base + threadIdx.x;
@@ -467,9 +468,21 @@ int vfk_enumerate(vf_ctx *c, int stage, uint32_t *dec, uint8_t *valid, int32_t *
 
 int vfk_featurize(vf_ctx *c, int stage, int32_t *feat) {
   vf_prof_scope prof(c, VF_PROF_FEATURIZE);
-  dim3 grid((unsigned)((c->Mpad / 256 + VF_FEAT_SPAN - 1) / VF_FEAT_SPAN), (unsigned)c->B);
+  // One block of candidates per workgroup while four workgroups fit every compute unit that way: what a
+  // small call waits for is the longest workgroup (one problem of 4096 ids 21.6 -> 6.8 us, four 22.9 ->
+  // 8.4, 64 problems 52 -> 40).  With more, the decision context is worth sharing (256: 193 against 184).
+  int ncu = 256;
+  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
+  const int blocks = (int)(c->Mpad / 256), span = (int64_t)blocks * c->B <= 4 * (int64_t)ncu ? 1 : VF_FEAT_SPAN;
+  const int fill = c->space.F == 256 ? 192 : 0;
+  const int per = fill + (blocks + span - 1) / span;
+  // Large calls keep a problem's rows on one XCD, so that one of the eight looks its pages up instead of
+  // all: 256 problems 184 -> 180 us, and 246 -> 203 for the first pass over a new buffer; small ones
+  // take all XCDs for every problem (four problems 10.4 -> 8.4 us).
+  const int xcds = span > 1 ? 8 : 1;
+  dim3 grid((unsigned)per * (unsigned)((c->B + xcds - 1) / xcds * xcds));
   hipLaunchKernelGGL(k_featurize, grid, dim3(256), 0, c->stream, tables_of(c), stage, (uint32_t)c->M,
-                     (uint32_t)c->Mpad, (int)c->space.F, feat);
+                     (uint32_t)c->Mpad, (int)c->space.F, fill, span, per, xcds, c->B, feat);
   VF_HIP(c, hipGetLastError());
   return VF_OK;
 }

@@ -156,6 +156,18 @@ struct DecScratch {
   int32_t ast[16], arec[16], acf[4];
 };
 
+// Row 64 + i of the 256-row layout: the neighbour stages' features (0 for stage `fresh`, whose rows
+// the caller has not committed yet).
+__device__ __forceinline__ int32_t nb_row(const Tables &t, int b, int stage, int i, int fresh) {
+  const size_t row = (size_t)b * t.S;
+  if (i < 144) {
+    const int k = i / 48 + 1, f = i % 48;
+    return stage - k >= 0 && stage - k != fresh ? t.cf[(row + stage - k) * 64 + f] : 0;
+  }
+  const int k = (i - 144) / 16 + 1, f = (i - 144) % 16;
+  return stage + k < t.S ? t.intr[(row + stage + k) * 16 + f] : 0;
+}
+
 __device__ void dec_fetch_rows(Dec &d, vf_space &sp, DecScratch &ds, const Tables &t, int b, int stage, int fresh) {
   const int tid = threadIdx.x, nt = blockDim.x, S = t.S;
   const size_t row = (size_t)b * S;
@@ -165,15 +177,7 @@ __device__ void dec_fetch_rows(Dec &d, vf_space &sp, DecScratch &ds, const Table
     d.intr[tid] = t.intr[(row + stage) * 16 + tid];
   }
   for (int i = tid; i < 192; i += nt) {
-    int32_t v = 0;
-    if (i < 144) {
-      int k = i / 48 + 1, f = i % 48;
-      if (stage - k >= 0 && stage - k != fresh) v = t.cf[(row + stage - k) * 64 + f];
-    } else {
-      int k = (i - 144) / 16 + 1, f = (i - 144) % 16;
-      if (stage + k < S) v = t.intr[(row + stage + k) * 16 + f];
-    }
-    d.nb[i] = v;
+    d.nb[i] = nb_row(t, b, stage, i, fresh);
   }
   // (the last five threads of the first wave: the first ones have the most to fetch above)
   if (tid == 59) ds.sc[0] = fresh >= 0 ? 0 : t.alive[b];
@@ -233,15 +237,7 @@ __device__ void build_dec(Dec &d, vf_space &sp, const Tables &t, int b, int stag
     d.intr[tid] = t.intr[(row + stage) * 16 + tid];
   }
   for (int i = tid; i < 192; i += nt) {
-    int32_t v = 0;
-    if (i < 144) {
-      int k = i / 48 + 1, f = i % 48;
-      if (stage - k >= 0) v = t.cf[(row + stage - k) * 64 + f];
-    } else {
-      int k = (i - 144) / 16 + 1, f = (i - 144) % 16;
-      if (stage + k < S) v = t.intr[(row + stage + k) * 16 + f];
-    }
-    d.nb[i] = v;
+    d.nb[i] = nb_row(t, b, stage, i, -1);
   }
   __syncthreads();
   if (tid == 0) {
