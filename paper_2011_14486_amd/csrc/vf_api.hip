@@ -506,12 +506,7 @@ int vf_greedy_schedule(vf_ctx *c, int first, int last, vf_state *out_states, int
       c->n_sched = i + 1;
     }
   }
-  const size_t n = (size_t)c->B * c->S;
-  if (out_states)
-    VF_HIP(c, hipMemcpyAsync(out_states, c->d_states, n * sizeof(vf_state), hipMemcpyDeviceToDevice, c->stream));
-  if (out_cids) VF_HIP(c, hipMemcpyAsync(out_cids, c->d_cids, n * 4, hipMemcpyDeviceToDevice, c->stream));
-  if (out_vals) VF_HIP(c, hipMemcpyAsync(out_vals, c->d_vals, n * 4, hipMemcpyDeviceToDevice, c->stream));
-  return VF_OK;
+  return vfk_copy_tables(c, out_states, out_cids, out_vals, nullptr);
 }
 
 int vf_set_noise(vf_ctx *c, float eps, uint64_t seed, int32_t first_rollout) {
@@ -557,13 +552,7 @@ int vf_beam_search(vf_ctx *c, int first, int last, vf_state *out_states, int32_t
     }
     c->n_sched = i + 1;
   }
-  const size_t n = (size_t)c->B * c->S;
-  if (out_states)
-    VF_HIP(c, hipMemcpyAsync(out_states, c->d_states, n * sizeof(vf_state), hipMemcpyDeviceToDevice, c->stream));
-  if (out_cids) VF_HIP(c, hipMemcpyAsync(out_cids, c->d_cids, n * 4, hipMemcpyDeviceToDevice, c->stream));
-  if (out_vals) VF_HIP(c, hipMemcpyAsync(out_vals, c->d_vals, n * 4, hipMemcpyDeviceToDevice, c->stream));
-  if (n_beams) VF_HIP(c, hipMemcpyAsync(n_beams, c->d_sel_n + 1, 4, hipMemcpyDeviceToDevice, c->stream));
-  return VF_OK;
+  return vfk_copy_tables(c, out_states, out_cids, out_vals, n_beams);
 }
 
 const char *vf_strerror(int code) {

@@ -216,6 +216,8 @@ struct vf_fast_dev {
 void vfk_fast_dev(const vf_ctx *c, bool generating, vf_fast_dev *fd, int *ks, int *NC);
 
 int vfk_setup_tables(vf_ctx *c);
+// the schedule tables to the caller's buffers (each nullable; n_beams: the schedules a beam search found)
+int vfk_copy_tables(vf_ctx *c, vf_state *out_states, int32_t *out_cids, float *out_vals, int32_t *n_beams);
 int vfk_reset_state(vf_ctx *c);
 // stages first.. become unscheduled again (tables as after committing stages 0..first-1)
 int vfk_rewind(vf_ctx *c, int first);

@@ -63,6 +63,20 @@ __global__ __launch_bounds__(256) void k_rewind(Tables t, int first) {
   if (tid == 0) t.alive[b] = first == 0 || t.cids[row + first - 1] >= 0;
 }
 
+// The tables to the caller's buffers, 18 words per stage: one launch instead of a copy per table
+// (4.5 us each on the GPU and about as much on the host).
+__global__ __launch_bounds__(256) void k_copy_tables(Tables t, size_t n, int32_t *states, int32_t *cids, float *vals,
+                                                     int32_t *n_beams, const int32_t *sel_n) {
+  const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+  if (states)
+    for (size_t i = i0; i < n * 16; i += step) states[i] = t.states[i];
+  if (cids)
+    for (size_t i = i0; i < n; i += step) cids[i] = t.cids[i];
+  if (vals)
+    for (size_t i = i0; i < n; i += step) vals[i] = t.vals[i];
+  if (n_beams && i0 == 0) n_beams[0] = sel_n[1];
+}
+
 __global__ __launch_bounds__(256) void k_fill_i32(int32_t *p, size_t n, int32_t v) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
@@ -433,6 +447,15 @@ __global__ __launch_bounds__(64) void k_beam_commit(Tables t, AltTables nw, int 
 
 int vfk_setup_tables(vf_ctx *c) {
   hipLaunchKernelGGL(k_setup, dim3(c->B), dim3(64), 0, c->stream, tables_of(c), c->d_intr, c->d_suffix);
+  VF_HIP(c, hipGetLastError());
+  return VF_OK;
+}
+
+int vfk_copy_tables(vf_ctx *c, vf_state *out_states, int32_t *out_cids, float *out_vals, int32_t *n_beams) {
+  if (!out_states && !out_cids && !out_vals && !n_beams) return VF_OK;
+  const size_t n = (size_t)c->S * c->B, blocks = (n * 16 + 255) / 256;
+  hipLaunchKernelGGL(k_copy_tables, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(256), 0, c->stream, tables_of(c), n,
+                     reinterpret_cast<int32_t *>(out_states), out_cids, out_vals, n_beams, (const int32_t *)c->d_sel_n);
   VF_HIP(c, hipGetLastError());
   return VF_OK;
 }
