@@ -153,11 +153,18 @@ int step(vf_ctx *c, int stage, int commit, int32_t *best_cid, float *best_val) {
     if (rc != VF_OK) return rc;
     return vfk_commit_from_partials(c, stage, nparts, commit, best_cid, best_val);
   }
+  int nparts = 0, part = 0;
+  if (vfk_small_generates(c)) {
+    int rc = vfk_prepare(c, stage);
+    if (rc == VF_OK)
+      rc = vfk_score_small(c, nullptr, 0, c->B, c->M, c->Mpad, 1, nullptr, 0, stage, nullptr, &nparts, &part);
+    if (rc != VF_OK) return rc;
+    return vfk_commit_from_partials(c, stage, nparts, commit, best_cid, best_val);
+  }
   int rc = ensure_feat(c);
   if (rc != VF_OK) return rc;
   rc = vfk_featurize(c, stage, c->d_feat);
   if (rc != VF_OK) return rc;
-  int nparts = 0;
   rc = vfk_score_mlp(c, c->d_feat, (int64_t)c->space.F * c->Mpad, c->B, c->M, c->Mpad, 1, nullptr, 0, &nparts, stage);
   if (rc != VF_OK) return rc;
   return vfk_commit_from_partials(c, stage, nparts, commit, best_cid, best_val);

@@ -243,6 +243,7 @@ int vfk_score_mlp(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob, i
                   const vf_partbuf *parts = nullptr, int *part_out = nullptr);
 // The same for small models (vf_small.hip), used where pm.small.w is set.
 int vfk_pack_small(vf_ctx *c, const float *weights_dev);
+bool vfk_small_generates(const vf_ctx *c);
 int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob, int64_t M, int64_t ld, int use_valid_row,
                     float *scores, int64_t ld_scores, int noise_stage, const vf_partbuf *parts, int *nparts_out, int *part_out);
 // Enumerate + featurize + score + partial argmin of one stage in a single kernel (bf16

@@ -314,10 +314,9 @@ struct EvalTabs {
   uint32_t vec_eff[3][8];     // ratio16(fac, cdiv(fac, vlen) * vlen)
   uint32_t par_eff1;          // the parallel efficiency of a single task
 };
-// first: the thread that takes entry 0 (the others follow it), for a caller whose first
-// threads are busy with something else.
-[[maybe_unused]] __device__ void fill_evaltabs(EvalTabs &tb, const Dec &d, const vf_space &sp, int first = 0) {
-  for (int i = (int)threadIdx.x - first; i >= 0 && i < 72; i += blockDim.x) {
+// Entries i0, i0 + step, ...
+[[maybe_unused]] __device__ __forceinline__ void fill_evaltabs_at(EvalTabs &tb, const Dec &d, const vf_space &sp, int i0, int step) {
+  for (int i = i0; i >= 0 && i < 72; i += step) {
     const int lvl = i / 24, dd = (i / 8) % 3, k = i % 8;
     const uint32_t f = k < sp.nf[dd] ? (uint32_t)sp.fac[dd][k] : 1u;
     const uint32_t o = cdiv(d.E[lvl][dd], f);
@@ -329,6 +328,11 @@ struct EvalTabs {
     }
     if (i == 0) tb.par_eff1 = ratio16(1u, smul(cdiv(1u, (uint32_t)sp.ncores), (uint32_t)sp.ncores));
   }
+}
+// By a workgroup.  first: the thread that takes entry 0 (the others follow it), for a caller whose
+// first threads are busy with something else.
+[[maybe_unused]] __device__ void fill_evaltabs(EvalTabs &tb, const Dec &d, const vf_space &sp, int first = 0) {
+  fill_evaltabs_at(tb, d, sp, (int)threadIdx.x - first, (int)blockDim.x);
 }
 
 // One candidate state from its digits: validity and (FEATS) the 64 core features.

@@ -1273,6 +1273,12 @@ int vfk_step_scores(vf_ctx *c, int stage) {
   int nparts = 0;
   if (vfk_seq_model(c)) return vfk_seq_step(c, stage, c->d_scores, c->Mpad, -1, &nparts);
   if (vfk_can_fuse_step(c)) return score_mlp(c, nullptr, 0, c->B, c->M, c->Mpad, 1, c->d_scores, c->Mpad, &nparts, stage, -1);
+  if (vfk_small_generates(c)) {
+    int part = 0;
+    rc = vfk_prepare(c, stage);
+    if (rc != VF_OK) return rc;
+    return vfk_score_small(c, nullptr, 0, c->B, c->M, c->Mpad, 1, c->d_scores, c->Mpad, -1, nullptr, &nparts, &part);
+  }
   // general models: materialise the features, score, mask
   const size_t fwant = (size_t)c->B * c->space.F * c->Mpad;
   rc = grow(c, c->d_feat, c->feat_elems, fwant);

@@ -28,6 +28,7 @@ typedef float floatx2 __attribute__((ext_vector_type(2), aligned(4)));
 
 constexpr int SMALL_MAX = 128;        // widest hidden layer
 constexpr int SMALL_LDS = 150 * 1024; // weights and biases
+constexpr int GEN_LDS = 124 * 1024;   // the same where every wave has a decision's context next to them
 
 // Input row (within a k-step of 16) of element e of lane half h: as they come for the first layer,
 // in the order of the accumulator's rows for the others.
@@ -69,7 +70,32 @@ struct SmallArgs {
   int32_t *pidx;
   int nparts, units, spp;
   NoiseArgs na;
+  const uint32_t *decpack;  // GEN: the decisions' contexts
 };
+
+// GEN: the candidates are enumerated and featurized where they are scored (x is not used); scores of
+// ids that are not valid candidates read +inf.  Every wave keeps the context of its problem.
+struct WaveDec {
+  DecPack pk;
+  EvalTabs tabs;
+};
+__device__ __forceinline__ void load_wave_dec(WaveDec &wd, const uint32_t *decpack, int p, int lane) {
+  uint32_t *const dst = reinterpret_cast<uint32_t *>(&wd.pk);
+#pragma unroll
+  for (int i = 0; i < (VF_DECPACK_DWORDS + 63) / 64; ++i)
+    if (i * 64 + lane < VF_DECPACK_DWORDS) dst[i * 64 + lane] = decpack[(size_t)p * VF_DECPACK_DWORDS + i * 64 + lane];
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  fill_evaltabs_at(wd.tabs, wd.pk.d, wd.pk.sp, lane, 64);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+__device__ __forceinline__ bool eval_wave(const WaveDec &wd, uint32_t cid, int32_t *core) {
+  return eval_digits<true>(wd.pk.d, wd.pk.sp, digits_small(wd.pk.sp, cid), &wd.tabs, core);
+}
+// value `lane group` of four (or two) registers, without indexing them
+__device__ __forceinline__ int32_t pick(int g, int32_t a, int32_t b) { return g ? b : a; }
+__device__ __forceinline__ int32_t pick(int g, int32_t a, int32_t b, int32_t c, int32_t d) {
+  return g & 2 ? (g & 1 ? d : c) : (g & 1 ? b : a);
+}
 
 __device__ __forceinline__ void stage_small(const SmallArgs &a, uint4 *wl, float *bl) {
 #pragma unroll 4
@@ -112,11 +138,12 @@ __device__ __forceinline__ void load_raw(int32_t (&r)[ROWS][N], const int32_t *p
 // of a sub-tile of 64 (64-128-128-1: 100 of them, 3200 cycles) and the conversion of its inputs cost
 // about the same; two waves per SIMD overlap one's with the other's, and the next 32 input rows are
 // always under way.
-template <int CT, int NT>
+template <int CT, int NT, bool GEN>
 __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint4 *const wl = reinterpret_cast<uint4 *>(smem);
   float *const bl = reinterpret_cast<float *>(wl + a.md.nw);
+  WaveDec &wd = reinterpret_cast<WaveDec *>(bl + (a.md.nbias + 3) / 4 * 4)[threadIdx.x >> 6];  // (GEN only)
   const int lane = threadIdx.x & 63, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   stage_small(a, wl, bl);
@@ -146,12 +173,18 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
     const int left = (int)(a.M - n0 < 32 * CT ? a.M - n0 : 32 * CT) - CT * (lane & 31);
     load_raw<16, 8, CT>(raw, row + CT * (lane & 31), a.ld, 8 * a.ld, left, n0 + 32 * CT <= a.M);
   };
-  const int stride = (int)gridDim.x * 8;
-  int u = (int)blockIdx.x + (int)gridDim.x * w, sub = 0;
-  if (u >= a.units) return;
+  // (GEN: units in a row, so that they mostly share a problem)
+  const int waves = (int)gridDim.x * 8, stride = GEN ? 1 : waves;
+  int u = (int)blockIdx.x + (int)gridDim.x * w, sub = 0, u_end = a.units;
+  if (GEN) {
+    u_end = (int)((int64_t)(u + 1) * a.units / waves);
+    u = (int)((int64_t)u * a.units / waves);
+  }
+  if (u >= u_end) return;
   int p = u / a.nparts, part = u - p * a.nparts;
   int64_t n0 = (int64_t)part * a.spp * 32 * CT;
-  fetch(p, n0, 0);
+  if constexpr (GEN) load_wave_dec(wd, a.decpack, p, lane);
+  else fetch(p, n0, 0);
   float v = __builtin_inff();
   int32_t vc = -1;
   for (;;) {
@@ -166,7 +199,7 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
       npart = nu - np * a.nparts;
       nn0 = (int64_t)npart * a.spp * 32 * CT;
     }
-    const bool more = nu < a.units;
+    const bool more = nu < u_end;
     if (!more) { np = p; nn0 = n0; }
     // (the weights and biases that a sub-tile starts with are read afresh from LDS for every one: kept
     // across the sub-tiles they would fill the registers)
@@ -175,8 +208,31 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
     bool ok[CT];
 #pragma unroll
     for (int c = 0; c < CT; ++c) ok[c] = n0 + CT * (lane & 31) + c < a.M;
-    // ---- first layer (a network without a hidden layer has one row tile there: its output vector)
+    uint4 own[GEN ? 4 : 1][CT];  // (GEN) the candidates' rows 0..63, as the k-steps 0..3 want them
+    bool closed = false;         // (GEN) no id of the sub-tile can be valid
+    if constexpr (GEN) {
+      const int64_t to = n0 + 32 * CT < a.M ? n0 + 32 * CT : a.M;
+      closed = range_closed(wd.pk.d, wd.pk.sp, (uint32_t)n0, (uint32_t)to);
+      if (!closed) {
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+          int32_t core[64];
+          // (evaluated behind the last id too: core must be defined)
+          const bool valid = eval_wave(wd, (uint32_t)(ok[c] ? n0 + CT * (lane & 31) + c : 0), core);
+          ok[c] = ok[c] && valid;
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            float f[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) f[e] = plog2_dev(pick(h, core[16 * s + e], core[16 * s + 8 + e]));
+            own[s][c] = make_uint4(pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3]), pack_bf16(f[4], f[5]), pack_bf16(f[6], f[7]));
+          }
+        }
+      }
+    }
     floatx16 acc[NT][CT];
+    if (!closed) {
+    // ---- first layer (a network without a hidden layer has one row tile there: its output vector)
     const int ks0 = a.md.kst[0];
 #pragma unroll
     for (int t = 0; t < NT; ++t)
@@ -188,8 +244,44 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
     uint4 x[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) x[t] = wp[t * ks0 * 64];
-    for (int ch = 0; ch < chunks; ++ch) {
+    auto products = [&](const uint4 (&in)[2][CT]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        wp += 64;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+#pragma unroll
+          for (int c = 0; c < CT; ++c) acc[t][c] = mfma(x[t], in[s][c], acc[t][c]);
+          x[t] = wp[t * ks0 * 64];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    };
+    if constexpr (GEN) {
+#pragma unroll
+      for (int ch = 0; ch < 2; ++ch) {
+        uint4 in[2][CT];
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) in[s][c] = own[2 * ch + s][c];
+        products(in);
+      }
+    }
+    for (int ch = GEN ? 2 : 0; ch < chunks; ++ch) {
       uint4 in[2][CT];
+      if constexpr (GEN) {
+        // rows 64..255, the same for all candidates of the decision (DecPack::stat holds them as pairs)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const uint32_t *nb = wd.pk.stat + 16 + (ch * 32 - 64 + 16 * s + 8 * h) / 2;
+          const uint4 q = make_uint4(nb[0], nb[1], nb[2], nb[3]);
+#pragma unroll
+          for (int c = 0; c < CT; ++c) in[s][c] = q;
+        }
+        products(in);
+        continue;
+      }
 #pragma unroll
       for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -205,17 +297,7 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
         }
       const bool onward = ch + 1 == chunks;  // (behind the last sub-tile of all: the same one once more)
       fetch(onward ? np : p, onward ? nn0 : n0, onward ? 0 : ch + 1);
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        wp += 64;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-#pragma unroll
-          for (int c = 0; c < CT; ++c) acc[t][c] = mfma(x[t], in[s][c], acc[t][c]);
-          x[t] = wp[t * ks0 * 64];
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
+      products(in);
     }
     // ---- the other hidden layers, two row tiles at a time (all of them at once would not leave
     // registers for the input rows under way), then the output vector as a row tile with one row
@@ -277,11 +359,15 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
         for (int c = 0; c < CT; ++c) acc[0][c] = mfma(y, act[s][c], acc[0][c]);
       }
     }
+    }  // (not closed)
     // ---- row 0 of the last product (element 0 of lanes 0..31) is the score
     {
       float s[CT];
 #pragma unroll
-      for (int c = 0; c < CT; ++c) s[c] = acc[0][c][0] + bl[a.md.boff[L - 1]];
+      for (int c = 0; c < CT; ++c) {
+        s[c] = closed ? __builtin_inff() : acc[0][c][0] + bl[a.md.boff[L - 1]];
+        if (GEN && (closed || !ok[c])) { s[c] = __builtin_inff(); ok[c] = false; }
+      }
       const int64_t n = n0 + CT * (lane & 31);
       if (lane < 32) {
         if (a.scores) {
@@ -312,6 +398,7 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
       }
     }
     if (!more) break;
+    if (GEN && np != p) load_wave_dec(wd, a.decpack, np, lane);
     u = nu; sub = nsub; p = np; part = npart; n0 = nn0;
   }
 }
@@ -319,7 +406,7 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
 // 16 * CT candidates per sub-tile, lane l has columns CT (l % 16) + 0 .. CT - 1 and rows 4 (l / 16) + 0..3
 // of every 16.  The output vector is a dot product on the vector ALU (a sixteenth of a row tile
 // would be used), the four lane groups' parts added at the end.
-template <int CT, int NT>
+template <int CT, int NT, bool GEN>
 __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
   // partial sums per accumulator, even and odd groups of 16 rows apart, where the registers allow it:
   // a sum of half as many terms is the more exact one
@@ -328,6 +415,7 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
   uint4 *const wl = reinterpret_cast<uint4 *>(smem);
   const floatx4 *const wf = reinterpret_cast<const floatx4 *>(smem);
   float *const bl = reinterpret_cast<float *>(wl + a.md.nw);
+  WaveDec &wd = reinterpret_cast<WaveDec *>(bl + (a.md.nbias + 3) / 4 * 4)[threadIdx.x >> 6];  // (GEN only)
   const int lane = threadIdx.x & 63, q = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   stage_small(a, wl, bl);
@@ -349,12 +437,18 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
       }
     }
   };
-  const int stride = (int)gridDim.x * 8;
-  int u = (int)blockIdx.x + (int)gridDim.x * w, sub = 0;
-  if (u >= a.units) return;
+  // (GEN: units in a row, so that they mostly share a problem)
+  const int waves = (int)gridDim.x * 8, stride = GEN ? 1 : waves;
+  int u = (int)blockIdx.x + (int)gridDim.x * w, sub = 0, u_end = a.units;
+  if (GEN) {
+    u_end = (int)((int64_t)(u + 1) * a.units / waves);
+    u = (int)((int64_t)u * a.units / waves);
+  }
+  if (u >= u_end) return;
   int p = u / a.nparts, part = u - p * a.nparts;
   int64_t n0 = (int64_t)part * a.spp * 16 * CT;
-  fetch(p, n0, 0);
+  if constexpr (GEN) load_wave_dec(wd, a.decpack, p, lane);
+  else fetch(p, n0, 0);
   float v = __builtin_inff();
   int32_t vc = -1;
   for (;;) {
@@ -368,7 +462,7 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
       npart = nu - np * a.nparts;
       nn0 = (int64_t)npart * a.spp * 16 * CT;
     }
-    const bool more = nu < a.units;
+    const bool more = nu < u_end;
     if (!more) { np = p; nn0 = n0; }
     // (the weights and biases that a sub-tile starts with are read afresh from LDS for every one: kept
     // across the sub-tiles they would fill the registers)
@@ -377,11 +471,31 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
     bool ok[CT];
 #pragma unroll
     for (int c = 0; c < CT; ++c) ok[c] = n0 + CT * (lane & 15) + c < a.M;
+    float own[GEN ? 4 : 1][4][CT];  // (GEN) the candidates' rows 0..63: group of 16, row of the lane group, column
+    bool closed = false;            // (GEN) no id of the sub-tile can be valid
+    if constexpr (GEN) {
+      const int64_t to = n0 + 16 * CT < a.M ? n0 + 16 * CT : a.M;
+      closed = range_closed(wd.pk.d, wd.pk.sp, (uint32_t)n0, (uint32_t)to);
+      if (!closed) {
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+          int32_t core[64];
+          const bool valid = eval_wave(wd, (uint32_t)(ok[c] ? n0 + CT * (lane & 15) + c : 0), core);
+          ok[c] = ok[c] && valid;
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              own[g][e][c] = plog2_dev(pick(q, core[16 * g + e], core[16 * g + 4 + e], core[16 * g + 8 + e], core[16 * g + 12 + e]));
+        }
+      }
+    }
     floatx4 acc[SP][NT][CT];
     float s[CT];
     const bool only = L == 1;  // no hidden layer: the inputs go straight into the output dot
 #pragma unroll
     for (int c = 0; c < CT; ++c) s[c] = 0.0f;
+    if (!closed) {
 #pragma unroll
     for (int sp = 0; sp < SP; ++sp)
 #pragma unroll
@@ -394,20 +508,7 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
     floatx4 x[TH];
 #pragma unroll
     for (int t = 0; t < TH; ++t) x[t] = wf[(only ? 0 : t * groups0 * 64) + at];
-    for (int ch = 0; ch < chunks; ++ch) {
-      float in[2][4][CT];
-#pragma unroll
-      for (int g = 0; g < 2; ++g)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int c = 0; c < CT; ++c) in[g][e][c] = plog2_dev(raw[4 * g + e][c]);
-      if (ch == 0 && a.use_valid_row) {
-#pragma unroll
-        for (int c = 0; c < CT; ++c) ok[c] = ok[c] && raw[4][c] != 0;
-      }
-      const bool onward = ch + 1 == chunks;  // (behind the last sub-tile of all: the same one once more)
-      fetch(onward ? np : p, onward ? nn0 : n0, onward ? 0 : ch + 1);
+    auto products = [&](const float (&in)[2][4][CT], int ch) __attribute__((always_inline)) {
 #pragma unroll
       for (int g = 0; g < 2; ++g) {
         const int kg = ch * 2 + g;
@@ -430,6 +531,48 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
           __builtin_amdgcn_sched_barrier(0);
         }
       }
+    };
+    if constexpr (GEN) {
+#pragma unroll
+      for (int ch = 0; ch < 2; ++ch) {
+        float in[2][4][CT];
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) in[g][e][c] = own[2 * ch + g][e][c];
+        products(in, ch);
+      }
+    }
+    for (int ch = GEN ? 2 : 0; ch < chunks; ++ch) {
+      float in[2][4][CT];
+      if constexpr (GEN) {
+        // rows 64..255, the same for all candidates of the decision
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float f = plog2_dev(wd.pk.d.nb[ch * 32 - 64 + 16 * g + 4 * q + e]);
+#pragma unroll
+            for (int c = 0; c < CT; ++c) in[g][e][c] = f;
+          }
+        products(in, ch);
+        continue;
+      }
+#pragma unroll
+      for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) in[g][e][c] = plog2_dev(raw[4 * g + e][c]);
+      if (ch == 0 && a.use_valid_row) {
+#pragma unroll
+        for (int c = 0; c < CT; ++c) ok[c] = ok[c] && raw[4][c] != 0;
+      }
+      const bool onward = ch + 1 == chunks;  // (behind the last sub-tile of all: the same one once more)
+      fetch(onward ? np : p, onward ? nn0 : n0, onward ? 0 : ch + 1);
+      products(in, ch);
     }
     if (!only) {
       // a finished layer: bias, ReLU, and its rows are the next one's inputs as they lie
@@ -490,12 +633,14 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
           for (int c = 0; c < CT; ++c) s[c] = fmaf(y[e], act[t][c][e], s[c]);
       }
     }
+    }  // (not closed)
     const float bout = bl[a.md.boff[L - 1]];
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
       s[c] += __shfl_xor(s[c], 16);
       s[c] += __shfl_xor(s[c], 32);
       s[c] += bout;
+      if (GEN && (closed || !ok[c])) { s[c] = __builtin_inff(); ok[c] = false; }
     }
     const int64_t n = n0 + CT * (lane & 15);
     if (lane < 16) {
@@ -517,6 +662,7 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
       vc = -1;
     }
     if (!more) break;
+    if (GEN && np != p) load_wave_dec(wd, a.decpack, np, lane);
     u = nu; sub = nsub; p = np; part = npart; n0 = nn0;
   }
 }
@@ -587,7 +733,15 @@ int vfk_pack_small(vf_ctx *c, const float *wdev) {
   return VF_OK;
 }
 
-// Scores on the kernels above.  part_out: candidates per partial minimum, a divisor of 128.
+// Whether the search's candidates can be generated in the kernels above.
+bool vfk_small_generates(const vf_ctx *c) {
+  const vf_small_dev &d = c->pm.small;
+  return c->has_model && d.w && c->model.kind == VF_MLP && c->model.dims[0] == c->space.F &&
+         (size_t)d.nw * 16 + (size_t)d.nbias * 4 <= GEN_LDS;
+}
+
+// Scores on the kernels above.  part_out: candidates per partial minimum, a divisor of 128.  x null: the
+// candidates of the decisions whose contexts d_decpack holds are generated (masked scores).
 int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob, int64_t M, int64_t ld, int use_valid_row,
                     float *scores, int64_t ld_scores, int noise_stage, const vf_partbuf *parts, int *nparts_out, int *part_out) {
   const bool bf16 = c->model.dtype == VF_BF16;
@@ -621,14 +775,18 @@ int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob,
   a.na.eps = noise_stage >= 0 ? c->noise_eps : 0.0f;
   a.na.k0 = (uint32_t)c->noise_seed; a.na.k1 = (uint32_t)(c->noise_seed >> 32);
   a.na.stage = noise_stage; a.na.first_rollout = c->noise_first;
-  const size_t smem = (size_t)a.md.nw * 16 + (size_t)a.md.nbias * 4;
+  a.decpack = c->d_decpack;
+  size_t smem = (size_t)a.md.nw * 16 + (size_t)a.md.nbias * 4;
+  if (!x) smem = (smem + 15) / 16 * 16 + 8 * sizeof(WaveDec);
   typedef void (*small_kernel)(SmallArgs);
-  static constexpr small_kernel kerns[2][2][4] = {
-      {{k_small_bf16<1, 1>, k_small_bf16<1, 2>, k_small_bf16<1, 3>, k_small_bf16<1, 4>},
-       {k_small_bf16<2, 1>, k_small_bf16<2, 2>, k_small_bf16<2, 3>, k_small_bf16<2, 4>}},
-      {{k_small_f32<1, 2>, k_small_f32<1, 4>, k_small_f32<1, 6>, k_small_f32<1, 8>},
-       {k_small_f32<2, 2>, k_small_f32<2, 4>, k_small_f32<2, 6>, k_small_f32<2, 8>}}};
-  const small_kernel kern = kerns[bf16 ? 0 : 1][ct - 1][a.md.NT * base / 32 - 1];
+#define VF_SMALL(k, ct, gen, n1, n2, n3, n4) {k<ct, n1, gen>, k<ct, n2, gen>, k<ct, n3, gen>, k<ct, n4, gen>}
+  static constexpr small_kernel kerns[2][2][2][4] = {
+      {{VF_SMALL(k_small_bf16, 1, false, 1, 2, 3, 4), VF_SMALL(k_small_bf16, 2, false, 1, 2, 3, 4)},
+       {VF_SMALL(k_small_f32, 1, false, 2, 4, 6, 8), VF_SMALL(k_small_f32, 2, false, 2, 4, 6, 8)}},
+      {{VF_SMALL(k_small_bf16, 1, true, 1, 2, 3, 4), VF_SMALL(k_small_bf16, 2, true, 1, 2, 3, 4)},
+       {VF_SMALL(k_small_f32, 1, true, 2, 4, 6, 8), VF_SMALL(k_small_f32, 2, true, 2, 4, 6, 8)}}};
+#undef VF_SMALL
+  const small_kernel kern = kerns[x ? 0 : 1][bf16 ? 0 : 1][ct - 1][a.md.NT * base / 32 - 1];
   vf_prof_scope prof(c, VF_PROF_SCORE);
   VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
   hipLaunchKernelGGL(kern, dim3((unsigned)(units < ncu ? units : ncu)), dim3(512), smem, c->stream, a);

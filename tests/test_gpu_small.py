@@ -72,3 +72,34 @@ def test_extreme_weights(vf, dtype):
     s, bi, bv = vf.vf_score(ctx, torch.from_numpy(x).cuda(), group=128)
     assert torch.isnan(s).all() and bi.tolist() == [-1, -1]
     vf.vf_destroy(ctx)
+
+
+@pytest.mark.parametrize("dims,dtype", [([64, 128, 128, 1], I.FP32), ([256, 96, 1], I.FP32), ([256, 1], I.FP32),
+                                        ([64, 96, 32, 1], I.BF16), ([256, 96, 64, 1], I.BF16), ([256, 1], I.BF16)])
+@pytest.mark.parametrize("B", [1, 70])
+def test_generated_candidates_equal_scored_features(vf, dims, dtype, B):
+    """A decision scored from the generated candidates against vf_score on vf_featurize's matrix: the
+    same features and the same arithmetic, so the same winner and the same bits (one or two columns
+    per lane, closed runs of ids, the last ids of a space that is no multiple of a tile).  fp32 with
+    70 problems: a lane then has two columns and one partial sum each, vf_score on 4608 vectors one
+    column and two partial sums, so values agree to 1e-5 (the bound of fp32 sums elsewhere), and the
+    winner's score is that close to the minimum."""
+    sp = I.make_space([1, 2, 4], [1, 2, 4, 8], [1, 4, 8], I.XC_INNER_PERMS, 2, 2, [I.ROOT, I.L1, I.L2, I.INLINE], 2, dims[0])
+    M = I.space_dense_count(sp)
+    pipes = np.stack([I.random_pipeline(4, 300 + b) for b in range(B)])
+    w, model = I.mlp_weights(dims, 8, bias_std=0.2), I.model_record(I.MLP, dims, dtype)
+    ctx = vf.vf_create(0)
+    vf.vf_set_space(ctx, sp); vf.vf_set_pipeline(ctx, pipes); vf.vf_set_model(ctx, model, w)
+    for i in range(4):
+        feat = vf.vf_featurize(ctx, i)
+        cids, vals = vf.vf_argmin_step(ctx, i, True)
+        for b in range(0, B, 9):
+            s = vf.vf_score(ctx, feat[b].contiguous(), M=M)[0].cpu().numpy()
+            s[feat[b, 16, :M].cpu().numpy() == 0] = np.inf
+            c = int(np.argmin(s)) if np.isfinite(s).any() else -1
+            if dtype == I.FP32 and B > 1 and c >= 0:
+                tol = 1e-5 * max(1.0, abs(float(s.min())))
+                assert abs(float(vals[b]) - float(s.min())) <= tol and s[int(cids[b])] - s.min() <= tol, (i, b)
+            else:
+                assert int(cids[b]) == c and float(vals[b]) == float(s.min()), (i, b)
+    vf.vf_destroy(ctx)
