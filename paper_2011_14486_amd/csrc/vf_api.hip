@@ -494,9 +494,13 @@ int vf_greedy_schedule(vf_ctx *c, int first, int last, vf_state *out_states, int
     const int rc = settle_whole(c, first > 0);
     if (rc != VF_OK) return rc;
   }
+  bool lists = false;
   if (first <= last && vfk_layer_pays(c) && !vfk_whole_pays(c)) {
     const int rc = vfk_greedy_layers(c, first, last);
-    if (rc != VF_OK) return rc;
+    if (rc != VF_OK && (rc != VF_ENOMEM || c->n_sched != first)) return rc;
+    lists = rc == VF_OK;  // (no memory for the lists: the other ways)
+  }
+  if (lists) {
   } else if (first <= last && vfk_whole_team(c) >= 1) {
     int rc = vfk_greedy_whole(c, first, last);
     if (rc != VF_OK) return rc;
@@ -545,8 +549,8 @@ int vf_beam_search(vf_ctx *c, int first, int last, vf_state *out_states, int32_t
   if (rc != VF_OK) return rc;
   if (first <= last && vfk_beam_lists(c)) {
     rc = vfk_beam_layers(c, first, last);
-    if (rc != VF_OK) return rc;
-    first = last + 1;
+    if (rc == VF_OK) first = last + 1;
+    else if (rc != VF_ENOMEM || c->n_sched != first) return rc;  // (no memory for the lists: id ranges)
   }
   for (int i = first; i <= last; ++i) {
     rc = vfk_step_scores(c, i);

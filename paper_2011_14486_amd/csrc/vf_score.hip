@@ -2,8 +2,9 @@
 //
 // Inputs are raw integer features, candidate-contiguous ([feature][candidate]); they
 // are normalised on load with a piecewise-linear log2 (Sec. 3.2: the network is fed
-// normalised feature values).  Three scorers:
-//   - fp32 MLP: plain FMA kernels, one layer per launch (small models);
+// normalised feature values).  Small networks have kernels of their own (vf_small.hip); for the
+// others there are three scorers:
+//   - fp32 MLP: plain FMA kernels, one layer per launch;
 //   - bf16 MLP: the whole layer chain in one kernel per tile of candidates.  The
 //     tile's activations live in LDS as bf16 [candidate][feature]; weights are the
 //     MFMA A operand (output feature = row), activations the B operand (candidate =
@@ -1219,7 +1220,8 @@ bool vfk_layer_pays(const vf_ctx *c) {
 int vfk_step_fused(vf_ctx *c, int stage, int *nparts_out) {
   if (vfk_layer_pays(c)) {
     const int rc = vfk_layer_open(c, stage);
-    return rc != VF_OK ? rc : vfk_layer_score(c, stage, nullptr, nparts_out);
+    if (rc == VF_OK) return vfk_layer_score(c, stage, nullptr, nparts_out);
+    if (rc != VF_ENOMEM) return rc;  // (no memory for the lists: id ranges need none)
   }
   return score_mlp(c, nullptr, 0, c->B, c->M, c->Mpad, 1, nullptr, 0, nparts_out, stage, stage);
 }

@@ -507,7 +507,7 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
     constexpr int TH = NT / 2;  // fragments in flight
     floatx4 x[TH];
 #pragma unroll
-    for (int t = 0; t < TH; ++t) x[t] = wf[(only ? 0 : t * groups0 * 64) + at];
+    for (int t = 0; t < TH; ++t) x[t] = only ? floatx4{0.0f, 0.0f, 0.0f, 0.0f} : wf[t * groups0 * 64 + at];
     auto products = [&](const float (&in)[2][4][CT], int ch) __attribute__((always_inline)) {
 #pragma unroll
       for (int g = 0; g < 2; ++g) {
@@ -776,7 +776,8 @@ int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob,
   a.na.k0 = (uint32_t)c->noise_seed; a.na.k1 = (uint32_t)(c->noise_seed >> 32);
   a.na.stage = noise_stage; a.na.first_rollout = c->noise_first;
   a.decpack = c->d_decpack;
-  size_t smem = (size_t)a.md.nw * 16 + (size_t)a.md.nbias * 4;
+  // (a kilobyte more: the last refill of a weight fragment reads behind the weights)
+  size_t smem = (size_t)a.md.nw * 16 + (size_t)a.md.nbias * 4 + 1024;
   if (!x) smem = (smem + 15) / 16 * 16 + 8 * sizeof(WaveDec);
   typedef void (*small_kernel)(SmallArgs);
 #define VF_SMALL(k, ct, gen, n1, n2, n3, n4) {k<ct, n1, gen>, k<ct, n2, gen>, k<ct, n3, gen>, k<ct, n4, gen>}

@@ -3,7 +3,8 @@
 // step of the greedy scan by itself - decision context, the list of valid candidates,
 // their features, V(s) with the bf16 MLP, the running minimum, the commit "s_i := s" -
 // so that a schedule costs one launch and nothing but the tables and the id list touches
-// memory.  Used from 24 problems on (below that the two launches per layer are faster).
+// memory (when: vfk_whole_team, vfk_whole_pays).  The same tile pipeline scores one decision of every
+// problem for the callers that go layer by layer (LAYER, vfk_layer_score).
 //
 // The MLP is the same contraction as in the per-layer scorer: weights are the MFMA A
 // operand and stream from L2 through a ring of registers, activations are the B operand
@@ -662,12 +663,13 @@ static whole_kernel whole_launch_shape(const vf_ctx *c, vf_fast_dev *fd, int *ks
   return NC == 64 ? k_whole<64, 4, 2, false> : k_whole<128, 2, 4, false>;
 }
 
-// Workgroups per problem for a whole-schedule launch, 0 = use the per-layer launches
+// Workgroups per problem for a whole-schedule launch where one is wanted (vfk_whole_pays, and decisions
+// of few tiles, see vfk_layer_pays), 0 = use the per-layer launches
 // (also when the model's tile does not fit the LDS of a compute unit next to its input
 // buffer, e.g. three hidden layers of 512 with all their biases).
 // 1 with more problems than half the compute units: every workgroup owns ceil(B / units)
 // problems from the first layer to the last and helps the others when it is done (measured
-// per step against the per-layer launches: 140 problems 3.6 instead of 5.1 ms, 160: 4.0
+// per step against the per-layer launches on id ranges: 140 problems 3.6 instead of 5.1 ms, 160: 4.0
 // instead of 5.6, 300: 7.0 instead of 8.5); with fewer problems a fixed team per problem, as
 // large as the compute units and the tiles of a decision allow, at most 16 (128 problems x
 // 2: 3.1 instead of 4.9 ms, 64 x 4: 2.1 instead of 3.4, 32 x 8: 1.7 instead of 2.2; helpers
@@ -725,7 +727,7 @@ int vfk_whole_team(const vf_ctx *c) {
 // both can run: with a problem for most compute units but none for a second round.  The launches per
 // layer deal out the tiles of all problems evenly and wait for nobody, but pay two launches and a
 // serial opening per layer (256-512-512-1, 20 layers of 4096 ids: 64 problems 1.61 against 1.14 ms per
-// layer, 128: 2.06 / 1.75, 160: 2.52 / 2.05, 200: 2.65 / 2.46, 256: 2.95 / 2.98, 300: 4.57 / 3.46;
+// schedule, 128: 2.06 / 1.75, 160: 2.52 / 2.05, 200: 2.65 / 2.46, 256: 2.95 / 2.98, 300: 4.57 / 3.46;
 // 100 layers of 16384 ids: 100 problems 13.0 / 11.6, 160: 17.1 / 16.9, 180: 18.4 / 18.6, 200: 19.7 / 20.5).
 bool vfk_whole_pays(const vf_ctx *c) {
   int ncu = 256;
