@@ -501,6 +501,7 @@ int vf_greedy_schedule(vf_ctx *c, int first, int last, vf_state *out_states, int
     lists = rc == VF_OK;  // (no memory for the lists: the other ways)
   }
   if (lists) {
+    // decided above
   } else if (first <= last && vfk_whole_team(c) >= 1) {
     int rc = vfk_greedy_whole(c, first, last);
     if (rc != VF_OK) return rc;

@@ -729,10 +729,17 @@ int vfk_whole_team(const vf_ctx *c) {
 // serial opening per layer (256-512-512-1, 20 layers of 4096 ids: 64 problems 1.61 against 1.14 ms per
 // schedule, 128: 2.06 / 1.75, 160: 2.52 / 2.05, 200: 2.65 / 2.46, 256: 2.95 / 2.98, 300: 4.57 / 3.46;
 // 100 layers of 16384 ids: 100 problems 13.0 / 11.6, 160: 17.1 / 16.9, 180: 18.4 / 18.6, 200: 19.7 / 20.5).
+// Decisions of 64 tiles or more leave the helpers enough to share, so that further rounds that are
+// more than three quarters full pay as well (the 100 layers again, other inputs: 300 problems 68.1 /
+// 66.1 ms, 384: 81.7 / 81.6, 448: 93.9 / 95.1, 512: 106.1 / 108.7, 768: 159.2 / 162.6; 4096 ids stay
+// with the lists: 512: 7.96 / 7.76).
 bool vfk_whole_pays(const vf_ctx *c) {
   int ncu = 256;
   (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
-  return c->B > ncu * 5 / 8 && c->B <= ncu && vfk_whole_team(c) >= 1;
+  const int64_t units = (c->B + (int64_t)ncu - 1) / ncu * ncu;
+  const int NC = c->pm.fast_rt == 4 ? 64 : 128;
+  const bool pays = c->B <= ncu ? c->B > ncu * 5 / 8 : (c->M + NC - 1) / NC >= 64 && c->B * (int64_t)4 > units * 3;
+  return pays && vfk_whole_team(c) >= 1;
 }
 
 // Algorithm 1 over stages first..last for every problem of the batch, one launch.

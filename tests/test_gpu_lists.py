@@ -53,6 +53,23 @@ def test_batch_on_lists_equals_single_problems(vf, dims):
     vf.vf_destroy(many)
 
 
+@pytest.mark.parametrize("B", [385, 512])
+def test_second_round_of_long_decisions_in_one_launch(vf, B):
+    """16384 ids, more problems than compute units: whole schedules in one launch (from three quarters
+    of the second round on) decide what the steps on lists decide, bit for bit."""
+    dims, sp = [256, 512, 512, 1], I.mobilenetv2_space()
+    pipes = np.stack([I.random_pipeline(3, 40 + b % 7) for b in range(B)])
+    ctx = context(vf, pipes, sp, I.model_record(I.MLP, dims, I.BF16), I.mlp_weights(dims, 4, bias_std=0.1))
+    vf.vf_set_noise(ctx, 0.2, 9, 0)
+    whole = [t.cpu().numpy() for t in vf.vf_greedy_schedule(ctx)]
+    vf.vf_reset_state(ctx)
+    for i in range(3):
+        vf.vf_argmin_step(ctx, i, True)
+    for a, b in zip(whole, vf.vf_greedy_schedule(ctx, first=3)):
+        assert np.array_equal(a, b.cpu().numpy())
+    vf.vf_destroy(ctx)
+
+
 @pytest.mark.parametrize("H", [32, 96, 256])
 def test_recurrent_batch_equals_single_problems(vf, H):
     """Many candidates run in tiles of 96, few in tiles of 64, with the same arithmetic per candidate:
