@@ -75,12 +75,14 @@ __device__ __forceinline__ void wave_min(float &v, int32_t &c) {
 // A product sigma(a) tanh(b) is one quotient: with u = 1 + e^{-a} and e = e^{-2|b|} it is
 // sign(b) (1 - e) / (u + e u) - two exponentials and one reciprocal instead of two and two, which
 // matters because these run at a quarter of the rate of ordinary instructions (8 instead of 10 per
-// cell).  e never overflows; u may become infinite, and the product is then 0, as it should be.  A NaN
+// cell).  u is infinite below a = -88 and the product is then 0.  e must not become 0 there (it would
+// from |b| = 44 on, and 0 u is a NaN): 2^-60 is added, which changes 1 - e and u + e u for no b, being
+// less than half an ulp of 1 where e is not small and of no weight next to 1 where it is.  A NaN
 // comes out as a NaN.
 __device__ __forceinline__ float sig_tanh(float a, float b) {
   constexpr float LOG2E = 1.44269504088896340736f;
   const float u = 1.0f + __builtin_amdgcn_exp2f(a * -LOG2E);
-  const float e = __builtin_amdgcn_exp2f(__builtin_fabsf(b) * (-2.0f * LOG2E));
+  const float e = __builtin_amdgcn_exp2f(__builtin_fabsf(b) * (-2.0f * LOG2E)) + 0x1p-60f;
   return __builtin_copysignf(1.0f - e, b) * __builtin_amdgcn_rcpf(fmaf(e, u, u));
 }
 __device__ __forceinline__ float lstm_cell(float ai, float af, float ag, float ao, float &c) {

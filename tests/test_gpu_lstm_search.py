@@ -198,3 +198,48 @@ def test_model_must_read_64_values_per_stage(vf, ovf):
     with pytest.raises(vf.VfError):
         vf.vf_greedy_schedule(ctx)
     vf.vf_destroy(ctx)
+
+
+def saturated_weights(H, seed):
+    """Unit u's gates i, f, o are pushed to 0 or 1 (biases -100 / 100) and g to -1, tanh(weights) or 1
+    (-60 / 0 / 60) in all 24 combinations: infinite and vanishing exponentials meet in both products of
+    a cell, and cells that add +-1 in every step pass 52, where e^{-2|c|} is no fp32 number any more."""
+    w = I.lstm_weights(64, H, seed=seed, bias_std=0.1)
+    b = w[4 * H * 64 + 4 * H * H:][:4 * H].reshape(4, H)
+    u = np.arange(H)
+    for gate, v in ((0, u % 2 * 200 - 100), (1, u // 2 % 2 * 200 - 100), (2, (u // 4 % 3 - 1) * 60), (3, u // 12 % 2 * 200 - 100)):
+        b[gate] += v
+    return w
+
+
+@pytest.mark.parametrize("T", [1, 3, 70])
+def test_saturated_gates_of_sequences(vf, ovf, T):
+    import torch
+    H = 96
+    w, model = saturated_weights(H, 5), I.model_record(I.LSTM, [64, H, 1], I.BF16)
+    xb = I.feature_sequences(0, 256, T=T, F=64, seed=12)[:200]
+    ctx = vf.vf_create(0)
+    vf.vf_set_model(ctx, model, w)
+    s, bi, bv = vf.vf_score(ctx, torch.from_numpy(xb.view(np.int16)).cuda().view(torch.bfloat16), vf.VF_X_SEQ_BF16)
+    s, ref = s.cpu().numpy(), ovf.score_lstm(model, w, xb)
+    vf.vf_destroy(ctx)
+    assert np.isfinite(ref).all() and score_err(s, ref) <= TOL[1]
+    assert int(bi[0]) == int(np.argmin(s)) and float(bv[0]) == s.min()
+
+
+@pytest.mark.parametrize("B", [3, 384])
+def test_saturated_gates_in_the_search(vf, ovf, B):
+    """Tiles of 64 entries (3 problems) and of 96 (384 problems of two tiles of ids each); 70 stages, so
+    that the prefix's cells saturate the output product as well."""
+    sp = I.make_space([1, 2], [1, 4], [1, 8], I.XC_INNER_PERMS[:2], 1, 2, [I.ROOT, I.L1, I.INLINE], 1, 64)
+    assert B < 100 or (I.space_dense_count(sp) + 63) // 64 * B >= 3 * 256
+    pipes = np.stack([I.random_pipeline(70, 5 + b % 3) for b in range(B)])
+    w, model = saturated_weights(32, 9), I.model_record(I.LSTM, [64, 32, 1], I.BF16)
+    ctx = vf.vf_create(0)
+    vf.vf_set_space(ctx, sp); vf.vf_set_pipeline(ctx, pipes); vf.vf_set_model(ctx, model, w)
+    st, cids, vals = [t.cpu().numpy() for t in vf.vf_greedy_schedule(ctx)]
+    vf.vf_destroy(ctx)
+    for b in range(3):
+        compare_schedule(ovf, pipes[b], sp, model, w, cids[b], vals[b], st[b], TOL[1])
+    for b in range(3, B):
+        assert np.array_equal(cids[b], cids[b % 3]) and np.array_equal(vals[b], vals[b % 3])
