@@ -800,13 +800,14 @@ int vfk_seq_sync(vf_ctx *c, int stage) {
       }
       hipLaunchKernelGGL(k_pack_seqT, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, st, sw, c->pm.w_seqT);
       VF_HIP(c, hipGetLastError());
-      {
-        const size_t nv = (size_t)H / 32 * (2 * (H / 16) + 8) * 1024;
-        if (hipMalloc((void **)&c->pm.w_seq_wide, nv * sizeof(uint16_t)) != hipSuccess) {
-          (void)hipGetLastError();
-          vfk_seq_free(c);
-          return VF_ENOMEM;
-        }
+    }
+    if (!c->pm.w_seq_wide) {
+      // (without memory for this second form every step runs in tiles of 64, see vfk_seq_step)
+      const size_t nv = (size_t)H / 32 * (2 * (H / 16) + 8) * 1024;
+      if (hipMalloc((void **)&c->pm.w_seq_wide, nv * sizeof(uint16_t)) != hipSuccess) {
+        (void)hipGetLastError();
+        c->pm.w_seq_wide = nullptr;
+      } else {
         hipLaunchKernelGGL(k_pack_seq_wide, dim3((unsigned)((nv + 255) / 256)), dim3(256), 0, st, sw, c->pm.w_seq_wide);
         VF_HIP(c, hipGetLastError());
       }
@@ -868,7 +869,7 @@ int vfk_seq_step(vf_ctx *c, int stage, float *scores, int64_t ld_scores, int noi
   // against 4.4 or 1.3 against 1.6, 16: 5.0 against 5.6, 64: 17.0 against 19.4; 1 problem: 2.9 against 2.2.
   int ncu = 256;
   (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
-  const bool wide = (c->M + 63) / 64 * c->B >= 3 * (int64_t)ncu;
+  const bool wide = c->pm.w_seq_wide && (c->M + 63) / 64 * c->B >= 3 * (int64_t)ncu;
   const int NC = wide ? SEQ_WIDE : 64;
   const int nparts = (int)((c->M + NC - 1) / NC);
   rc = vfk_ensure_parts(c, (size_t)nparts * c->B);

@@ -1,0 +1,85 @@
+"""The library's host code on a runtime without a GPU (hip_stub.c: launches are written down, not run):
+allocation failures, launch limits, arguments of launches."""
+import ctypes as C
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+def make_library(stub_path):
+    """libvf.so bound to the stub (which has to be in the process first)."""
+    from paper_2011_14486_amd import binding
+    stub = C.CDLL(stub_path, mode=C.RTLD_GLOBAL)
+    stub.stub_fail.argtypes = [C.c_size_t, C.c_size_t]
+    stub.stub_log.restype = C.c_char_p
+    vf = C.CDLL(binding.LIB_PATH)
+    vf.vf_create.argtypes = [C.POINTER(C.c_void_p), C.c_int, C.c_void_p]
+    vf.vf_padded_count.restype = C.c_int64
+    vf.vf_set_model.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t]
+    return stub, vf
+
+
+def context(vf, pipes, space, model, w):
+    ctx = C.c_void_p()
+    keep = [np.ascontiguousarray(a) for a in (pipes, space, model, w)]
+    p = [C.c_void_p(a.ctypes.data) for a in keep]
+    assert vf.vf_create(C.byref(ctx), 0, None) == 0
+    assert vf.vf_set_space(ctx, p[1]) == 0
+    assert vf.vf_set_pipeline(ctx, p[0], pipes.shape[1], pipes.shape[0]) == 0
+    assert vf.vf_set_model(ctx, p[2], p[3], w.size) == 0
+    return ctx
+
+
+def recurrent_weights(stub, vf):
+    """The second form of the recurrent weights cannot be had: the search goes on with tiles of 64, now
+    and when memory is back; k_seq_step_wide never runs without its weights."""
+    from paper_2011_14486_amd import inputs as I
+    H, B = 256, 32
+    ctx = context(vf, np.stack([I.resnet18_shaped()] * B), I.resnet18_space(256), I.model_record(I.LSTM, [64, H, 1], I.BF16),
+                  I.lstm_weights(64, H))
+    size = H // 32 * (2 * (H // 16) + 8) * 1024 * 2
+    stub.stub_fail(size, size)
+    rc = vf.vf_argmin_step(ctx, 0, 1, None, None)
+    stub.stub_fail(1, 0)
+    assert rc == 0, rc
+    assert vf.vf_argmin_step(ctx, 1, 1, None, None) == 0
+    steps = [l.split() for l in stub.stub_log().decode().splitlines() if "k_seq_step" in l]
+    assert len(steps) == 2 and all(s[2] == "1" for s in steps), steps
+    vf.vf_destroy(ctx)
+    # with memory: tiles of 96
+    stub.stub_clear()
+    ctx = context(vf, np.stack([I.resnet18_shaped()] * B), I.resnet18_space(256), I.model_record(I.LSTM, [64, H, 1], I.BF16),
+                  I.lstm_weights(64, H))
+    assert vf.vf_argmin_step(ctx, 0, 1, None, None) == 0
+    assert "k_seq_step_wide" in stub.stub_log().decode()
+    vf.vf_destroy(ctx)
+
+
+@pytest.fixture(scope="module")
+def stub_path(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-Wall", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-o", out,
+                    os.path.join(HERE, "hip_stub.c")], check=True)
+    from paper_2011_14486_amd import binding
+    if not os.path.exists(binding.LIB_PATH):
+        from paper_2011_14486_amd.build import build_lib
+        build_lib()
+    return out
+
+
+@pytest.mark.parametrize("case", ["recurrent_weights"])
+def test_host_path(stub_path, case):
+    # (a process of its own: the stub takes the place of the whole runtime)
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), stub_path, case], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+if __name__ == "__main__":
+    sys.path.insert(0, ROOT)
+    globals()[sys.argv[2]](*make_library(sys.argv[1]))
