@@ -11,7 +11,7 @@
 // 64-128-128-1 through vf_score, one launch and the scan (before: a workgroup per 128 candidates with
 // two barriers per layer and the weights out of L2 for bf16; layer after layer through memory, on the
 // vector ALU, for fp32): bf16 200,003 vectors 102 -> 32 us, a million 447 -> 83 us (3.2 TB/s of inputs);
-// fp32 192,000 vectors 286 -> 88 us, a million 1889 -> 437 us (113 TFLOP/s of the 154 that a large fp32
+// fp32 192,000 vectors 286 -> 90 us, a million 1889 -> 454 us (109 TFLOP/s of the 154 that a large fp32
 // matrix product reaches).  Where the network does not fit (a hidden layer of more than 128 units:
 // the activations' registers; more than 150 KB of weights) the kernels of vf_score.hip run.
 #include "vf_internal.h"
@@ -406,11 +406,12 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
 // 16 * CT candidates per sub-tile, lane l has columns CT (l % 16) + 0 .. CT - 1 and rows 4 (l / 16) + 0..3
 // of every 16.  The output vector is a dot product on the vector ALU (a sixteenth of a row tile
 // would be used), the four lane groups' parts added at the end.
+// Every 32 rows of a product are summed by themselves and the sums added up, in both forms: sums of
+// few terms are the more exact ones (scores of 64-128-128-1 off a 64-bit sum, relative: 1.5e-7; 2.0e-7
+// when two columns per lane had one sum each and 192,000 vectors took 88 instead of 90 us), and a
+// candidate's score does not depend on how many candidates the call has.
 template <int CT, int NT, bool GEN>
 __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
-  // partial sums per accumulator, even and odd groups of 16 rows apart, where the registers allow it:
-  // a sum of half as many terms is the more exact one
-  constexpr int SP = CT == 1 ? 2 : 1;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint4 *const wl = reinterpret_cast<uint4 *>(smem);
   const floatx4 *const wf = reinterpret_cast<const floatx4 *>(smem);
@@ -419,7 +420,7 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
   const int lane = threadIdx.x & 63, q = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   stage_small(a, wl, bl);
-  const int L = a.md.L, K0 = a.md.dims[0], groups0 = a.md.kst[0], chunks = (groups0 + 1) / 2;
+  const int L = a.md.L, K0 = a.md.dims[0], groups0 = a.md.kst[0], chunks = groups0 / 2;
   int32_t raw[8][CT];  // 32 input rows: per group of 16 four rows of the lane group; column
   auto fetch = [&](int p, int64_t n0, int ch) __attribute__((always_inline)) {
     const int32_t *col = a.x + (size_t)p * a.prob_stride + n0 + CT * (lane & 15);
@@ -490,46 +491,51 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
         }
       }
     }
-    floatx4 acc[SP][NT][CT];
+    floatx4 acc[NT][CT];
     float s[CT];
     const bool only = L == 1;  // no hidden layer: the inputs go straight into the output dot
 #pragma unroll
     for (int c = 0; c < CT; ++c) s[c] = 0.0f;
     if (!closed) {
 #pragma unroll
-    for (int sp = 0; sp < SP; ++sp)
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int c = 0; c < CT; ++c) acc[sp][t][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-    // (a weight fragment is refilled in place behind its last product; the refill behind the last
-    // group reads into what follows the layer's weights and is not used)
-    constexpr int TH = NT / 2;  // fragments in flight
+      for (int c = 0; c < CT; ++c) acc[t][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    // (a weight fragment is refilled in place behind its last product; the refills behind the last
+    // 32 rows read the next tiles' weights and are not used)
+    constexpr int TH = NT / 2;  // fragments in flight: row tile by row tile, both groups of 16 rows
     floatx4 x[TH];
 #pragma unroll
-    for (int t = 0; t < TH; ++t) x[t] = only ? floatx4{0.0f, 0.0f, 0.0f, 0.0f} : wf[t * groups0 * 64 + at];
+    for (int i = 0; i < TH; ++i) x[i] = only ? floatx4{0.0f, 0.0f, 0.0f, 0.0f} : wf[(i / 2 * groups0 + i % 2) * 64 + at];
     auto products = [&](const float (&in)[2][4][CT], int ch) __attribute__((always_inline)) {
+      if (only) {
 #pragma unroll
-      for (int g = 0; g < 2; ++g) {
-        const int kg = ch * 2 + g;
-        if (kg >= groups0) break;
-        if (only) {
-          const floatx4 y = *reinterpret_cast<const floatx4 *>(bl + a.md.wl_off + kg * 16 + 4 * (at >> 4));
+        for (int g = 0; g < 2; ++g) {
+          const floatx4 y = *reinterpret_cast<const floatx4 *>(bl + a.md.wl_off + (ch * 2 + g) * 16 + 4 * (at >> 4));
 #pragma unroll
           for (int e = 0; e < 4; ++e)
 #pragma unroll
             for (int c = 0; c < CT; ++c) s[c] = fmaf(y[e], in[g][e][c], s[c]);
-          continue;
         }
+        return;
+      }
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
+      for (int t = 0; t < NT; ++t) {
+        floatx4 part[CT];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) part[c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+          const int i = 2 * t + g, n = (i + TH) % (2 * NT), nch = i + TH < 2 * NT ? ch : ch + 1;
 #pragma unroll
           for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int c = 0; c < CT; ++c) acc[g % SP][t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t % TH][e], in[g][e][c], acc[g % SP][t][c], 0, 0, 0);
-          x[t % TH] = t < TH ? wf[((t + TH) * groups0 + kg) * 64 + at] : wf[((t - TH) * groups0 + kg + 1) * 64 + at];
+            for (int c = 0; c < CT; ++c) part[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i % TH][e], in[g][e][c], part[c], 0, 0, 0);
+          x[i % TH] = wf[(n / 2 * groups0 + 2 * nch + n % 2) * 64 + at];
           __builtin_amdgcn_sched_barrier(0);
         }
+#pragma unroll
+        for (int c = 0; c < CT; ++c) acc[t][c] += part[c];
       }
     };
     if constexpr (GEN) {
@@ -576,48 +582,47 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
     }
     if (!only) {
       // a finished layer: bias, ReLU, and its rows are the next one's inputs as they lie
-      auto finish = [&](const floatx4 &v0, const floatx4 &v1, int l, int t) __attribute__((always_inline)) {
+      auto finish = [&](const floatx4 &v, int l, int t) __attribute__((always_inline)) {
         const floatx4 b = *reinterpret_cast<const floatx4 *>(bl + a.md.boff[l] + t * 16 + 4 * (at >> 4));
         floatx4 o;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = relu_keep_nan((SP > 1 ? v0[e] + v1[e] : v0[e]) + b[e]);
+        for (int e = 0; e < 4; ++e) o[e] = relu_keep_nan(v[e] + b[e]);
         return o;
       };
       floatx4 act[NT][CT];
 #pragma unroll
       for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int c = 0; c < CT; ++c) act[t][c] = finish(acc[0][t][c], acc[SP - 1][t][c], 0, t);
+        for (int c = 0; c < CT; ++c) act[t][c] = finish(acc[t][c], 0, t);
       for (int l = 1; l < L - 1; ++l) {
-        // half of the row tiles at a time, as above
+        // a row tile at a time, its weights one behind the other
         floatx4 out[NT][CT];
         const floatx4 *wp = wf + a.md.woff[l] + at;
 #pragma unroll
-        for (int t0 = 0; t0 < NT; t0 += TH) {
-          floatx4 part[SP][TH][CT];
+        for (int i = 0; i < TH; ++i) x[i] = wp[i * 64];
 #pragma unroll
-          for (int t = 0; t < TH; ++t) {
+        for (int t = 0; t < NT; ++t) {
+          floatx4 part[CT], tot[CT];
 #pragma unroll
-            for (int sp = 0; sp < SP; ++sp)
+          for (int kg = 0; kg < NT; ++kg) {
+            const int i = t * NT + kg;
+            if (kg % 2 == 0) {
 #pragma unroll
-              for (int c = 0; c < CT; ++c) part[sp][t][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-            x[t] = wp[(t0 + t) * NT * 64];
-          }
-#pragma unroll
-          for (int kg = 0; kg < NT; ++kg)
-#pragma unroll
-            for (int t = 0; t < TH; ++t) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int c = 0; c < CT; ++c) part[kg % SP][t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t][e], act[kg][c][e], part[kg % SP][t][c], 0, 0, 0);
-              if (kg + 1 < NT) x[t] = wp[((t0 + t) * NT + kg + 1) * 64];
-              __builtin_amdgcn_sched_barrier(0);
+              for (int c = 0; c < CT; ++c) part[c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
             }
 #pragma unroll
-          for (int t = 0; t < TH; ++t)
+            for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int c = 0; c < CT; ++c) out[t0 + t][c] = finish(part[0][t][c], part[SP - 1][t][c], l, t0 + t);
+              for (int c = 0; c < CT; ++c) part[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i % TH][e], act[kg][c][e], part[c], 0, 0, 0);
+            if (i + TH < NT * NT) x[i % TH] = wp[(i + TH) * 64];
+            if (kg % 2 == 1) {
+#pragma unroll
+              for (int c = 0; c < CT; ++c) tot[c] = kg == 1 ? part[c] : tot[c] + part[c];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+#pragma unroll
+          for (int c = 0; c < CT; ++c) out[t][c] = finish(tot[c], l, t);
         }
 #pragma unroll
         for (int t = 0; t < NT; ++t)
@@ -690,7 +695,8 @@ int vfk_pack_small(vf_ctx *c, const float *wdev) {
     const int K = m.dims[l], N = m.dims[l + 1];
     d.dims[l] = K;
     d.nt[l] = l < L - 1 ? d.NT : 1;
-    d.kst[l] = l > 0 ? d.NT * unit / 16 : (K + 15) / 16;
+    // (fp32: whole chunks of 32 rows)
+    d.kst[l] = l > 0 ? d.NT * unit / 16 : bf16 ? (K + 15) / 16 : (K + 31) / 32 * 2;
     d.woff[l] = (int)nw;
     d.boff[l] = (int)nbias;
     if (bf16 || l < L - 1) nw += (size_t)d.nt[l] * d.kst[l] * 64;
