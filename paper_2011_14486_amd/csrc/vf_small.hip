@@ -154,6 +154,8 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
   auto mfma = [](uint4 x, uint4 y, floatx16 z) __attribute__((always_inline)) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), z, 0, 0, 0);
   };
+  // (Rows that fill the row tiles up have zero weights.  On an infinite activation their products are
+  // NaN with the sign bit set, 0xffc00000, of which the ReLU on the bits makes 0 again.)
   // plus bias, rounded to bf16, ReLU on the pairs: half a row tile of the accumulator as the B operand
   // of a k-step.  (The bias as the products' first addend would be less work, but the sums would be
   // less exact: 4.1e-5 instead of 3.3e-5 off a 64-bit sum in the scores of 64-128-128-1.)
@@ -623,6 +625,17 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
           }
 #pragma unroll
           for (int c = 0; c < CT; ++c) out[t][c] = finish(tot[c], l, t);
+          // (the rows that fill the tiles up behind the layer's own stay 0: zero weights on an infinite
+          // activation have made them NaN)
+          const int rows = a.md.dims[l + 1] - 16 * t;
+          if (rows < 16) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (4 * (at >> 4) + e >= rows) {
+#pragma unroll
+                for (int c = 0; c < CT; ++c) out[t][c][e] = 0.0f;
+              }
+          }
         }
 #pragma unroll
         for (int t = 0; t < NT; ++t)

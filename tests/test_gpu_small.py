@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2011_14486_amd import inputs as I
-from tests.util import TOL
+from tests.util import TOL, score_err
 
 pytestmark = pytest.mark.gpu
 
@@ -96,6 +96,33 @@ def test_generated_candidates_equal_scored_features(vf, dims, dtype, B):
             c = int(np.argmin(s)) if np.isfinite(s).any() else -1
             assert int(cids[b]) == c and float(vals[b]) == float(s.min()), (i, b)
     vf.vf_destroy(ctx)
+
+
+@pytest.mark.parametrize("dims,dtype", [([64, 64, 32, 1], I.BF16), ([256, 128, 32, 96, 1], I.BF16), ([64, 128, 33, 1], I.FP32),
+                                        ([50, 64, 7, 20, 1], I.FP32)])
+@pytest.mark.parametrize("M", [300, 40001])
+def test_infinite_activations(vf, ovf, dims, dtype, M):
+    """A first-layer unit that overflows to infinity where x[0] is large, in networks whose later
+    layers are narrower than the widest one: their own units all get -inf from it and rest at 0, and
+    the rows that fill their tiles up must not turn the infinity into a NaN."""
+    import torch
+    w = I.mlp_weights(dims, 3, bias_std=0.2)
+    w[0] = 1e38                                                     # W_1[0][0]: inf from plog2(x) > 3.4 on
+    n1 = dims[0] * dims[1] + dims[1]
+    w[n1:n1 + dims[1] * dims[2]].reshape(dims[2], dims[1])[:, 0] = -1.0
+    model = I.model_record(I.MLP, dims, dtype)
+    rng = np.random.default_rng(2)
+    x = np.floor(np.exp2(rng.random((dims[0], M)) * 20.0)).astype(np.int32)
+    x[0] = np.where(rng.random(M) < 0.5, 0, 1 << 19)
+    ctx = vf.vf_create(0)
+    vf.vf_set_model(ctx, model, w)
+    s, bi, bv = vf.vf_score(ctx, torch.from_numpy(x).cuda())
+    vf.vf_destroy(ctx)
+    some = np.r_[0:300, M - 100:M]
+    ref = ovf.score_mlp(model, w, np.ascontiguousarray(x[:, some]))
+    s = s.cpu().numpy()
+    assert np.isfinite(ref).all() and score_err(s[some], ref) <= TOL[dtype]
+    assert int(bi[0]) == int(np.argmin(s)) and float(bv[0]) == s.min()
 
 
 @pytest.mark.parametrize("dims,dtype", NETS)
