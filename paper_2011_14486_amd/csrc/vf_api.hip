@@ -494,26 +494,32 @@ int vf_greedy_schedule(vf_ctx *c, int first, int last, vf_state *out_states, int
     const int rc = settle_whole(c, first > 0);
     if (rc != VF_OK) return rc;
   }
-  bool lists = false;
-  if (first <= last && vfk_layer_pays(c) && !vfk_whole_pays(c)) {
-    const int rc = vfk_greedy_layers(c, first, last);
+  // What wants candidate lists of all problems comes first: layer by layer on lists, or whole schedules
+  // in one launch.  Without memory for the lists the launches per layer below decide the same on id
+  // ranges.
+  int rc = VF_OK;
+  bool decided = first > last;
+  if (!decided) {
+    if (vfk_layer_pays(c) && !vfk_whole_pays(c)) {
+      rc = vfk_greedy_layers(c, first, last);
+      decided = rc == VF_OK;
+    } else if (vfk_whole_team(c) >= 1) {
+      rc = vfk_greedy_whole(c, first, last);
+      decided = rc == VF_OK;
+      if (decided) c->n_sched = last + 1;
+    }
     if (rc != VF_OK && (rc != VF_ENOMEM || c->n_sched != first)) return rc;
-    lists = rc == VF_OK;  // (no memory for the lists: the other ways)
   }
-  if (lists) {
-    // decided above
-  } else if (first <= last && vfk_whole_team(c) >= 1) {
-    int rc = vfk_greedy_whole(c, first, last);
-    if (rc != VF_OK) return rc;
-    c->n_sched = last + 1;
-  } else if (first <= last && vfk_can_chain(c)) {
+  if (decided) {
+    // nothing left to do
+  } else if (vfk_can_chain(c)) {
     // a few problems: one launch per layer, each taking the decision of the layer before
-    int rc = vfk_greedy_chain(c, first, last);
+    rc = vfk_greedy_chain(c, first, last);
     if (rc != VF_OK) return rc;
     c->n_sched = last + 1;
   } else {
     for (int i = first; i <= last; ++i) {
-      int rc = step(c, i, 1, nullptr, nullptr);
+      rc = step(c, i, 1, nullptr, nullptr);
       if (rc != VF_OK) return rc;
       c->n_sched = i + 1;
     }

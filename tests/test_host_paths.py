@@ -61,6 +61,30 @@ def recurrent_weights(stub, vf):
     vf.vf_destroy(ctx)
 
 
+def candidate_lists(stub, vf):
+    """No memory for the candidate lists: a greedy schedule is decided on id ranges, whether it would
+    have run layer by layer (64 problems) or in one launch (200)."""
+    from paper_2011_14486_amd import inputs as I
+    dims = [256, 512, 512, 1]
+    for B, kernel in ((64, "k_open_layer"), (200, "k_whole")):
+        ctx = context(vf, np.stack([I.resnet18_shaped()] * B), I.resnet18_space(256), I.model_record(I.MLP, dims, I.BF16),
+                      I.mlp_weights(dims))
+        size = B * vf.vf_padded_count(ctx) * 4
+        stub.stub_clear()
+        stub.stub_fail(size, size)
+        rc = vf.vf_greedy_schedule(ctx, 0, 19, None, None, None)
+        stub.stub_fail(1, 0)
+        log = stub.stub_log().decode()
+        assert rc == 0 and vf.vf_n_scheduled(ctx) == 20, rc
+        assert kernel not in log and log.count("k_mlp_fast") == 20, log
+        # with memory
+        assert vf.vf_reset_state(ctx) == 0
+        stub.stub_clear()
+        assert vf.vf_greedy_schedule(ctx, 0, 19, None, None, None) == 0
+        assert kernel in stub.stub_log().decode()
+        vf.vf_destroy(ctx)
+
+
 @pytest.fixture(scope="module")
 def stub_path(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
@@ -73,7 +97,7 @@ def stub_path(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("case", ["recurrent_weights"])
+@pytest.mark.parametrize("case", ["recurrent_weights", "candidate_lists"])
 def test_host_path(stub_path, case):
     # (a process of its own: the stub takes the place of the whole runtime)
     r = subprocess.run([sys.executable, os.path.abspath(__file__), stub_path, case], cwd=ROOT, capture_output=True, text=True)
