@@ -116,13 +116,13 @@ __global__ __launch_bounds__(256) void k_enumerate(Tables t, int stage, uint32_t
 // 16384 ids 248 -> 194 us; four or sixteen shared rows per workgroup: 206 us).
 constexpr int VF_FEAT_SPAN = 4;
 __global__ __launch_bounds__(256) void k_featurize(Tables t, int stage, uint32_t M, uint32_t Mpad, int F, int fill,
-                                                   int span, int per, int xcds, int B, int32_t *feat) {
+                                                   int span, int per, int xcds, int b0, int B, int32_t *feat) {
   __shared__ Dec d;
   __shared__ vf_space sp;
   __shared__ __attribute__((aligned(16))) int32_t tile[32][256];
   // per: workgroups per problem; xcds = 8: a problem's workgroups go to one XCD (workgroups are dealt
-  // out to the eight in turn)
-  const int q = (int)blockIdx.x / xcds, b = q / per * xcds + (int)blockIdx.x % xcds, bx = q % per;
+  // out to the eight in turn); b0: the launch's first problem
+  const int q = (int)blockIdx.x / xcds, b = b0 + q / per * xcds + (int)blockIdx.x % xcds, bx = q % per;
   if (b >= B) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   int32_t *out = feat + (size_t)b * F * Mpad;
@@ -503,10 +503,14 @@ int vfk_featurize(vf_ctx *c, int stage, int32_t *feat) {
   // all: 256 problems 184 -> 180 us, and 246 -> 203 for the first pass over a new buffer; small ones
   // take all XCDs for every problem (four problems 10.4 -> 8.4 us).
   const int xcds = span > 1 ? 8 : 1;
-  dim3 grid((unsigned)per * (unsigned)((c->B + xcds - 1) / xcds * xcds));
-  hipLaunchKernelGGL(k_featurize, grid, dim3(256), 0, c->stream, tables_of(c), stage, (uint32_t)c->M,
-                     (uint32_t)c->Mpad, (int)c->space.F, fill, span, per, xcds, c->B, feat);
-  VF_HIP(c, hipGetLastError());
+  // (a launch takes less than 2^32 work-items: 193 workgroups per problem are too many for about 87,000)
+  const int most = (int)(0xffffffffu / 256u / (unsigned)per) / xcds * xcds;
+  for (int b0 = 0; b0 < c->B; b0 += most) {
+    const int n = c->B - b0 < most ? (c->B - b0 + xcds - 1) / xcds * xcds : most;
+    hipLaunchKernelGGL(k_featurize, dim3((unsigned)per * (unsigned)n), dim3(256), 0, c->stream, tables_of(c), stage,
+                       (uint32_t)c->M, (uint32_t)c->Mpad, (int)c->space.F, fill, span, per, xcds, b0, c->B, feat);
+    VF_HIP(c, hipGetLastError());
+  }
   return VF_OK;
 }
 

@@ -141,3 +141,19 @@ def test_error_codes(vf, ovf):
     assert e.value.code == vf.VF_ESTATE
     assert vf.lib().vf_strerror(-2).decode().startswith("call out of order")
     vf.vf_destroy(ctx)
+
+
+def test_features_of_more_problems_than_a_launch_takes(vf):
+    """90,000 problems of 256 rows: 193 workgroups each are more than 2^32 work-items, so that the last
+    problems come from a second launch.  All problems are the same one."""
+    import torch
+    B, sp = 90000, I.make_space([1, 2], [1, 2], [1, 2], [(0, 1, 2)], 1, 1, [I.ROOT], 1, 256)
+    ctx = vf.vf_create(0)
+    vf.vf_set_space(ctx, sp)
+    vf.vf_set_pipeline(ctx, np.stack([I.random_pipeline(2, 3)] * B))
+    feat = vf.vf_featurize(ctx, 0)
+    first = feat[0].clone()
+    assert int(first[16].sum()) > 0 and int(first[208:224].sum()) > 0
+    for b in range(0, B, 10000):
+        assert bool((feat[b:b + 10000] == first).all()), b
+    vf.vf_destroy(ctx)

@@ -85,6 +85,22 @@ def candidate_lists(stub, vf):
         vf.vf_destroy(ctx)
 
 
+def many_problems(stub, vf):
+    """Features of 90,000 problems of a small space: 193 workgroups of 256 each would be more work-items
+    than a launch takes."""
+    from paper_2011_14486_amd import inputs as I
+    B, sp = 90000, I.make_space([1, 2], [1, 2], [1, 2], [(0, 1, 2)], 1, 1, [I.ROOT], 1, 256)
+    pipe = I.random_pipeline(1, 3)
+    dims = [256, 512, 512, 1]
+    ctx = context(vf, np.stack([pipe] * B), sp, I.model_record(I.MLP, dims, I.BF16), I.mlp_weights(dims))
+    stub.stub_clear()
+    rc = vf.vf_featurize(ctx, 0, C.c_void_p(4096))  # (written down, not run)
+    assert rc == 0, rc
+    grids = [int(l.split()[1]) for l in stub.stub_log().decode().splitlines() if "k_featurize" in l]
+    assert len(grids) == 2 and B * 193 <= sum(grids) < (B + 8) * 193, grids
+    vf.vf_destroy(ctx)
+
+
 @pytest.fixture(scope="module")
 def stub_path(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
@@ -97,7 +113,7 @@ def stub_path(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("case", ["recurrent_weights", "candidate_lists"])
+@pytest.mark.parametrize("case", ["recurrent_weights", "candidate_lists", "many_problems"])
 def test_host_path(stub_path, case):
     # (a process of its own: the stub takes the place of the whole runtime)
     r = subprocess.run([sys.executable, os.path.abspath(__file__), stub_path, case], cwd=ROOT, capture_output=True, text=True)
