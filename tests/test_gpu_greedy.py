@@ -45,6 +45,18 @@ def compare_schedule(ovf, pipe, space, model, w, cids, vals, states, tol):
     return n_forced
 
 
+def greedy_with_launches(vf, ctx):
+    """The tables of a schedule from s_0 and the number of scoring launches it took: one where the
+    whole-schedule launch ran, one per layer elsewhere."""
+    vf.vf_reset_state(ctx)
+    vf.vf_profile_enable(ctx, True)
+    vf.vf_profile_read(ctx, 1)
+    out = [t.cpu().numpy() for t in vf.vf_greedy_schedule(ctx)]
+    n = vf.vf_profile_read(ctx, 1)[1]
+    vf.vf_profile_enable(ctx, False)
+    return out, n
+
+
 @pytest.mark.parametrize("order", ["output_first", "input_first"])
 def test_tiny_config(vf, ovf, order):
     pipe, sp = I.tiny_conv_relu(order), I.tiny_space()
@@ -157,13 +169,13 @@ def test_mobilenet_shaped_all_stages(vf, ovf):
     vf.vf_destroy(ctx)
 
 
-@pytest.mark.parametrize("B,eps", [(100, 0.3), (64, 0.3), (160, 0.3), (130, 0.0)])
-def test_whole_schedule_launch_100_stages_16384_ids(vf, ovf, B, eps):
-    """The whole-schedule launch on the 100-stage pipeline with 16384 candidate ids per decision,
-    as the benchmark times it: 100 noisy rollouts (owners, and the compute units that fixed teams
-    of two would leave idle as their helpers), 64 (fixed teams of four workgroups per problem),
-    160 (more problems than half the compute units: owners and helpers), and 130 copies without
-    noise.  The checker looks at layers sampled over the whole schedule for a few rollouts, each
+@pytest.mark.parametrize("B,eps,one_launch", [(100, 0.3, False), (64, 0.3, False), (160, 0.3, False), (130, 0.0, False),
+                                              (200, 0.3, True)])
+def test_whole_schedule_launch_100_stages_16384_ids(vf, ovf, B, eps, one_launch):
+    """Whole schedules of the 100-stage pipeline with 16384 candidate ids per decision: up to 160
+    rollouts layer by layer on lists of valid candidates (100 noisy ones are what the benchmark
+    times; 130 copies without noise), 200 in one launch (owners, and the other compute units as
+    their helpers).  The checker looks at layers sampled over the whole schedule for a few rollouts, each
     decision under the GPU's own prefix; every rollout must replay to its state records."""
     pipe, sp = I.mobilenetv2_shaped(), I.mobilenetv2_space()
     dims = [256, 512, 512, 1]
@@ -173,12 +185,12 @@ def test_whole_schedule_launch_100_stages_16384_ids(vf, ovf, B, eps):
     ctx = vf.vf_create(0)
     vf.vf_set_space(ctx, sp); vf.vf_set_pipeline(ctx, np.repeat(pipe[None], B, axis=0)); vf.vf_set_model(ctx, model, w)
     vf.vf_set_noise(ctx, eps, seed)
-    vf.vf_profile_enable(ctx, True); vf.vf_profile_counts(ctx)
-    st, cids, vals = [t.cpu().numpy() for t in vf.vf_greedy_schedule(ctx)]
+    (st, cids, vals), launches = greedy_with_launches(vf, ctx)
     scored, valid = vf.vf_profile_counts(ctx)
     vf.vf_destroy(ctx)
+    assert launches == (1 if one_launch else len(pipe))
     assert (cids >= 0).all() and np.isfinite(vals).all()
-    assert scored == valid > 0                       # lists of valid candidates: the one-launch path ran
+    assert scored == valid > 0                       # lists of valid candidates
     if eps == 0.0:
         assert (cids == cids[0]).all() and (vals == vals[0]).all() and (st == st[0]).all()
         sample = [0]
@@ -193,23 +205,27 @@ def test_whole_schedule_launch_100_stages_16384_ids(vf, ovf, B, eps):
         assert np.array_equal(rst, st[k])
 
 
-def test_fused_step_ragged_tiles_uneven_share(vf, ovf):
-    """The fused enumerate+featurize+score kernel with a candidate count that is not a
-    multiple of its tile (ragged last tile) and more (problem, tile) pairs than
-    workgroups, unevenly divided: every problem's schedule equals the checker's."""
+@pytest.mark.parametrize("dims,followed", [([256, 512, 512, 1], 37), ([256, 512, 512, 512, 512, 1], 5)])
+def test_fused_step_ragged_tiles_uneven_share(vf, ovf, dims, followed):
+    """A candidate count that is not a multiple of a tile (ragged last tile) and more (problem,
+    tile) pairs than workgroups, unevenly divided, on lists of valid candidates and (four hidden
+    layers: their biases do not fit the LDS next to a list's tile) in the fused enumerate +
+    featurize + score kernel on id ranges: schedules equal the checker's."""
     sp = I.make_space([1, 2, 3, 8], [1, 2, 5], [1, 4, 16], [(0, 1, 2), (2, 1, 0), (1, 0, 2)], 2, 2,
                       [I.ROOT, I.L1, I.L2, I.INLINE], 3, 256)
     assert I.space_dense_count(sp) == 5184 and 5184 % 128 != 0
     S, B = 4, 37
     pipes = np.stack([I.random_pipeline(S, 300 + b) for b in range(B)])
-    dims = [256, 512, 512, 1]
     w = I.mlp_weights(dims, 5, bias_std=0.1)
     model = I.model_record(I.MLP, dims, I.BF16)
     ctx = vf.vf_create(0)
     vf.vf_set_space(ctx, sp); vf.vf_set_pipeline(ctx, pipes); vf.vf_set_model(ctx, model, w)
-    st, cids, vals = vf.vf_greedy_schedule(ctx)
-    st, cids, vals = st.cpu().numpy(), cids.cpu().numpy(), vals.cpu().numpy()
-    for b in range(B):
+    vf.vf_profile_enable(ctx, True); vf.vf_profile_counts(ctx)
+    st, cids, vals = [t.cpu().numpy() for t in vf.vf_greedy_schedule(ctx)]
+    scored, valid = vf.vf_profile_counts(ctx)
+    vf.vf_profile_enable(ctx, False)
+    assert (scored == valid) == (len(dims) == 4)      # (only lists leave the invalid ids out)
+    for b in range(0, B, 37 // followed):
         compare_schedule(ovf, pipes[b], sp, model, w, cids[b], vals[b], st[b], TOL[1])
     # the unfused route (featurize to memory, then score) takes the same decisions
     pre = cids[:, :2].copy()
@@ -369,13 +385,15 @@ def test_whole_schedule_launch_equals_layer_by_layer(vf, ovf):
     vf.vf_destroy(ctx)
 
 
-def test_wide_network_two_problems_per_workgroup(vf, ovf):
+@pytest.mark.parametrize("B,fy,one_launch", [(512, [1, 4], False), (200, [1, 4], True), (400, [1, 2, 3, 4, 5, 6, 7, 8], True)])
+def test_wide_network_two_problems_per_workgroup(vf, ovf, B, fy, one_launch):
     """Hidden width 1024 (tiles of 64 candidates, four row tiles per wave, the first-layer fold
-    at that width) with twice as many problems as compute units, so that every workgroup of the
-    whole-schedule launch runs two problems one after the other; against the per-layer path
-    and, for some problems, the checker."""
-    B, S = 512, 4
-    sp = I.make_space([1, 2, 4], [1, 4], [4, 8], [(0, 1, 2), (2, 1, 0)], 2, 2,
+    at that width): twice as many problems as compute units layer by layer on lists; 200 problems
+    of short decisions in the whole-schedule launch; and 400 of 4608 ids there, where workgroups
+    run two problems one after the other and then help.  Against the steps by hand and, for some
+    problems, the checker."""
+    S = 4
+    sp = I.make_space([1, 2, 4], fy, [4, 8], [(0, 1, 2), (2, 1, 0)] + ([(1, 0, 2)] if len(fy) > 2 else []), 2, 2,
                       [I.ROOT, I.L1, I.L2, I.INLINE], 2, 256)
     pipes = np.stack([I.random_pipeline(S, 1000 + k, max_hw=20, max_c=24) for k in range(B)])
     dims = [256, 1024, 1024, 1]
@@ -383,14 +401,15 @@ def test_wide_network_two_problems_per_workgroup(vf, ovf):
     model = I.model_record(I.MLP, dims, I.BF16)
     ctx = vf.vf_create(0)
     vf.vf_set_space(ctx, sp); vf.vf_set_pipeline(ctx, pipes); vf.vf_set_model(ctx, model, w)
-    whole = [t.cpu().numpy() for t in vf.vf_greedy_schedule(ctx)]
+    whole, launches = greedy_with_launches(vf, ctx)
+    assert launches == (1 if one_launch else S)
     vf.vf_reset_state(ctx)
     for i in range(S):
         vf.vf_argmin_step(ctx, i, True)
     steps = [t.cpu().numpy() for t in vf.vf_greedy_schedule(ctx, first=S)]
     for a, b in zip(whole, steps):
         assert np.array_equal(a, b)
-    for b in (0, 255, 256, 511):
+    for b in (0, min(255, B - 2), B // 2, B - 1):
         compare_schedule(ovf, pipes[b], sp, model, w, whole[1][b], whole[2][b], whole[0][b], TOL[1])
     vf.vf_destroy(ctx)
 
@@ -434,15 +453,17 @@ def test_whole_schedule_candidate_lists_against_the_checker(vf, ovf, seed):
     vf.vf_destroy(ctx)
 
 
-@pytest.mark.parametrize("B", [24, 48, 100])
-def test_team_of_workgroups_per_problem(vf, ovf, B):
-    """Between 24 problems and half the compute units vf_greedy_schedule gives every problem a
-    team of workgroups that meet once per layer: same tables as the per-layer launches, with
-    noise, from a prefix, with a problem that ends early; some problems against the checker."""
+@pytest.mark.parametrize("B,fx,team", [(24, [1, 2, 4], True), (42, [1, 2, 4], True), (64, [1, 2], True), (128, [1], True),
+                                       (48, [1, 2, 4], False), (100, [1, 2, 4], False)])
+def test_team_of_workgroups_per_problem(vf, ovf, B, fx, team):
+    """From 24 problems to half the compute units, and with no more tiles of all problems than
+    compute units, vf_greedy_schedule gives every problem a team of workgroups that meet once per
+    layer (6, 6, 4 and 2 of them here); with more tiles it goes layer by layer on lists.  Same
+    tables as steps by hand, with noise, from a prefix, with a problem that ends early; some
+    problems against the checker."""
     pipes = I.resnet18_batch(B, seed=9)
     pipes[3, 2, 3] = 2
-    sp = I.make_space([1, 2, 4], [1, 4], [4, 8], [(0, 1, 2), (2, 1, 0)], 2, 2,
-                      [I.ROOT, I.L1, I.L2, I.INLINE], 2, 256)
+    sp = I.make_space(fx, [1, 4], [4, 8], [(0, 1, 2), (2, 1, 0)], 2, 2, [I.ROOT, I.L1, I.L2, I.INLINE], 2, 256)
     dims = [256, 512, 512, 1]
     w = I.mlp_weights(dims, 4)
     model = I.model_record(I.MLP, dims, I.BF16)
@@ -451,8 +472,8 @@ def test_team_of_workgroups_per_problem(vf, ovf, B):
     vf.vf_set_space(ctx, sp); vf.vf_set_pipeline(ctx, pipes); vf.vf_set_model(ctx, model, w)
     for eps in (0.0, 0.1):
         vf.vf_set_noise(ctx, eps, seed=5)
-        vf.vf_reset_state(ctx)
-        whole = [t.cpu().numpy() for t in vf.vf_greedy_schedule(ctx)]
+        whole, launches = greedy_with_launches(vf, ctx)
+        assert launches == (1 if team else S)
         vf.vf_reset_state(ctx)
         for i in range(S):
             vf.vf_argmin_step(ctx, i, True)
@@ -470,14 +491,16 @@ def test_team_of_workgroups_per_problem(vf, ovf, B):
     vf.vf_destroy(ctx)
 
 
-@pytest.mark.parametrize("dims", [[256, 512, 1], [256, 512, 512, 512, 1], [64, 512, 512, 1], [256, 1024, 1]])
-def test_whole_schedule_launch_other_depths(vf, ovf, dims):
-    """vf_greedy_schedule with a team per problem for other network shapes: one hidden layer
-    (the next tile's features cannot be produced next to the layer that reads the input buffer),
-    three hidden layers (their tile no longer fits the LDS next to the input buffer: the call
-    falls back to the launches per layer), 64 input rows (no shared rows to fold), the wide
-    tile.  Same tables as stepping layer by layer; two problems against the checker."""
-    B = 24
+@pytest.mark.parametrize("dims,B,one_launch", [([256, 512, 1], 24, True), ([256, 512, 512, 512, 1], 24, False),
+                                               ([64, 512, 512, 1], 24, True), ([256, 1024, 1], 24, False),
+                                               ([256, 1024, 1], 200, True)])
+def test_whole_schedule_launch_other_depths(vf, ovf, dims, B, one_launch):
+    """vf_greedy_schedule for other network shapes: one hidden layer (the next tile's features
+    cannot be produced next to the layer that reads the input buffer), three hidden layers (the
+    whole-schedule launch does not take them: the call goes layer by layer), 64 input rows (no
+    shared rows to fold), the wide tile (24 problems have more tiles of 64 than there are compute
+    units: lists; 200: one launch).  Same tables as stepping layer by layer; two problems against
+    the checker."""
     pipes = I.resnet18_batch(B, seed=21)
     sp = I.make_space([1, 2, 4], [1, 4], [4, 8], [(0, 1, 2), (2, 1, 0)], 2, 2,
                       [I.ROOT, I.L1, I.L2, I.INLINE], 2, dims[0])
@@ -486,7 +509,8 @@ def test_whole_schedule_launch_other_depths(vf, ovf, dims):
     S = pipes.shape[1]
     ctx = vf.vf_create(0)
     vf.vf_set_space(ctx, sp); vf.vf_set_pipeline(ctx, pipes); vf.vf_set_model(ctx, model, w)
-    whole = [t.cpu().numpy() for t in vf.vf_greedy_schedule(ctx)]
+    whole, launches = greedy_with_launches(vf, ctx)
+    assert launches == (1 if one_launch else S)
     vf.vf_reset_state(ctx)
     for i in range(S):
         vf.vf_argmin_step(ctx, i, True)
@@ -501,9 +525,10 @@ def test_whole_schedule_launch_other_depths(vf, ovf, dims):
 @pytest.mark.parametrize("B", [200, 300])
 def test_whole_schedule_launch_with_helpers(vf, ovf, B):
     """200 problems on 256 compute units: the workgroups without a problem of their own help
-    the others from the first layers on (and the ones that finish early later); 300 problems:
-    some workgroups own two problems and the others help them when they are done.  A problem
-    that ends early and exploration noise included.  Same tables as stepping layer by layer;
+    the others from the first layers on (and the ones that finish early later).  300 problems of
+    these short decisions go layer by layer on lists (test_gpu_lists.py has batches of long ones
+    whose owners run two problems and are then helped).  A problem that ends early and exploration
+    noise included.  Same tables as stepping layer by layer;
     the counters say that only listed candidates were scored; two problems against the checker."""
     pipes = I.resnet18_batch(B, seed=33)
     pipes[5, 2, 3] = 2
@@ -517,12 +542,10 @@ def test_whole_schedule_launch_with_helpers(vf, ovf, B):
     vf.vf_set_space(ctx, sp); vf.vf_set_pipeline(ctx, pipes); vf.vf_set_model(ctx, model, w)
     for eps in (0.0, 0.1):
         vf.vf_set_noise(ctx, eps, seed=3)
-        vf.vf_reset_state(ctx)
-        vf.vf_profile_enable(ctx, True); vf.vf_profile_counts(ctx)
-        whole = [t.cpu().numpy() for t in vf.vf_greedy_schedule(ctx)]
+        vf.vf_profile_counts(ctx)
+        whole, launches = greedy_with_launches(vf, ctx)
         scored, valid = vf.vf_profile_counts(ctx)
-        vf.vf_profile_enable(ctx, False)
-        assert scored == valid > 0
+        assert scored == valid > 0 and launches == (1 if B == 200 else S)
         vf.vf_reset_state(ctx)
         for i in range(S):
             vf.vf_argmin_step(ctx, i, True)

@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2011_14486_amd import inputs as I
+from tests.test_gpu_greedy import greedy_with_launches
 
 pytestmark = pytest.mark.gpu
 
@@ -61,7 +62,8 @@ def test_second_round_of_long_decisions_in_one_launch(vf, B):
     pipes = np.stack([I.random_pipeline(3, 40 + b % 7) for b in range(B)])
     ctx = context(vf, pipes, sp, I.model_record(I.MLP, dims, I.BF16), I.mlp_weights(dims, 4, bias_std=0.1))
     vf.vf_set_noise(ctx, 0.2, 9, 0)
-    whole = [t.cpu().numpy() for t in vf.vf_greedy_schedule(ctx)]
+    whole, launches = greedy_with_launches(vf, ctx)
+    assert launches == 1
     vf.vf_reset_state(ctx)
     for i in range(3):
         vf.vf_argmin_step(ctx, i, True)
