@@ -29,14 +29,15 @@ def layer_scores(ovf, pipe, sp, model, w, pre, i):
     return ovf.score_mlp(model, w, feat, M=M).astype(np.float64), feat[16, :M] != 0
 
 
-def check_beam(ovf, pipe, sp, model, w, run, K, tol):
+def check_beam(ovf, pipe, sp, model, w, run, K, tol, start=()):
     """Layer by layer (run(last) = the GPU search stopped after layer `last`): the checker
     scores every extension of the GPU's survivors of the layer before; the GPU's survivors
     of this layer must be the smallest ones (up to the score tolerance at the cut), in
-    order, with matching values and state records."""
-    S = len(pipe)
-    prev, vals_prev = [()], [np.zeros(0, np.float32)]
-    for i in range(S):
+    order, with matching values and state records.  start: the committed prefix the search
+    starts from (decisions that carry no value)."""
+    S, n0 = len(pipe), len(start)
+    prev, vals_prev = [tuple(start)], [np.zeros(0, np.float32)]
+    for i in range(n0, S):
         cids, vals, states, n_beams = run(i)
         items = []
         for b, pre in enumerate(prev):
@@ -47,7 +48,7 @@ def check_beam(ovf, pipe, sp, model, w, run, K, tol):
         items.sort()
         if not items:
             # dead end: the survivors of the layer before are kept as they were
-            assert n_beams == len(prev) or (prev == [()] and n_beams == 1)
+            assert n_beams == len(prev) or (prev == [tuple(start)] and n_beams == 1)
             for j, pre in enumerate(prev):
                 assert tuple(int(t) for t in cids[j, :i]) == pre and (cids[j, i:] == -1).all()
             return
@@ -64,7 +65,7 @@ def check_beam(ovf, pipe, sp, model, w, run, K, tol):
             got.append((score_of[key], key))
             err = abs(float(vals[j, i]) - score_of[key]) / max(abs(score_of[key]), scale)
             assert err <= tol, (i, j, err)
-            assert np.array_equal(vals[j, :i], vals_prev[key[0]][:i])
+            assert np.array_equal(vals[j, n0:i], vals_prev[key[0]][n0:i])
             rst, _ = ovf.states(pipe, sp, cids[j, :i + 1])
             assert np.array_equal(states[j, :i + 1], rst) and not states[j, i + 1:].any()
         cut = items[len(rows) - 1][0]
@@ -94,12 +95,15 @@ def make_ctx(vf, pipe, sp, model, w, K):
     return ctx, run
 
 
-@pytest.mark.parametrize("K", [1, 4, 16, 40])
-def test_beam_fused_bf16(vf, ovf, K):
+@pytest.mark.parametrize("K,dims", [(1, [256, 512, 512, 1]), (4, [256, 512, 512, 1]), (16, [256, 512, 512, 1]),
+                                    (40, [256, 512, 512, 1]), (3, [256, 512, 512, 512, 512, 1])])
+def test_beam_fused_bf16(vf, ovf, K, dims):
+    """One slot and (three slots) a network of four hidden layers, whose biases do not fit next to a
+    list's tile: the scorer on id ranges and the selection passes; otherwise lists of valid
+    candidates."""
     sp = I.make_space([1, 2, 3, 8], [1, 2, 5], [1, 4, 16], [(0, 1, 2), (2, 1, 0), (1, 0, 2)], 2, 2,
                       [I.ROOT, I.L1, I.L2, I.INLINE], 2, 256)
     pipe = I.random_pipeline(4, 41)
-    dims = [256, 512, 512, 1]
     w = I.mlp_weights(dims, 3, bias_std=0.1)
     model = I.model_record(I.MLP, dims, I.BF16)
     ctx, run = make_ctx(vf, pipe, sp, model, w, K)
@@ -130,13 +134,14 @@ def test_beam_fp32_tiny_config_with_ties(vf, ovf, K):
     vf.vf_destroy(ctx)
 
 
-def test_beam_general_widths_and_prefix(vf, ovf):
-    """A model outside the fused path (features materialised, scores masked afterwards), and a
-    search that starts from a committed prefix (the way Algorithm 2 completes schedules)."""
+@pytest.mark.parametrize("dims", [[64, 96, 32, 1], [64, 160, 32, 1]])
+def test_beam_general_widths_and_prefix(vf, ovf, dims):
+    """Models outside the fused path - a small one, which generates its candidates itself, and one for
+    which the features are materialised and the scores masked afterwards - and a search that starts
+    from a committed prefix (the way Algorithm 2 completes schedules)."""
     sp = I.make_space([1, 2, 4], [1, 2], [1, 4], [(0, 1, 2), (2, 1, 0)], 2, 1,
                       [I.ROOT, I.L1, I.L2, I.INLINE], 1, 64)
     pipe = I.random_pipeline(4, 52)
-    dims = [64, 96, 32, 1]
     w = I.mlp_weights(dims, 9, bias_std=0.1)
     model = I.model_record(I.MLP, dims, I.BF16)
     ctx, run = make_ctx(vf, pipe, sp, model, w, 5)
@@ -150,7 +155,15 @@ def test_beam_general_widths_and_prefix(vf, ovf):
     vf.vf_set_state(ctx, np.full((5, 1), first, np.int32))
     st2, c2, v2, nb2 = vf.vf_beam_search(ctx, first=1)
     c2 = c2.cpu().numpy()
-    assert (c2[c2[:, 0] >= 0, 0] == first).all() and c2[0].tolist() == cids[0].tolist()
+    assert (c2[c2[:, 0] >= 0, 0] == first).all()
+    if dims[1] == 96:  # (this network's best schedule is found from its first decision as well)
+        assert c2[0].tolist() == cids[0].tolist()
+
+    def onwards(last):
+        vf.vf_set_state(ctx, np.full((5, 1), first, np.int32))
+        st, cids, vals, nb = vf.vf_beam_search(ctx, 1, last)
+        return cids.cpu().numpy(), vals.cpu().numpy(), st.cpu().numpy(), int(nb.cpu()[0])
+    check_beam(ovf, pipe, sp, model, w, onwards, 5, TOL[1], start=(first,))
     with pytest.raises(vf.VfError):
         vf.vf_beam_search(ctx, first=0)                      # not the next stage
     other = I.random_pipeline(4, 53)

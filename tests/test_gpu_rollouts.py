@@ -67,18 +67,19 @@ def test_noisy_rollouts_fused_bf16(vf, ovf, B):
     vf.vf_destroy(ctx)
 
 
-def test_noisy_rollouts_unfused_path(vf, ovf):
-    """A model outside the fused path: features materialised, generic MFMA scorer."""
+@pytest.mark.parametrize("dims,dtype", [([64, 96, 32, 1], I.BF16), ([64, 160, 32, 1], I.BF16), ([64, 160, 1], I.FP32)])
+def test_noisy_rollouts_unfused_path(vf, ovf, dims, dtype):
+    """Models outside the fused path: a small one, which generates its candidates itself, and larger
+    ones on materialised features (generic MFMA scorer; fp32 layer kernels)."""
     sp = I.make_space([1, 2, 4], [1, 2], [1, 4], [(0, 1, 2), (2, 1, 0)], 2, 1,
                       [I.ROOT, I.L1, I.L2, I.INLINE], 1, 64)
     pipe = I.random_pipeline(4, 52)
-    dims = [64, 96, 32, 1]
     w = I.mlp_weights(dims, 9, bias_std=0.1)
-    model = I.model_record(I.MLP, dims, I.BF16)
+    model = I.model_record(I.MLP, dims, dtype)
     B, eps, seed = 4, 0.2, 5
     ctx, cids, vals, st = gpu_rollouts(vf, pipe, sp, model, w, B, eps, seed)
     for k in range(B):
-        check_layers(ovf, pipe, sp, model, w, cids[k], vals[k], st[k], TOL[1], eps=eps, seed=seed, rollout=k)
+        check_layers(ovf, pipe, sp, model, w, cids[k], vals[k], st[k], TOL[dtype], eps=eps, seed=seed, rollout=k)
     ref = ovf.rollouts(pipe, sp, model, w, eps, seed, B)
     assert (ref["cids"] == cids).mean() > 0.5      # (and mostly the checker's own rollouts outright)
     vf.vf_destroy(ctx)

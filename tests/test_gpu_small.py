@@ -75,12 +75,15 @@ def test_extreme_weights(vf, dtype):
 
 
 @pytest.mark.parametrize("dims,dtype", [([64, 128, 128, 1], I.FP32), ([256, 96, 1], I.FP32), ([256, 1], I.FP32),
-                                        ([64, 96, 32, 1], I.BF16), ([256, 96, 64, 1], I.BF16), ([256, 1], I.BF16)])
+                                        ([64, 96, 32, 1], I.BF16), ([256, 96, 64, 1], I.BF16), ([256, 1], I.BF16),
+                                        ([256, 128, 1], I.FP32), ([256, 128, 128, 128, 1], I.BF16)])
 @pytest.mark.parametrize("B", [1, 70])
 def test_generated_candidates_equal_scored_features(vf, dims, dtype, B):
     """A decision scored from the generated candidates against vf_score on vf_featurize's matrix: the
     same features and the same arithmetic, so the same winner and the same bits (one or two columns
-    per lane, closed runs of ids, the last ids of a space that is no multiple of a tile)."""
+    per lane, closed runs of ids, the last ids of a space that is no multiple of a tile).  The last
+    two networks leave no room for the decisions' contexts: their step takes the matrix itself, with
+    its validity row."""
     sp = I.make_space([1, 2, 4], [1, 2, 4, 8], [1, 4, 8], I.XC_INNER_PERMS, 2, 2, [I.ROOT, I.L1, I.L2, I.INLINE], 2, dims[0])
     M = I.space_dense_count(sp)
     pipes = np.stack([I.random_pipeline(4, 300 + b) for b in range(B)])
