@@ -199,12 +199,14 @@ int vf_argmin_step(vf_ctx *ctx, int stage, int commit, int32_t *best_cid_dev, fl
  * out_states_dev[batch][S] the committed states s_1..s_n so far (all stages),
  * out_cids_dev[batch][S] the chosen candidate ids, out_values_dev[batch][S] their
  * values; entries of stages not scheduled yet are zero states, -1 and +inf.
- * A few problems take one launch per layer, more of them two.  Where it is faster (a problem
- * for most compute units, or from 24 problems on decisions of few candidates; the model's tile
- * must fit the LDS) the layers run inside one launch: with fewer problems than half the compute
- * units several workgroups share a problem from the start, with more a workgroup that has
- * finished its own problems helps with the ones still running; workgroups that share a problem
- * meet once per layer with a bounded wait.  Should such a wait ever run out (the GPU shared with work that never ends), the
+ * A few problems take one launch per layer, more of them two.  With a problem for most compute
+ * units, and from 24 problems on decisions of few candidates, the layers run inside one launch (the
+ * model's tile must fit the LDS): with fewer problems than half the compute units several workgroups
+ * share a problem from the start, with more a workgroup that has finished its own problems helps
+ * with the ones still running; workgroups that share a problem meet once per layer with a bounded
+ * wait.  Without device memory for the candidate lists that these ways keep, the call goes on with
+ * launches per layer on id ranges, which decide the same.
+ * Should such a wait ever run out (the GPU shared with work that never ends), the
  * launch still ends, and the problems it did not finish read -1 / +inf / zero state from the
  * first unfinished layer on.  The library learns of it when the stream has got there:
  * vf_sync_status waits for that and reports it; otherwise the next call that builds on the

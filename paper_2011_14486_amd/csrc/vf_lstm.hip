@@ -468,8 +468,8 @@ __global__ __launch_bounds__(512) void k_seq_step(SeqDev md, int stage, int64_t 
 // cores idle.  Here the stream serves 96 entries, so that the products take as long as the stream, and
 // a wave does its 32 hidden units in two passes of 16 (all four gates: two row tiles, three column
 // tiles, 96 accumulators), with the waves 0..3 ahead of the waves 4..7 by wave priority: on every SIMD
-// one wave's gates run under the other wave's products.  A step of 96 takes about 22k cycles, 19k of
-// them vector work of the gates (202 cycles per cell and wave, 128 of those in 5 exp and 3 rcp).
+// one wave's gates run under the other wave's products.  A step of 96 takes about 22k cycles, 20k of
+// them vector work of the gates (210 cycles per cell and wave, 128 of those in 5 exp and 3 rcp).
 // 64 problems of 20 layers, H = 256: 19.4 -> 17.0 ms per schedule, H = 128 8.7 -> 7.5, 12 layers of other
 // shapes 5.4 -> 3.1.  (128 entries: the accumulators and cell states leave no registers, and what is
 // spilled in the gates comes back behind the weight fragments under way: 28.6 ms.)

@@ -663,18 +663,17 @@ static whole_kernel whole_launch_shape(const vf_ctx *c, vf_fast_dev *fd, int *ks
   return NC == 64 ? k_whole<64, 4, 2, false> : k_whole<128, 2, 4, false>;
 }
 
-// Workgroups per problem for a whole-schedule launch where one is wanted (vfk_whole_pays, and decisions
-// of few tiles, see vfk_layer_pays), 0 = use the per-layer launches
-// (also when the model's tile does not fit the LDS of a compute unit next to its input
-// buffer, e.g. three hidden layers of 512 with all their biases).
-// 1 with more problems than half the compute units: every workgroup owns ceil(B / units)
-// problems from the first layer to the last and helps the others when it is done (measured
-// per step against the per-layer launches on id ranges: 140 problems 3.6 instead of 5.1 ms, 160: 4.0
-// instead of 5.6, 300: 7.0 instead of 8.5); with fewer problems a fixed team per problem, as
-// large as the compute units and the tiles of a decision allow, at most 16 (128 problems x
-// 2: 3.1 instead of 4.9 ms, 64 x 4: 2.1 instead of 3.4, 32 x 8: 1.7 instead of 2.2; helpers
-// instead of fixed teams are slower there: 64 problems 2.9 ms); below 24 problems the
-// meetings cost what the launches did.
+// Workgroups per problem for a whole-schedule launch, 0 = it is not used (among others when the
+// model's tile does not fit the LDS of a compute unit next to its input buffer, e.g. three hidden
+// layers of 512 with all their biases).
+// 1 with more problems than half the compute units: every workgroup owns ceil(B / units) problems
+// from the first layer to the last and helps the others when it is done (vfk_whole_pays says where
+// this is wanted).  With fewer problems, from 24 on, a fixed team per problem, as large as the compute
+// units and the tiles of a decision allow, at most 16.  That is for decisions of few candidates: where
+// all problems have more tiles than there are compute units the lists go first (vfk_layer_pays).
+// The line at 24 is older than the present launches per layer, which are faster there (256-512-512-1,
+// 20 layers, teams against launches per layer: 24 problems of 768 ids 0.89 / 0.61 ms, 42: 1.25 / 0.62,
+// 64 of 512 ids 1.21 / 0.64, 128 of 256 ids 1.20 / 0.64).
 int vfk_whole_team(const vf_ctx *c) {
   if (!vfk_can_fuse_step(c)) return 0;
   {
@@ -707,7 +706,7 @@ int vfk_whole_team(const vf_ctx *c) {
   // (a mailbox names a problem in 23 bits, a layer's tiles are counted in 16)
   if (c->B >= (1 << 23) || (c->M + 63) / 64 > 65535) return 0;
   if (c->B > ncu / 2) return 1;
-  if (c->B < 24) return 0;  // a handful of problems: the per-layer launches are faster (16: 1.3 against 1.6 ms)
+  if (c->B < 24) return 0;  // a handful of problems: a launch per layer (16 of 768 ids: 0.44 against 0.74 ms)
   int maxw = 0;
   for (int l = 0; l < c->model.n_layers; ++l) if (c->model.dims[l] > maxw) maxw = c->model.dims[l];
   const int NC = maxw > 512 ? 64 : 128;
@@ -715,20 +714,17 @@ int vfk_whole_team(const vf_ctx *c) {
   int team = ncu / c->B;
   if (team > nparts) team = nparts;
   if (team > 16) team = 16;
-  // Fixed teams that leave a fifth of the compute units without work, on decisions long enough
-  // for helpers to pay (100 rollouts of the 100-stage pipeline, 16384 ids: teams of two use 200
-  // of 256 units, 26.9 ms; owners with the other 156 as helpers 25.2 ms; with 4096 ids per
-  // decision the teams stay ahead, 2.45 against 2.6 ms)
-  if (team >= 2 && (ncu - c->B * team) * 5 >= ncu && nparts >= 64) return 1;
   return team >= 2 ? team : 0;
 }
 
-// Whether whole schedules in one launch are faster than two launches per layer on lists, where
-// both can run: with a problem for most compute units but none for a second round.  The launches per
+// Whether whole schedules in one launch are preferred to two launches per layer on lists, where both
+// can run: with a problem for most compute units but none for a second round.  The launches per
 // layer deal out the tiles of all problems evenly and wait for nobody, but pay two launches and a
-// serial opening per layer (256-512-512-1, 20 layers of 4096 ids: 64 problems 1.61 against 1.14 ms per
-// schedule, 128: 2.06 / 1.75, 160: 2.52 / 2.05, 200: 2.65 / 2.46, 256: 2.95 / 2.98, 300: 4.57 / 3.46;
-// 100 layers of 16384 ids: 100 problems 13.0 / 11.6, 160: 17.1 / 16.9, 180: 18.4 / 18.6, 200: 19.7 / 20.5).
+// serial opening per layer.  256-512-512-1, one launch against lists: 100 layers of 16384 ids, 100 problems
+// 13.0 / 11.6 ms, 160: 17.1 / 16.9, 180: 18.4 / 18.6, 200: 19.7 / 20.5; 20 layers of 4096 ids, 64 problems
+// 1.61 / 1.14, 128: 2.06 / 1.75, 160: 2.64 / 2.22, 200: 2.88 / 2.66, 230: 2.99 / 2.96, 256: 3.15 / 3.23,
+// 300: 4.57 / 3.46.  (The line at five eighths is that of the long decisions: with 4096 ids the lists
+// stay ahead up to about 230 problems.)
 // Decisions of 64 tiles or more leave the helpers enough to share, so that further rounds that are
 // more than three quarters full pay as well (the 100 layers again, other inputs: 300 problems 68.1 /
 // 66.1 ms, 384: 81.7 / 81.6, 448: 93.9 / 95.1, 512: 106.1 / 108.7, 768: 159.2 / 162.6; 4096 ids stay
