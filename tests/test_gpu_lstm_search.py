@@ -166,8 +166,9 @@ def test_rollouts_with_noise(vf, ovf):
     vf.vf_destroy(ctx)
 
 
-@pytest.mark.parametrize("K", [1, 6])
+@pytest.mark.parametrize("K", [1, 6, 128])
 def test_beam_search(vf, ovf, K):
+    """(128 slots of six tiles of 64 ids: scores from tiles of 96)"""
     sp = I.make_space([1, 2, 4], [1, 4], [1, 2], [(0, 1, 2), (2, 1, 0)], 2, 2,
                       [I.ROOT, I.L1, I.L2, I.INLINE], 1, 64)
     pipe = I.random_pipeline(4, 31)
