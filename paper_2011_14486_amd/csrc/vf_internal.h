@@ -61,7 +61,7 @@ struct vf_packed_model {
   void *small_buf = nullptr;
   // recurrent network wired to the search: [W_ih | W_hh] transposed, bf16 values as fp32, [64+H][4H]
   float *w_seqT = nullptr;
-  uint16_t *w_seq_wide = nullptr;  // both in MFMA order for tiles of 96 candidates: see k_seq_step_wide
+  uint16_t *w_seq_wide = nullptr;  // both in MFMA order by tiles of 16 units: see k_pack_seq_wide
 };
 
 struct vf_ctx {
@@ -115,6 +115,7 @@ struct vf_ctx {
   float *d_seq_P[2] = {nullptr, nullptr};         // [B][4H] biases + W_hh h: gates of the next step
   float *d_seq_hs[2] = {nullptr, nullptr};        // [B] head predictions summed over the committed stages
   int32_t *d_seq_list = nullptr, *d_seq_count = nullptr;  // [B][Mpad] valid ids of the decision, [B] their number
+  uint16_t *d_seq_rows = nullptr;                 // [B][Mpad][64] normalised features of the listed candidates, bf16
   int seq_stage = -1;                             // committed stages folded into the state, -1: none valid
   int seq_cur = 0;                                // which set is current
   // exploration noise added to the scores in the argmin scan of step / greedy calls

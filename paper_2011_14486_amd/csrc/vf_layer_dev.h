@@ -18,6 +18,79 @@ struct OpenScratch {
   int npairs, ncand;
 };
 
+// Ordered list of a decision's valid ids, written down directly from the validity rules: per
+// (compute_at, store_at) digit pair that is open - the level is offered and the hoist does not exceed
+// it - the valid ids are the products of the split factors that fit the level's region with every
+// loop order / vectorize / parallel choice; an inlining pair has the single id with every other digit
+// zero.  In three parts with a workgroup barrier behind each of the first two.
+// First: the split factors that fit (nine threads, i = 0..8).
+[[maybe_unused]] __device__ __forceinline__ void list_factors(const DecPack &pk, OpenScratch &os, int i) {
+  const int lvl = i / 3, dd = i % 3;
+  int cnt = 0;
+  for (int k = 0; k < pk.sp.nf[dd]; ++k)
+    if ((uint32_t)pk.sp.fac[dd][k] <= pk.d.E[lvl][dd]) os.ok[lvl][dd][cnt++] = k;
+  os.nok[lvl][dd] = cnt;
+  os.rcp[lvl][dd] = 1.0f / (float)(cnt > 0 ? cnt : 1);
+}
+// Second: the open pairs numbered and given their first list position in order (one wave; lane j
+// looks at pair j = (store_at digit, compute_at digit)).
+[[maybe_unused]] __device__ __forceinline__ void list_pairs(const DecPack &pk, OpenScratch &os, int lane) {
+  const int rest_n = pk.sp.nperm * pk.sp.nvec * pk.sp.npar;
+  const int npairs_all = pk.sp.nsat * pk.sp.ncat;
+  int cnt = 0, cat = 0, dec = 0;
+  if (lane < npairs_all && lane < 12) {
+    const int isat = lane / pk.sp.ncat, icat = lane % pk.sp.ncat;
+    cat = pk.sp.cat[icat];
+    dec = (int)((uint32_t)icat << 24 | (uint32_t)isat << 28);
+    if (pk.d.lvl_ok[cat] != 0) {
+      if (cat == VF_INLINE) cnt = isat == 0 ? 1 : 0;
+      else if (isat <= cat) cnt = os.nok[cat][0] * os.nok[cat][1] * os.nok[cat][2] * rest_n;
+    }
+  }
+  int np = 0, pos = 0;
+#pragma unroll
+  for (int j = 0; j < 12; ++j) {
+    const int cj = __builtin_amdgcn_readlane(cnt, j);
+    if (cj == 0) continue;
+    const int catj = __builtin_amdgcn_readlane(cat, j), decj = __builtin_amdgcn_readlane(dec, j);
+    if (lane == 0) {
+      os.pos[np] = pos;
+      os.cat[np] = catj;
+      os.dec[np] = decj;
+    }
+    pos += cj;
+    ++np;
+  }
+  if (lane == 0) {
+    os.pos[np] = pos;
+    os.npairs = np;
+    os.ncand = pos;
+  }
+}
+// Third: the packed digits of entry k (pos_r: the pairs' first positions in registers, 0x7fffffff
+// behind the last pair, so that an entry's pair is found without a chain of dependent reads).
+[[maybe_unused]] __device__ __forceinline__ uint32_t list_entry(const DecPack &pk, const OpenScratch &os, const int (&pos_r)[12], int k,
+                                               float rcp_perm, float rcp_vec) {
+  int q = 0;
+#pragma unroll
+  for (int j = 1; j < 12; ++j) q += k >= pos_r[j] ? 1 : 0;
+  const int cat = os.cat[q];
+  uint32_t dec = (uint32_t)os.dec[q];
+  if (cat != VF_INLINE) {
+    uint32_t r = (uint32_t)(k - os.pos[q]), nxt;
+    const uint32_t nx = os.nok[cat][0], ny = os.nok[cat][1], nc = os.nok[cat][2];
+    nxt = div_small(r, nx, os.rcp[cat][0]); const uint32_t jx = r - nxt * nx; r = nxt;
+    nxt = div_small(r, ny, os.rcp[cat][1]); const uint32_t jy = r - nxt * ny; r = nxt;
+    nxt = div_small(r, nc, os.rcp[cat][2]); const uint32_t jc = r - nxt * nc; r = nxt;
+    const int ix = os.ok[cat][0][jx], iy = os.ok[cat][1][jy], ic = os.ok[cat][2][jc];
+    nxt = div_small(r, (uint32_t)pk.sp.nperm, rcp_perm); const uint32_t ip = r - nxt * (uint32_t)pk.sp.nperm; r = nxt;
+    const uint32_t par = div_small(r, (uint32_t)pk.sp.nvec, rcp_vec), vec = r - par * (uint32_t)pk.sp.nvec;
+    dec |= (uint32_t)ix | (uint32_t)iy << 4 | (uint32_t)ic << 8 | (uint32_t)ip << 12 | (uint32_t)vec << 16 |
+           (uint32_t)par << 20;
+  }
+  return dec;
+}
+
 // Opens a decision whose context (pk.d, pk.sp) is in LDS: quotient tables, the shared input rows
 // as the first layer wants them, the folded bias, the ordered list of the valid candidates with
 // its length (os.ncand).  Every thread of a workgroup of 512 calls it; the list is complete for
@@ -31,85 +104,18 @@ __device__ __forceinline__ void open_layer(DecPack &pk, EvalTabs &tabs, OpenScra
   // (wave 4)
   fill_evaltabs(tabs, pk.d, pk.sp);
   if (tid >= 128 && tid < 128 + VF_STAT_WORDS) pk.stat[tid - 128] = stat_word(pk.d, tid - 128);
-  // Ordered list of the decision's valid ids, written down directly from the validity
-  // rules: per (compute_at, store_at) digit pair that is open - the level is offered and
-  // the hoist does not exceed it - the valid ids are the products of the split factors
-  // that fit the level's region with every loop order / vectorize / parallel choice;
-  // an inlining pair has the single id with every other digit zero.  The list holds the
-  // digits, packed, rather than the id: the evaluation works on digits, and putting an id
-  // together takes a few multiplications where taking it apart takes as many divisions.
-  if (tid >= 256 && tid < 265) {
-    const int lvl = (tid - 256) / 3, dd = (tid - 256) % 3;
-    int cnt = 0;
-    for (int k = 0; k < pk.sp.nf[dd]; ++k)
-      if ((uint32_t)pk.sp.fac[dd][k] <= pk.d.E[lvl][dd]) os.ok[lvl][dd][cnt++] = k;
-    os.nok[lvl][dd] = cnt;
-    os.rcp[lvl][dd] = 1.0f / (float)(cnt > 0 ? cnt : 1);
-  }
+  // (the list holds the digits, packed, rather than the id: the evaluation works on digits, and putting
+  // an id together takes a few multiplications where taking it apart takes as many divisions)
+  if (tid >= 256 && tid < 265) list_factors(pk, os, tid - 256);
   __syncthreads();
-  const int rest_n = pk.sp.nperm * pk.sp.nvec * pk.sp.npar;
   const float rcp_perm = 1.0f / (float)pk.sp.nperm, rcp_vec = 1.0f / (float)pk.sp.nvec;
-  if (w == 0) {
-    // lane j looks at pair j = (store_at digit, compute_at digit); the open pairs are then
-    // numbered and given their first list position in order
-    const int npairs_all = pk.sp.nsat * pk.sp.ncat;
-    int cnt = 0, cat = 0, dec = 0;
-    if (lane < npairs_all && lane < 12) {
-      const int isat = lane / pk.sp.ncat, icat = lane % pk.sp.ncat;
-      cat = pk.sp.cat[icat];
-      dec = (int)((uint32_t)icat << 24 | (uint32_t)isat << 28);
-      if (pk.d.lvl_ok[cat] != 0) {
-        if (cat == VF_INLINE) cnt = isat == 0 ? 1 : 0;
-        else if (isat <= cat) cnt = os.nok[cat][0] * os.nok[cat][1] * os.nok[cat][2] * rest_n;
-      }
-    }
-    int np = 0, pos = 0;
-#pragma unroll
-    for (int j = 0; j < 12; ++j) {
-      const int cj = __builtin_amdgcn_readlane(cnt, j);
-      if (cj == 0) continue;
-      const int catj = __builtin_amdgcn_readlane(cat, j), decj = __builtin_amdgcn_readlane(dec, j);
-      if (lane == 0) {
-        os.pos[np] = pos;
-        os.cat[np] = catj;
-        os.dec[np] = decj;
-      }
-      pos += cj;
-      ++np;
-    }
-    if (lane == 0) {
-      os.pos[np] = pos;
-      os.npairs = np;
-      os.ncand = pos;
-    }
-  }
+  if (w == 0) list_pairs(pk, os, lane);
   fold_bias<RT>(wf, pk.stat, md.dims[0] == 256, w, lane, md.aux + md.bias_off[0], bias_out);
   __syncthreads();  // the pairs are numbered, the bias is complete
-  // (the pairs' first positions into registers: the pair of an entry is then found without
-  // a chain of dependent reads)
   int pos_r[12];
 #pragma unroll
   for (int j = 0; j < 12; ++j) pos_r[j] = j < os.npairs ? os.pos[j] : 0x7fffffff;
-  for (int k = tid; k < os.ncand; k += 512) {
-    int q = 0;
-#pragma unroll
-    for (int j = 1; j < 12; ++j) q += k >= pos_r[j] ? 1 : 0;
-    const int cat = os.cat[q];
-    uint32_t dec = (uint32_t)os.dec[q];
-    if (cat != VF_INLINE) {
-      uint32_t r = (uint32_t)(k - os.pos[q]), nxt;
-      const uint32_t nx = os.nok[cat][0], ny = os.nok[cat][1], nc = os.nok[cat][2];
-      nxt = div_small(r, nx, os.rcp[cat][0]); const uint32_t jx = r - nxt * nx; r = nxt;
-      nxt = div_small(r, ny, os.rcp[cat][1]); const uint32_t jy = r - nxt * ny; r = nxt;
-      nxt = div_small(r, nc, os.rcp[cat][2]); const uint32_t jc = r - nxt * nc; r = nxt;
-      const int ix = os.ok[cat][0][jx], iy = os.ok[cat][1][jy], ic = os.ok[cat][2][jc];
-      nxt = div_small(r, (uint32_t)pk.sp.nperm, rcp_perm); const uint32_t ip = r - nxt * (uint32_t)pk.sp.nperm; r = nxt;
-      const uint32_t par = div_small(r, (uint32_t)pk.sp.nvec, rcp_vec), vec = r - par * (uint32_t)pk.sp.nvec;
-      dec |= (uint32_t)ix | (uint32_t)iy << 4 | (uint32_t)ic << 8 | (uint32_t)ip << 12 | (uint32_t)vec << 16 |
-             (uint32_t)par << 20;
-    }
-    idlist[k] = dec;
-  }
+  for (int k = tid; k < os.ncand; k += 512) idlist[k] = list_entry(pk, os, pos_r, k, rcp_perm, rcp_vec);
 }
 
 // Leaves an opened decision in memory (every thread of a workgroup of 512; bias: the folded one).

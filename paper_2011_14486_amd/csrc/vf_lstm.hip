@@ -16,6 +16,7 @@ namespace {
 
 #include "vf_sched_dev.h"
 #include "vf_score_dev.h"
+#include "vf_layer_dev.h"
 
 // fp32 blob of the model: W_ih[4H][64], W_hh[4H][H], b_ih[4H], b_hh[4H], w_head[H], b_head
 struct SeqWeights {
@@ -462,257 +463,9 @@ __global__ __launch_bounds__(512) void k_seq_step(SeqDev md, int stage, int64_t 
   }
 }
 
-// The same for tiles of 96 entries.  What bounds k_seq_step is that its two phases alternate: the
-// contraction of a tile of 64 waits for the weight stream (512 KB per step out of L2 at H = 256, 1.5
-// times what its products take), then the gates keep the vector ALUs busy for as long with the matrix
-// cores idle.  Here the stream serves 96 entries, so that the products take as long as the stream, and
-// a wave does its 32 hidden units in two passes of 16 (all four gates: two row tiles, three column
-// tiles, 96 accumulators), with the waves 0..3 ahead of the waves 4..7 by wave priority: on every SIMD
-// one wave's gates run under the other wave's products.  A step of 96 takes about 22k cycles, 20k of
-// them vector work of the gates (210 cycles per cell and wave, 128 of those in 5 exp and 3 rcp).
-// 64 problems of 20 layers, H = 256: 19.4 -> 17.0 ms per schedule, H = 128 8.7 -> 7.5, 12 layers of other
-// shapes 5.4 -> 3.1.  (128 entries: the accumulators and cell states leave no registers, and what is
-// spilled in the gates comes back behind the weight fragments under way: 28.6 ms.)
-// The weights are one stream per wave (k_pack_seq_wide): per pass the k-steps of h, then those of x;
-// row tile 0 of a pass holds gate i of its units in rows 0..15 and gate f in rows 16..31, row tile 1
-// the gates g and o.  The first step's x lies in the h buffer that the second step writes.
-constexpr int SEQ_WIDE = 96;
-template <int PD>
-__global__ __launch_bounds__(512) void k_seq_step_wide(SeqDev md, const uint16_t *w_wide, int stage, float *scores,
-                                                       int64_t ld_scores, float *pval, int32_t *pidx, NoiseArgs na) {
-  constexpr int NC = SEQ_WIDE, CT = NC / 32;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int H = md.H, S = md.S, H4 = 4 * H, hld = H + 8;
-  uint16_t *hs = reinterpret_cast<uint16_t *>(smem);                    // [2][NC][max(hld, 72)]
-  const int hcol = hld < 72 ? 72 : hld;
-  float *gls = reinterpret_cast<float *>(hs + (size_t)2 * NC * hcol);   // [2][4H]
-  float *red = gls + 2 * H4;                                            // [8][NC]
-  float *whs = red + 8 * NC;                                            // [H]
-  int32_t *okf = reinterpret_cast<int32_t *>(whs + H);                  // [NC] candidate id + 1, 0 = none
-  __shared__ DecPack pk;
-  __shared__ float sv[2];
-  __shared__ int32_t sc[2];
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int b = blockIdx.y, nparts = gridDim.x;
-  const int64_t n0 = (int64_t)blockIdx.x * NC;
-  const size_t slot = (size_t)b * nparts + blockIdx.x;
-
-  const int nvalid = md.count[b];
-  if (n0 >= nvalid) {
-    if (tid == 0) {
-      pval[slot] = __builtin_inff();
-      pidx[slot] = -1;
-    }
-    return;
-  }
-  if (tid < VF_DECPACK_DWORDS)
-    reinterpret_cast<uint32_t *>(&pk)[tid] = md.decpack[(size_t)b * VF_DECPACK_DWORDS + tid];
-  const bool active = w < H / 32;
-  const int wu = active ? w : 0;  // idle waves shadow the first units but never store
-  const int ksh = H / 16;
-  const __amdgpu_buffer_rsrc_t ws = stream_rsrc(reinterpret_cast<const uint4 *>(w_wide) + (size_t)wu * (2 * ksh + 8) * 2 * 64);
-  const int voff = 16 * lane;
-  // (the first step's x part sits behind the passes' h parts)
-  int wstep = 2 * ksh + PD;
-  uint4 ring[PD][2];
-#pragma unroll
-  for (int j = 0; j < PD; ++j)
-#pragma unroll
-    for (int r = 0; r < 2; ++r) ring[j][r] = stream_load(ws, voff, (2 * ksh + j) * 2 + r);
-  for (int i = tid; i < H4; i += 512) gls[i] = md.P[(size_t)b * H4 + i];
-  for (int i = tid; i < H; i += 512) whs[i] = md.aux[H4 + i];
-  __syncthreads();
-  if (tid < 4 * NC) {
-    // four threads per candidate, each producing 16 of the 64 core rows (what a thread does not
-    // store is dead code in its copy); padding columns are evaluated too and store zeros
-    const int n = tid % NC, part = tid / NC;
-    const bool inb = (n0 + n) < nvalid;
-    const uint32_t cid = inb ? (uint32_t)md.list[(size_t)b * md.Mpad + n0 + n] : 0u;
-    int32_t core[64];
-    uint32_t dec;
-    auto put = [&](const int32_t *v, int row0) {
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        uint4 q;
-        q.x = pack_bf16(plog2_dev(v[8 * k + 0]), plog2_dev(v[8 * k + 1]));
-        q.y = pack_bf16(plog2_dev(v[8 * k + 2]), plog2_dev(v[8 * k + 3]));
-        q.z = pack_bf16(plog2_dev(v[8 * k + 4]), plog2_dev(v[8 * k + 5]));
-        q.w = pack_bf16(plog2_dev(v[8 * k + 6]), plog2_dev(v[8 * k + 7]));
-        if (!inb) q = make_uint4(0u, 0u, 0u, 0u);
-        reinterpret_cast<uint4 *>(hs + (size_t)n * hcol + row0)[k] = q;
-      }
-    };
-    if (part == 0) {
-      const bool okc = eval_candidate<true>(pk.d, pk.sp, cid, dec, core);
-      okf[n] = inb && okc ? (int32_t)cid + 1 : 0;
-      put(core, 0);
-    } else if (part == 1) {
-      eval_candidate<true>(pk.d, pk.sp, cid, dec, core);
-      put(core + 16, 16);
-    } else if (part == 2) {
-      eval_candidate<true>(pk.d, pk.sp, cid, dec, core);
-      put(core + 32, 32);
-    } else {
-      eval_candidate<true>(pk.d, pk.sp, cid, dec, core);
-      put(core + 48, 48);
-    }
-  }
-  // cell state: per pass and column tile a lane's eight units 8 q + 4 (lane / 32) + e of the pass's 16
-  float cst[2][CT][8];
-  float vsum[CT];
-#pragma unroll
-  for (int ps = 0; ps < 2; ++ps)
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const float4 cv = *reinterpret_cast<const float4 *>(md.cpre + (size_t)b * H + wu * 32 + 16 * ps + 8 * q + 4 * (lane >> 5));
-#pragma unroll
-      for (int c = 0; c < CT; ++c) {
-        cst[ps][c][4 * q + 0] = cv.x; cst[ps][c][4 * q + 1] = cv.y;
-        cst[ps][c][4 * q + 2] = cv.z; cst[ps][c][4 * q + 3] = cv.w;
-      }
-    }
-#pragma unroll
-  for (int c = 0; c < CT; ++c) vsum[c] = 0.0f;
-  __syncthreads();
-
-  for (int t = stage; t < S; ++t) {
-    const int k = t - stage;
-    // the next step's biases, fetched now, parked in LDS after this step's passes
-    const bool fetch_g = (t + 1 < S) && tid < H;
-    float4 gnext = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (fetch_g) gnext = reinterpret_cast<const float4 *>(md.G + ((size_t)b * S + t + 1) * H4)[tid];
-    const uint16_t *src = hs + (size_t)(k & 1) * NC * hcol;
-    uint16_t *hout = hs + (size_t)((k + 1) & 1) * NC * hcol;
-    if (active) {
-#pragma unroll
-    for (int ps = 0; ps < 2; ++ps) {
-      int u0 = wu * 32 + 16 * ps + 4 * (lane >> 5);  // the lane's units: u0 + 8 q + e
-      asm volatile("" : "+v"(u0));                   // (biases read afresh every step, not kept across them)
-      floatx16 acc[2][CT];
-      const uint16_t *bb = src + (size_t)(lane & 31) * hcol + 8 * (lane >> 5);
-      const int nsteps = k == 0 ? 4 : ksh;
-      if (w < 4) __builtin_amdgcn_s_setprio(3);
-      else __builtin_amdgcn_s_setprio(1);
-      {
-        uint4 bcur[CT];
-#pragma unroll
-        for (int c = 0; c < CT; ++c) bcur[c] = *reinterpret_cast<const uint4 *>(bb + (size_t)c * 32 * hcol);
-        __builtin_amdgcn_s_waitcnt(0x0070);  // (see contract_layer)
-        auto round = [&](int s0, auto startc) __attribute__((always_inline)) {
-          constexpr bool starts = decltype(startc)::value;
-          if (ps == 1 && s0 + PD >= nsteps) wstep = 0;  // the next step's first fragments
-#pragma unroll
-          for (int j = 0; j < PD; ++j) {
-            if constexpr (starts) {
-              if (j == 0) {
-                // the first k-step takes the step's gate biases as its addend, row tile by row tile,
-                // so that one of the two bias vectors is in registers at a time
-                const float *bias = gls + (size_t)(k & 1) * H4 + u0;
-#pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                  floatx16 bg;
-#pragma unroll
-                  for (int g = 0; g < 4; ++g) {
-                    const float4 v = *reinterpret_cast<const float4 *>(bias + (2 * r + (g >> 1)) * H + 8 * (g & 1));
-                    bg[4 * g + 0] = v.x; bg[4 * g + 1] = v.y; bg[4 * g + 2] = v.z; bg[4 * g + 3] = v.w;
-                  }
-#pragma unroll
-                  for (int c = 0; c < CT; ++c) {
-                    acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ring[0][r]),
-                                                                       __builtin_bit_cast(bf16x8, bcur[c]), bg, 0, 0, 0);
-                    if (r == 1) bcur[c] = *reinterpret_cast<const uint4 *>(bb + (size_t)c * 32 * hcol + 16);
-                  }
-                  ring[0][r] = stream_load(ws, voff, wstep * 2 + r);
-                  __builtin_amdgcn_sched_barrier(0);
-                }
-                continue;
-              }
-            }
-#pragma unroll
-            for (int i = 0; i < 2 * CT; ++i) {
-              const int c = i / 2, r = i % 2;
-              acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ring[j][r]),
-                                                                 __builtin_bit_cast(bf16x8, bcur[c]), acc[r][c], 0, 0, 0);
-              if (r == 1) bcur[c] = *reinterpret_cast<const uint4 *>(bb + (size_t)c * 32 * hcol + (s0 + j + 1) * 16);
-              if (c == CT - 1) ring[j][r] = stream_load(ws, voff, (wstep + j) * 2 + r);
-              __builtin_amdgcn_sched_barrier(0);
-            }
-          }
-          wstep += PD;
-        };
-        round(0, vf_tag<true>{});
-        for (int s0 = PD; s0 < nsteps; s0 += PD) round(s0, vf_tag<false>{});
-      }
-      __builtin_amdgcn_s_setprio(0);
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const float4 whv = *reinterpret_cast<const float4 *>(whs + u0 + 8 * q);
-        const float whq[4] = {whv.x, whv.y, whv.z, whv.w};
-#pragma unroll
-        for (int c = 0; c < CT; ++c) {
-          float hv[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            float cn = cst[ps][c][4 * q + e];
-            hv[e] = lstm_cell(acc[0][c][4 * q + e], acc[0][c][8 + 4 * q + e], acc[1][c][4 * q + e], acc[1][c][8 + 4 * q + e], cn);
-            cst[ps][c][4 * q + e] = cn;
-            vsum[c] = fmaf(whq[e], hv[e], vsum[c]);
-          }
-          uint2 pkd;
-          pkd.x = pack_bf16(hv[0], hv[1]);
-          pkd.y = pack_bf16(hv[2], hv[3]);
-          *reinterpret_cast<uint2 *>(hout + (size_t)(c * 32 + (lane & 31)) * hcol + u0 + 8 * q) = pkd;
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-    }
-    }
-    if (fetch_g) reinterpret_cast<float4 *>(gls + (size_t)((k + 1) & 1) * H4)[tid] = gnext;
-    __syncthreads();  // h_t and the next step's biases are in place
-  }
-
-#pragma unroll
-  for (int c = 0; c < CT; ++c) {
-    const float v = vsum[c] + __shfl_xor(vsum[c], 32);
-    if (lane < 32) red[w * NC + c * 32 + lane] = active ? v : 0.0f;
-  }
-  __syncthreads();
-  if (tid < (NC + 63) / 64 * 64) {
-    const bool col = tid < NC;
-    float s = md.hsum[b] + (float)(S - stage) * md.aux[H4 + H];
-#pragma unroll
-    for (int g = 0; g < 8; ++g) s += col ? red[g * NC + tid] : 0.0f;
-    const int32_t cid = col ? okf[tid] - 1 : -1;
-    const bool ok = cid >= 0;
-    if (scores && ok) scores[(size_t)b * ld_scores + cid] = s;
-    if (na.eps != 0.0f) s = add_noise(na, s, b, cid);
-    float v = __builtin_inff();
-    int32_t c = -1;
-    if (ok && s < v) { v = s; c = cid; }
-    wave_min(v, c);
-    if (md.stat) {
-      const int nok = __popcll(__ballot(ok));
-      if (lane == 0) {
-        atomicAdd(&md.stat[0], (unsigned long long)nok);
-        atomicAdd(&md.stat[1], (unsigned long long)nok);
-      }
-    }
-    if (lane == 0) { sv[w] = v; sc[w] = c; }
-  }
-  __syncthreads();
-  if (tid == 0) {
-    float v = sv[0];
-    int32_t c = sc[0];
-    take_min(v, c, sv[1], sc[1]);
-    pval[slot] = v;
-    pidx[slot] = c;
-  }
-}
-
-// The weights of k_seq_step_wide: out[wave][step][row tile][lane][8], steps = k-steps of h of pass 0,
-// of pass 1, then the four k-steps of x of either pass.
+// The weights of k_seq_step_held and k_seq_step_wide: out[32 units][step][row tile][lane][8], steps = k-steps
+// of h of the first 16 units ("pass 0"), of the other 16, then the four k-steps of x of either half; row
+// tile 0 holds gate i of the 16 units in rows 0..15 and gate f in rows 16..31, row tile 1 the gates g and o.
 __global__ __launch_bounds__(256) void k_pack_seq_wide(SeqWeights sw, uint16_t *out) {
   const int H = sw.H, ksh = H / 16, steps = 2 * ksh + 8;
   const int i = blockIdx.x * 256 + threadIdx.x;
@@ -724,6 +477,455 @@ __global__ __launch_bounds__(256) void k_pack_seq_wide(SeqWeights sw, uint16_t *
   const int k = s * 16 + 8 * (lane >> 5) + e;
   const float v = of_x ? sw.Wih[(size_t)(gate * H + unit) * 64 + k] : sw.Whh[(size_t)(gate * H + unit) * H + k];
   out[i] = (uint16_t)bf16_bits(v);
+}
+
+// ---- networks whose recurrent weights fit the registers of one workgroup (H <= 192)
+
+// Opens decision `stage` of problem blockIdx.y for the two scorers below: the ordered list of its valid
+// candidates, their number, and each one's 64 normalised features as a row of bfloat16.  A thread
+// has one candidate: the evaluation runs at full occupancy, and none of its registers is taken from
+// the scorers, which keep their weights there from one tile to the next.  Also: +inf into the masked score
+// array (nullable), no minimum into the parts behind the last tile.  The list comes from the validity
+// rules, not from a scan over the ids (one workgroup per problem, 10 us): 5 us for one problem, 18 for 64.
+__global__ __launch_bounds__(128) void k_seq_open(const uint32_t *decpack, uint32_t M, int64_t Mpad, int32_t *list, int32_t *count,
+                                                  uint16_t *rows, float *scores, float *pval, int32_t *pidx, int nparts,
+                                                  int tile) {
+  __shared__ DecPack pk;
+  __shared__ EvalTabs tabs;
+  __shared__ OpenScratch os;
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int64_t k = (int64_t)blockIdx.x * 128 + tid;  // (Mpad is a multiple of 256)
+  for (int i = tid; i < VF_DECPACK_DWORDS; i += 128) reinterpret_cast<uint32_t *>(&pk)[i] = decpack[(size_t)b * VF_DECPACK_DWORDS + i];
+  if (scores) scores[(size_t)b * Mpad + k] = __builtin_inff();
+  __syncthreads();
+  fill_evaltabs(tabs, pk.d, pk.sp);
+  if (tid >= 119) list_factors(pk, os, tid - 119);
+  __syncthreads();
+  if (tid < 64) list_pairs(pk, os, lane);
+  __syncthreads();
+  const int n = os.ncand;
+  if (blockIdx.x == 0) {
+    if (tid == 0) count[b] = n;
+    for (int i = (n + tile - 1) / tile + tid; i < nparts; i += 128) {
+      pval[(size_t)b * nparts + i] = __builtin_inff();
+      pidx[(size_t)b * nparts + i] = -1;
+    }
+  }
+  if (k >= n) return;
+  int pos_r[12];
+#pragma unroll
+  for (int j = 0; j < 12; ++j) pos_r[j] = j < os.npairs ? os.pos[j] : 0x7fffffff;
+  const Digits g = unpack_digits(list_entry(pk, os, pos_r, (int)k, 1.0f / (float)pk.sp.nperm, 1.0f / (float)pk.sp.nvec));
+  int32_t core[64];
+  eval_digits<true>(pk.d, pk.sp, g, &tabs, core);
+  list[(size_t)b * Mpad + k] = (int32_t)id_of(pk.sp, g);
+  uint4 *dst = reinterpret_cast<uint4 *>(rows + ((size_t)b * Mpad + k) * 64);
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    uint4 o;
+    o.x = pack_bf16(plog2_dev(core[8 * q + 0]), plog2_dev(core[8 * q + 1]));
+    o.y = pack_bf16(plog2_dev(core[8 * q + 2]), plog2_dev(core[8 * q + 3]));
+    o.z = pack_bf16(plog2_dev(core[8 * q + 4]), plog2_dev(core[8 * q + 5]));
+    o.w = pack_bf16(plog2_dev(core[8 * q + 6]), plog2_dev(core[8 * q + 7]));
+    dst[q] = o;
+  }
+}
+
+// A workgroup's share of the tiles of NC list entries of all problems, in problem-major order: tiles
+// [t_begin, t_end), the first one being tile `tile` of problem `b` (every thread of the NW waves gets
+// the same; wsum: NW words of LDS, at: two).  false: no tile.
+template <int NW, int NC>
+__device__ __forceinline__ bool seq_share(const int32_t *count, int B, int tid, int lane, int w, int32_t *wsum, int32_t *at,
+                                          int &t_begin, int &t_end) {
+  constexpr int NT = 64 * NW;
+  const int per = (B + NT - 1) / NT;  // a thread counts `per` consecutive problems
+  int mine = 0;
+  for (int q = 0; q < per; ++q) {
+    const int b = tid * per + q;
+    if (b < B) mine += (count[b] + NC - 1) / NC;
+  }
+  int upto = mine;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int o = __shfl_up(upto, off);
+    if (lane >= off) upto += o;
+  }
+  if (lane == 63) wsum[w] = upto;
+  __syncthreads();
+  int total = 0;
+#pragma unroll
+  for (int q = 0; q < NW; ++q) {
+    if (q == w) upto += total;
+    total += wsum[q];
+  }
+  t_begin = (int)((int64_t)blockIdx.x * total / gridDim.x);
+  t_end = (int)((int64_t)(blockIdx.x + 1) * total / gridDim.x);
+  if (t_begin >= t_end) return false;
+  if (t_begin >= upto - mine && t_begin < upto) {
+    // the thread whose problems hold the first tile
+    int b = tid * per, first = upto - mine;
+    for (;;) {
+      const int n = (count[b] + NC - 1) / NC;
+      if (t_begin < first + n) break;
+      first += n;
+      ++b;
+    }
+    at[0] = b;
+    at[1] = t_begin - first;
+  }
+  return true;
+}
+
+// The end of a tile, by one wave: the head's predictions of the tile's columns (red: [NW][NC], the waves'
+// parts), the scores if they are wanted, the tile's first minimum.
+template <int NW, int NC>
+__device__ __forceinline__ void seq_tile_end(const SeqDev &md, const float *red, float constant, int b, int n0, int nvalid, int lane,
+                                             float *scores, int64_t ld_scores, float *pval, int32_t *pidx, size_t slot,
+                                             const NoiseArgs &na) {
+  const bool ok = lane < NC && n0 + lane < nvalid;
+  const int32_t cid = ok ? md.list[(size_t)b * md.Mpad + n0 + lane] : -1;
+  float s = md.hsum[b] + constant;
+#pragma unroll
+  for (int g = 0; g < NW; ++g) s += red[g * NC + (lane & (NC - 1))];
+  if (scores && ok) scores[(size_t)b * ld_scores + cid] = s;
+  if (na.eps != 0.0f) s = add_noise(na, s, b, cid);
+  float v = __builtin_inff();
+  int32_t c = -1;
+  if (ok && s < v) { v = s; c = cid; }
+  wave_min(v, c);
+  if (md.stat) {
+    const int nok = __popcll(__ballot(ok));
+    if (lane == 0) {
+      atomicAdd(&md.stat[0], (unsigned long long)nok);
+      atomicAdd(&md.stat[1], (unsigned long long)nok);
+    }
+  }
+  if (lane == 0) {
+    pval[slot] = v;
+    pidx[slot] = c;
+  }
+}
+
+// Cell states of a wave's unit tile `u` of 16 at the problem's prefix: a lane has units
+// 8 q + 4 (lane / 32) + e.
+__device__ __forceinline__ void seq_state(float (&cst)[8], const float *cpre, int u, int lane) {
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const float4 cv = *reinterpret_cast<const float4 *>(cpre + u * 16 + 8 * q + 4 * (lane >> 5));
+    cst[4 * q + 0] = cv.x; cst[4 * q + 1] = cv.y; cst[4 * q + 2] = cv.z; cst[4 * q + 3] = cv.w;
+  }
+}
+
+// LDS of k_seq_step_held and k_seq_step_wide: weights, h buffers, gate biases, head, the waves' predictions.
+template <int KS, int NW, int NC, int LK>
+struct SeqHeldLds {
+  static constexpr int H = 16 * KS, HLD = H + 8;
+  uint4 w[KS * LK * 128 + 1];                        // [unit tile][LK][2][64]
+  __attribute__((aligned(16))) uint16_t h[2][NC * HLD];
+  __attribute__((aligned(16))) float g[2][4 * H];    // this step's gate biases and the next one's
+  __attribute__((aligned(16))) float wh[H];
+  float red[NW * NC];
+  int32_t wsum[NW], at[2];
+};
+
+// The candidates that k_seq_open listed, one cell step on their own features and one per later stage,
+// H = 16 KS <= 192 hidden units.  A workgroup holds all of W_hh and goes through its share of the tiles of
+// 32 candidates: wave w has the four gates of units 16 w .. 16 w + 15, RK k-steps of its weights in
+// registers and the others in LDS, so that a step takes nothing from memory but the next step's gate
+// biases.  (Streaming W_hh out of L2 for every step, in tiles of 96 with 32 units per wave, left one wave of
+// eight at work for H = 32, and a wave waits for its fragments longer than it computes.)  What bounds a
+// step now is the vector work of the gates, 28 instructions per cell: a wave by itself issues one
+// every six to seven cycles, so a SIMD wants several - 8, 4 and 2 workgroups per compute unit for H = 32,
+// 64 and 96, each at its own place in a step, so that one's gates run under another's products.
+// Measured per schedule of 64 problems of 20 layers, before and now: H = 32 5.83 -> 1.65 ms, 64 7.07 ->
+// 2.89, 128 7.78 -> 5.04, 192 11.2 -> 6.9; one problem: 1.16 -> 0.70, 1.22 -> 0.75, 1.37 -> 0.96, 2.0 -> 1.24 ms.
+template <int KS, int WPE, int RK>
+__global__ __launch_bounds__(KS * 64, WPE) void k_seq_step_held(SeqDev md, const uint16_t *w_wide, const uint16_t *rows, int stage, int B,
+                                                          float *scores, int64_t ld_scores, float *pval, int32_t *pidx, int nparts,
+                                                          NoiseArgs na) {
+  constexpr int H = 16 * KS, NT = 64 * KS, NC = 32, LK = KS - RK;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  SeqHeldLds<KS, KS, NC, LK> &sh = *reinterpret_cast<SeqHeldLds<KS, KS, NC, LK> *>(smem);
+  constexpr int HLD = H + 8;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int S = md.S;
+  int t_begin, t_end;
+  if (!seq_share<KS, NC>(md.count, B, tid, lane, w, sh.wsum, sh.at, t_begin, t_end)) return;
+
+  const __amdgpu_buffer_rsrc_t ws = stream_rsrc(w_wide);
+  const int voff = 16 * lane, base = (w >> 1) * (2 * KS + 8);
+  const int hfrag = (base + (w & 1) * KS) * 2, xfrag = (base + 2 * KS + 4 * (w & 1)) * 2;
+  uint4 *const wl = sh.w + w * LK * 128 + lane;
+  bf16x8 wr[RK][2];
+#pragma unroll
+  for (int s = 0; s < KS; ++s)
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const uint4 f = stream_load(ws, voff, hfrag + s * 2 + r);
+      if (s < RK) wr[s < RK ? s : 0][r] = __builtin_bit_cast(bf16x8, f);
+      else wl[((s - RK) * 2 + r) * 64] = f;
+    }
+  for (int i = tid; i < H; i += NT) sh.wh[i] = md.aux[4 * H + i];
+  const float bhead = md.aux[5 * H];
+  __syncthreads();
+  int b = __builtin_amdgcn_readfirstlane(sh.at[0]), tile = __builtin_amdgcn_readfirstlane(sh.at[1]);
+  const int u0 = 16 * w + 4 * (lane >> 5);  // the lane's units: u0 + 8 q + e
+
+  for (int t = t_begin; t < t_end; ++t, ++tile) {
+    int nvalid = md.count[b];
+    while (tile * NC >= nvalid) {
+      ++b;
+      tile = 0;
+      nvalid = md.count[b];
+    }
+    const int n0 = tile * NC;
+    // (a ragged tile's last rows are whatever is there: their columns are dropped at the end)
+    const uint4 *xrow = reinterpret_cast<const uint4 *>(rows + ((size_t)b * md.Mpad + n0 + (lane & 31)) * 64) + (lane >> 5);
+    if (tid < H) reinterpret_cast<float4 *>(sh.g[0])[tid] = reinterpret_cast<const float4 *>(md.P + (size_t)b * 4 * H)[tid];
+    float cst[1][8], vsum[1] = {0.0f};
+    seq_state(cst[0], md.cpre + (size_t)b * H, w, lane);
+    __syncthreads();
+    auto step = [&](int st, auto firstc) __attribute__((always_inline)) {
+      constexpr bool first = decltype(firstc)::value;
+      const int k = st - stage;
+      // the next step's biases, fetched now, parked in LDS after this step's gates
+      const bool fetch_g = st + 1 < S && tid < H;
+      float4 gnext = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      if (fetch_g) gnext = reinterpret_cast<const float4 *>(md.G + ((size_t)b * S + st + 1) * 4 * H)[tid];
+      const float *bias = sh.g[k & 1] + u0;
+      floatx16 acc[2][1];
+      if constexpr (first) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          bf16x8 a[2], bv[1];
+#pragma unroll
+          for (int r = 0; r < 2; ++r) a[r] = __builtin_bit_cast(bf16x8, stream_load(ws, voff, xfrag + s * 2 + r));
+          bv[0] = __builtin_bit_cast(bf16x8, xrow[2 * s]);
+          lstm_products<1>(acc, s == 0, bias, H, a, bv);
+          if (s == 1) __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+        const uint16_t *bb = sh.h[k & 1] + (lane & 31) * HLD + 8 * (lane >> 5);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          bf16x8 a[2], bv[1];
+          bv[0] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(bb + s * 16));
+#pragma unroll
+          for (int r = 0; r < 2; ++r) {
+            if (s < RK) a[r] = wr[s < RK ? s : 0][r];
+            else a[r] = __builtin_bit_cast(bf16x8, wl[((s - RK) * 2 + r) * 64]);
+          }
+          lstm_products<1>(acc, s == 0, bias, H, a, bv);
+        }
+      }
+      lstm_gates<1>(acc, cst, vsum, sh.wh + u0, sh.h[(k + 1) & 1] + (lane & 31) * HLD + u0, 0);
+      if (fetch_g) reinterpret_cast<float4 *>(sh.g[(k + 1) & 1])[tid] = gnext;
+      __syncthreads();  // h and the next step's biases are in place
+    };
+    step(stage, vf_tag<true>{});
+    for (int st = stage + 1; st < S; ++st) step(st, vf_tag<false>{});
+
+    vsum[0] += __shfl_xor(vsum[0], 32);
+    if (lane < 32) sh.red[w * NC + lane] = vsum[0];
+    __syncthreads();
+    if (w == 0)
+      seq_tile_end<KS, NC>(md, sh.red, (float)(S - stage) * bhead, b, n0, nvalid, lane, scores, ld_scores, pval, pidx,
+                           (size_t)b * nparts + tile, na);
+    // (red is written again behind the next tile's first barrier; g[0] and the h buffers were last read in
+    // front of the barrier that ended the last step)
+  }
+}
+
+// The same for H = 224 and 256: W_hh (401 and 512 KB) is more than a compute unit holds.  A wave has 32
+// units in two passes of 16; of a pass's KS k-steps RK stay in registers, LK in LDS, the others stream
+// out of L2 through a ring of two, spread evenly between them.  Tiles are of 32 candidates (CT = 1) or, where
+// there are enough of them, 64: the stream then serves twice as many.  On its SIMD a wave of the first
+// four (group A) shares the vector unit and the matrix core with one of the others (group B), and a
+// step has four phases with a barrier behind each, in which one has its products while the other has
+// its gates:
+//   A: rest of products 0, gates 0 | products 1 | gates 1    | next step's products 0 as far as h is there
+//   B: products 0                  | gates 0    | products 1 | gates 1
+// (A's last phase leaves out the units that B's last gates are about to write.)  What bounds it: a phase
+// is as long as its gates, which take a single wave 1700 cycles for 8 x 64 cells with products beside
+// them, where the products take 1000 to 1400; without the phases both waves contract at the same time
+// and the second one does its gates alone (+3 %).  Holding more of the weights or more waves in flight
+// both want the registers of the other.  64 problems of 20 layers, H = 256: 17.4 -> 15.5 ms (tiles of 96, all
+// weights streamed), 8: 3.48 -> 2.85, one: 2.24 -> 1.55.
+template <int KS, int CT, int RK, int LK>
+struct SeqWidePlan {
+  static constexpr int NW = KS / 2, SK = KS - RK - LK;
+  static constexpr int LATE = NW - 4;  // unit tiles that are written last: pass 1 of waves 4..
+  // the order of the k-steps (unit tiles): those tiles last
+  static constexpr int order(int i) {
+    return i < KS - LATE ? (i < 8 ? i : 8 + 2 * (i - 8)) : 9 + 2 * (i - (KS - LATE));
+  }
+  static constexpr bool streamed(int i) { return (i + 1) * SK / KS > i * SK / KS; }
+  static constexpr int stream_index(int i) { return i * SK / KS; }      // of a streamed place in the order
+  static constexpr int held_index(int i) { return i - i * SK / KS; }    // of any other: < RK registers, else LDS
+  static constexpr int stream_step(int j) { return order(((j + 1) * KS + SK - 1) / SK - 1); }
+};
+template <int KS, int CT, int RK, int LK>
+__global__ __launch_bounds__(KS * 32, 2) void k_seq_step_wide(SeqDev md, const uint16_t *w_wide, const uint16_t *rows, int stage, int B,
+                                                         float *scores, int64_t ld_scores, float *pval, int32_t *pidx, int nparts,
+                                                         NoiseArgs na) {
+  using Plan = SeqWidePlan<KS, CT, RK, LK>;
+  constexpr int H = 16 * KS, NW = Plan::NW, NT = 64 * NW, NC = 32 * CT, SK = Plan::SK, PD = 2, HLD = H + 8;
+  static_assert(NW > 4 && NW <= 8 && SK >= PD, "two groups of waves, a stream");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  SeqHeldLds<KS, NW, NC, LK> &sh = *reinterpret_cast<SeqHeldLds<KS, NW, NC, LK> *>(smem);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int S = md.S;
+  int t_begin, t_end;
+  if (!seq_share<NW, NC>(md.count, B, tid, lane, w, sh.wsum, sh.at, t_begin, t_end)) return;
+
+  const __amdgpu_buffer_rsrc_t ws = stream_rsrc(w_wide);
+  const int voff = 16 * lane, hfrag = w * (2 * KS + 8) * 2, xfrag = hfrag + 4 * KS;  // (pass 1: KS, or 4, k-steps on)
+  uint4 *const wl = sh.w + w * 2 * LK * 128 + lane;
+  bf16x8 wr[2][RK][2], ring[PD][2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+#pragma unroll
+    for (int i = 0; i < KS; ++i)
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        if (Plan::streamed(i)) continue;
+        const uint4 f = stream_load(ws, voff, hfrag + (p * KS + Plan::order(i)) * 2 + r);
+        const int at = Plan::held_index(i);
+        if (at < RK) wr[p][at < RK ? at : 0][r] = __builtin_bit_cast(bf16x8, f);
+        else wl[((p * LK + at - RK) * 2 + r) * 64] = f;
+      }
+#pragma unroll
+  for (int j = 0; j < PD; ++j)
+#pragma unroll
+    for (int r = 0; r < 2; ++r) ring[j][r] = __builtin_bit_cast(bf16x8, stream_load(ws, voff, hfrag + Plan::stream_step(j) * 2 + r));
+  for (int i = tid; i < H; i += NT) sh.wh[i] = md.aux[4 * H + i];
+  const float bhead = md.aux[5 * H];
+  __syncthreads();
+  int b = __builtin_amdgcn_readfirstlane(sh.at[0]), tile = __builtin_amdgcn_readfirstlane(sh.at[1]);
+
+  for (int t = t_begin; t < t_end; ++t, ++tile) {
+    int nvalid = md.count[b];
+    while (tile * NC >= nvalid) {
+      ++b;
+      tile = 0;
+      nvalid = md.count[b];
+    }
+    const int n0 = tile * NC;
+    // (a ragged tile's last rows are whatever is there: their columns are dropped at the end)
+    const uint4 *xrow = reinterpret_cast<const uint4 *>(rows + ((size_t)b * md.Mpad + n0 + (lane & 31)) * 64) + (lane >> 5);
+    if (tid < H) reinterpret_cast<float4 *>(sh.g[0])[tid] = reinterpret_cast<const float4 *>(md.P + (size_t)b * 4 * H)[tid];
+    float cst[2][CT][8], vsum[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      vsum[c] = 0.0f;
+      seq_state(cst[0][c], md.cpre + (size_t)b * H, 2 * w, lane);
+      seq_state(cst[1][c], md.cpre + (size_t)b * H, 2 * w + 1, lane);
+    }
+    __syncthreads();
+
+    floatx16 acc[2][CT];
+    // products of pass p of the tile's first step: the candidates' own features
+    auto products_x = [&](int p) __attribute__((always_inline)) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        bf16x8 a[2], bv[CT];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) a[r] = __builtin_bit_cast(bf16x8, stream_load(ws, voff, xfrag + (4 * p + s) * 2 + r));
+#pragma unroll
+        for (int c = 0; c < CT; ++c) bv[c] = __builtin_bit_cast(bf16x8, xrow[c * 32 * 8 + 2 * s]);
+        lstm_products<CT>(acc, s == 0, sh.g[0] + 32 * w + 16 * p + 4 * (lane >> 5), H, a, bv);
+        if (s & 1) __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    // products of pass p of step k, places [i0, i1) of the order
+    auto products_h = [&](int p, int k, int i0, int i1) __attribute__((always_inline)) {
+      const uint16_t *bb = sh.h[k & 1] + (lane & 31) * HLD + 8 * (lane >> 5);
+      const float *bias = sh.g[k & 1] + 32 * w + 16 * p + 4 * (lane >> 5);
+      bf16x8 bv[CT], al[2];  // a place's activations, and its weights where they come from LDS
+      auto fetch = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+          bv[c] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(bb + c * 32 * HLD + Plan::order(i) * 16));
+        if (!Plan::streamed(i) && Plan::held_index(i) >= RK) {
+#pragma unroll
+          for (int r = 0; r < 2; ++r) al[r] = __builtin_bit_cast(bf16x8, wl[((p * LK + Plan::held_index(i) - RK) * 2 + r) * 64]);
+        }
+      };
+      fetch(i0);
+#pragma unroll
+      for (int i = i0; i < i1; ++i) {
+        bf16x8 a[2], bc[CT];
+        const int j = Plan::stream_index(i), at = Plan::held_index(i), slot = (p * SK + j) % PD;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+          if (Plan::streamed(i)) a[r] = ring[slot][r];
+          else if (at < RK) a[r] = wr[p][at < RK ? at : 0][r];
+          else a[r] = al[r];
+        }
+#pragma unroll
+        for (int c = 0; c < CT; ++c) bc[c] = bv[c];
+        if (i + 1 < i1) fetch(i + 1);  // (under this place's products)
+        __builtin_amdgcn_sched_barrier(0);
+        lstm_products<CT>(acc, i == 0, bias, H, a, bc);
+        if (Plan::streamed(i)) {
+          // the slot takes the streamed place PD further on: of this pass, or of the other one
+          const int n = j + PD;
+          const int step = n < SK ? p * KS + Plan::stream_step(n < SK ? n : 0) : (p ^ 1) * KS + Plan::stream_step(n < SK ? 0 : n - SK);
+#pragma unroll
+          for (int r = 0; r < 2; ++r) ring[slot][r] = __builtin_bit_cast(bf16x8, stream_load(ws, voff, hfrag + step * 2 + r));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    auto gates = [&](int p, int k) __attribute__((always_inline)) {
+      const int u0 = 32 * w + 16 * p + 4 * (lane >> 5);
+      lstm_gates<CT>(acc, cst[p], vsum, sh.wh + u0, sh.h[(k + 1) & 1] + (lane & 31) * HLD + u0, 32 * HLD);
+    };
+    if (w < 4) {
+      products_x(0);
+      for (int k = 0; k < S - stage; ++k) {
+        // the next step's biases (a float4 per thread of this group), fetched now, parked in LDS behind the gates
+        const bool more = k + 1 < S - stage, fetch_g = more && tid < H;
+        float4 gnext = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (fetch_g) gnext = reinterpret_cast<const float4 *>(md.G + ((size_t)b * S + stage + k + 1) * 4 * H)[tid];
+        if (k > 0) products_h(0, k, KS - Plan::LATE, KS);
+        gates(0, k);
+        __syncthreads();
+        if (k > 0) products_h(1, k, 0, KS);
+        else products_x(1);
+        __syncthreads();
+        gates(1, k);
+        if (fetch_g) reinterpret_cast<float4 *>(sh.g[(k + 1) & 1])[tid] = gnext;
+        __syncthreads();
+        if (more) products_h(0, k + 1, 0, KS - Plan::LATE);
+        __syncthreads();
+      }
+    } else {
+      for (int k = 0; k < S - stage; ++k) {
+        if (k > 0) products_h(0, k, 0, KS);
+        else products_x(0);
+        __syncthreads();
+        gates(0, k);
+        __syncthreads();
+        if (k > 0) products_h(1, k, 0, KS);
+        else products_x(1);
+        __syncthreads();
+        gates(1, k);
+        __syncthreads();
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      const float v = vsum[c] + __shfl_xor(vsum[c], 32);
+      if (lane < 32) sh.red[w * NC + c * 32 + lane] = v;
+    }
+    __syncthreads();
+    if (w == 0)
+      seq_tile_end<NW, NC>(md, sh.red, (float)(S - stage) * bhead, b, n0, nvalid, lane, scores, ld_scores, pval, pidx,
+                           (size_t)b * nparts + tile, na);
+  }
 }
 
 SeqWeights weights_of(const vf_ctx *c) {
@@ -754,15 +956,46 @@ bool vfk_seq_model(const vf_ctx *c) {
 
 void vfk_seq_free(vf_ctx *c) {
   void *ps[] = {c->d_seq_G, c->d_seq_h[0], c->d_seq_h[1], c->d_seq_c[0], c->d_seq_c[1],
-                c->d_seq_P[0], c->d_seq_P[1], c->d_seq_hs[0], c->d_seq_hs[1], c->d_seq_list, c->d_seq_count};
+                c->d_seq_P[0], c->d_seq_P[1], c->d_seq_hs[0], c->d_seq_hs[1], c->d_seq_list, c->d_seq_count, c->d_seq_rows};
   for (void *p : ps)
     if (p) (void)hipFree(p);
   c->d_seq_G = nullptr;
   c->d_seq_list = nullptr;
   c->d_seq_count = nullptr;
+  c->d_seq_rows = nullptr;
   for (int k = 0; k < 2; ++k) c->d_seq_h[k] = c->d_seq_c[k] = c->d_seq_P[k] = c->d_seq_hs[k] = nullptr;
   c->seq_stage = -1;
   c->seq_cur = 0;
+}
+
+// The scorer for networks of H hidden units: its workgroups per compute unit, threads, LDS, candidates
+// per tile.  many: more than about one round of tiles.  At H = 128 two workgroups of 128 registers then
+// are better than one of all (64 problems 5.66 -> 5.04 ms; 8: 1.30 against 1.39), above 192 tiles of 64
+// (H = 256: 64 problems 16.8 -> 15.5 ms; 8: 2.84 against 2.98).
+struct HeldKernel {
+  void (*fn)(SeqDev, const uint16_t *, const uint16_t *, int, int, float *, int64_t, float *, int32_t *, int, NoiseArgs);
+  int per_cu, threads, tile;
+  size_t lds;
+};
+template <int KS, int WPE, int RK>
+static HeldKernel held_kernel(int per_cu) {
+  return {k_seq_step_held<KS, WPE, RK>, per_cu, KS * 64, 32, sizeof(SeqHeldLds<KS, KS, 32, KS - RK>)};
+}
+template <int KS, int CT, int RK, int LK>
+static HeldKernel wide_kernel() {
+  return {k_seq_step_wide<KS, CT, RK, LK>, 1, KS * 32, 32 * CT, sizeof(SeqHeldLds<KS, KS / 2, 32 * CT, LK>)};
+}
+static HeldKernel held_kernel_of(int H, bool many) {
+  switch (H / 32) {
+    case 1: return held_kernel<2, 4, 2>(8);
+    case 2: return held_kernel<4, 4, 4>(4);
+    case 3: return held_kernel<6, 3, 6>(2);
+    case 4: return many ? held_kernel<8, 4, 5>(2) : held_kernel<8, 2, 8>(1);
+    case 5: return held_kernel<10, 3, 8>(1);
+    case 6: return held_kernel<12, 3, 9>(1);
+    case 7: return many ? wide_kernel<14, 2, 1, 3>() : wide_kernel<14, 1, 5, 4>();
+    default: return many ? wide_kernel<16, 2, 1, 2>() : wide_kernel<16, 1, 5, 3>();
+  }
 }
 
 // Tables and prefix state of the recurrence for the context's pipeline, model and
@@ -786,6 +1019,10 @@ int vfk_seq_sync(vf_ctx *c, int stage) {
       (void)hipGetLastError();
       vfk_seq_free(c);
       return VF_ENOMEM;
+    }
+    if (hipMalloc((void **)&c->d_seq_rows, (size_t)B * c->Mpad * 64 * sizeof(uint16_t)) != hipSuccess) {
+      (void)hipGetLastError();  // (without memory for the rows the scorers below evaluate the candidates themselves)
+      c->d_seq_rows = nullptr;
     }
     const size_t n = (size_t)B * S * 4 * H;
     hipLaunchKernelGGL(k_seq_tables, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, c->d_intr, sw,
@@ -864,13 +1101,12 @@ int vfk_seq_step(vf_ctx *c, int stage, float *scores, int64_t ld_scores, int noi
   rc = vfk_prepare(c, stage);
   if (rc != VF_OK) return rc;
   const int H = c->model.dims[1];
-  // Tiles of 96 where tiles of 64 would be more than about one round of the compute units (a third
-  // of the ids is valid, as a rule): 8 problems of 4096 ids 3.1 against 3.4 ms or 1.3 against 1.1, 12: 4.7
-  // against 4.4 or 1.3 against 1.6, 16: 5.0 against 5.6, 64: 17.0 against 19.4; 1 problem: 2.9 against 2.2.
   int ncu = 256;
   (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
-  const bool wide = c->pm.w_seq_wide && (c->M + 63) / 64 * c->B >= 3 * (int64_t)ncu;
-  const int NC = wide ? SEQ_WIDE : 64;
+  // (a third of the ids is valid, as a rule: three rounds of ids in tiles of 64)
+  const HeldKernel hk = held_kernel_of(H, (c->M + 63) / 64 * c->B >= 3 * (int64_t)ncu);
+  const bool held = c->pm.w_seq_wide && c->d_seq_rows;
+  const int NC = held ? hk.tile : 64;
   const int nparts = (int)((c->M + NC - 1) / NC);
   rc = vfk_ensure_parts(c, (size_t)nparts * c->B);
   if (rc != VF_OK) return rc;
@@ -881,34 +1117,38 @@ int vfk_seq_step(vf_ctx *c, int stage, float *scores, int64_t ld_scores, int noi
   md.decpack = c->d_decpack;
   md.list = c->d_seq_list; md.count = c->d_seq_count; md.Mpad = c->Mpad;
   md.stat = c->profiling ? c->d_stat : nullptr;
-  hipLaunchKernelGGL(k_seq_compact, dim3((unsigned)c->B), dim3(1024), 0, c->stream, c->d_decpack, (uint32_t)c->M,
-                     (int64_t)c->Mpad, c->d_seq_list, c->d_seq_count, scores);
-  VF_HIP(c, hipGetLastError());
   NoiseArgs na;
   na.eps = noise_stage >= 0 ? c->noise_eps : 0.0f;
   na.k0 = (uint32_t)c->noise_seed; na.k1 = (uint32_t)(c->noise_seed >> 32);
   na.stage = noise_stage; na.first_rollout = c->noise_first;
+  *nparts_out = nparts;
+  if (held) {
+    hipLaunchKernelGGL(k_seq_open, dim3((unsigned)(c->Mpad / 128), (unsigned)c->B), dim3(128), 0, c->stream, c->d_decpack,
+                       (uint32_t)c->M, (int64_t)c->Mpad, c->d_seq_list, c->d_seq_count, c->d_seq_rows, scores, c->d_pval,
+                       c->d_pidx, nparts, hk.tile);
+    VF_HIP(c, hipGetLastError());
+    vf_prof_scope prof(c, VF_PROF_SCORE);
+    VF_HIP(c, hipFuncSetAttribute((const void *)hk.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)hk.lds));
+    const int64_t most = (int64_t)nparts * c->B, fit = (int64_t)hk.per_cu * ncu;
+    hipLaunchKernelGGL(hk.fn, dim3((unsigned)(most < fit ? most : fit)), dim3(hk.threads), hk.lds, c->stream, md,
+                       (const uint16_t *)c->pm.w_seq_wide, (const uint16_t *)c->d_seq_rows, stage, c->B, scores, ld_scores,
+                       c->d_pval, c->d_pidx, nparts, na);
+    VF_HIP(c, hipGetLastError());
+    return VF_OK;
+  }
+  hipLaunchKernelGGL(k_seq_compact, dim3((unsigned)c->B), dim3(1024), 0, c->stream, c->d_decpack, (uint32_t)c->M,
+                     (int64_t)c->Mpad, c->d_seq_list, c->d_seq_count, scores);
+  VF_HIP(c, hipGetLastError());
   const int hld = H + 8;
   const size_t smem = (size_t)NC * 72 * 2 + (size_t)2 * NC * hld * 2 + (size_t)2 * 4 * H * 4 + (size_t)8 * NC * 4 +
                       (size_t)H * 4 + (size_t)2 * NC * 4;
   {
     vf_prof_scope prof(c, VF_PROF_SCORE);
-    if (wide) {
-      const int hcol = hld < 72 ? 72 : hld;
-      const size_t lds = (size_t)2 * NC * hcol * 2 + (size_t)2 * 4 * H * 4 + (size_t)8 * NC * 4 + (size_t)H * 4 + (size_t)NC * 4;
-      VF_HIP(c, hipFuncSetAttribute((const void *)k_seq_step_wide<2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-      hipLaunchKernelGGL(k_seq_step_wide<2>, dim3((unsigned)nparts, (unsigned)c->B), dim3(512), lds, c->stream, md,
-                         (const uint16_t *)c->pm.w_seq_wide, stage, scores, ld_scores, c->d_pval, c->d_pidx, na);
-      VF_HIP(c, hipGetLastError());
-      *nparts_out = nparts;
-      return VF_OK;
-    }
     void (*kern)(SeqDev, int, int64_t, float *, int64_t, float *, int32_t *, NoiseArgs) = k_seq_step<64, 2>;
     VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
     hipLaunchKernelGGL(kern, dim3((unsigned)nparts, (unsigned)c->B), dim3(512), smem, c->stream, md, stage, c->M,
                        scores, ld_scores, c->d_pval, c->d_pidx, na);
     VF_HIP(c, hipGetLastError());
   }
-  *nparts_out = nparts;
   return VF_OK;
 }

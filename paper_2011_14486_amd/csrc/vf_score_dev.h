@@ -85,12 +85,67 @@ __device__ __forceinline__ float sig_tanh(float a, float b) {
   const float e = __builtin_amdgcn_exp2f(__builtin_fabsf(b) * (-2.0f * LOG2E)) + 0x1p-60f;
   return __builtin_copysignf(1.0f - e, b) * __builtin_amdgcn_rcpf(fmaf(e, u, u));
 }
-__device__ __forceinline__ float lstm_cell(float ai, float af, float ag, float ao, float &c) {
+__device__ __forceinline__ float lstm_cell_state(float ai, float af, float ag, float c) {
   constexpr float LOG2E = 1.44269504088896340736f;
   const float fg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(af * -LOG2E));
-  const float cn = fmaf(fg, c, sig_tanh(ai, ag));
-  c = cn;
-  return sig_tanh(ao, cn);
+  return fmaf(fg, c, sig_tanh(ai, ag));
+}
+__device__ __forceinline__ float lstm_cell(float ai, float af, float ag, float ao, float &c) {
+  c = lstm_cell_state(ai, af, ag, c);
+  return sig_tanh(ao, c);
+}
+
+// The products of one k-step with a unit tile's two fragments of 32 gate rows (row tile 0: gates i and f of
+// the 16 units, row tile 1: g and o).  start: the accumulators come out as product + bias (bias: the
+// lane's first unit of gate i, gates H apart).
+template <int CT>
+__device__ __forceinline__ void lstm_products(floatx16 (&acc)[2][CT], bool start, const float *bias, int H, const bf16x8 (&a)[2],
+                                             const bf16x8 (&bv)[CT]) {
+  if (start) {
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      floatx16 bg;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 v = *reinterpret_cast<const float4 *>(bias + (2 * r + (g >> 1)) * H + 8 * (g & 1));
+        bg[4 * g + 0] = v.x; bg[4 * g + 1] = v.y; bg[4 * g + 2] = v.z; bg[4 * g + 3] = v.w;
+      }
+#pragma unroll
+      for (int c = 0; c < CT; ++c) acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[r], bv[c], bg, 0, 0, 0);
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+      for (int r = 0; r < 2; ++r) acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[r], bv[c], acc[r][c], 0, 0, 0);
+  }
+}
+
+// The gates of a unit tile: cells and predictions advance, h goes to LDS (hout: the lane's column
+// and first unit, column tiles cstride elements apart; whs: the head's weights from the lane's first unit).
+template <int CT>
+__device__ __forceinline__ void lstm_gates(const floatx16 (&acc)[2][CT], float (&cst)[CT][8], float (&vsum)[CT], const float *whs,
+                                          uint16_t *hout, int cstride) {
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const float4 whv = *reinterpret_cast<const float4 *>(whs + 8 * q);
+    const float whq[4] = {whv.x, whv.y, whv.z, whv.w};
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      float hv[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = 4 * q + e;
+        hv[e] = lstm_cell(acc[0][c][j], acc[0][c][8 + j], acc[1][c][j], acc[1][c][8 + j], cst[c][j]);
+        vsum[c] = fmaf(whq[e], hv[e], vsum[c]);
+      }
+      uint2 pkd;
+      pkd.x = pack_bf16(hv[0], hv[1]);
+      pkd.y = pack_bf16(hv[2], hv[3]);
+      *reinterpret_cast<uint2 *>(hout + c * cstride + 8 * q) = pkd;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
 }
 
 // ---- pieces of the fused bf16 MLP that the per-layer scorer and the whole-schedule kernel share

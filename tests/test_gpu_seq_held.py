@@ -1,0 +1,54 @@
+"""GPU parity of the recurrent search at every width that the network can have: the forms that hold the
+recurrent weights in registers and LDS (one, two or several workgroups per compute unit, with and without
+a stream for what does not fit), tiles of 32 and of 64 candidates, lists that end inside and at the end of a
+tile, problems without candidates in between."""
+import numpy as np
+import pytest
+
+from paper_2011_14486_amd import inputs as I
+from tests.test_gpu_lstm_search import compare_schedule, setup
+from tests.util import TOL
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def vf():
+    import paper_2011_14486_amd as pkg
+    return pkg.load()
+
+
+@pytest.mark.parametrize("H", range(32, 257, 32))
+def test_every_width(vf, ovf, H):
+    """One problem (tiles of 32) and 70 (768 tiles of 64 ids or more: the forms for throughput) of
+    different lists: ids, values and states of the batch are those of single problems, bit for bit, and the
+    checker's (the same tolerance as everywhere for bf16)."""
+    sp = I.make_space([1, 2, 4], [1, 3, 4], [1, 2, 8], I.ALL_PERMS[:2], 2, 2, [I.ROOT, I.L1, I.L2, I.INLINE], 2, 64)
+    B = 70
+    assert (I.space_dense_count(sp) + 63) // 64 * B >= 3 * 256
+    pipes = np.stack([I.random_pipeline(4, 60 + b % 9) for b in range(B)])
+    ctx, model, w = setup(vf, pipes, sp, H)
+    st, cids, vals = [t.cpu().numpy() for t in vf.vf_greedy_schedule(ctx)]
+    vf.vf_destroy(ctx)
+    for b in (0, 4, 8):
+        compare_schedule(ovf, pipes[b], sp, model, w, cids[b], vals[b], st[b], TOL[1])
+    for b in range(9):
+        one, _, _ = setup(vf, pipes[b], sp, H)
+        s1, c1, v1 = [t.cpu().numpy()[0] for t in vf.vf_greedy_schedule(one)]
+        vf.vf_destroy(one)
+        for k in range(b, B, 9):
+            assert np.array_equal(c1, cids[k]) and np.array_equal(v1, vals[k]) and np.array_equal(s1, st[k])
+
+
+@pytest.mark.parametrize("H", [32, 128, 192, 256])
+@pytest.mark.parametrize("fx,fy,fc", [([1], [1], [1]), ([1, 2, 4, 8], [1, 2, 4, 8], [1, 2]), ([1, 2, 4], [1, 2, 3, 4], [1, 2, 4]),
+                                      ([1, 2, 4, 8], [1, 2, 4, 8], [1, 2, 3, 4]), ([1, 2, 3, 4, 5], [1, 2, 3, 4, 5], [1, 2, 3])])
+def test_ends_of_tiles(vf, ovf, H, fx, fy, fc):
+    """Lists of 1, 32, 36, 64 and 75 entries."""
+    sp = I.make_space(fx, fy, fc, I.ALL_PERMS[:1], 1, 1, [I.ROOT], 1, 64)
+    pipe = I.random_pipeline(3, 13)
+    assert (pipe[:, 1:4] >= [max(fx), max(fy), max(fc)]).all()  # (every candidate is valid)
+    ctx, model, w = setup(vf, pipe, sp, H)
+    st, cids, vals = [t.cpu().numpy()[0] for t in vf.vf_greedy_schedule(ctx)]
+    vf.vf_destroy(ctx)
+    compare_schedule(ovf, pipe, sp, model, w, cids, vals, st, TOL[1])
