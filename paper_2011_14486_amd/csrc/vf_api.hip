@@ -410,8 +410,7 @@ static int score_call(vf_ctx *c, const void *x, int32_t x_kind, int64_t M, int64
     rc = vfk_score_mlp(c, (const int32_t *)x, 0, 1, M, ld, 0, scores, ld, &nparts, -1, parts, &part);
   } else if (x_kind == VF_X_SEQ_BF16) {
     if (c->model.kind != VF_LSTM || ld < 0 || ld > (1 << 20)) return VF_EINVAL;
-    rc = vfk_score_lstm(c, (const uint16_t *)x, M, (int)ld, scores, &nparts, parts);
-    part = 64;
+    rc = vfk_score_lstm(c, (const uint16_t *)x, M, (int)ld, scores, &nparts, parts, &part);
   } else {
     return VF_EINVAL;
   }

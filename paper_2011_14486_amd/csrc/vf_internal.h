@@ -292,8 +292,8 @@ void vfk_beam_swap(vf_ctx *c);
 // whether a beam search works on lists of valid candidates, and all its layers (vf_beam.hip)
 bool vfk_beam_lists(const vf_ctx *c);
 int vfk_beam_layers(vf_ctx *c, int first, int last);
-int vfk_score_lstm(vf_ctx *c, const uint16_t *x, int64_t M, int T, float *scores, int *nparts_out,
-                   const vf_partbuf *parts = nullptr);
+int vfk_score_lstm(vf_ctx *c, const uint16_t *x, int64_t M, int T, float *scores, int *nparts_out, const vf_partbuf *parts,
+                   int *part_out);
 int vfk_argmin_groups(vf_ctx *c, int64_t M, int nparts, int parts_per_group, int ngroups,
                       int32_t *best_idx, float *best_val, const vf_partbuf *parts = nullptr);
 // The static scratch array of vf_score_static on the current device (looked up once per

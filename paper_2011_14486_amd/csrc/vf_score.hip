@@ -991,6 +991,143 @@ __global__ __launch_bounds__(512) void k_lstm_bf16(const uint16_t *x, int64_t M,
   }
 }
 
+// LDS of k_lstm_held: weights, two steps' inputs, two steps' h, gate biases, head, the waves' predictions.
+constexpr int LSTM_HELD = 32;  // sequences per tile
+template <int KSX, int KSH, int LK>
+struct LstmHeldLds {
+  static constexpr int H = 16 * KSH, XLD = 16 * KSX + 8, HLD = H + 8;
+  uint4 w[KSH * LK * 128 + 1];                                  // [wave][LK][2][64]
+  __attribute__((aligned(16))) uint16_t x[2][LSTM_HELD * XLD];
+  __attribute__((aligned(16))) uint16_t h[2][LSTM_HELD * HLD];
+  __attribute__((aligned(16))) float bias[4 * H];
+  __attribute__((aligned(16))) float wh[H];
+  float red[KSH * LSTM_HELD];
+};
+
+// The same for networks whose weights a workgroup can hold (F = 16 KSX inputs, H = 16 KSH units): wave w has
+// the four gates of units 16 w .. 16 w + 15, its k-steps of x and of h - RK of them in registers, the
+// others in LDS -, and the workgroup goes through tiles of 32 sequences, `span` consecutive ones per
+// minimum.  A step takes nothing from memory but the inputs of the step after next.  k_lstm_bf16 streams the
+// weights out of L2 for every step and has 32 units per wave, so that of its eight waves one, two, ... are
+// at work for H = 32, 64, ...  What is left of a step is the chain of its products, its gates and the
+// barrier (0.9 us at H = 32, 2 at 128).  Before and now, T = 50, 64 sequences, F = 32: H = 32 155 -> 50 us, 64
+// 170 -> 55, 128 197 -> 87, 192 334 -> 133; F = 128: H = 32 200 -> 68, 128 245 -> 103; T = 25, 16,384 sequences,
+// F = 128: H = 32 114 -> 50 us, 64 125 -> 53, 96 136 -> 103, 128 147 -> 119; F = 32, H = 192 181 -> 148.
+template <int KSX, int KSH, int WPE, int RK>
+__global__ __launch_bounds__(KSH * 64, WPE) void k_lstm_held(const uint16_t *x, int64_t M, int T, LstmDev md, int span, float *scores,
+                                                            float *pval, int32_t *pidx) {
+  constexpr int F = 16 * KSX, H = 16 * KSH, NT = 64 * KSH, KS = KSX + KSH, LK = KS - RK, NC = LSTM_HELD;
+  constexpr int XLD = F + 8, HLD = H + 8, CPR = F / 8, CH = NC * CPR, XPT = (CH + NT - 1) / NT;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  LstmHeldLds<KSX, KSH, LK> &sh = *reinterpret_cast<LstmHeldLds<KSX, KSH, LK> *>(smem);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  // fragments of 32 gate rows x 16 inputs (row tile 0: gates i, f of the wave's 16 units, row tile 1: g, o) out
+  // of the packed matrix, whose fragments hold one gate of 32 units
+  const __amdgpu_buffer_rsrc_t ws = stream_rsrc(md.w_pack);
+  const int voff = 16 * (((lane >> 4) & 1) * 64 + (lane & 32) + 16 * (w & 1) + (lane & 15));
+  uint4 *const wl = sh.w + w * LK * 128 + lane;
+  bf16x8 wr[RK][2];
+#pragma unroll
+  for (int s = 0; s < KS; ++s)
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const uint4 f = stream_load(ws, voff, ((w >> 1) * KS + s) * 4 + 2 * r);
+      if (s < RK) wr[s < RK ? s : 0][r] = __builtin_bit_cast(bf16x8, f);
+      else wl[((s - RK) * 2 + r) * 64] = f;
+    }
+  for (int i = tid; i < 4 * H; i += NT) sh.bias[i] = md.aux[i];
+  for (int i = tid; i < H; i += NT) sh.wh[i] = md.aux[4 * H + i];
+  const float bhead = md.aux[5 * H];
+  const int u0 = 16 * w + 4 * (lane >> 5);  // the lane's units: u0 + 8 q + e
+  const int ntiles = (int)((M + NC - 1) / NC), nparts = (ntiles + span - 1) / span;
+  auto weights = [&](int s, bf16x8 (&a)[2]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      if (s < RK) a[r] = wr[s < RK ? s : 0][r];
+      else a[r] = __builtin_bit_cast(bf16x8, wl[((s - RK) * 2 + r) * 64]);
+    }
+  };
+
+  for (int part = (int)blockIdx.x; part < nparts; part += (int)gridDim.x) {
+    float best = __builtin_inff();
+    int32_t best_at = -1;
+    for (int tile = part * span; tile < ntiles && tile < (part + 1) * span; ++tile) {
+      const int64_t n0 = (int64_t)tile * NC;
+      uint4 xr[XPT];
+      auto fetch = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < XPT; ++q) {
+          const int ch = tid + q * NT, n = ch / CPR, kc = ch % CPR;
+          xr[q] = make_uint4(0u, 0u, 0u, 0u);
+          if (ch < CH && t < T && n0 + n < M) xr[q] = *reinterpret_cast<const uint4 *>(x + ((size_t)(n0 + n) * T + t) * F + kc * 8);
+        }
+      };
+      auto stash = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < XPT; ++q) {
+          const int ch = tid + q * NT, n = ch / CPR, kc = ch % CPR;
+          if (ch < CH) *reinterpret_cast<uint4 *>(sh.x[buf] + n * XLD + kc * 8) = xr[q];
+        }
+      };
+      fetch(0);
+      for (int i = tid; i < NC * HLD / 2; i += NT) reinterpret_cast<uint32_t *>(sh.h[0])[i] = 0u;
+      stash(0);
+      fetch(1);
+      float cst[1][8], vsum[1] = {0.0f};
+#pragma unroll
+      for (int j = 0; j < 8; ++j) cst[0][j] = 0.0f;
+      __syncthreads();
+      const int row = lane & 31, k8 = 8 * (lane >> 5);
+      for (int t = 0; t < T; ++t) {
+        // x_{t+1} (fetched during the step before) goes to the buffer last read at t - 1
+        stash((t + 1) & 1);
+        fetch(t + 2);
+        floatx16 acc[2][1];
+#pragma unroll
+        for (int s = 0; s < KSX; ++s) {
+          bf16x8 a[2], bv[1];
+          bv[0] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(sh.x[t & 1] + row * XLD + k8 + s * 16));
+          weights(s, a);
+          lstm_products<1>(acc, s == 0, sh.bias + u0, H, a, bv);
+        }
+        __syncthreads();  // h_{t-1} is complete; x_{t+1} is visible for the next step
+#pragma unroll
+        for (int s = 0; s < KSH; ++s) {
+          bf16x8 a[2], bv[1];
+          bv[0] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(sh.h[t & 1] + row * HLD + k8 + s * 16));
+          weights(KSX + s, a);
+          lstm_products<1>(acc, false, nullptr, H, a, bv);
+        }
+        lstm_gates<1>(acc, cst, vsum, sh.wh + u0, sh.h[(t + 1) & 1] + row * HLD + u0, 0);
+      }
+      // v = sum_t (w . h_t + b): the two lane halves, then the waves in order
+      vsum[0] += __shfl_xor(vsum[0], 32);
+      if (lane < 32) sh.red[w * NC + lane] = vsum[0];
+      __syncthreads();
+      if (w == 0) {
+        float s = (float)T * bhead;
+#pragma unroll
+        for (int g = 0; g < KSH; ++g) s += sh.red[g * NC + row];
+        const bool inb = lane < NC && n0 + lane < M;
+        if (scores && inb) scores[n0 + lane] = s;
+        float v = __builtin_inff();
+        int32_t c = -1;
+        if (inb && s < v) { v = s; c = (int32_t)(n0 + lane); }
+        wave_min(v, c);
+        take_min(best, best_at, v, c);
+      }
+      // (the next tile's first stores go to x[0], x[1] and h[0]: every wave is past its last reads of them, which
+      // lie in front of the barrier above)
+    }
+    if (tid == 0) {
+      pval[part] = best;
+      pidx[part] = best_at;
+    }
+  }
+}
+
 template <typename T>
 int grow(vf_ctx *c, T *&p, size_t &have, size_t want) {
   if (want <= have) return VF_OK;
@@ -1485,13 +1622,50 @@ static int score_mlp(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob
   return VF_OK;
 }
 
-int vfk_score_lstm(vf_ctx *c, const uint16_t *x, int64_t M, int T, float *scores, int *nparts_out,
-                   const vf_partbuf *parts) {
+namespace {
+// k_lstm_held for F inputs and H units (fn null: the weights are more than the registers and LDS of a
+// compute unit, or F is a width without an instance) and its workgroups per compute unit.
+struct LstmHeld {
+  void (*fn)(const uint16_t *, int64_t, int, LstmDev, int, float *, float *, int32_t *);
+  int per_cu;
+  size_t lds;
+};
+template <int KSX, int KSH, int WPE, int RK>
+LstmHeld lstm_held(int per_cu) {
+  return {k_lstm_held<KSX, KSH, WPE, RK>, per_cu, sizeof(LstmHeldLds<KSX, KSH, KSX + KSH - RK>)};
+}
+LstmHeld lstm_held_of(int F, int H) {
+  switch (F * 1000 + H) {
+    case 32032: return lstm_held<2, 2, 4, 4>(8);
+    case 32064: return lstm_held<2, 4, 4, 6>(4);
+    case 32096: return lstm_held<2, 6, 3, 8>(2);
+    case 32128: return lstm_held<2, 8, 2, 10>(1);
+    case 32160: return lstm_held<2, 10, 3, 8>(1);
+    case 32192: return lstm_held<2, 12, 3, 9>(1);
+    case 64032: return lstm_held<4, 2, 3, 6>(6);
+    case 64064: return lstm_held<4, 4, 3, 8>(3);
+    case 64096: return lstm_held<4, 6, 3, 9>(2);
+    case 64128: return lstm_held<4, 8, 2, 12>(1);
+    case 64160: return lstm_held<4, 10, 3, 8>(1);
+    case 128032: return lstm_held<8, 2, 2, 10>(4);
+    case 128064: return lstm_held<8, 4, 2, 12>(2);
+    case 128096: return lstm_held<8, 6, 2, 14>(1);
+    case 128128: return lstm_held<8, 8, 2, 16>(1);
+  }
+  return {nullptr, 0, 0};
+}
+}  // namespace
+
+int vfk_score_lstm(vf_ctx *c, const uint16_t *x, int64_t M, int T, float *scores, int *nparts_out, const vf_partbuf *parts,
+                   int *part_out) {
   const vf_model &m = c->model;
-  constexpr int NC = 64;
   LstmDev md;
   md.F = m.dims[0]; md.H = m.dims[1]; md.w_pack = c->pm.w_pack; md.aux = c->pm.aux;
-  const int xld = md.F + 8, hld = md.H + 8;
+  const LstmHeld held = lstm_held_of(md.F, md.H);
+  // (a minimum per tile of 32, or per two of them where that would be more than vf_score_static has room for)
+  const int span = held.fn && M <= (int64_t)LSTM_HELD * VF_STATIC_PARTS ? 1 : 2;
+  const int NC = held.fn ? LSTM_HELD * span : 64;
+  *part_out = NC;
   const int nparts = (int)((M + NC - 1) / NC);
   float *pval = nullptr;
   int32_t *pidx = nullptr;
@@ -1503,20 +1677,28 @@ int vfk_score_lstm(vf_ctx *c, const uint16_t *x, int64_t M, int T, float *scores
     if (rc != VF_OK) return rc;
     pval = c->d_pval; pidx = c->d_pidx;
   }
+  *nparts_out = nparts;
+  if (nparts == 0) return VF_OK;
+  vf_prof_scope prof(c, VF_PROF_SCORE);
+  if (held.fn) {
+    const int fit = held.per_cu * compute_units(c);
+    VF_HIP(c, hipFuncSetAttribute((const void *)held.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)held.lds));
+    hipLaunchKernelGGL(held.fn, dim3((unsigned)(nparts < fit ? nparts : fit)), dim3((unsigned)(4 * md.H)), held.lds, c->stream, x, M, T,
+                       md, span, scores, pval, pidx);
+    VF_HIP(c, hipGetLastError());
+    return VF_OK;
+  }
+  const int xld = md.F + 8, hld = md.H + 8;
   const size_t smem = (size_t)2 * NC * xld * 2 + (size_t)2 * NC * hld * 2 + (size_t)8 * NC * 4 +
                       (size_t)(5 * md.H + 1) * 4;
-  if (nparts > 0) {
-    vf_prof_scope prof(c, VF_PROF_SCORE);
-    // ring depth 2: F and H are multiples of 32, so both parts have an even number of
-    // k-steps (depth 4 spills registers and measured slower)
-    void (*kern)(const uint16_t *, int64_t, int, LstmDev, int, int, float *, float *, int32_t *) =
-        md.F <= 128 ? k_lstm_bf16<NC, 2, 2> : k_lstm_bf16<NC, 4, 2>;
-    VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-    hipLaunchKernelGGL(kern, dim3((unsigned)nparts), dim3(512), smem, c->stream, x, M, T, md, xld, hld, scores,
-                       pval, pidx);
-    VF_HIP(c, hipGetLastError());
-  }
-  *nparts_out = nparts;
+  // ring depth 2: F and H are multiples of 32, so both parts have an even number of
+  // k-steps (depth 4 spills registers and measured slower)
+  void (*kern)(const uint16_t *, int64_t, int, LstmDev, int, int, float *, float *, int32_t *) =
+      md.F <= 128 ? k_lstm_bf16<64, 2, 2> : k_lstm_bf16<64, 4, 2>;
+  VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+  hipLaunchKernelGGL(kern, dim3((unsigned)nparts), dim3(512), smem, c->stream, x, M, T, md, xld, hld, scores,
+                     pval, pidx);
+  VF_HIP(c, hipGetLastError());
   return VF_OK;
 }
 

@@ -7,7 +7,7 @@ import pytest
 
 from paper_2011_14486_amd import inputs as I
 from tests.test_gpu_lstm_search import compare_schedule, setup
-from tests.util import TOL
+from tests.util import TOL, score_err
 
 pytestmark = pytest.mark.gpu
 
@@ -52,3 +52,42 @@ def test_ends_of_tiles(vf, ovf, H, fx, fy, fc):
     st, cids, vals = [t.cpu().numpy()[0] for t in vf.vf_greedy_schedule(ctx)]
     vf.vf_destroy(ctx)
     compare_schedule(ovf, pipe, sp, model, w, cids, vals, st, TOL[1])
+
+
+@pytest.mark.parametrize("F,H", [(F, H) for F in (32, 64, 128) for H in range(32, 193, 32)])
+def test_sequences(vf, ovf, F, H):
+    """Sequences through the networks that a workgroup holds and (F = 128 with H > 128, 64 with 192) the
+    smallest ones that it does not: one tile, ragged tiles, minima per group."""
+    import torch
+    w, model = I.lstm_weights(F, H, seed=4, bias_std=0.2), I.model_record(I.LSTM, [F, H, 1], I.BF16)
+    ctx = vf.vf_create(0)
+    vf.vf_set_model(ctx, model, w)
+    for M, T, group in ((1, 3, 0), (32, 1, 0), (300, 2, 128), (33, 6, 0)):
+        rng = np.random.default_rng([F, H, M])
+        x = torch.from_numpy((rng.random((M, T, F)) * 20).astype(np.float32)).to(torch.bfloat16)
+        s, bi, bv = vf.vf_score(ctx, x.cuda(), vf.VF_X_SEQ_BF16, group=group)
+        s, bi, bv = s.cpu().numpy(), bi.cpu().numpy(), bv.cpu().numpy()
+        assert score_err(s, ovf.score_lstm(model, w, x.view(torch.int16).numpy().view(np.uint16))) <= TOL[1]
+        g = group or M
+        for k in range(len(bi)):
+            part = s[k * g:(k + 1) * g]
+            assert bi[k] == k * g + int(np.argmin(part)) and bv[k] == part.min()
+    vf.vf_destroy(ctx)
+
+
+def test_more_sequences_than_minima(vf):
+    """Above 32 * 65536 sequences a minimum covers two tiles: the scores are those of a small call."""
+    import torch
+    F, H, M = 32, 32, 32 * 65536 + 65
+    w, model = I.lstm_weights(F, H, seed=4, bias_std=0.2), I.model_record(I.LSTM, [F, H, 1], I.BF16)
+    ctx = vf.vf_create(0)
+    vf.vf_set_model(ctx, model, w)
+    x = (torch.rand((M, 1, F), device="cuda", generator=torch.Generator(device="cuda").manual_seed(1)) * 20).to(torch.bfloat16)
+    s, bi, bv = vf.vf_score(ctx, x, vf.VF_X_SEQ_BF16)
+    tail, _, _ = vf.vf_score(ctx, x[-1000:].contiguous(), vf.VF_X_SEQ_BF16)
+    assert torch.equal(s[-1000:], tail)
+    assert float(bv[0]) == float(s.min()) and int(bi[0]) == int((s == s.min()).to(torch.int8).argmax())
+    s2, bi2, bv2 = vf.vf_score(ctx, x, vf.VF_X_SEQ_BF16, group=128)
+    want = torch.nn.functional.pad(s, (0, -M % 128), value=float("inf")).reshape(-1, 128)
+    assert torch.equal(s2, s) and torch.equal(bv2, want.min(dim=1).values)
+    vf.vf_destroy(ctx)
