@@ -57,6 +57,12 @@ struct vf_packed_model {
   // the candidate.  The stream with the first layer cut to k-steps 1..3 (rows 16..63)
   uint16_t *w_stream_fold = nullptr;
   size_t wave_stride_fold = 0;
+  // the other bf16 MLPs, for scoring: the same stream with every hidden layer filled up with units of
+  // zero weights to 256 pad_rt (0: not laid out), and the biases and output vector filled up likewise
+  uint16_t *w_pad = nullptr;
+  float *aux_pad = nullptr;
+  size_t pad_stride = 0;
+  int pad_rt = 0;
   vf_small_dev small;              // small.w null: not small enough
   void *small_buf = nullptr;
   // recurrent network wired to the search: [W_ih | W_hh] transposed, bf16 values as fp32, [64+H][4H]

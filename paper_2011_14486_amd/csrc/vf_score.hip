@@ -164,6 +164,11 @@ __global__ __launch_bounds__(256) void k_copy_f32(const float *src, float *dst, 
   if (i < n) dst[i] = round_bf16 ? bf16_val(src[i]) : src[i];
 }
 
+__global__ __launch_bounds__(256) void k_copy_padded(const float *src, int n, float *dst, int room, int round_bf16) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < room) dst[i] = i < n ? (round_bf16 ? bf16_val(src[i]) : src[i]) : 0.0f;
+}
+
 // The whole MLP for a tile of NC candidates.  8 waves; wave w owns the output row
 // tiles w, w+8, ... (at most RT of them) of every hidden layer and all NC/32 candidate
 // column tiles.  The weight fragments of a wave form one stream over all layers; a
@@ -373,8 +378,9 @@ __global__ __launch_bounds__(512) void k_mlp_bf16(const int32_t *x, int64_t prob
 
 // Stream order for k_mlp_fast: wave w's fragments of all hidden layers back to back,
 // out[w][step][r][lane][e] with step running over (layer, k step) and row tile
-// w + 8 r; `pad` zero steps follow so that the prefetch never leaves the buffer.
-__global__ __launch_bounds__(256) void k_pack_stream(const float *blob, vf_fast_dev md, int RT, int steps_total,
+// w + 8 r; `pad` zero steps follow so that the prefetch never leaves the buffer.  md: the widths in the
+// stream; real: those of the blob (rows and columns past them are zero).
+__global__ __launch_bounds__(256) void k_pack_stream(const float *blob, vf_fast_dev md, vf_fast_dev real, int RT, int steps_total,
                                                      int pad, uint16_t *out) {
   // of the first layer only md.k0 k-steps are packed, starting with step md.k0ofs
   const size_t per_wave = (size_t)(steps_total + pad) * RT * 512;
@@ -390,11 +396,11 @@ __global__ __launch_bounds__(256) void k_pack_stream(const float *blob, vf_fast_
   if (step < steps_total) {
     size_t off = 0;
     for (int l = 0; l < md.L - 1; ++l) {
-      const int K = md.dims[l], N = md.dims[l + 1], ksteps = l == 0 ? md.k0 : K / 16;
+      const int K = real.dims[l], N = real.dims[l + 1], ksteps = l == 0 ? md.k0 : md.dims[l] / 16;
       if (step < ksteps) {
         const int kstep = l == 0 ? step + md.k0ofs : step;
         const int row = (w + 8 * r) * 32 + (lane & 31), k = kstep * 16 + 8 * (lane >> 5) + e;
-        v = (uint16_t)bf16_bits(blob[off + (size_t)row * K + k]);
+        if (row < N && k < K) v = (uint16_t)bf16_bits(blob[off + (size_t)row * K + k]);
         break;
       }
       step -= ksteps;
@@ -436,8 +442,8 @@ struct GenArgs {
 
 // ONE (with GEN): the network has a single hidden layer.
 // CHAIN (with GEN): the launch can also take the decision of the stage before (GenArgs::prev_stage).
-template <int NC, int RT, int PD, bool GEN, bool ONE = false, bool CHAIN = false>
-__global__ __launch_bounds__(512) void k_mlp_fast(const int32_t *x, int64_t prob_stride, int64_t M, int64_t ld,
+template <int NC, int RT, int PD, bool GEN, bool ONE = false, bool CHAIN = false, int WPE = 2>
+__global__ __launch_bounds__(512, WPE) void k_mlp_fast(const int32_t *x, int64_t prob_stride, int64_t M, int64_t ld,
                                                   int use_valid_row, vf_fast_dev md, int ks, float *scores,
                                                   int64_t ld_scores, float *pval, int32_t *pidx, int nparts,
                                                   int nprob, GenArgs ga, NoiseArgs na) {
@@ -1189,8 +1195,81 @@ void vfk_free_model(vf_ctx *c) {
   if (c->pm.w_seqT) (void)hipFree(c->pm.w_seqT);
   if (c->pm.w_seq_wide) (void)hipFree(c->pm.w_seq_wide);
   if (c->pm.small_buf) (void)hipFree(c->pm.small_buf);
+  if (c->pm.w_pad) (void)hipFree(c->pm.w_pad);
+  if (c->pm.aux_pad) (void)hipFree(c->pm.aux_pad);
   if (c->pm.aux) (void)hipFree(c->pm.aux);
   c->pm = vf_packed_model();
+}
+
+// The layout of a network whose hidden layers are filled up to W = 256 rt units: as the fused kernels take it.
+static void padded_dev(const vf_ctx *c, int rt, vf_fast_dev *fd) {
+  const vf_model &m = c->model;
+  const int L = m.n_layers, W = 256 * rt;
+  *fd = vf_fast_dev();
+  fd->L = L;
+  fd->dims[0] = m.dims[0];
+  size_t off = 0;
+  for (int l = 0; l < L; ++l) {
+    fd->dims[l + 1] = l + 1 < L ? W : 1;
+    fd->bias_off[l] = off;
+    off += l + 1 < L ? W : 4;  // (the output vector behind them 16-byte aligned)
+  }
+  fd->wl_off = off;
+  fd->naux = (int)off + W;
+  fd->k0 = m.dims[0] / 16;
+  fd->w_stream = reinterpret_cast<const uint4 *>(c->pm.w_pad);
+  fd->wave_stride = c->pm.pad_stride;
+  fd->aux = c->pm.aux_pad;
+}
+
+// bf16 MLPs of any other hidden widths: packed for k_mlp_fast with every hidden layer filled up to the same
+// multiple of 256.  A unit of zero weights is 0 behind its ReLU (also where an input is infinite: the
+// product's NaN has its sign bit set, and the ReLU makes a zero of that) and meets zero weights in the
+// next layer.  Up to 8 times the products of the network itself; k_mlp_bf16 waits for its weights and for its
+// inputs in turn.  1,000,000 vectors, before and now: 256-256-128-1 1343 -> 397 us, 256-256-256-256-1 1566 -> 512,
+// 512-256-128-1 2410 -> 653, 256-512-256-1 1606 -> 738, 256-1024-512-1 3363 -> 1932, 256-288-1 (3.6 times the products)
+// 1214 -> 431, 64-192-192-1 456 -> 194; 100 vectors 15-47 -> 14-30 us.
+static int pack_padded(vf_ctx *c, const float *wdev) {
+  const vf_model &m = c->model;
+  vf_packed_model &pm = c->pm;
+  const int L = m.n_layers;
+  if (L < 2 || m.dims[0] % 64 != 0) return VF_OK;
+  int maxh = 0;
+  double real = 0.0;
+  for (int l = 1; l < L; ++l) {
+    if (m.dims[l] > maxh) maxh = m.dims[l];
+    real += (double)m.dims[l - 1] * m.dims[l];
+  }
+  const int rt = maxh <= 256 ? 1 : maxh <= 512 ? 2 : 4, W = 256 * rt;
+  if (rt < 4 && m.dims[0] > 512) return VF_OK;  // (tiles of 128 would not fit the LDS)
+  if ((double)m.dims[0] * W + (L - 2.0) * W * W > 8.0 * real) return VF_OK;
+  auto blocks = [](size_t n) { return dim3((unsigned)((n + 255) / 256)); };
+  int steps = m.dims[0] / 16 + (L - 2) * (W / 16);
+  const int pad = 8;
+  const size_t per_wave = (size_t)(steps + pad) * rt * 512;
+  VF_HIP(c, hipMalloc((void **)&pm.w_pad, per_wave * 8 * sizeof(uint16_t)));
+  vf_fast_dev fd, in = vf_fast_dev();
+  padded_dev(c, rt, &fd);
+  VF_HIP(c, hipMalloc((void **)&pm.aux_pad, (size_t)fd.naux * sizeof(float)));
+  in.L = L;
+  for (int l = 0; l < 8; ++l) in.dims[l] = m.dims[l];
+  hipLaunchKernelGGL(k_pack_stream, blocks(per_wave * 8), dim3(256), 0, c->stream, wdev, fd, in, rt, steps, pad, pm.w_pad);
+  VF_HIP(c, hipGetLastError());
+  size_t off = 0;
+  for (int l = 0; l < L; ++l) {
+    const int K = m.dims[l], N = m.dims[l + 1], room = l + 1 < L ? W : 4;
+    const float *Wl = wdev + off, *b = Wl + (size_t)K * N;
+    hipLaunchKernelGGL(k_copy_padded, blocks((size_t)room), dim3(256), 0, c->stream, b, N, pm.aux_pad + fd.bias_off[l], room, 0);
+    VF_HIP(c, hipGetLastError());
+    if (l == L - 1) {
+      hipLaunchKernelGGL(k_copy_padded, blocks((size_t)W), dim3(256), 0, c->stream, Wl, K, pm.aux_pad + fd.wl_off, W, 1);
+      VF_HIP(c, hipGetLastError());
+    }
+    off += (size_t)K * N + N;
+  }
+  pm.pad_stride = per_wave / 8;
+  pm.pad_rt = rt;
+  return VF_OK;
 }
 
 int vfk_pack_model(vf_ctx *c, const float *wdev) {
@@ -1270,7 +1349,7 @@ int vfk_pack_model(vf_ctx *c, const float *wdev) {
       for (int l = 0; l < 8; ++l) fd.dims[l] = m.dims[l];
       fd.k0 = m.dims[0] / 16;
       fd.k0ofs = 0;
-      hipLaunchKernelGGL(k_pack_stream, blocks(per_wave * 8), dim3(256), 0, st, wdev, fd, rt, steps, pad, pm.w_stream);
+      hipLaunchKernelGGL(k_pack_stream, blocks(per_wave * 8), dim3(256), 0, st, wdev, fd, fd, rt, steps, pad, pm.w_stream);
       VF_HIP(c, hipGetLastError());
       pm.wave_stride = per_wave / 8;
       pm.fast_rt = rt;
@@ -1284,13 +1363,13 @@ int vfk_pack_model(vf_ctx *c, const float *wdev) {
         VF_HIP(c, hipMalloc((void **)&pm.w_stream_fold, per_wave_f * 8 * sizeof(uint16_t)));
         fd.k0 = VF_K0_OWN;
         fd.k0ofs = 1;
-        hipLaunchKernelGGL(k_pack_stream, blocks(per_wave_f * 8), dim3(256), 0, st, wdev, fd, rt, fsteps, pad,
+        hipLaunchKernelGGL(k_pack_stream, blocks(per_wave_f * 8), dim3(256), 0, st, wdev, fd, fd, rt, fsteps, pad,
                            pm.w_stream_fold);
         VF_HIP(c, hipGetLastError());
         pm.wave_stride_fold = per_wave_f / 8;
       }
     }
-    return VF_OK;
+    return rt ? VF_OK : pack_padded(c, wdev);
   }
   // LSTM, bf16
   const int F = m.dims[0], H = m.dims[1];
@@ -1545,7 +1624,12 @@ static int score_mlp(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob
   // units: then tiles of 64 spread the same work over twice as many of them, and the
   // contraction of a tile - most of the time a layer takes - is half as long.
   const bool narrow = !wide && gen_stage >= 0 && c->pm.fast_rt && ((M + 127) / 128) * nprob * 2 <= ncu;  // (see narrow_step)
-  const int NC = (wide || narrow) ? 64 : 128;
+  // Hidden layers of up to 256 units, given inputs: tiles of 64 and two workgroups on a compute unit, so that
+  // one's input loads run beside the other's products (1,000,000 vectors 256-256-128-1 450 -> 397 us, 100 of
+  // them 16.5 -> 14.4; the tile of 128 with 128 registers spills 41); tiles of 128 where vf_score_static's
+  // array does not hold the minima of tiles of 64.
+  const bool pad1 = gen_stage < 0 && c->pm.pad_rt == 1 && M <= (int64_t)64 * VF_STATIC_PARTS;
+  const int NC = (wide || narrow || pad1) ? 64 : 128;
   *part_out = NC;
   const int nparts = (int)((M + NC - 1) / NC);
   float *pval = nullptr;
@@ -1605,6 +1689,23 @@ static int score_mlp(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob
     VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_fast));
     hipLaunchKernelGGL(kern, grid, dim3(512), smem_fast, st, x, prob_stride, M, ld, use_valid_row, fd, ks, scores,
                        ld_scores, pval, pidx, nparts, nprob, ga, na);
+    VF_HIP(c, hipGetLastError());
+  } else if (nparts > 0 && gen_stage < 0 && c->pm.pad_rt) {
+    vf_prof_scope prof(c, VF_PROF_SCORE);
+    const int rt = c->pm.pad_rt, ksp = (m.dims[0] > 256 * rt ? m.dims[0] : 256 * rt) + 8;
+    vf_fast_dev fd;
+    padded_dev(c, rt, &fd);
+    GenArgs ga = {};
+    ga.prev_stage = -1;
+    const size_t lds = (size_t)NC * ksp * 2 + (size_t)9 * NC * 4 + (size_t)fd.naux * 4;
+    const int64_t tiles = (int64_t)nparts * nprob, fit = (int64_t)ncu * (pad1 ? 2 : 1);
+    auto kern = pad1      ? k_mlp_fast<64, 1, 4, false, false, false, 4>
+                : rt == 1 ? k_mlp_fast<128, 1, 4, false>
+                : rt == 2 ? k_mlp_fast<128, 2, 4, false>
+                          : k_mlp_fast<64, 4, 4, false>;
+    VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles < fit ? tiles : fit)), dim3(512), lds, st, x, prob_stride, M, ld, use_valid_row, fd,
+                       ksp, scores, ld_scores, pval, pidx, nparts, nprob, ga, na);
     VF_HIP(c, hipGetLastError());
   } else if (nparts > 0) {
     vf_prof_scope prof(c, VF_PROF_SCORE);
