@@ -135,6 +135,104 @@ __device__ int block_select(KEY key, uint32_t n, int want, unsigned long long *s
   return (int)below;
 }
 
+// One pass of the selection for scorers that leave masked scores [slot][Mpad] by id: every block of 1024 R
+// pairs is reduced to its `want` smallest, ordered by (value, index).  First pass (idx_in null): the
+// values are the scores, index = slot * Mpad + candidate id, columns from M on are skipped; later ones
+// read the pairs of the pass before.  sel_n (nullable, the last pass: one block) receives the count.  +inf and
+// NaN never survive.  A layer of 4096 ids and 16 slots: 25 + 25 us with 16 rounds of block-wide minima,
+// 10 + 7 now; 6000 ids and 64 slots: 3 x 25 us of sorting, 11 + 14 now.
+template <int R>
+__global__ __launch_bounds__(SEL_THREADS) void k_select_pass(const float *val_in, const int32_t *idx_in, uint32_t n, uint32_t M,
+                                                             uint32_t Mpad, int want, float *val_out, int32_t *idx_out, int32_t *sel_n) {
+  __shared__ unsigned long long sorted[SEL_CAP];
+  const uint32_t base = blockIdx.x * (uint32_t)(SEL_THREADS * R);
+  const uint32_t here = n - base < (uint32_t)(SEL_THREADS * R) ? n - base : (uint32_t)(SEL_THREADS * R);
+  auto key = [&](uint32_t i) {
+    const uint32_t at = base + (i < here ? i : 0u);
+    const float v = val_in[at];
+    if (idx_in) return idx_in[at] >= 0 ? topk_key(v, idx_in[at]) : NO_KEY;
+    return v < __builtin_inff() && at % Mpad < M ? topk_key(v, (int32_t)at) : NO_KEY;
+  };
+  int found = block_select<R>(key, here, want, sorted);
+  if (found > want) found = want;
+  for (int r = threadIdx.x; r < want; r += SEL_THREADS) {
+    const bool is = r < found;
+    val_out[(size_t)blockIdx.x * want + r] = is ? topk_value(sorted[r]) : __builtin_inff();
+    idx_out[(size_t)blockIdx.x * want + r] = is ? (int32_t)(uint32_t)sorted[r] : -1;
+  }
+  if (sel_n && threadIdx.x == 0) {
+    sel_n[0] = found;
+    if (found > 0) sel_n[1] = found;
+  }
+}
+
+// block-wide first minimum of (v, c); every thread gets the result
+__device__ void block_min(float &v, int32_t &c, float *sv, int32_t *sc) {
+  for (int off = 32; off > 0; off >>= 1) {
+    float ov = __shfl_down(v, off);
+    int32_t oc = __shfl_down(c, off);
+    take_min(v, c, ov, oc);
+  }
+  const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) { sv[w] = v; sc[w] = c; }
+  __syncthreads();
+  v = sv[0]; c = sc[0];
+  for (int k = 1; k < nw; ++k) take_min(v, c, sv[k], sc[k]);
+}
+
+// The same pass for up to four survivors, 2048 pairs per block: k rounds of a block-wide first minimum (one
+// 4 us, four 8 us per pass).
+__global__ __launch_bounds__(256) void k_topk_pass_few(const float *val_in, const int32_t *idx_in, uint32_t n,
+                                                   uint32_t M, uint32_t Mpad, int k, float *val_out,
+                                                   int32_t *idx_out, int32_t *sel_n) {
+  __shared__ float sv[4];
+  __shared__ int32_t sc[4];
+  const uint32_t base = blockIdx.x * 2048u;
+  float v[8];
+  int32_t id[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const uint32_t i = base + threadIdx.x + e * 256u;
+    float s = __builtin_inff();
+    int32_t ix = -1;
+    if (i < n) {
+      if (idx_in) {
+        ix = idx_in[i];
+        if (ix >= 0) s = val_in[i];
+      } else if ((i % Mpad) < M) {
+        const float t = val_in[i];
+        if (t < s) { s = t; ix = (int32_t)i; }  // NaN and +inf never survive
+      }
+    }
+    v[e] = s;
+    id[e] = ix;
+  }
+  int found = 0;
+  for (int r = 0; r < k; ++r) {
+    float bv = __builtin_inff();
+    int32_t bi = -1;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (id[e] >= 0 && (v[e] < bv || (v[e] == bv && (bi < 0 || id[e] < bi)))) { bv = v[e]; bi = id[e]; }
+    block_min(bv, bi, sv, sc);
+    if (threadIdx.x == 0) {
+      val_out[(size_t)blockIdx.x * k + r] = bv;
+      idx_out[(size_t)blockIdx.x * k + r] = bi;
+    }
+    if (bi >= 0) {
+      ++found;
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (id[e] == bi) id[e] = -1;  // indices are unique: only the owner retires it
+    }
+  }
+  if (sel_n && threadIdx.x == 0) {
+    sel_n[0] = found;
+    if (found > 0) sel_n[1] = found;
+  }
+}
+
 // The survivors of a layer: the `want` smallest of all scores, ordered by (score, slot, candidate
 // id); +inf and NaN never survive.  The lists are in ascending id order, so list positions order
 // as the ids do.  No part of 64 entries outside the `want` parts with the smallest minima can hold
@@ -254,6 +352,48 @@ __global__ __launch_bounds__(512) void k_beam_advance(Tables t, AltTables nw, in
 }
 
 }  // namespace
+
+// The survivors of the masked scores in d_scores: d_sel_val / d_sel_idx / d_sel_n.
+int vfk_beam_select(vf_ctx *c) {
+  // (3 slots of 6000 ids, two layers: 88 us with k_topk_pass_few, 96 without; 8 slots: 145 against 107)
+  const int k = c->B;
+  const bool few = k <= 4;
+  // pairs of one block: the last pass, the others
+  const uint32_t MOST = few ? 2048 : 16 * SEL_THREADS, BLOCK = few ? 2048 : 4 * SEL_THREADS;
+  uint32_t n = (uint32_t)((size_t)c->B * c->Mpad);
+  const size_t want = n > MOST ? (size_t)((n + BLOCK - 1) / BLOCK) * k : 0;
+  if (want > c->tk_elems) {
+    if (c->d_tk_val) { VF_HIP(c, hipStreamSynchronize(c->stream)); (void)hipFree(c->d_tk_val); (void)hipFree(c->d_tk_idx); }
+    c->d_tk_val = nullptr; c->d_tk_idx = nullptr; c->tk_elems = 0;
+    if (hipMalloc((void **)&c->d_tk_val, want * 8) != hipSuccess || hipMalloc((void **)&c->d_tk_idx, want * 8) != hipSuccess) {
+      (void)hipGetLastError();
+      return VF_ENOMEM;
+    }
+    c->tk_elems = want;
+  }
+  // (buffers alternate between the two halves; a pass leaves at most a quarter of its pairs: k <= 1024)
+  float *va = c->d_tk_val, *vb = va ? va + want : nullptr;
+  int32_t *ia = c->d_tk_idx, *ib = ia ? ia + want : nullptr;
+  const float *vin = c->d_scores;
+  const int32_t *iin = nullptr;
+  while (n > MOST) {
+    const uint32_t blocks = (n + BLOCK - 1) / BLOCK;
+    hipLaunchKernelGGL(few ? k_topk_pass_few : k_select_pass<4>, dim3(blocks), dim3(few ? 256 : SEL_THREADS), 0, c->stream, vin, iin, n,
+                       (uint32_t)c->M, (uint32_t)c->Mpad, k, va, ia, (int32_t *)nullptr);
+    VF_HIP(c, hipGetLastError());
+    vin = va; iin = ia;
+    n = blocks * (uint32_t)k;
+    std::swap(va, vb);
+    std::swap(ia, ib);
+  }
+  hipLaunchKernelGGL(few               ? k_topk_pass_few
+                     : n <= SEL_THREADS ? k_select_pass<1>
+                     : n <= BLOCK       ? k_select_pass<4>
+                                        : k_select_pass<16>,
+                     dim3(1), dim3(few ? 256 : SEL_THREADS), 0, c->stream, vin, iin, n, (uint32_t)c->M, (uint32_t)c->Mpad, k, c->d_sel_val, c->d_sel_idx, c->d_sel_n);
+  VF_HIP(c, hipGetLastError());
+  return VF_OK;
+}
 
 // With more than 64 tiles of 128 ids in a layer.  Below that the launches on id ranges are as fast
 // (256-512-512-1, whole search: 20 layers of 4096 ids, 2 slots 0.79 against 0.82 ms here, 4 slots 0.93

@@ -293,6 +293,8 @@ int vfk_scores_buffer(vf_ctx *c);
 // beam search pieces (vf_sched.hip)
 int vfk_beam_init(vf_ctx *c, int first_stage);
 int vfk_beam_select_commit(vf_ctx *c, int stage);
+// the B smallest of the masked scores in d_scores (vf_beam.hip)
+int vfk_beam_select(vf_ctx *c);
 // the two sets of state tables change places
 void vfk_beam_swap(vf_ctx *c);
 // whether a beam search works on lists of valid candidates, and all its layers (vf_beam.hip)

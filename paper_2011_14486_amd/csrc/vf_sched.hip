@@ -235,130 +235,6 @@ __global__ __launch_bounds__(256) void k_commit(Tables t, int stage, int nparts,
 // B*M scores survive, ordered by (score, parent slot, candidate id); survivor j copies
 // its parent's schedule into slot j of the other table set and commits its candidate.
 
-__device__ __forceinline__ void take_min_u(float &v, int32_t &c, float ov, int32_t oc) {
-  if (oc >= 0 && (ov < v || (ov == v && (c < 0 || oc < c)))) { v = ov; c = oc; }
-}
-
-// block-wide first minimum of (v, c); every thread gets the result
-__device__ void block_min(float &v, int32_t &c, float *sv, int32_t *sc) {
-  for (int off = 32; off > 0; off >>= 1) {
-    float ov = __shfl_down(v, off);
-    int32_t oc = __shfl_down(c, off);
-    take_min_u(v, c, ov, oc);
-  }
-  const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) { sv[w] = v; sc[w] = c; }
-  __syncthreads();
-  v = sv[0]; c = sc[0];
-  for (int k = 1; k < nw; ++k) take_min_u(v, c, sv[k], sc[k]);
-}
-
-// The same selection pass for a few survivors: k rounds of a block-wide first minimum
-// (cheaper than sorting while k is small).
-__global__ __launch_bounds__(256) void k_topk_pass_few(const float *val_in, const int32_t *idx_in, uint32_t n,
-                                                   uint32_t M, uint32_t Mpad, int k, float *val_out,
-                                                   int32_t *idx_out, int32_t *sel_n) {
-  __shared__ float sv[4];
-  __shared__ int32_t sc[4];
-  const uint32_t base = blockIdx.x * 2048u;
-  float v[8];
-  int32_t id[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const uint32_t i = base + threadIdx.x + e * 256u;
-    float s = __builtin_inff();
-    int32_t ix = -1;
-    if (i < n) {
-      if (idx_in) {
-        ix = idx_in[i];
-        if (ix >= 0) s = val_in[i];
-      } else if ((i % Mpad) < M) {
-        const float t = val_in[i];
-        if (t < s) { s = t; ix = (int32_t)i; }  // NaN and +inf never survive
-      }
-    }
-    v[e] = s;
-    id[e] = ix;
-  }
-  int found = 0;
-  for (int r = 0; r < k; ++r) {
-    float bv = __builtin_inff();
-    int32_t bi = -1;
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-      if (id[e] >= 0 && (v[e] < bv || (v[e] == bv && (bi < 0 || id[e] < bi)))) { bv = v[e]; bi = id[e]; }
-    block_min(bv, bi, sv, sc);
-    if (threadIdx.x == 0) {
-      val_out[(size_t)blockIdx.x * k + r] = bv;
-      idx_out[(size_t)blockIdx.x * k + r] = bi;
-    }
-    if (bi >= 0) {
-      ++found;
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (id[e] == bi) id[e] = -1;  // indices are unique: only the owner retires it
-    }
-  }
-  if (sel_n && threadIdx.x == 0) {
-    sel_n[0] = found;
-    if (found > 0) sel_n[1] = found;
-  }
-}
-
-// One selection pass: every block reduces 2048 (value, index) pairs to its k smallest,
-// ordered by (value, index), with a bitonic sort of the keys in LDS.  First pass
-// (idx_in == nullptr): values are the masked scores, index = slot * Mpad + candidate id,
-// columns >= M are skipped.  Later passes read the pairs of the pass before.  The last
-// pass (one block) also counts.  +inf and NaN never survive.
-__global__ __launch_bounds__(256) void k_topk_pass(const float *val_in, const int32_t *idx_in, uint32_t n,
-                                                   uint32_t M, uint32_t Mpad, int k, float *val_out,
-                                                   int32_t *idx_out, int32_t *sel_n) {
-  constexpr unsigned long long NONE = ~0ull;
-  __shared__ unsigned long long keys[2048];
-  const uint32_t base = blockIdx.x * 2048u;
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const uint32_t i = base + tid + e * 256u;
-    unsigned long long key = NONE;
-    if (i < n) {
-      if (idx_in) {
-        const int32_t ix = idx_in[i];
-        if (ix >= 0) key = topk_key(val_in[i], ix);
-      } else if ((i % Mpad) < M) {
-        const float t = val_in[i];
-        if (t < __builtin_inff()) key = topk_key(t, (int32_t)i);
-      }
-    }
-    keys[tid + e * 256] = key;
-  }
-  for (int size = 2; size <= 2048; size <<= 1)
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      __syncthreads();
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int t = tid + e * 256;
-        const int lo = 2 * t - (t & (stride - 1)), hi = lo + stride;
-        const bool up = (lo & size) == 0;
-        const unsigned long long a = keys[lo], b = keys[hi];
-        if ((a > b) == up) { keys[lo] = b; keys[hi] = a; }
-      }
-    }
-  __syncthreads();
-  for (int r = tid; r < k; r += 256) {
-    const unsigned long long key = keys[r];
-    val_out[(size_t)blockIdx.x * k + r] = key == NONE ? __builtin_inff() : topk_value(key);
-    idx_out[(size_t)blockIdx.x * k + r] = key == NONE ? -1 : (int32_t)(uint32_t)key;
-  }
-  if (sel_n && tid == 0) {
-    int found = 0;
-    for (int r = 0; r < k; ++r) found += keys[r] != NONE;
-    sel_n[0] = found;
-    if (found > 0) sel_n[1] = found;
-  }
-}
-
 // First layer of a beam search: only slot 0 (the context's current schedule of
 // problem 0) is live; the other slots and the whole second table set are cleared.
 __global__ __launch_bounds__(256) void k_beam_init(Tables t, AltTables alt, int B, int32_t *sel_n) {
@@ -593,37 +469,8 @@ void vfk_beam_swap(vf_ctx *c) {
 // scores of the layer are in d_scores: select the survivors, commit them into the other
 // table set, swap the sets
 int vfk_beam_select_commit(vf_ctx *c, int stage) {
-  const uint32_t total = (uint32_t)((size_t)c->B * c->Mpad);
-  const int nchunks = (int)((total + 2047u) / 2048u), k = c->B;
-  const size_t want = (size_t)nchunks * k;
-  if (want > c->tk_elems) {
-    if (c->d_tk_val) { VF_HIP(c, hipStreamSynchronize(c->stream)); (void)hipFree(c->d_tk_val); (void)hipFree(c->d_tk_idx); }
-    c->d_tk_val = nullptr; c->d_tk_idx = nullptr; c->tk_elems = 0;
-    if (hipMalloc((void **)&c->d_tk_val, want * 8) != hipSuccess || hipMalloc((void **)&c->d_tk_idx, want * 8) != hipSuccess) {
-      (void)hipGetLastError();
-      return VF_ENOMEM;
-    }
-    c->tk_elems = want;
-  }
-  // passes of 2048 -> k until one block is left; buffers alternate between the two halves
-  float *va = c->d_tk_val, *vb = c->d_tk_val + want;
-  int32_t *ia = c->d_tk_idx, *ib = c->d_tk_idx + want;
-  const float *vin = c->d_scores;
-  const int32_t *iin = nullptr;
-  uint32_t n = total;
-  for (;;) {
-    const int blocks = (int)((n + 2047u) / 2048u);
-    const bool last_pass = blocks == 1;
-    hipLaunchKernelGGL(k <= 16 ? k_topk_pass_few : k_topk_pass, dim3(blocks), dim3(256), 0, c->stream, vin, iin, n, (uint32_t)c->M,
-                       (uint32_t)c->Mpad, k, last_pass ? c->d_sel_val : va, last_pass ? c->d_sel_idx : ia,
-                       last_pass ? c->d_sel_n : (int32_t *)nullptr);
-    VF_HIP(c, hipGetLastError());
-    if (last_pass) break;
-    vin = va; iin = ia;
-    n = (uint32_t)blocks * (uint32_t)k;
-    std::swap(va, vb);
-    std::swap(ia, ib);
-  }
+  const int rc = vfk_beam_select(c);
+  if (rc != VF_OK) return rc;
   {
     vf_prof_scope prof(c, VF_PROF_COMMIT);
     hipLaunchKernelGGL(k_beam_commit, dim3(c->B), dim3(64), 0, c->stream, tables_of(c), alt_of(c), stage,

@@ -48,3 +48,29 @@ def test_shares(vf, ovf, B, facs, dtype):
             sc, ok = ovf.decision_scores(pipes[0], sp, model, w, cids[j, :2], 2)
             c = cids[j, 2]
             assert ok[c] and abs(sc[c] - vals[j, 2]) <= TOL[0 if dtype == I.FP32 else 1] * max(abs(sc[c]), np.sqrt(np.mean(sc[ok] ** 2)))
+
+
+@pytest.mark.parametrize("const", [True, False])
+@pytest.mark.parametrize("K,fac", [(4, [1, 2, 4]), (5, [1, 2, 4]), (17, [1, 2, 4, 8]), (300, [1, 2, 4]), (1024, [1, 2])])
+def test_selection_from_masked_scores(vf, ovf, K, fac, const):
+    """One and several passes, up to four survivors and many; const: every state has the same value, so that all
+    scores tie and the survivors are the first (slot, id) pairs."""
+    sp = I.make_space(fac, fac, fac, I.ALL_PERMS[:2], 2, 2, [I.ROOT, I.L1, I.L2, I.INLINE], 2, 64)
+    dims, pipe = [64, 32, 1], I.random_pipeline(3, 21)
+    w = I.mlp_weights(dims, 5, bias_std=0.1)
+    if const:
+        w = np.zeros_like(w)
+        w[-1] = 0.75
+    model = I.model_record(I.MLP, dims, I.FP32)
+    ctx = vf.vf_create(0)
+    vf.vf_set_space(ctx, sp); vf.vf_set_pipeline(ctx, np.stack([pipe] * K)); vf.vf_set_model(ctx, model, w)
+    st, cids, vals, nb = (t.cpu().numpy() for t in vf.vf_beam_search(ctx))
+    vf.vf_destroy(ctx)
+    ref = ovf.beam(pipe, sp, K, model, w)
+    assert nb[0] == ref["n_beams"] > 0
+    if const:
+        assert np.array_equal(cids, ref["cids"]) and np.array_equal(vals, ref["values"])
+    else:  # (fp32: the same survivors' values up to the tolerance, in order)
+        n = int(nb[0])
+        scale = np.maximum(np.abs(ref["values"][:n, -1]), np.sqrt(np.mean(ref["values"][:n, -1] ** 2)))
+        assert np.all(np.diff(vals[:n, -1]) >= 0) and np.all(np.abs(vals[:n, -1] - ref["values"][:n, -1]) <= TOL[0] * scale)
