@@ -551,7 +551,8 @@ int vf_beam_search(vf_ctx *c, int first, int last, vf_state *out_states, int32_t
   DeviceGuard g(c->device);
   int rc = settle_whole(c, first > 0);
   if (rc != VF_OK) return rc;
-  rc = vfk_beam_init(c, first);
+  rc = vfk_seq_flush(c);  // (a search before this one may have left its last survivors' step to do)
+  if (rc == VF_OK) rc = vfk_beam_init(c, first);
   if (rc != VF_OK) return rc;
   if (first <= last && vfk_beam_lists(c)) {
     rc = vfk_beam_layers(c, first, last);

@@ -124,6 +124,7 @@ struct vf_ctx {
   uint16_t *d_seq_rows = nullptr;                 // [B][Mpad][64] normalised features of the listed candidates, bf16
   int seq_stage = -1;                             // committed stages folded into the state, -1: none valid
   int seq_cur = 0;                                // which set is current
+  int seq_pending = 0;                            // the step at the commit of seq_stage is still to do: 1 in place, 2 to the other set
   // exploration noise added to the scores in the argmin scan of step / greedy calls
   float noise_eps = 0.0f;
   uint64_t noise_seed = 0;
@@ -262,6 +263,7 @@ void vfk_seq_free(vf_ctx *c);
 int vfk_seq_sync(vf_ctx *c, int stage);
 int vfk_seq_advance(vf_ctx *c, int stage);
 int vfk_seq_advance_beam(vf_ctx *c, int stage);
+int vfk_seq_flush(vf_ctx *c);
 int vfk_seq_step(vf_ctx *c, int stage, float *scores, int64_t ld_scores, int noise_stage, int *nparts_out);
 int vfk_greedy_whole(vf_ctx *c, int first, int last);
 // One decision of every problem on lists of valid candidates (vf_whole.hip): open the decisions of

@@ -75,14 +75,35 @@ __global__ __launch_bounds__(256) void k_pack_seqT(SeqWeights sw, float *WT) {
   WT[i] = bf16_val(k < 64 ? sw.Wih[(size_t)r * 64 + k] : sw.Whh[(size_t)r * H + (k - 64)]);
 }
 
-__global__ __launch_bounds__(1024) void k_seq_advance(Tables t, int stage, SeqWeights sw, const float *WT, SeqState src,
-                                                      SeqState dst, const int32_t *sel_idx, const int32_t *sel_n,
-                                                      int64_t Mpad, int B) {
-  __shared__ float x[SEQ_PB][64], z[SEQ_PB][1024], hn[SEQ_PB][256], hraw[SEQ_PB][256];
-  __shared__ int from_s[SEQ_PB], mode_s[SEQ_PB];  // 0: leave alone, 1: carry the state over, 2: one cell step
+struct SeqAdvance {
+  Tables t;
+  int stage;
+  SeqWeights sw;
+  const float *WT;
+  SeqState src, dst;
+  const int32_t *sel_idx, *sel_n;
+  int64_t Mpad;
+  int B;
+};
+struct SeqAdvanceShared {
+  float x[SEQ_PB][64], z[SEQ_PB][1024], hn[SEQ_PB][256], hraw[SEQ_PB][256];
+  int from_s[SEQ_PB], mode_s[SEQ_PB];  // 0: leave alone, 1: carry the state over, 2: one cell step
+};
+// A workgroup of 1024: problems b0 .. b0 + SEQ_PB - 1.
+__device__ __forceinline__ void seq_advance(const SeqAdvance &a, SeqAdvanceShared &sh, int b0) {
+  const Tables &t = a.t;
+  const SeqWeights &sw = a.sw;
+  const SeqState &src = a.src, &dst = a.dst;
+  const float *const WT = a.WT;
+  const int32_t *const sel_idx = a.sel_idx, *const sel_n = a.sel_n;
+  const int64_t Mpad = a.Mpad;
+  const int stage = a.stage, B = a.B;
+  auto &x = sh.x;
+  auto &z = sh.z;
+  auto &hn = sh.hn, &hraw = sh.hraw;
+  auto &from_s = sh.from_s, &mode_s = sh.mode_s;
   const int tid = threadIdx.x, lane = tid & 63;
   const int H = sw.H, H4 = 4 * H, S = t.S;
-  const int b0 = blockIdx.x * SEQ_PB;
   if (tid < SEQ_PB) {
     const int b = b0 + tid;
     int mode = 0, from = b;
@@ -164,6 +185,10 @@ __global__ __launch_bounds__(1024) void k_seq_advance(Tables t, int stage, SeqWe
       else if (mode_s[pb] == 1) dst.P[(size_t)(b0 + pb) * H4 + tid] = src.P[(size_t)from_s[pb] * H4 + tid];
     }
   }
+}
+__global__ __launch_bounds__(1024) void k_seq_advance(SeqAdvance a) {
+  __shared__ SeqAdvanceShared sh;
+  seq_advance(a, sh, blockIdx.x * SEQ_PB);
 }
 
 // The valid candidates of decision (problem b, stage), in ascending id order:
@@ -482,52 +507,86 @@ __global__ __launch_bounds__(256) void k_pack_seq_wide(SeqWeights sw, uint16_t *
 // ---- networks whose recurrent weights fit the registers of one workgroup (H <= 192)
 
 // Opens decision `stage` of problem blockIdx.y for the two scorers below: the ordered list of its valid
-// candidates, their number, and each one's 64 normalised features as a row of bfloat16.  A thread
-// has one candidate: the evaluation runs at full occupancy, and none of its registers is taken from
+// candidates, their number, and each one's 64 normalised features as a row of bfloat16.  The
+// evaluation runs at full occupancy here, and none of its registers is taken from
 // the scorers, which keep their weights there from one tile to the next.  Also: +inf into the masked score
 // array (nullable), no minimum into the parts behind the last tile.  The list comes from the validity
-// rules, not from a scan over the ids (one workgroup per problem, 10 us): 5 us for one problem, 18 for 64.
-__global__ __launch_bounds__(128) void k_seq_open(const uint32_t *decpack, uint32_t M, int64_t Mpad, int32_t *list, int32_t *count,
-                                                  uint16_t *rows, float *scores, float *pval, int32_t *pidx, int nparts,
-                                                  int tile) {
-  __shared__ DecPack pk;
-  __shared__ EvalTabs tabs;
-  __shared__ OpenScratch os;
-  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
-  const int64_t k = (int64_t)blockIdx.x * 128 + tid;  // (Mpad is a multiple of 256)
-  for (int i = tid; i < VF_DECPACK_DWORDS; i += 128) reinterpret_cast<uint32_t *>(&pk)[i] = decpack[(size_t)b * VF_DECPACK_DWORDS + i];
-  if (scores) scores[(size_t)b * Mpad + k] = __builtin_inff();
+// rules, not from a scan over the ids (one workgroup per problem, 10 us): 8 us for one problem, 18 for 64.
+// The first `nadv` workgroups do something else: the prefix's step at the commit in front of this decision
+// (seq_advance), which needs nothing of this and takes as long, so that the two make one launch (schedules of
+// one problem of 20 layers, H = 32 0.70 -> 0.57 ms, 256 1.56 -> 1.51).
+constexpr int SEQ_OPEN = 256;  // candidates per workgroup, four threads each
+__global__ __launch_bounds__(1024) void k_seq_open(const uint32_t *decpack, uint32_t M, int64_t Mpad, int32_t *list, int32_t *count,
+                                                   uint16_t *rows, float *scores, float *pval, int32_t *pidx, int nparts, int tile,
+                                                   int nadv, SeqAdvance adv) {
+  __shared__ union {
+    struct {
+      DecPack pk;
+      EvalTabs tabs;
+      OpenScratch os;
+    } o;
+    SeqAdvanceShared a;
+  } sh;
+  if ((int)blockIdx.x < nadv) {
+    seq_advance(adv, sh.a, (int)blockIdx.x * SEQ_PB);
+    return;
+  }
+  DecPack &pk = sh.o.pk;
+  EvalTabs &tabs = sh.o.tabs;
+  OpenScratch &os = sh.o.os;
+  const int per = (int)(Mpad / SEQ_OPEN), at = (int)blockIdx.x - nadv, b = at / per, chunk = at - b * per;
+  const int tid = threadIdx.x, lane = tid & 63, n = tid & (SEQ_OPEN - 1);
+  const int part = __builtin_amdgcn_readfirstlane(tid / SEQ_OPEN);
+  const int64_t k = (int64_t)chunk * SEQ_OPEN + n;
+  if (tid < VF_DECPACK_DWORDS) reinterpret_cast<uint32_t *>(&pk)[tid] = decpack[(size_t)b * VF_DECPACK_DWORDS + tid];
+  if (scores && part == 3) scores[(size_t)b * Mpad + k] = __builtin_inff();
   __syncthreads();
   fill_evaltabs(tabs, pk.d, pk.sp);
-  if (tid >= 119) list_factors(pk, os, tid - 119);
+  if (tid >= 1015) list_factors(pk, os, tid - 1015);
   __syncthreads();
   if (tid < 64) list_pairs(pk, os, lane);
   __syncthreads();
-  const int n = os.ncand;
-  if (blockIdx.x == 0) {
-    if (tid == 0) count[b] = n;
-    for (int i = (n + tile - 1) / tile + tid; i < nparts; i += 128) {
+  const int have = os.ncand;
+  if (chunk == 0) {
+    if (tid == 0) count[b] = have;
+    for (int i = (have + tile - 1) / tile + tid; i < nparts; i += 1024) {
       pval[(size_t)b * nparts + i] = __builtin_inff();
       pidx[(size_t)b * nparts + i] = -1;
     }
   }
-  if (k >= n) return;
+  if (k >= have) return;
   int pos_r[12];
 #pragma unroll
   for (int j = 0; j < 12; ++j) pos_r[j] = j < os.npairs ? os.pos[j] : 0x7fffffff;
   const Digits g = unpack_digits(list_entry(pk, os, pos_r, (int)k, 1.0f / (float)pk.sp.nperm, 1.0f / (float)pk.sp.nvec));
   int32_t core[64];
-  eval_digits<true>(pk.d, pk.sp, g, &tabs, core);
-  list[(size_t)b * Mpad + k] = (int32_t)id_of(pk.sp, g);
-  uint4 *dst = reinterpret_cast<uint4 *>(rows + ((size_t)b * Mpad + k) * 64);
+  // sixteen rows of two 16-byte stores (what a thread does not store is dead code in its copy)
+  auto put = [&](int row0) __attribute__((always_inline)) {
+    uint4 *dst = reinterpret_cast<uint4 *>(rows + ((size_t)b * Mpad + k) * 64 + row0);
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    uint4 o;
-    o.x = pack_bf16(plog2_dev(core[8 * q + 0]), plog2_dev(core[8 * q + 1]));
-    o.y = pack_bf16(plog2_dev(core[8 * q + 2]), plog2_dev(core[8 * q + 3]));
-    o.z = pack_bf16(plog2_dev(core[8 * q + 4]), plog2_dev(core[8 * q + 5]));
-    o.w = pack_bf16(plog2_dev(core[8 * q + 6]), plog2_dev(core[8 * q + 7]));
-    dst[q] = o;
+    for (int q = 0; q < 2; ++q) {
+      const int32_t *v = core + row0 + 8 * q;
+      uint4 o;
+      o.x = pack_bf16(plog2_dev(v[0]), plog2_dev(v[1]));
+      o.y = pack_bf16(plog2_dev(v[2]), plog2_dev(v[3]));
+      o.z = pack_bf16(plog2_dev(v[4]), plog2_dev(v[5]));
+      o.w = pack_bf16(plog2_dev(v[6]), plog2_dev(v[7]));
+      dst[q] = o;
+    }
+  };
+  if (part == 0) {
+    eval_digits<true>(pk.d, pk.sp, g, &tabs, core);
+    list[(size_t)b * Mpad + k] = (int32_t)id_of(pk.sp, g);
+    put(0);
+  } else if (part == 1) {
+    eval_digits<true>(pk.d, pk.sp, g, &tabs, core);
+    put(16);
+  } else if (part == 2) {
+    eval_digits<true>(pk.d, pk.sp, g, &tabs, core);
+    put(32);
+  } else {
+    eval_digits<true>(pk.d, pk.sp, g, &tabs, core);
+    put(48);
   }
 }
 
@@ -965,6 +1024,7 @@ void vfk_seq_free(vf_ctx *c) {
   c->d_seq_rows = nullptr;
   for (int k = 0; k < 2; ++k) c->d_seq_h[k] = c->d_seq_c[k] = c->d_seq_P[k] = c->d_seq_hs[k] = nullptr;
   c->seq_stage = -1;
+  c->seq_pending = 0;
   c->seq_cur = 0;
 }
 
@@ -996,6 +1056,22 @@ static HeldKernel held_kernel_of(int H, bool many) {
     case 7: return many ? wide_kernel<14, 2, 1, 3>() : wide_kernel<14, 1, 5, 4>();
     default: return many ? wide_kernel<16, 2, 1, 2>() : wide_kernel<16, 1, 5, 3>();
   }
+}
+
+// The step of the prefix at the commit of `stage`.  how: 1 in place, 2 from the parents' set to the other one.
+static SeqAdvance advance_of(const vf_ctx *c, int stage, int how) {
+  SeqAdvance a;
+  a.t = tables_of(c);
+  a.stage = stage;
+  a.sw = weights_of(c);
+  a.WT = c->pm.w_seqT;
+  a.src = state_of(c, c->seq_cur);
+  a.dst = how == 2 ? state_of(c, c->seq_cur ^ 1) : a.src;
+  a.sel_idx = how == 2 ? c->d_sel_idx : nullptr;
+  a.sel_n = how == 2 ? c->d_sel_n : nullptr;
+  a.Mpad = (int64_t)c->Mpad;
+  a.B = c->B;
+  return a;
 }
 
 // Tables and prefix state of the recurrence for the context's pipeline, model and
@@ -1051,45 +1127,49 @@ int vfk_seq_sync(vf_ctx *c, int stage) {
     }
     c->seq_stage = -1;
   }
-  if (c->seq_stage == stage) return VF_OK;
+  if (c->seq_stage == stage && !c->seq_pending) return VF_OK;
+  if (c->seq_pending && c->seq_stage >= 0 && c->seq_stage + 1 == stage) return VF_OK;  // (the caller's to do)
   c->seq_cur = 0;
   const size_t n = (size_t)B * 4 * H;
   const SeqState s0 = state_of(c, 0);
   hipLaunchKernelGGL(k_seq_reset, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, sw, B, s0.hfb, s0.cpre, s0.P,
                      s0.hsum);
   VF_HIP(c, hipGetLastError());
+  c->seq_pending = 0;
   for (int t = 0; t < stage; ++t) {
-    hipLaunchKernelGGL(k_seq_advance, dim3((unsigned)((B + SEQ_PB - 1) / SEQ_PB)), dim3(1024), 0, st, tables_of(c), t, sw,
-                       (const float *)c->pm.w_seqT, s0, s0, (const int32_t *)nullptr, (const int32_t *)nullptr,
-                       (int64_t)c->Mpad, B);
+    hipLaunchKernelGGL(k_seq_advance, dim3((unsigned)((B + SEQ_PB - 1) / SEQ_PB)), dim3(1024), 0, st, advance_of(c, t, 1));
     VF_HIP(c, hipGetLastError());
   }
   c->seq_stage = stage;
   return VF_OK;
 }
 
-// after the commit of `stage`: one more step of every problem's prefix recurrence
+// After the commit of `stage`: one more step of every problem's prefix recurrence.  It is left for the
+// launch that opens the next decision (vfk_seq_step), or for whoever needs it earlier (vfk_seq_flush).
 int vfk_seq_advance(vf_ctx *c, int stage) {
-  if (c->seq_stage != stage) return VF_OK;  // not in step: rebuilt at the next use
-  const SeqState s = state_of(c, c->seq_cur);
-  hipLaunchKernelGGL(k_seq_advance, dim3((unsigned)((c->B + SEQ_PB - 1) / SEQ_PB)), dim3(1024), 0, c->stream,
-                     tables_of(c), stage, weights_of(c), (const float *)c->pm.w_seqT, s, s, (const int32_t *)nullptr,
-                     (const int32_t *)nullptr, (int64_t)c->Mpad, c->B);
-  VF_HIP(c, hipGetLastError());
-  c->seq_stage = stage + 1;
+  if (c->seq_stage == stage) c->seq_pending = 1;  // (not in step: rebuilt at the next use)
   return VF_OK;
 }
 
 // beam search: slot j of the new layer continues the recurrence of its parent slot
 int vfk_seq_advance_beam(vf_ctx *c, int stage) {
-  if (c->seq_stage != stage) return VF_OK;
-  const SeqState src = state_of(c, c->seq_cur), dst = state_of(c, c->seq_cur ^ 1);
+  if (c->seq_stage == stage) c->seq_pending = 2;
+  return VF_OK;
+}
+
+static void advanced(vf_ctx *c) {
+  if (c->seq_pending == 2) c->seq_cur ^= 1;
+  c->seq_stage += 1;
+  c->seq_pending = 0;
+}
+
+// A step that was left undone, by itself: before anything it reads changes (the survivors of a beam).
+int vfk_seq_flush(vf_ctx *c) {
+  if (!c->seq_pending || c->seq_stage < 0 || !c->d_seq_G) return VF_OK;
   hipLaunchKernelGGL(k_seq_advance, dim3((unsigned)((c->B + SEQ_PB - 1) / SEQ_PB)), dim3(1024), 0, c->stream,
-                     tables_of(c), stage, weights_of(c), (const float *)c->pm.w_seqT, src, dst,
-                     (const int32_t *)c->d_sel_idx, (const int32_t *)c->d_sel_n, (int64_t)c->Mpad, c->B);
+                     advance_of(c, c->seq_stage, c->seq_pending));
   VF_HIP(c, hipGetLastError());
-  c->seq_cur ^= 1;
-  c->seq_stage = stage + 1;
+  advanced(c);
   return VF_OK;
 }
 
@@ -1105,11 +1185,21 @@ int vfk_seq_step(vf_ctx *c, int stage, float *scores, int64_t ld_scores, int noi
   (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
   // (a third of the ids is valid, as a rule: three rounds of ids in tiles of 64)
   const HeldKernel hk = held_kernel_of(H, (c->M + 63) / 64 * c->B >= 3 * (int64_t)ncu);
-  const bool held = c->pm.w_seq_wide && c->d_seq_rows;
+  const bool held = c->pm.w_seq_wide && c->d_seq_rows && c->Mpad / SEQ_OPEN * c->B < (1 << 21);  // (a launch has less than 2^32 threads)
   const int NC = held ? hk.tile : 64;
   const int nparts = (int)((c->M + NC - 1) / NC);
   rc = vfk_ensure_parts(c, (size_t)nparts * c->B);
   if (rc != VF_OK) return rc;
+  if (!held) {
+    rc = vfk_seq_flush(c);
+    if (rc != VF_OK) return rc;
+  }
+  SeqAdvance adv = {};
+  const int nadv = c->seq_pending ? (c->B + SEQ_PB - 1) / SEQ_PB : 0;
+  if (nadv) {
+    adv = advance_of(c, c->seq_stage, c->seq_pending);
+    advanced(c);  // (by k_seq_open below)
+  }
   const SeqState s = state_of(c, c->seq_cur);
   SeqDev md;
   md.H = H; md.S = c->S; md.w_pack = c->pm.w_pack; md.aux = c->pm.aux;
@@ -1123,9 +1213,9 @@ int vfk_seq_step(vf_ctx *c, int stage, float *scores, int64_t ld_scores, int noi
   na.stage = noise_stage; na.first_rollout = c->noise_first;
   *nparts_out = nparts;
   if (held) {
-    hipLaunchKernelGGL(k_seq_open, dim3((unsigned)(c->Mpad / 128), (unsigned)c->B), dim3(128), 0, c->stream, c->d_decpack,
-                       (uint32_t)c->M, (int64_t)c->Mpad, c->d_seq_list, c->d_seq_count, c->d_seq_rows, scores, c->d_pval,
-                       c->d_pidx, nparts, hk.tile);
+    hipLaunchKernelGGL(k_seq_open, dim3((unsigned)nadv + (unsigned)(c->Mpad / SEQ_OPEN) * (unsigned)c->B), dim3(1024), 0, c->stream,
+                       c->d_decpack, (uint32_t)c->M, (int64_t)c->Mpad, c->d_seq_list, c->d_seq_count, c->d_seq_rows, scores, c->d_pval,
+                       c->d_pidx, nparts, hk.tile, nadv, adv);
     VF_HIP(c, hipGetLastError());
     vf_prof_scope prof(c, VF_PROF_SCORE);
     VF_HIP(c, hipFuncSetAttribute((const void *)hk.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)hk.lds));

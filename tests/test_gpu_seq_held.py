@@ -91,3 +91,44 @@ def test_more_sequences_than_minima(vf):
     want = torch.nn.functional.pad(s, (0, -M % 128), value=float("inf")).reshape(-1, 128)
     assert torch.equal(s2, s) and torch.equal(bv2, want.min(dim=1).values)
     vf.vf_destroy(ctx)
+
+
+@pytest.mark.parametrize("K", [3, 20])
+def test_searches_one_behind_the_other(vf, K):
+    """The prefix's last step is done by whoever opens the next decision: a beam, a greedy schedule and single
+    steps on top of each other decide what they decide on the same prefix set by hand, bit for bit."""
+    sp = I.make_space([1, 2, 4], [1, 3], [1, 2, 8], I.ALL_PERMS[:2], 2, 2, [I.ROOT, I.L1, I.L2, I.INLINE], 1, 64)
+    pipes = np.stack([I.random_pipeline(6, 77)] * K)
+
+    def context():
+        return setup(vf, pipes, sp, 64)[0]
+
+    def host(ts):
+        return [t.cpu().numpy() for t in ts]
+
+    def on_prefix(cids, n, what):
+        c = context()
+        vf.vf_set_state(c, np.ascontiguousarray(cids[:, :n]))
+        out = host(what(c))
+        vf.vf_destroy(c)
+        return out
+    ctx = context()
+    first = host(vf.vf_beam_search(ctx, 0, 1))[1]
+    got = host(vf.vf_greedy_schedule(ctx, 2, 3))                    # every slot goes on by itself
+    for a, b in zip(on_prefix(first, 2, lambda c: vf.vf_greedy_schedule(c, 2, 3)), got):
+        assert np.array_equal(a[:, 2:4], b[:, 2:4])
+    got = host(vf.vf_beam_search(ctx, 4, 4))                        # from slot 0's schedule
+    mixed = np.repeat(got[1][:1], K, axis=0)
+    want = on_prefix(mixed, 4, lambda c: vf.vf_beam_search(c, 4, 4))
+    assert np.array_equal(want[1], got[1]) and np.array_equal(want[2][:, 4], got[2][:, 4])
+    nb = int(got[3][0])
+    again = host(vf.vf_beam_search(ctx, 5, 5))                      # and from the best of those
+    want = on_prefix(np.repeat(got[1][:1], K, axis=0), 5, lambda c: vf.vf_beam_search(c, 5, 5))
+    assert nb == K and np.array_equal(want[1], again[1]) and np.array_equal(want[2][:, 5], again[2][:, 5])
+    vf.vf_reset_state(ctx)
+    for i in range(2):
+        vf.vf_argmin_step(ctx, i, True)
+    vf.vf_reset_state(ctx)                                          # (a step left undone does not outlive its state)
+    a, b = host(vf.vf_greedy_schedule(ctx)), on_prefix(first[:, :0], 0, vf.vf_greedy_schedule)
+    assert all(np.array_equal(x, y) for x, y in zip(a, b))
+    vf.vf_destroy(ctx)
