@@ -499,7 +499,7 @@ int vf_greedy_schedule(vf_ctx *c, int first, int last, vf_state *out_states, int
   int rc = VF_OK;
   bool decided = first > last;
   if (!decided) {
-    if (vfk_layer_pays(c) && !vfk_whole_pays(c)) {
+    if (vfk_greedy_layers_pay(c) && !vfk_whole_pays(c)) {
       rc = vfk_greedy_layers(c, first, last);
       decided = rc == VF_OK;
     } else if (vfk_whole_team(c) >= 1) {

@@ -277,6 +277,7 @@ int vfk_layer_score(vf_ctx *c, int noise_stage, float *scores, int *nparts_out);
 // whether lists pay for a step of this context (vf_score.hip), and Algorithm 1 over stages
 // first..last on them
 bool vfk_layer_pays(const vf_ctx *c);
+bool vfk_greedy_layers_pay(const vf_ctx *c);  // the same for whole schedules
 bool vfk_whole_pays(const vf_ctx *c);
 int vfk_greedy_layers(vf_ctx *c, int first, int last);
 int vfk_step_fused(vf_ctx *c, int stage, int *nparts_out);
