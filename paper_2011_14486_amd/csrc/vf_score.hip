@@ -109,7 +109,8 @@ __global__ __launch_bounds__(VF_PART) void k_argmin_parts(const float *scores, i
 }
 
 // Final scan per group of candidates over the partial minima: a wave per group, or sixteen
-// where the groups have many (one group of 1563 parts: 14 us with one wave, whose reads follow each other).
+// where the groups have many (one group of 1563 parts: 14 us with one wave, whose reads follow each other;
+// eight reads of a thread under way at once, 64-32-1 bf16, 1,000,000 vectors: 55.5 -> 49.0 us).
 __global__ __launch_bounds__(1024) void k_argmin_groups(const float *pval, const int32_t *pidx, int nparts,
                                                         int parts_per_group, int32_t *best_idx, float *best_val) {
   __shared__ float sv[16];
@@ -120,13 +121,29 @@ __global__ __launch_bounds__(1024) void k_argmin_groups(const float *pval, const
   if (hi > nparts) hi = nparts;
   float v = __builtin_inff();
   int32_t c = -1;
-  for (int p = lo + (int)threadIdx.x; p < hi; p += (int)blockDim.x) take_min(v, c, pval[p], pidx[p]);
-  wave_min(v, c);
-  if (nw > 1) {
+  if (nw == 1) {
+    for (int p = lo + lane; p < hi; p += 64) take_min(v, c, pval[p], pidx[p]);
+    wave_min(v, c);
+  } else {
+    for (int p = lo + (int)threadIdx.x; p < hi; p += 8 * 1024) {
+      float pv[8];
+      int32_t pi[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int q = p + j * 1024 < hi ? p + j * 1024 : p;
+        pv[j] = pval[q];
+        pi[j] = pidx[q];
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) take_min(v, c, pv[j], pi[j]);
+    }
+    wave_min(v, c);
     if (lane == 0) { sv[w] = v; sc[w] = c; }
     __syncthreads();
-    if (threadIdx.x == 0)
-      for (int k = 1; k < nw; ++k) take_min(v, c, sv[k], sc[k]);
+    if (w > 0) return;
+    v = lane < 16 ? sv[lane] : __builtin_inff();
+    c = lane < 16 ? sc[lane] : -1;
+    wave_min(v, c);
   }
   if (threadIdx.x == 0) {
     if (best_idx) best_idx[g] = c;
