@@ -1264,10 +1264,16 @@ static int pack_padded(vf_ctx *c, const float *wdev) {
   int steps = m.dims[0] / 16 + (L - 2) * (W / 16);
   const int pad = 8;
   const size_t per_wave = (size_t)(steps + pad) * rt * 512;
-  VF_HIP(c, hipMalloc((void **)&pm.w_pad, per_wave * 8 * sizeof(uint16_t)));
   vf_fast_dev fd, in = vf_fast_dev();
   padded_dev(c, rt, &fd);
-  VF_HIP(c, hipMalloc((void **)&pm.aux_pad, (size_t)fd.naux * sizeof(float)));
+  if (hipMalloc((void **)&pm.w_pad, per_wave * 8 * sizeof(uint16_t)) != hipSuccess ||
+      hipMalloc((void **)&pm.aux_pad, (size_t)fd.naux * sizeof(float)) != hipSuccess) {
+    (void)hipGetLastError();  // (without memory for this second form the network runs in k_mlp_bf16)
+    if (pm.w_pad) (void)hipFree(pm.w_pad);
+    pm.w_pad = nullptr;
+    pm.aux_pad = nullptr;
+    return VF_OK;
+  }
   in.L = L;
   for (int l = 0; l < 8; ++l) in.dims[l] = m.dims[l];
   hipLaunchKernelGGL(k_pack_stream, blocks(per_wave * 8), dim3(256), 0, c->stream, wdev, fd, in, rt, steps, pad, pm.w_pad);
