@@ -43,18 +43,48 @@ def test_widths(vf, ovf, dims, M, group):
         assert bv[k] == s[k * g:(k + 1) * g].min()
 
 
-def test_infinite_activations_and_sizes(vf, ovf):
-    """An infinite hidden value meets the zero weights of the units that fill the next layer up: they stay 0.
-    Scores do not depend on the size of the call (tiles of 64, and of 128 above 64 * 65536 vectors)."""
+def layers(dims, w):
+    """Views of the flat weights: (matrix, bias) per layer."""
+    out, off = [], 0
+    for K, N in zip(dims, dims[1:]):
+        out.append((w[off:off + K * N].reshape(N, K), w[off + K * N:off + K * N + N]))
+        off += K * N + N
+    return out
+
+
+# one, two and four row tiles per wave, one and two filled-up layers behind the infinite value
+@pytest.mark.parametrize("dims", [[64, 160, 96, 1], [64, 160, 96, 192, 1], [64, 288, 160, 1], [192, 512, 480, 32, 1],
+                                  [64, 544, 608, 1], [64, 992, 1024, 96, 1]])
+@pytest.mark.parametrize("passes", [False, True])
+def test_infinite_activations(vf, ovf, dims, passes):
+    """An infinite hidden value meets the zero weights of the units that fill the next layer up: they stay 0, and
+    no NaN comes of them.  passes: one real unit of every further layer takes the infinity on, all others
+    get minus infinity, so that every score is +inf; otherwise all real units get minus infinity, so
+    that every score is finite."""
+    w, model = I.mlp_weights(dims, 3, bias_std=0.1), I.model_record(I.MLP, dims, I.BF16)
+    net, at = layers(dims, w), 5
+    net[0][1][at] = np.inf
+    for W, _ in net[1:-1]:
+        W[:, at] = -np.abs(W[:, at]) - 0.01
+        if not passes:
+            break
+        W[7, at] = 0.5
+        at = 7
+    net[-1][0][0, at] = 0.5 if passes else net[-1][0][0, at]
+    M = 300
+    rng = np.random.default_rng(dims)
+    raw = np.floor(2.0 ** (rng.random((dims[0], M)) * 20)).astype(np.int32)
+    ref = ovf.score_mlp(model, w, raw)
+    assert (ref == np.inf).all() if passes else np.isfinite(ref).all()
+    s, _, _ = score(vf, dims, w, raw)
+    assert score_err(s, ref) <= TOL[1]
+
+
+def test_sizes(vf):
+    """Scores do not depend on the size of the call (tiles of 64, and of 128 above 64 * 65536 vectors)."""
     import torch
     dims, M = [64, 160, 96, 1], 64 * 65536 + 7
     w, model = I.mlp_weights(dims, 3, bias_std=0.1), I.model_record(I.MLP, dims, I.BF16)
-    inf = w.copy()
-    inf[64 * 160 + 5] = np.inf                                # bias of hidden unit 5
-    raw = np.arange(64 * 300, dtype=np.int32).reshape(64, 300)
-    s, _, _ = score(vf, dims, inf, raw)
-    ref = ovf.score_mlp(model, inf, raw)
-    assert not np.isfinite(ref).all() and score_err(s, ref) <= TOL[1]
     ctx = vf.vf_create(0)
     vf.vf_set_model(ctx, model, w)
     x = torch.randint(0, 1 << 20, (64, M), dtype=torch.int32, device="cuda", generator=torch.Generator(device="cuda").manual_seed(2))
