@@ -273,7 +273,9 @@ int vf_set_space(vf_ctx *c, const vf_space *s) {
   VF_HIP(c, hipStreamSynchronize(c->stream));
   c->space = *s;
   c->M = M;
-  c->Mpad = (M + 255) / 256 * 256;
+  const int64_t Mpad = (M + 255) / 256 * 256;
+  if (Mpad != c->Mpad) vfk_seq_free(c);  // (the recurrent search's lists and rows have the old space's size)
+  c->Mpad = Mpad;
   VF_HIP(c, hipMemcpyAsync(c->d_space, &c->space, sizeof(vf_space), hipMemcpyHostToDevice, c->stream));
   VF_HIP(c, hipStreamSynchronize(c->stream));
   c->has_space = true;

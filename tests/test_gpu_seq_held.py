@@ -132,3 +132,17 @@ def test_searches_one_behind_the_other(vf, K):
     a, b = host(vf.vf_greedy_schedule(ctx)), on_prefix(first[:, :0], 0, vf.vf_greedy_schedule)
     assert all(np.array_equal(x, y) for x, y in zip(a, b))
     vf.vf_destroy(ctx)
+
+
+def test_spaces_one_behind_the_other(vf, ovf):
+    """A larger and a smaller space on the same context: each search as on a context of its own."""
+    pipe = I.random_pipeline(4, 61)
+    spaces = [I.make_space([1, 2], [1, 2], [1, 2], I.ALL_PERMS[:1], 1, 1, [I.ROOT], 1, 64),
+              I.make_space([1, 2, 4], [1, 2, 4], [1, 2, 4], I.ALL_PERMS, 2, 2, [I.ROOT, I.L1], 1, 64)]
+    ctx, model, w = setup(vf, np.stack([pipe] * 3), spaces[0], 64)
+    for sp in (spaces[0], spaces[1], spaces[0]):
+        vf.vf_set_space(ctx, sp)
+        st, cids, vals = [t.cpu().numpy() for t in vf.vf_greedy_schedule(ctx)]
+        for b in range(3):
+            compare_schedule(ovf, pipe, sp, model, w, cids[b], vals[b], st[b], TOL[1])
+    vf.vf_destroy(ctx)

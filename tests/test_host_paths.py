@@ -61,6 +61,29 @@ def recurrent_weights(stub, vf):
     vf.vf_destroy(ctx)
 
 
+def recurrent_spaces(stub, vf):
+    """A larger space behind a recurrent search: lists and rows of its size, not of the old one's."""
+    from paper_2011_14486_amd import inputs as I
+    H, B = 64, 4
+    small = I.make_space([1, 2], [1, 2], [1, 2], I.ALL_PERMS[:1], 1, 1, [I.ROOT], 1, 64)
+    large = I.make_space([1, 2, 4], [1, 2, 4], [1, 2, 4], I.ALL_PERMS, 2, 2, [I.ROOT, I.L1], 1, 64)
+    ctx = context(vf, np.stack([I.random_pipeline(3, 5)] * B), small, I.model_record(I.LSTM, [64, H, 1], I.BF16),
+                  I.lstm_weights(64, H))
+    assert vf.vf_argmin_step(ctx, 0, 1, None, None) == 0
+    assert vf.vf_set_space(ctx, C.c_void_p(large.ctypes.data)) == 0
+    Mpad = vf.vf_padded_count(ctx)
+    assert Mpad == 1536
+    for each, rc, kernel in ((4, -3, None), (128, 0, "k_seq_compact")):  # lists; rows, without which the other scorer runs
+        assert vf.vf_reset_state(ctx) == 0
+        stub.stub_clear()
+        stub.stub_fail(B * Mpad * each, B * Mpad * each)
+        assert vf.vf_argmin_step(ctx, 0, 1, None, None) == rc
+        stub.stub_fail(1, 0)
+        log = stub.stub_log().decode()
+        assert "k_seq_open" not in log and (rc != 0 or kernel in log), log
+    vf.vf_destroy(ctx)
+
+
 def candidate_lists(stub, vf):
     """No memory for the candidate lists: a greedy schedule is decided on id ranges, whether it would
     have run layer by layer (64 problems) or in one launch (200)."""
@@ -113,7 +136,7 @@ def stub_path(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("case", ["recurrent_weights", "candidate_lists", "many_problems"])
+@pytest.mark.parametrize("case", ["recurrent_weights", "recurrent_spaces", "candidate_lists", "many_problems"])
 def test_host_path(stub_path, case):
     # (a process of its own: the stub takes the place of the whole runtime)
     r = subprocess.run([sys.executable, os.path.abspath(__file__), stub_path, case], cwd=ROOT, capture_output=True, text=True)
