@@ -1196,11 +1196,8 @@ int vfk_seq_step(vf_ctx *c, int stage, float *scores, int64_t ld_scores, int noi
   }
   SeqAdvance adv = {};
   const int nadv = c->seq_pending ? (c->B + SEQ_PB - 1) / SEQ_PB : 0;
-  if (nadv) {
-    adv = advance_of(c, c->seq_stage, c->seq_pending);
-    advanced(c);  // (by k_seq_open below)
-  }
-  const SeqState s = state_of(c, c->seq_cur);
+  if (nadv) adv = advance_of(c, c->seq_stage, c->seq_pending);
+  const SeqState s = state_of(c, c->seq_pending == 2 ? c->seq_cur ^ 1 : c->seq_cur);  // behind that step
   SeqDev md;
   md.H = H; md.S = c->S; md.w_pack = c->pm.w_pack; md.aux = c->pm.aux;
   md.G = c->d_seq_G; md.P = s.P; md.cpre = s.cpre; md.hsum = s.hsum;
@@ -1217,6 +1214,7 @@ int vfk_seq_step(vf_ctx *c, int stage, float *scores, int64_t ld_scores, int noi
                        c->d_decpack, (uint32_t)c->M, (int64_t)c->Mpad, c->d_seq_list, c->d_seq_count, c->d_seq_rows, scores, c->d_pval,
                        c->d_pidx, nparts, hk.tile, nadv, adv);
     VF_HIP(c, hipGetLastError());
+    if (nadv) advanced(c);
     vf_prof_scope prof(c, VF_PROF_SCORE);
     VF_HIP(c, hipFuncSetAttribute((const void *)hk.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)hk.lds));
     const int64_t most = (int64_t)nparts * c->B, fit = (int64_t)hk.per_cu * ncu;

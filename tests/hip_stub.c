@@ -17,10 +17,17 @@ static dim3 cfg_grid, cfg_block;
 static size_t cfg_shared;
 static hipStream_t cfg_stream;
 static char static_array[1 << 20];
+static char refused[100];
+static int refused_skip;
 
 /* hipMalloc of lo..hi bytes fails from now on (lo > hi: none does) */
 void stub_fail(size_t lo, size_t hi) { fail_lo = lo; fail_hi = hi; }
-/* the launches so far, one "kernel grid first-pointer second-argument" a line */
+/* the launch after the next `skip` ones of kernels whose names hold `name` is refused (NULL: none is) */
+void stub_fail_launch(const char *name, int skip) {
+  snprintf(refused, sizeof refused, "%s", name ? name : "");
+  refused_skip = skip;
+}
+/* the launches so far, one "kernel grid weights" a line */
 const char *stub_log(void) { return log_text; }
 void stub_clear(void) { log_len = 0; log_text[0] = 0; }
 
@@ -108,6 +115,10 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t sh
   if ((unsigned long long)g.x * b.x >> 32 || (unsigned long long)g.y * b.y >> 32 || (unsigned long long)g.z * b.z >> 32 ||
       !g.x || !g.y || !g.z)
     return err(hipErrorInvalidConfiguration);
+  if (refused[0] && strstr(name, refused) && refused_skip-- == 0) {
+    refused[0] = 0;
+    return err(hipErrorLaunchFailure);
+  }
   /* (k_seq_step_wide's second argument is its weights) */
   const void *weights = strstr(name, "k_seq_step_wide") ? *(void **)args[1] : (void *)1;
   if (log_len + 300 < sizeof log_text)

@@ -18,6 +18,7 @@ def make_library(stub_path):
     stub = C.CDLL(stub_path, mode=C.RTLD_GLOBAL)
     stub.stub_fail.argtypes = [C.c_size_t, C.c_size_t]
     stub.stub_log.restype = C.c_char_p
+    stub.stub_fail_launch.argtypes = [C.c_char_p, C.c_int]
     vf = C.CDLL(binding.LIB_PATH)
     vf.vf_create.argtypes = [C.POINTER(C.c_void_p), C.c_int, C.c_void_p]
     vf.vf_padded_count.restype = C.c_int64
@@ -84,6 +85,31 @@ def recurrent_spaces(stub, vf):
     vf.vf_destroy(ctx)
 
 
+def refused_opening(stub, vf):
+    """The launch that opens a decision and does the prefix's step is refused: the context does not take the
+    step for done, the schedule goes on with it."""
+    from paper_2011_14486_amd import inputs as I
+    B = 4
+    ctx = context(vf, np.stack([I.random_pipeline(4, 5)] * B), I.tiny_space(64), I.model_record(I.LSTM, [64, 64, 1], I.BF16),
+                  I.lstm_weights(64, 64))
+    stub.stub_fail_launch(b"k_seq_open", 1)
+    assert vf.vf_greedy_schedule(ctx, 0, 3, None, None, None) == -4
+    assert vf.vf_n_scheduled(ctx) == 1
+    assert vf.vf_greedy_schedule(ctx, 1, 3, None, None, None) == 0
+    grids = [int(l.split()[1]) for l in stub.stub_log().decode().splitlines() if "k_seq_open" in l]
+    plain = B * vf.vf_padded_count(ctx) // 256
+    assert grids == [plain] + [plain + 1] * 3, grids  # (four problems to a workgroup of the step)
+    # a beam: the step goes from one set of states to the other
+    assert vf.vf_reset_state(ctx) == 0
+    stub.stub_clear()
+    stub.stub_fail_launch(b"k_seq_open", 1)
+    assert vf.vf_beam_search(ctx, 0, 3, None, None, None, None) == -4
+    assert vf.vf_n_scheduled(ctx) == 1 and vf.vf_argmin_step(ctx, 1, 0, None, None) == 0
+    grids = [int(l.split()[1]) for l in stub.stub_log().decode().splitlines() if "k_seq_open" in l]
+    assert grids == [plain, plain + 1], grids
+    vf.vf_destroy(ctx)
+
+
 def candidate_lists(stub, vf):
     """No memory for the candidate lists: a greedy schedule is decided on id ranges, whether it would
     have run layer by layer (64 problems) or in one launch (200)."""
@@ -136,7 +162,7 @@ def stub_path(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("case", ["recurrent_weights", "recurrent_spaces", "candidate_lists", "many_problems"])
+@pytest.mark.parametrize("case", ["recurrent_weights", "recurrent_spaces", "refused_opening", "candidate_lists", "many_problems"])
 def test_host_path(stub_path, case):
     # (a process of its own: the stub takes the place of the whole runtime)
     r = subprocess.run([sys.executable, os.path.abspath(__file__), stub_path, case], cwd=ROOT, capture_output=True, text=True)
