@@ -170,6 +170,11 @@ int step(vf_ctx *c, int stage, int commit, int32_t *best_cid, float *best_val) {
   return vfk_commit_from_partials(c, stage, nparts, commit, best_cid, best_val);
 }
 
+// The end of a call that committed decisions with the recurrent network: the prefix's step behind the last
+// of them runs in this call, not in the one that decides next.  (Inside a call it goes along with the
+// opening of the next decision; behind the last stage there is nothing to decide.)
+int finish_prefix(vf_ctx *c) { return c->n_sched < c->S ? vfk_seq_flush(c) : VF_OK; }
+
 int settle_whole(vf_ctx *c, bool wait);
 
 struct DeviceGuard {
@@ -477,8 +482,9 @@ int vf_argmin_step(vf_ctx *c, int stage, int commit, int32_t *best_cid, float *b
   int rc = settle_whole(c, stage > 0);
   if (rc != VF_OK) return rc;
   rc = step(c, stage, commit, best_cid, best_val);
-  if (rc == VF_OK && commit) c->n_sched = stage + 1;
-  return rc;
+  if (rc != VF_OK || !commit) return rc;
+  c->n_sched = stage + 1;
+  return finish_prefix(c);
 }
 
 int vf_greedy_schedule(vf_ctx *c, int first, int last, vf_state *out_states, int32_t *out_cids, float *out_vals) {
@@ -525,7 +531,8 @@ int vf_greedy_schedule(vf_ctx *c, int first, int last, vf_state *out_states, int
       c->n_sched = i + 1;
     }
   }
-  return vfk_copy_tables(c, out_states, out_cids, out_vals, nullptr);
+  rc = vfk_copy_tables(c, out_states, out_cids, out_vals, nullptr);
+  return rc == VF_OK ? finish_prefix(c) : rc;
 }
 
 int vf_set_noise(vf_ctx *c, float eps, uint64_t seed, int32_t first_rollout) {
@@ -553,7 +560,7 @@ int vf_beam_search(vf_ctx *c, int first, int last, vf_state *out_states, int32_t
   DeviceGuard g(c->device);
   int rc = settle_whole(c, first > 0);
   if (rc != VF_OK) return rc;
-  rc = vfk_seq_flush(c);  // (a search before this one may have left its last survivors' step to do)
+  rc = vfk_seq_flush(c);  // (a search that failed may have left its last survivors' step to do)
   if (rc == VF_OK) rc = vfk_beam_init(c, first);
   if (rc != VF_OK) return rc;
   if (first <= last && vfk_beam_lists(c)) {
@@ -572,7 +579,8 @@ int vf_beam_search(vf_ctx *c, int first, int last, vf_state *out_states, int32_t
     }
     c->n_sched = i + 1;
   }
-  return vfk_copy_tables(c, out_states, out_cids, out_vals, n_beams);
+  rc = vfk_copy_tables(c, out_states, out_cids, out_vals, n_beams);
+  return rc == VF_OK ? finish_prefix(c) : rc;
 }
 
 const char *vf_strerror(int code) {

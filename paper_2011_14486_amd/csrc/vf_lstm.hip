@@ -1145,7 +1145,7 @@ int vfk_seq_sync(vf_ctx *c, int stage) {
 }
 
 // After the commit of `stage`: one more step of every problem's prefix recurrence.  It is left for the
-// launch that opens the next decision (vfk_seq_step), or for whoever needs it earlier (vfk_seq_flush).
+// launch that opens the call's next decision (vfk_seq_step); behind its last one vfk_seq_flush does it.
 int vfk_seq_advance(vf_ctx *c, int stage) {
   if (c->seq_stage == stage) c->seq_pending = 1;  // (not in step: rebuilt at the next use)
   return VF_OK;
@@ -1163,7 +1163,8 @@ static void advanced(vf_ctx *c) {
   c->seq_pending = 0;
 }
 
-// A step that was left undone, by itself: before anything it reads changes (the survivors of a beam).
+// A step that was left undone, by itself: at the end of a call, and before anything it reads changes (the
+// survivors of a beam).
 int vfk_seq_flush(vf_ctx *c) {
   if (!c->seq_pending || c->seq_stage < 0 || !c->d_seq_G) return VF_OK;
   hipLaunchKernelGGL(k_seq_advance, dim3((unsigned)((c->B + SEQ_PB - 1) / SEQ_PB)), dim3(1024), 0, c->stream,

@@ -95,8 +95,8 @@ def test_more_sequences_than_minima(vf):
 
 @pytest.mark.parametrize("K", [3, 20])
 def test_searches_one_behind_the_other(vf, K):
-    """The prefix's last step is done by whoever opens the next decision: a beam, a greedy schedule and single
-    steps on top of each other decide what they decide on the same prefix set by hand, bit for bit."""
+    """The prefix's step goes along with the opening of a call's next decision, the last one at the call's end: a
+    beam, a greedy schedule and single steps on top of each other decide what they decide on the same prefix set by hand, bit for bit."""
     sp = I.make_space([1, 2, 4], [1, 3], [1, 2, 8], I.ALL_PERMS[:2], 2, 2, [I.ROOT, I.L1, I.L2, I.INLINE], 1, 64)
     pipes = np.stack([I.random_pipeline(6, 77)] * K)
 
@@ -128,7 +128,7 @@ def test_searches_one_behind_the_other(vf, K):
     vf.vf_reset_state(ctx)
     for i in range(2):
         vf.vf_argmin_step(ctx, i, True)
-    vf.vf_reset_state(ctx)                                          # (a step left undone does not outlive its state)
+    vf.vf_reset_state(ctx)                                          # (nothing of it outlives its state)
     a, b = host(vf.vf_greedy_schedule(ctx)), on_prefix(first[:, :0], 0, vf.vf_greedy_schedule)
     assert all(np.array_equal(x, y) for x, y in zip(a, b))
     vf.vf_destroy(ctx)

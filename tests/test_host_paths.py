@@ -110,6 +110,32 @@ def refused_opening(stub, vf):
     vf.vf_destroy(ctx)
 
 
+def prefix_step_in_call(stub, vf):
+    """The prefix's step behind a call's last commit is launched by that call, whatever decided it; behind the last
+    stage there is none."""
+    from paper_2011_14486_amd import inputs as I
+    B, S = 4, 5
+    ctx = context(vf, np.stack([I.random_pipeline(S, 5)] * B), I.tiny_space(64), I.model_record(I.LSTM, [64, 64, 1], I.BF16),
+                  I.lstm_weights(64, 64))
+    plain = B * vf.vf_padded_count(ctx) // 256
+
+    def steps(call, *args):
+        """Prefix steps of a call: launches of their own, and workgroups next to an opening."""
+        stub.stub_clear()
+        assert call(ctx, *args) == 0
+        lines = [l.split() for l in stub.stub_log().decode().splitlines()]
+        return (sum("k_seq_advance" in l[0] for l in lines), sum(int(l[1]) - plain for l in lines if "k_seq_open" in l[0]))
+
+    assert steps(vf.vf_argmin_step, 0, 0, None, None) == (0, 0)
+    assert steps(vf.vf_argmin_step, 0, 1, None, None) == (1, 0)
+    assert steps(vf.vf_greedy_schedule, 1, 2, None, None, None) == (1, 1)
+    assert steps(vf.vf_beam_search, 3, 3, None, None, None, None) == (1, 0)
+    assert steps(vf.vf_argmin_step, 4, 1, None, None) == (0, 0)
+    assert vf.vf_reset_state(ctx) == 0
+    assert steps(vf.vf_greedy_schedule, 0, S - 1, None, None, None) == (0, S - 1)
+    vf.vf_destroy(ctx)
+
+
 def candidate_lists(stub, vf):
     """No memory for the candidate lists: a greedy schedule is decided on id ranges, whether it would
     have run layer by layer (64 problems) or in one launch (200)."""
@@ -162,7 +188,7 @@ def stub_path(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("case", ["recurrent_weights", "recurrent_spaces", "refused_opening", "candidate_lists", "many_problems"])
+@pytest.mark.parametrize("case", ["recurrent_weights", "recurrent_spaces", "refused_opening", "prefix_step_in_call", "candidate_lists", "many_problems"])
 def test_host_path(stub_path, case):
     # (a process of its own: the stub takes the place of the whole runtime)
     r = subprocess.run([sys.executable, os.path.abspath(__file__), stub_path, case], cwd=ROOT, capture_output=True, text=True)
