@@ -77,12 +77,18 @@ struct SmallArgs {
   int block, nblocks;
 };
 
+// What a kernel scores: given features, the valid ids that its waves collect, or ids as they come.
+enum { GIVEN = 0, COLLECTED = 1, IDS = 2 };
+
 // GEN: the candidates are enumerated and featurized where they are scored (x is not used); scores of
 // ids that are not valid candidates read +inf.  Every wave keeps the context of its problem, looks its ids
 // over a block at a time - their digits and the validity rules, a lane each - and collects the valid
 // ones until a sub-tile is full, so that the network runs on valid candidates only (a third of the ids, as a
 // rule).  64-128-128-1 fp32, 6000 ids, per schedule of two decisions: 64 problems 413 -> 285 us, 16: 160 -> 102;
 // 256-96-64-1 bf16, one decision of 4096 ids: 200 problems 91 -> 69 us, 37: 31 -> 25.
+// A share of one block of a sub-tile's ids has nothing to collect: the ids go on as they come (IDS), and the
+// evaluation itself tells the valid ones (6000 ids, one problem: 57.2 us by way of the queue, 55.6 without; two
+// problems 59.1 / 57.7; one problem in bf16 42.9 / 41.9).
 struct WaveDec {
   DecPack pk;
   EvalTabs tabs;
@@ -102,15 +108,12 @@ __device__ __forceinline__ bool eval_wave(const WaveDec &wd, uint32_t cid, int32
 }
 // Goes on through the share's blocks (blk: the next one) until `want` valid ids are queued or there are
 // no more blocks; masked ids' scores are written.  All lanes call it.
-// (A share of one block of a sub-tile's ids has nothing to collect: they go on as they are, and the
-// evaluation itself tells the valid ones.)
 __device__ __forceinline__ void fill_queue(WaveDec &wd, const SmallArgs &a, int p, int &blk, int &queued, int want, int lane) {
-  const bool as_is = a.nparts == a.nblocks && a.block == want;
   while (queued < want && blk < a.nblocks) {
     const int64_t n0 = (int64_t)blk * a.block, to = n0 + a.block < a.M ? n0 + a.block : a.M;
     const bool in = n0 + lane < to;
     bool valid = in && !range_closed(wd.pk.d, wd.pk.sp, (uint32_t)n0, (uint32_t)to);
-    if (valid && !as_is)
+    if (valid)
       valid = eval_digits<false>(wd.pk.d, wd.pk.sp, digits_small(wd.pk.sp, (uint32_t)(n0 + lane)), nullptr, nullptr);
     if (a.scores && in && !valid) a.scores[(size_t)p * a.ld_scores + n0 + lane] = __builtin_inff();
     const unsigned long long m = __ballot(valid);
@@ -187,8 +190,9 @@ __device__ __forceinline__ void load_raw(int32_t (&r)[ROWS][N], const int32_t *p
 // of a sub-tile of 64 (64-128-128-1: 100 of them, 3200 cycles) and the conversion of its inputs cost
 // about the same; two waves per SIMD overlap one's with the other's, and the next 32 input rows are
 // always under way.
-template <int CT, int NT, bool GEN>
+template <int CT, int NT, int MODE>
 __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
+  constexpr bool GEN = MODE != GIVEN, DIRECT = MODE == IDS;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint4 *const wl = reinterpret_cast<uint4 *>(smem);
   float *const bl = reinterpret_cast<float *>(wl + a.md.nw);
@@ -249,9 +253,16 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
     }
     int have = 0;  // (GEN) candidates of this sub-tile
     if constexpr (GEN) {
-      fill_queue(wd, a, p, blk, queued, 32 * CT, lane);
-      have = queued < 32 * CT ? queued : 32 * CT;
-      ends = blk >= a.nblocks && queued == have;
+      if constexpr (DIRECT) {
+        n0 = (int64_t)blk * (32 * CT);
+        have = (int)(a.M - n0 < 32 * CT ? a.M - n0 : 32 * CT);
+        blk += a.nparts;
+        ends = blk >= a.nblocks;
+      } else {
+        fill_queue(wd, a, p, blk, queued, 32 * CT, lane);
+        have = queued < 32 * CT ? queued : 32 * CT;
+        ends = blk >= a.nblocks && queued == have;
+      }
       nu = ends ? u + stride : u;
     }
     const bool more = nu < u_end;
@@ -266,10 +277,12 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
     uint32_t id[CT];  // (GEN)
     if constexpr (GEN) {
 #pragma unroll
-      for (int c = 0; c < CT; ++c) id[c] = ok[c] ? wd.queue[CT * (lane & 31) + c] : 0u;
+      for (int c = 0; c < CT; ++c)
+        id[c] = !ok[c] ? 0u : DIRECT ? (uint32_t)n0 + CT * (lane & 31) + c : wd.queue[CT * (lane & 31) + c];
     }
     uint4 own[GEN ? 4 : 1][CT];  // (GEN) the candidates' rows 0..63, as the k-steps 0..3 want them
-    const bool closed = GEN && have == 0;  // (only a share without any candidate)
+    // (GEN) no candidate in the share, or in the block
+    const bool closed = GEN && (DIRECT ? range_closed(wd.pk.d, wd.pk.sp, (uint32_t)n0, (uint32_t)(n0 + have)) : have == 0);
     if constexpr (GEN) {
       if (!closed) {
 #pragma unroll
@@ -461,7 +474,7 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
     }
     if (!more) break;
     if constexpr (GEN) {
-      drop_queue(wd, queued, have, lane);
+      if constexpr (!DIRECT) drop_queue(wd, queued, have, lane);
       if (ends) {
         np = nu / a.nparts;
         blk = nu - np * a.nparts;
@@ -481,8 +494,9 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
 // few terms are the more exact ones (scores of 64-128-128-1 off a 64-bit sum, relative: 1.5e-7; 2.0e-7
 // when two columns per lane had one sum each and 192,000 vectors took 88 instead of 90 us), and a
 // candidate's score does not depend on how many candidates the call has.
-template <int CT, int NT, bool GEN>
+template <int CT, int NT, int MODE>
 __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
+  constexpr bool GEN = MODE != GIVEN, DIRECT = MODE == IDS;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint4 *const wl = reinterpret_cast<uint4 *>(smem);
   const floatx4 *const wf = reinterpret_cast<const floatx4 *>(smem);
@@ -533,9 +547,16 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
     }
     int have = 0;  // (GEN) candidates of this sub-tile
     if constexpr (GEN) {
-      fill_queue(wd, a, p, blk, queued, 16 * CT, lane);
-      have = queued < 16 * CT ? queued : 16 * CT;
-      ends = blk >= a.nblocks && queued == have;
+      if constexpr (DIRECT) {
+        n0 = (int64_t)blk * (16 * CT);
+        have = (int)(a.M - n0 < 16 * CT ? a.M - n0 : 16 * CT);
+        blk += a.nparts;
+        ends = blk >= a.nblocks;
+      } else {
+        fill_queue(wd, a, p, blk, queued, 16 * CT, lane);
+        have = queued < 16 * CT ? queued : 16 * CT;
+        ends = blk >= a.nblocks && queued == have;
+      }
       nu = ends ? u + stride : u;
     }
     const bool more = nu < u_end;
@@ -550,10 +571,12 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
     uint32_t id[CT];  // (GEN)
     if constexpr (GEN) {
 #pragma unroll
-      for (int c = 0; c < CT; ++c) id[c] = ok[c] ? wd.queue[CT * (lane & 15) + c] : 0u;
+      for (int c = 0; c < CT; ++c)
+        id[c] = !ok[c] ? 0u : DIRECT ? (uint32_t)n0 + CT * (lane & 15) + c : wd.queue[CT * (lane & 15) + c];
     }
     float own[GEN ? 4 : 1][4][CT];  // (GEN) the candidates' rows 0..63: group of 16, row of the lane group, column
-    const bool closed = GEN && have == 0;  // (only a share without any candidate)
+    // (GEN) no candidate in the share, or in the block
+    const bool closed = GEN && (DIRECT ? range_closed(wd.pk.d, wd.pk.sp, (uint32_t)n0, (uint32_t)(n0 + have)) : have == 0);
     if constexpr (GEN) {
       if (!closed) {
 #pragma unroll
@@ -758,7 +781,7 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
     }
     if (!more) break;
     if constexpr (GEN) {
-      drop_queue(wd, queued, have, lane);
+      if constexpr (!DIRECT) drop_queue(wd, queued, have, lane);
       if (ends) {
         np = nu / a.nparts;
         blk = nu - np * a.nparts;
@@ -865,6 +888,7 @@ int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob,
   *nparts_out = a.nparts;
   *part_out = part;
   a.block = a.nblocks = 0;
+  bool ids = false;
   if (!x) {
     // blocks of 64 ids, of fewer down to a sub-tile's where there would not be two of them per wave; as many
     // shares per problem as there are waves for it, or four where a wave has several problems
@@ -875,6 +899,7 @@ int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob,
     a.nblocks = (int)((M + block - 1) / block);
     const int64_t each = nprob * 2 > waves ? 4 : waves / nprob;
     a.nparts = each < a.nblocks ? (int)each : a.nblocks;
+    ids = a.nparts == a.nblocks && block == base * ct;
     *nparts_out = a.nparts;
   }
   const int64_t units = (int64_t)a.nparts * nprob;
@@ -899,14 +924,14 @@ int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob,
   size_t smem = (size_t)a.md.nw * 16 + (size_t)a.md.nbias * 4 + 1024;
   if (!x) smem = (smem + 15) / 16 * 16 + 8 * sizeof(WaveDec);
   typedef void (*small_kernel)(SmallArgs);
-#define VF_SMALL(k, ct, gen, n1, n2, n3, n4) {k<ct, n1, gen>, k<ct, n2, gen>, k<ct, n3, gen>, k<ct, n4, gen>}
-  static constexpr small_kernel kerns[2][2][2][4] = {
-      {{VF_SMALL(k_small_bf16, 1, false, 1, 2, 3, 4), VF_SMALL(k_small_bf16, 2, false, 1, 2, 3, 4)},
-       {VF_SMALL(k_small_f32, 1, false, 2, 4, 6, 8), VF_SMALL(k_small_f32, 2, false, 2, 4, 6, 8)}},
-      {{VF_SMALL(k_small_bf16, 1, true, 1, 2, 3, 4), VF_SMALL(k_small_bf16, 2, true, 1, 2, 3, 4)},
-       {VF_SMALL(k_small_f32, 1, true, 2, 4, 6, 8), VF_SMALL(k_small_f32, 2, true, 2, 4, 6, 8)}}};
+#define VF_SMALL(k, ct, mode, n1, n2, n3, n4) {k<ct, n1, mode>, k<ct, n2, mode>, k<ct, n3, mode>, k<ct, n4, mode>}
+#define VF_SMALL_ALL(mode)                                                                                  \
+  {{VF_SMALL(k_small_bf16, 1, mode, 1, 2, 3, 4), VF_SMALL(k_small_bf16, 2, mode, 1, 2, 3, 4)},              \
+   {VF_SMALL(k_small_f32, 1, mode, 2, 4, 6, 8), VF_SMALL(k_small_f32, 2, mode, 2, 4, 6, 8)}}
+  static constexpr small_kernel kerns[3][2][2][4] = {VF_SMALL_ALL(GIVEN), VF_SMALL_ALL(COLLECTED), VF_SMALL_ALL(IDS)};
+#undef VF_SMALL_ALL
 #undef VF_SMALL
-  const small_kernel kern = kerns[x ? 0 : 1][bf16 ? 0 : 1][ct - 1][a.md.NT * base / 32 - 1];
+  const small_kernel kern = kerns[x ? GIVEN : ids ? IDS : COLLECTED][bf16 ? 0 : 1][ct - 1][a.md.NT * base / 32 - 1];
   vf_prof_scope prof(c, VF_PROF_SCORE);
   VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
   const int grid = units < ncu ? (int)units : ncu;

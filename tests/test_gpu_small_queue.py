@@ -18,7 +18,7 @@ def vf():
 
 
 @pytest.mark.parametrize("dtype", [I.FP32, I.BF16])
-@pytest.mark.parametrize("B,facs", [(1, 4), (9, 5), (40, 7), (70, 4), (300, 3), (1100, 2)])
+@pytest.mark.parametrize("B,facs", [(1, 4), (5, 4), (9, 5), (40, 7), (70, 4), (300, 3), (1100, 2)])
 def test_shares(vf, ovf, B, facs, dtype):
     """Ids, values and states of a batch are those of single problems, bit for bit, and the checker's; a beam's
     masked scores are +inf where an id is not valid (every survivor is a candidate of its parent)."""

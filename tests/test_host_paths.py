@@ -2,6 +2,7 @@
 allocation failures, launch limits, arguments of launches."""
 import ctypes as C
 import os
+import re
 import subprocess
 import sys
 
@@ -136,6 +137,25 @@ def prefix_step_in_call(stub, vf):
     vf.vf_destroy(ctx)
 
 
+def small_networks(stub, vf):
+    """Which ids the small networks' kernels take: as they come where a wave has one sub-tile of them, else
+    the valid ones."""
+    from paper_2011_14486_amd import inputs as I
+
+    def kernel(B, space, dtype):
+        dims = [64, 128, 128, 1]
+        ctx = context(vf, np.stack([I.tiny_conv_relu()] * B), space, I.model_record(I.MLP, dims, dtype), I.mlp_weights(dims))
+        stub.stub_clear()
+        assert vf.vf_argmin_step(ctx, 0, 0, None, None) == 0
+        vf.vf_destroy(ctx)
+        name, = [l for l in stub.stub_log().decode().splitlines() if "k_small" in l]
+        return [int(n) for n in re.findall(r"ILi(\d+)ELi(\d+)ELi(\d+)E", name)[0]]  # columns per lane, row tiles, which ids
+
+    for dtype, rows in ((I.FP32, 8), (I.BF16, 4)):
+        assert kernel(1, I.tiny_space(64), dtype) == [1, rows, 2]
+        assert kernel(64, I.tiny_space(64), dtype) == [2, rows, 1]
+
+
 def candidate_lists(stub, vf):
     """No memory for the candidate lists: a greedy schedule is decided on id ranges, whether it would
     have run layer by layer (64 problems) or in one launch (200)."""
@@ -188,7 +208,7 @@ def stub_path(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("case", ["recurrent_weights", "recurrent_spaces", "refused_opening", "prefix_step_in_call", "candidate_lists", "many_problems"])
+@pytest.mark.parametrize("case", ["recurrent_weights", "recurrent_spaces", "refused_opening", "prefix_step_in_call", "small_networks", "candidate_lists", "many_problems"])
 def test_host_path(stub_path, case):
     # (a process of its own: the stub takes the place of the whole runtime)
     r = subprocess.run([sys.executable, os.path.abspath(__file__), stub_path, case], cwd=ROOT, capture_output=True, text=True)
