@@ -41,6 +41,28 @@ int64_t dense_count(const vf_space *s) {
   return m;
 }
 
+// Per stage the share of the ids that are root-level candidates whose splits fit, mean over the problems:
+// those are valid behind any prefix.
+void note_root_share(vf_ctx *c) {
+  const vf_space &sp = c->space;
+  int root = 0;
+  for (int k = 0; k < sp.ncat; ++k) root += sp.cat[k] == VF_ROOT;
+  c->root_share.assign((size_t)c->S, 0.0f);
+  if (!root) return;
+  const double pairs = (double)root / (sp.ncat * sp.nsat), splits = (double)sp.nf[0] * sp.nf[1] * sp.nf[2];
+  for (int j = 0; j < c->S; ++j) {
+    double fit = 0.0;
+    for (int b = 0; b < c->B; ++b) {
+      const int32_t *w = c->h_stages[(size_t)b * c->S + j].w;
+      int n[3] = {0, 0, 0};
+      for (int d = 0; d < 3; ++d)
+        for (int k = 0; k < sp.nf[d]; ++k) n[d] += sp.fac[d][k] <= w[1 + d];
+      fit += (double)n[0] * n[1] * n[2];
+    }
+    c->root_share[j] = (float)(pairs * fit / (splits * c->B));
+  }
+}
+
 bool stages_ok(const vf_stage *st, int S, int B) {
   for (int b = 0; b < B; ++b)
     for (int j = 0; j < S; ++j) {
@@ -284,7 +306,10 @@ int vf_set_space(vf_ctx *c, const vf_space *s) {
   VF_HIP(c, hipMemcpyAsync(c->d_space, &c->space, sizeof(vf_space), hipMemcpyHostToDevice, c->stream));
   VF_HIP(c, hipStreamSynchronize(c->stream));
   c->has_space = true;
-  if (c->has_pipeline) return vf_reset_state(c);
+  if (c->has_pipeline) {
+    note_root_share(c);
+    return vf_reset_state(c);
+  }
   return VF_OK;
 }
 
@@ -316,6 +341,7 @@ int vf_set_pipeline(vf_ctx *c, const vf_stage *st, int S, int B) {
   }
   c->h_stages.assign(st, st + n);
   c->beam_checked = false;
+  note_root_share(c);
   VF_HIP(c, hipMemcpyAsync(c->d_stages, st, n * sizeof(vf_stage), hipMemcpyHostToDevice, c->stream));
   VF_HIP(c, hipStreamSynchronize(c->stream));  // the host array may go away after return
   rc = vfk_setup_tables(c);

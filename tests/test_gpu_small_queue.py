@@ -50,6 +50,38 @@ def test_shares(vf, ovf, B, facs, dtype):
             assert ok[c] and abs(sc[c] - vals[j, 2]) <= TOL[0 if dtype == I.FP32 else 1] * max(abs(sc[c]), np.sqrt(np.mean(sc[ok] ** 2)))
 
 
+@pytest.mark.parametrize("dtype", [I.FP32, I.BF16])
+@pytest.mark.parametrize("B,last", [(5, 8), (70, 8), (70, 99), (500, 99)])
+def test_mostly_valid(vf, ovf, B, last, dtype):
+    """Spaces of root-level candidates of which all or seven in eight are valid: a wave takes its ids as they
+    come.  A batch as single problems, single problems as the checker, a beam's survivors valid."""
+    sp = I.make_space([1, 2, 4], [1, 2, 4], [1, 2, 4, 5, 6, 7, 8, last], I.ALL_PERMS[:5], 2, 1, [I.ROOT], 1, 64)
+    pipe = I.tiny_conv_relu()
+    pipes = np.stack([pipe] * B)
+    assert (pipe[:, 1:4] >= [4, 4, 8]).all() and I.space_dense_count(sp) % 32 == 16
+    dims = [64, 96, 32, 1]
+    w, model = I.mlp_weights(dims, 5, bias_std=0.1), I.model_record(I.MLP, dims, dtype)
+    tol = TOL[0 if dtype == I.FP32 else 1]
+
+    def run(p, beam=False):
+        ctx = vf.vf_create(0)
+        vf.vf_set_space(ctx, sp); vf.vf_set_pipeline(ctx, p); vf.vf_set_model(ctx, model, w)
+        out = [t.cpu().numpy() for t in (vf.vf_beam_search(ctx)[:3] if beam else vf.vf_greedy_schedule(ctx))]
+        vf.vf_destroy(ctx)
+        return out
+    st, cids, vals = run(pipes)
+    s1, c1, v1 = (a[0] for a in run(pipe))
+    compare_schedule(ovf, pipe, sp, model, w, c1, v1, s1, tol)
+    assert (cids == c1).all() and (vals == v1).all() and (st == s1).all()
+    if B <= 70:
+        _, cids, vals = run(pipes, beam=True)
+        assert len(set(map(tuple, cids))) == B
+        for j in range(0, B, 7):
+            sc, ok = ovf.decision_scores(pipe, sp, model, w, cids[j, :1], 1)
+            c = cids[j, 1]
+            assert ok[c] and abs(sc[c] - vals[j, 1]) <= tol * max(abs(sc[c]), np.sqrt(np.mean(sc[ok] ** 2)))
+
+
 @pytest.mark.parametrize("const", [True, False])
 @pytest.mark.parametrize("K,fac", [(4, [1, 2, 4]), (5, [1, 2, 4]), (17, [1, 2, 4, 8]), (300, [1, 2, 4]), (1024, [1, 2])])
 def test_selection_from_masked_scores(vf, ovf, K, fac, const):

@@ -138,8 +138,8 @@ def prefix_step_in_call(stub, vf):
 
 
 def small_networks(stub, vf):
-    """Which ids the small networks' kernels take: as they come where a wave has one sub-tile of them, else
-    the valid ones."""
+    """Which ids the small networks' kernels take: as they come where a wave has one sub-tile of them or nearly all
+    are valid (then with the columns per lane for as many), else the valid ones."""
     from paper_2011_14486_amd import inputs as I
 
     def kernel(B, space, dtype):
@@ -154,6 +154,10 @@ def small_networks(stub, vf):
     for dtype, rows in ((I.FP32, 8), (I.BF16, 4)):
         assert kernel(1, I.tiny_space(64), dtype) == [1, rows, 2]
         assert kernel(64, I.tiny_space(64), dtype) == [2, rows, 1]
+        for last, ids in ((8, 2), (99, 2), (None, 1)):  # all valid, seven in eight, three in four
+            fc = [1, 2, 4, 5, 6, 7, 8, 8][:7] + [last] if last else [1, 2, 4, 5, 6, 8, 99, 99]
+            root = I.make_space([1, 2, 4, 8], [1, 2, 4, 8], fc, I.ALL_PERMS[:4], 2, 2, [I.ROOT], 1, 64)
+            assert kernel(200, root, dtype) == [2, rows, ids], last
 
 
 def candidate_lists(stub, vf):
