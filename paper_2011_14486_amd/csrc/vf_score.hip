@@ -1242,10 +1242,19 @@ static void padded_dev(const vf_ctx *c, int rt, vf_fast_dev *fd) {
 // bf16 MLPs of any other hidden widths: packed for k_mlp_fast with every hidden layer filled up to the same
 // multiple of 256.  A unit of zero weights is 0 behind its ReLU (also where an input is infinite: the
 // product's NaN has its sign bit set, and the ReLU makes a zero of that) and meets zero weights in the
-// next layer.  Up to 8 times the products of the network itself; k_mlp_bf16 waits for its weights and for its
-// inputs in turn.  1,000,000 vectors, before and now: 256-256-128-1 1343 -> 397 us, 256-256-256-256-1 1566 -> 512,
-// 512-256-128-1 2410 -> 653, 256-512-256-1 1606 -> 738, 256-1024-512-1 3363 -> 1932, 256-288-1 (3.6 times the products)
-// 1214 -> 431, 64-192-192-1 456 -> 194; 100 vectors 15-47 -> 14-30 us.
+// next layer.  k_mlp_bf16 waits for its weights and for its inputs in turn.  1,000,000 vectors, before and now:
+// 256-256-128-1 1343 -> 397 us, 256-256-256-256-1 1566 -> 512, 512-256-128-1 2410 -> 653, 256-512-256-1 1606 -> 738,
+// 256-1024-512-1 3363 -> 1932, 256-288-1 (3.6 times the products) 1214 -> 431, 64-192-192-1 456 -> 194; 100 vectors
+// 15-47 -> 14-30 us.
+// Where: at most 8 times the products of the network itself, and above 256 units not where small hidden layers
+// behind the first one are filled up to square ones that the first layer does not make up for: k_mlp_bf16 gains
+// with every input row, the filled-up network loses with every such layer.  100 / 500,000 vectors, k_mlp_bf16 and
+// filled up: inside the line 256-544-128-1 29.9 / 1135 and 29.5 / 892 us, 64-288-288-1 18.1 / 290 and 17.3 / 219,
+// 256-768-32-1 34.9 / 1303 and 29.2 / 893, 128-544-544-1 27.9 / 837 and 26.5 / 771; outside 64-288-256-128-64-1
+// 25 / 399 and 34 / 483, 64-288-160-96-1 20.3 / 326 and 25.6 / 349, 256-640-320-160-1 42.6 / 1533 and 53.9 / 1472,
+// 64-544-288-1 23.1 / 653 and 24.9 / 648, 192-544-128-1 26.9 / 970 and 28.0 / 824, 512-544-288-96-1 49.6 / 2092 and
+// 61.9 / 1777.  Up to 256 units all of 14 networks gained, at 8 times the products too (64-32-256-1 13.6 / 180 and
+// 13.9 / 94).
 static int pack_padded(vf_ctx *c, const float *wdev) {
   const vf_model &m = c->model;
   vf_packed_model &pm = c->pm;
@@ -1260,6 +1269,9 @@ static int pack_padded(vf_ctx *c, const float *wdev) {
   const int rt = maxh <= 256 ? 1 : maxh <= 512 ? 2 : 4, W = 256 * rt;
   if (rt < 4 && m.dims[0] > 512) return VF_OK;  // (tiles of 128 would not fit the LDS)
   if ((double)m.dims[0] * W + (L - 2.0) * W * W > 8.0 * real) return VF_OK;
+  double filled = 0.0;  // of the layers behind the first one: how far the larger part of each is filling
+  for (int l = 1; l < L - 1; ++l) filled += 1.0 - 2.0 * m.dims[l] * m.dims[l + 1] / ((double)W * W);
+  if (rt > 1 && 256.0 * filled > 48.0 + 0.8 * (m.dims[0] < 256 ? m.dims[0] : 256)) return VF_OK;
   auto blocks = [](size_t n) { return dim3((unsigned)((n + 255) / 256)); };
   int steps = m.dims[0] / 16 + (L - 2) * (W / 16);
   const int pad = 8;

@@ -53,7 +53,7 @@ def layers(dims, w):
 
 
 # one, two and four row tiles per wave, one and two filled-up layers behind the infinite value
-@pytest.mark.parametrize("dims", [[64, 160, 96, 1], [64, 160, 96, 192, 1], [64, 288, 160, 1], [192, 512, 480, 32, 1],
+@pytest.mark.parametrize("dims", [[64, 160, 96, 1], [64, 160, 96, 192, 1], [64, 288, 288, 1], [192, 512, 480, 32, 1],
                                   [64, 544, 608, 1], [64, 992, 1024, 96, 1]])
 @pytest.mark.parametrize("passes", [False, True])
 def test_infinite_activations(vf, ovf, dims, passes):
