@@ -1033,9 +1033,10 @@ struct LstmHeldLds {
 // minimum.  A step takes nothing from memory but the inputs of the step after next.  k_lstm_bf16 streams the
 // weights out of L2 for every step and has 32 units per wave, so that of its eight waves one, two, ... are
 // at work for H = 32, 64, ...  What is left of a step is the chain of its products, its gates and the
-// barrier (0.9 us at H = 32, 2 at 128).  Before and now, T = 50, 64 sequences, F = 32: H = 32 155 -> 50 us, 64
-// 170 -> 55, 128 197 -> 87, 192 334 -> 133; F = 128: H = 32 200 -> 68, 128 245 -> 103; T = 25, 16,384 sequences,
-// F = 128: H = 32 114 -> 50 us, 64 125 -> 53, 96 136 -> 103, 128 147 -> 119; F = 32, H = 192 181 -> 148.
+// barrier (0.9 us at H = 32, 2 at 128).  k_lstm_bf16 and this, T = 50, 64 sequences, F = 32: H = 32 155 / 50 us, 64
+// 169 / 54, 128 196 / 87, 192 333 / 133; F = 128: H = 32 199 / 68, 128 245 / 103; F = 160, H = 64 266 / 73; F = 256:
+// H = 32 300 / 104, 64 312 / 88, 96 325 / 119; T = 10, 16,384 sequences, F = 96: H = 32 49 / 25 us, 128 69 / 58;
+// F = 128: H = 32 52 / 26, 64 57 / 30, 96 65 / 52, 128 76 / 62; F = 256: H = 32 80 / 35, 96 94 / 66; F = 32, H = 192 95 / 78.
 template <int KSX, int KSH, int WPE, int RK>
 __global__ __launch_bounds__(KSH * 64, WPE) void k_lstm_held(const uint16_t *x, int64_t M, int T, LstmDev md, int span, float *scores,
                                                             float *pval, int32_t *pidx) {
@@ -1772,36 +1773,64 @@ static int score_mlp(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob
 }
 
 namespace {
-// k_lstm_held for F inputs and H units (fn null: the weights are more than the registers and LDS of a
-// compute unit, or F is a width without an instance) and its workgroups per compute unit.
-struct LstmHeld {
-  void (*fn)(const uint16_t *, int64_t, int, LstmDev, int, float *, float *, int32_t *);
-  int per_cu;
-  size_t lds;
+// How k_lstm_held holds the weights of F = 16 KSX inputs and H = 16 KSH units: wpe waves per SIMD share its
+// registers, of which a step needs some for itself (accumulators, cells, addresses, the inputs under way)
+// and a k-step of weights takes eight; what does not fit them goes to the LDS.  Four or three waves per SIMD
+// where they can be of several workgroups and (nearly) all weights stay in registers.
+template <int KSX, int KSH>
+struct LstmHeldPlan {
+  static constexpr int KS = KSX + KSH, XPT = (KSX + KSH - 1) / KSH;
+  static constexpr int most(int wpe) { return ((wpe == 4 ? 128 - 80 : wpe == 3 ? 168 - 96 : 256 - 128) - 5 * (XPT - 1)) / 8; }
+  static constexpr int wpe = KS <= most(4) && 16 / KSH >= 2 ? 4 : KSH > 8 || (KS <= most(3) + 1 && 12 / KSH >= 2) ? 3 : 2;
+  static constexpr size_t room = 160 * 1024, lds_of_less = sizeof(LstmHeldLds<KSX, KSH, KS - (KS < most(wpe) ? KS : most(wpe)) + 1>);
+  // (more than eight waves: a k-step less in registers where the LDS has room for it, H = 160 2 to 3 % faster)
+  static constexpr int RK = KS < most(wpe) ? KS : KSH > 8 && lds_of_less <= room ? most(wpe) - 1 : most(wpe);
+  static constexpr size_t lds = sizeof(LstmHeldLds<KSX, KSH, KS - RK>);
+  static constexpr bool fits = KSH <= 4 * wpe && lds <= room;
+  static constexpr int by_lds = (int)(room / lds), by_waves = 4 * wpe / KSH;
+  static constexpr int per_cu = by_lds < by_waves ? by_lds : by_waves;
 };
-template <int KSX, int KSH, int WPE, int RK>
-LstmHeld lstm_held(int per_cu) {
-  return {k_lstm_held<KSX, KSH, WPE, RK>, per_cu, sizeof(LstmHeldLds<KSX, KSH, KSX + KSH - RK>)};
+// The kernel for F inputs and H units and its workgroups per compute unit; fn null: the weights are more
+// than the registers and LDS of a compute unit.
+struct LstmHeld {
+  void (*fn)(const uint16_t *, int64_t, int, LstmDev, int, float *, float *, int32_t *) = nullptr;
+  int per_cu = 0;
+  size_t lds = 0;
+};
+template <int KSX, int KSH>
+LstmHeld lstm_held() {
+  using Plan = LstmHeldPlan<KSX, KSH>;
+  LstmHeld h;
+  if constexpr (Plan::fits) {
+    h.fn = k_lstm_held<KSX, KSH, Plan::wpe, Plan::RK>;
+    h.per_cu = Plan::per_cu;
+    h.lds = Plan::lds;
+  }
+  return h;
+}
+template <int KSX>
+LstmHeld lstm_held_inputs(int H) {
+  switch (H / 32) {
+    case 1: return lstm_held<KSX, 2>();
+    case 2: return lstm_held<KSX, 4>();
+    case 3: return lstm_held<KSX, 6>();
+    case 4: return lstm_held<KSX, 8>();
+    case 5: return lstm_held<KSX, 10>();
+    case 6: return lstm_held<KSX, 12>();
+    default: return LstmHeld();  // (W_hh alone is more)
+  }
 }
 LstmHeld lstm_held_of(int F, int H) {
-  switch (F * 1000 + H) {
-    case 32032: return lstm_held<2, 2, 4, 4>(8);
-    case 32064: return lstm_held<2, 4, 4, 6>(4);
-    case 32096: return lstm_held<2, 6, 3, 8>(2);
-    case 32128: return lstm_held<2, 8, 2, 10>(1);
-    case 32160: return lstm_held<2, 10, 3, 8>(1);
-    case 32192: return lstm_held<2, 12, 3, 9>(1);
-    case 64032: return lstm_held<4, 2, 3, 6>(6);
-    case 64064: return lstm_held<4, 4, 3, 8>(3);
-    case 64096: return lstm_held<4, 6, 3, 9>(2);
-    case 64128: return lstm_held<4, 8, 2, 12>(1);
-    case 64160: return lstm_held<4, 10, 3, 8>(1);
-    case 128032: return lstm_held<8, 2, 2, 10>(4);
-    case 128064: return lstm_held<8, 4, 2, 12>(2);
-    case 128096: return lstm_held<8, 6, 2, 14>(1);
-    case 128128: return lstm_held<8, 8, 2, 16>(1);
+  switch (F / 32) {
+    case 1: return lstm_held_inputs<2>(H);
+    case 2: return lstm_held_inputs<4>(H);
+    case 3: return lstm_held_inputs<6>(H);
+    case 4: return lstm_held_inputs<8>(H);
+    case 5: return lstm_held_inputs<10>(H);
+    case 6: return lstm_held_inputs<12>(H);
+    case 7: return lstm_held_inputs<14>(H);
+    default: return lstm_held_inputs<16>(H);
   }
-  return {nullptr, 0, 0};
 }
 }  // namespace
 

@@ -54,10 +54,10 @@ def test_ends_of_tiles(vf, ovf, H, fx, fy, fc):
     compare_schedule(ovf, pipe, sp, model, w, cids, vals, st, TOL[1])
 
 
-@pytest.mark.parametrize("F,H", [(F, H) for F in (32, 64, 128) for H in range(32, 193, 32)])
+@pytest.mark.parametrize("F,H", [(F, H) for F in range(32, 257, 32) for H in range(32, 193, 32)])
 def test_sequences(vf, ovf, F, H):
-    """Sequences through the networks that a workgroup holds and (F = 128 with H > 128, 64 with 192) the
-    smallest ones that it does not: one tile, ragged tiles, minima per group."""
+    """Sequences through the networks that a workgroup holds and the smallest ones that it does not (F = 96 with
+    H = 160, 256 with 128): one tile, ragged tiles, minima per group."""
     import torch
     w, model = I.lstm_weights(F, H, seed=4, bias_std=0.2), I.model_record(I.LSTM, [F, H, 1], I.BF16)
     ctx = vf.vf_create(0)

@@ -160,6 +160,24 @@ def small_networks(stub, vf):
             assert kernel(200, root, dtype) == [2, rows, ids], last
 
 
+def sequence_widths(stub, vf):
+    """Sequences: a network whose weights fit a compute unit is held there, whatever its widths."""
+    from paper_2011_14486_amd import inputs as I
+    widest = {32: 192, 64: 160, 96: 128, 128: 128, 160: 128, 192: 128, 224: 96, 256: 96}
+    ctx = context(vf, np.stack([I.resnet18_shaped()]), I.resnet18_space(256), I.model_record(I.LSTM, [32, 32, 1], I.BF16),
+                  I.lstm_weights(32, 32))
+    at, n = C.c_void_p(4096), C.c_int64  # (addresses are written down, not used)
+    for F in widest:
+        for H in range(32, 257, 32):
+            m, w = I.model_record(I.LSTM, [F, H, 1], I.BF16), I.lstm_weights(F, H)
+            assert vf.vf_set_model(ctx, C.c_void_p(m.ctypes.data), C.c_void_p(w.ctypes.data), w.size) == 0
+            stub.stub_clear()
+            assert vf.vf_score(ctx, at, 1, n(1000), n(7), C.c_int32(0), at, at, at) == 0
+            log = stub.stub_log().decode()
+            assert ("k_lstm_held" in log) == (H <= widest[F]) and ("k_lstm_bf16" in log) == (H > widest[F]), (F, H, log)
+    vf.vf_destroy(ctx)
+
+
 def candidate_lists(stub, vf):
     """No memory for the candidate lists: a greedy schedule is decided on id ranges, whether it would
     have run layer by layer (64 problems) or in one launch (200)."""
@@ -212,7 +230,7 @@ def stub_path(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("case", ["recurrent_weights", "recurrent_spaces", "refused_opening", "prefix_step_in_call", "small_networks", "candidate_lists", "many_problems"])
+@pytest.mark.parametrize("case", ["recurrent_weights", "recurrent_spaces", "refused_opening", "prefix_step_in_call", "small_networks", "sequence_widths", "candidate_lists", "many_problems"])
 def test_host_path(stub_path, case):
     # (a process of its own: the stub takes the place of the whole runtime)
     r = subprocess.run([sys.executable, os.path.abspath(__file__), stub_path, case], cwd=ROOT, capture_output=True, text=True)
