@@ -119,8 +119,8 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t sh
     refused[0] = 0;
     return err(hipErrorLaunchFailure);
   }
-  /* (k_seq_step_wide's second argument is its weights) */
-  const void *weights = strstr(name, "k_seq_step_wide") ? *(void **)args[1] : (void *)1;
+  /* (the second argument of k_seq_step_held and k_seq_step_wide is their weights) */
+  const void *weights = strstr(name, "k_seq_step_held") || strstr(name, "k_seq_step_wide") ? *(void **)args[1] : (void *)1;
   if (log_len + 300 < sizeof log_text)
     log_len += (size_t)snprintf(log_text + log_len, sizeof log_text - log_len, "%s %u %d\n", name, g.x, weights != NULL);
   return hipSuccess;

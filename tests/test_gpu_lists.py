@@ -74,8 +74,8 @@ def test_second_round_of_long_decisions_in_one_launch(vf, B):
 
 @pytest.mark.parametrize("H", [32, 96, 256])
 def test_recurrent_batch_equals_single_problems(vf, H):
-    """Many candidates run in tiles of 96, few in tiles of 64, with the same arithmetic per candidate:
-    ids and values of every layer are bit-identical (idle waves at H = 32 and 96; ragged tiles; noise)."""
+    """Many candidates run in the forms for throughput, few in those for latency, with the same arithmetic per
+    candidate: ids and values of every layer are bit-identical (ragged tiles; noise)."""
     sp, B = I.resnet18_space(256), 14                # 14 * 64 tiles of 64 ids: more than 3 * 256
     pipes = np.stack([I.random_pipeline(5, 90 + b) for b in range(B)])
     w, model = I.lstm_weights(64, H, seed=6, bias_std=0.2), I.model_record(I.LSTM, [64, H, 1], I.BF16)

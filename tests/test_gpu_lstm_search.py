@@ -168,7 +168,7 @@ def test_rollouts_with_noise(vf, ovf):
 
 @pytest.mark.parametrize("K", [1, 6, 128])
 def test_beam_search(vf, ovf, K):
-    """(128 slots of six tiles of 64 ids: scores from tiles of 96)"""
+    """One slot, a few, and 128 of six tiles of 64 ids (the forms for throughput)."""
     sp = I.make_space([1, 2, 4], [1, 4], [1, 2], [(0, 1, 2), (2, 1, 0)], 2, 2,
                       [I.ROOT, I.L1, I.L2, I.INLINE], 1, 64)
     pipe = I.random_pipeline(4, 31)
@@ -230,8 +230,8 @@ def test_saturated_gates_of_sequences(vf, ovf, T):
 
 @pytest.mark.parametrize("B", [3, 384])
 def test_saturated_gates_in_the_search(vf, ovf, B):
-    """Tiles of 64 entries (3 problems) and of 96 (384 problems of two tiles of ids each); 70 stages, so
-    that the prefix's cells saturate the output product as well."""
+    """A few tiles (3 problems) and many (384 problems of two tiles of 64 ids each); 70 stages, so that the
+    prefix's cells saturate the output product as well."""
     sp = I.make_space([1, 2], [1, 4], [1, 8], I.XC_INNER_PERMS[:2], 1, 2, [I.ROOT, I.L1, I.INLINE], 1, 64)
     assert B < 100 or (I.space_dense_count(sp) + 63) // 64 * B >= 3 * 256
     pipes = np.stack([I.random_pipeline(70, 5 + b % 3) for b in range(B)])

@@ -39,28 +39,35 @@ def context(vf, pipes, space, model, w):
 
 
 def recurrent_weights(stub, vf):
-    """The second form of the recurrent weights cannot be had: the search goes on with tiles of 64, now
-    and when memory is back; k_seq_step_wide never runs without its weights."""
+    """The second form of the recurrent weights, or the rows of the candidates, cannot be had: the search goes on
+    with the scorer that needs neither, now and when memory is back; the others never run without their weights."""
     from paper_2011_14486_amd import inputs as I
-    H, B = 256, 32
-    ctx = context(vf, np.stack([I.resnet18_shaped()] * B), I.resnet18_space(256), I.model_record(I.LSTM, [64, H, 1], I.BF16),
-                  I.lstm_weights(64, H))
-    size = H // 32 * (2 * (H // 16) + 8) * 1024 * 2
-    stub.stub_fail(size, size)
-    rc = vf.vf_argmin_step(ctx, 0, 1, None, None)
-    stub.stub_fail(1, 0)
-    assert rc == 0, rc
-    assert vf.vf_argmin_step(ctx, 1, 1, None, None) == 0
-    steps = [l.split() for l in stub.stub_log().decode().splitlines() if "k_seq_step" in l]
-    assert len(steps) == 2 and all(s[2] == "1" for s in steps), steps
-    vf.vf_destroy(ctx)
-    # with memory: tiles of 96
-    stub.stub_clear()
-    ctx = context(vf, np.stack([I.resnet18_shaped()] * B), I.resnet18_space(256), I.model_record(I.LSTM, [64, H, 1], I.BF16),
-                  I.lstm_weights(64, H))
-    assert vf.vf_argmin_step(ctx, 0, 1, None, None) == 0
-    assert "k_seq_step_wide" in stub.stub_log().decode()
-    vf.vf_destroy(ctx)
+    B = 32
+    for H, kernel in ((64, "k_seq_step_held"), (256, "k_seq_step_wide")):
+        args = (np.stack([I.resnet18_shaped()] * B), I.resnet18_space(256), I.model_record(I.LSTM, [64, H, 1], I.BF16),
+                I.lstm_weights(64, H))
+        for size in (H // 32 * (2 * (H // 16) + 8) * 1024 * 2, B * 4096 * 128):
+            ctx = context(vf, *args)
+            assert vf.vf_padded_count(ctx) == 4096
+            stub.stub_clear()
+            stub.stub_fail(size, size)
+            rc = vf.vf_argmin_step(ctx, 0, 1, None, None)
+            stub.stub_fail(1, 0)
+            assert rc == 0, rc
+            assert vf.vf_argmin_step(ctx, 1, 1, None, None) == 0
+            log = stub.stub_log().decode()
+            steps = [l.split() for l in log.splitlines() if "k_seq_step" in l]
+            assert len(steps) == 2 and all(s[2] == "1" for s in steps), steps
+            assert "k_seq_step_" not in log and log.count("k_seq_compact") == 2 and "k_seq_open" not in log, log
+            vf.vf_destroy(ctx)
+        # with memory
+        stub.stub_clear()
+        ctx = context(vf, *args)
+        assert vf.vf_argmin_step(ctx, 0, 1, None, None) == 0
+        log = stub.stub_log().decode()
+        assert kernel in log and "k_seq_open" in log and "k_seq_compact" not in log
+        assert all(l.split()[2] == "1" for l in log.splitlines())
+        vf.vf_destroy(ctx)
 
 
 def recurrent_spaces(stub, vf):
