@@ -262,7 +262,9 @@ int vf_timer_elapsed_ms(vf_ctx *ctx, float *ms_host);
 /* Per-kernel timing for benchmarks.  While enabled, vf_featurize, vf_score,
  * vf_argmin_step and vf_greedy_schedule bracket each launch of their featurize
  * (which = 0), scoring (1) and commit (2) kernels with HIP events on the context's
- * stream.  vf_profile_read synchronises, returns the summed duration and the number
+ * stream.  (Most searches featurize inside the scoring kernel; with a recurrent network the
+ * launch that lists a decision's candidates and their features is the featurize one.)
+ * vf_profile_read synchronises, returns the summed duration and the number
  * of launches of one kind since the last read of that kind, and clears them. */
 enum { VF_PROF_FEATURIZE = 0, VF_PROF_SCORE = 1, VF_PROF_COMMIT = 2 };
 int vf_profile_enable(vf_ctx *ctx, int enable);

@@ -1211,10 +1211,13 @@ int vfk_seq_step(vf_ctx *c, int stage, float *scores, int64_t ld_scores, int noi
   na.stage = noise_stage; na.first_rollout = c->noise_first;
   *nparts_out = nparts;
   if (held) {
-    hipLaunchKernelGGL(k_seq_open, dim3((unsigned)nadv + (unsigned)(c->Mpad / SEQ_OPEN) * (unsigned)c->B), dim3(1024), 0, c->stream,
-                       c->d_decpack, (uint32_t)c->M, (int64_t)c->Mpad, c->d_seq_list, c->d_seq_count, c->d_seq_rows, scores, c->d_pval,
-                       c->d_pidx, nparts, hk.tile, nadv, adv);
-    VF_HIP(c, hipGetLastError());
+    {
+      vf_prof_scope prof(c, VF_PROF_FEATURIZE);
+      hipLaunchKernelGGL(k_seq_open, dim3((unsigned)nadv + (unsigned)(c->Mpad / SEQ_OPEN) * (unsigned)c->B), dim3(1024), 0, c->stream,
+                         c->d_decpack, (uint32_t)c->M, (int64_t)c->Mpad, c->d_seq_list, c->d_seq_count, c->d_seq_rows, scores,
+                         c->d_pval, c->d_pidx, nparts, hk.tile, nadv, adv);
+      VF_HIP(c, hipGetLastError());
+    }
     if (nadv) advanced(c);
     vf_prof_scope prof(c, VF_PROF_SCORE);
     VF_HIP(c, hipFuncSetAttribute((const void *)hk.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)hk.lds));

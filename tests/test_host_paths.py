@@ -185,6 +185,19 @@ def sequence_widths(stub, vf):
     vf.vf_destroy(ctx)
 
 
+def profiled_launches(stub, vf):
+    """The recurrent search's launches that the per-kernel timing brackets, per decision: the one that makes the
+    features, the scorer, the commit."""
+    from paper_2011_14486_amd import inputs as I
+    ctx = context(vf, np.stack([I.random_pipeline(4, 5)] * 2), I.tiny_space(64), I.model_record(I.LSTM, [64, 64, 1], I.BF16),
+                  I.lstm_weights(64, 64))
+    assert vf.vf_profile_enable(ctx, 1) == 0 and vf.vf_greedy_schedule(ctx, 0, 3, None, None, None) == 0
+    for which in range(3):
+        n = C.c_int64()
+        assert vf.vf_profile_read(ctx, which, None, C.byref(n)) == 0 and n.value == 4, (which, n.value)
+    vf.vf_destroy(ctx)
+
+
 def candidate_lists(stub, vf):
     """No memory for the candidate lists: a greedy schedule is decided on id ranges, whether it would
     have run layer by layer (64 problems) or in one launch (200)."""
@@ -237,7 +250,7 @@ def stub_path(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("case", ["recurrent_weights", "recurrent_spaces", "refused_opening", "prefix_step_in_call", "small_networks", "sequence_widths", "candidate_lists", "many_problems"])
+@pytest.mark.parametrize("case", ["recurrent_weights", "recurrent_spaces", "refused_opening", "prefix_step_in_call", "small_networks", "sequence_widths", "profiled_launches", "candidate_lists", "many_problems"])
 def test_host_path(stub_path, case):
     # (a process of its own: the stub takes the place of the whole runtime)
     r = subprocess.run([sys.executable, os.path.abspath(__file__), stub_path, case], cwd=ROOT, capture_output=True, text=True)
