@@ -64,7 +64,7 @@ hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hip
 }
 hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t st) { (void)st; memset(d, v, n); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t s) { (void)s; return hipSuccess; }
-hipError_t hipEventCreate(hipEvent_t *e) { *e = NULL; return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)static_array; return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned f) { (void)f; *e = NULL; return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t e) { (void)e; return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { (void)e; (void)s; return hipSuccess; }
