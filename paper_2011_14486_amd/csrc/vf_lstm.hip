@@ -696,8 +696,10 @@ struct SeqHeldLds {
 // step now is the vector work of the gates, 28 instructions per cell: a wave by itself issues one
 // every six to seven cycles, so a SIMD wants several - 8, 4 and 2 workgroups per compute unit for H = 32,
 // 64 and 96, each at its own place in a step, so that one's gates run under another's products.
-// Measured per schedule of 64 problems of 20 layers, before and now: H = 32 5.83 -> 1.65 ms, 64 7.07 ->
-// 2.89, 128 7.78 -> 5.04, 192 11.2 -> 6.9; one problem: 1.16 -> 0.70, 1.22 -> 0.75, 1.37 -> 0.96, 2.0 -> 1.24 ms.
+// Schedules of 20 ResNet-18-shaped layers of 4096 ids (each problem its own widths and resolution), with
+// W_hh streamed and now: 64 problems H = 32 5.52 -> 1.75 ms, 64 4.90 -> 2.16, 128 6.45 -> 4.36, 192 12.4 -> 7.8;
+// one problem 1.15 -> 0.56, 1.21 -> 0.61, 1.36 -> 0.83, 2.01 -> 1.16 ms (in all; the opening of a decision and the
+// prefix's step have become cheaper as well).
 template <int KS, int WPE, int RK>
 __global__ __launch_bounds__(KS * 64, WPE) void k_seq_step_held(SeqDev md, const uint16_t *w_wide, const uint16_t *rows, int stage, int B,
                                                           float *scores, int64_t ld_scores, float *pval, int32_t *pidx, int nparts,
@@ -809,8 +811,8 @@ __global__ __launch_bounds__(KS * 64, WPE) void k_seq_step_held(SeqDev md, const
 // is as long as its gates, which take a single wave 1700 cycles for 8 x 64 cells with products beside
 // them, where the products take 1000 to 1400; without the phases both waves contract at the same time
 // and the second one does its gates alone (+3 %).  Holding more of the weights or more waves in flight
-// both want the registers of the other.  64 problems of 20 layers, H = 256: 17.4 -> 15.5 ms (tiles of 96, all
-// weights streamed), 8: 3.48 -> 2.85, one: 2.24 -> 1.55.
+// both want the registers of the other.  The schedules above, H = 256: 64 problems 13.7 -> 11.0 ms (before: tiles of
+// 96, all weights streamed), 8: 2.87 -> 2.42, one: 2.23 -> 1.49.
 template <int KS, int CT, int RK, int LK>
 struct SeqWidePlan {
   static constexpr int NW = KS / 2, SK = KS - RK - LK;
@@ -1030,8 +1032,9 @@ void vfk_seq_free(vf_ctx *c) {
 
 // The scorer for networks of H hidden units: its workgroups per compute unit, threads, LDS, candidates
 // per tile.  many: more than about one round of tiles.  At H = 128 two workgroups of 128 registers then
-// are better than one of all (64 problems 5.66 -> 5.04 ms; 8: 1.30 against 1.39), above 192 tiles of 64
-// (H = 256: 64 problems 16.8 -> 15.5 ms; 8: 2.84 against 2.98).
+// are better than one of all, above 192 tiles of 64.  Schedules as above, not many / many: H = 128 4
+// problems 0.89 / 1.11 ms, 8: 1.15 / 1.18, 12: 1.41 / 1.35, 16: 1.64 / 1.59, 64: 4.88 / 4.36; H = 224 8: 1.76 / 1.97, 12:
+// 2.47 / 2.43, 16: 2.67 / 2.82, 64: 8.42 / 7.96; H = 256 8: 2.46 / 2.54, 12: 3.08 / 2.82, 16: 3.75 / 3.77, 64: 12.3 / 11.4.
 struct HeldKernel {
   void (*fn)(SeqDev, const uint16_t *, const uint16_t *, int, int, float *, int64_t, float *, int32_t *, int, NoiseArgs);
   int per_cu, threads, tile;

@@ -150,6 +150,8 @@ __device__ __forceinline__ void stage_small(const SmallArgs &a, uint4 *wl, float
 // on one, and with neighbours on different XCDs those lines are fetched twice.  Neighbours dealt out / in
 // runs, odd numbers of vectors: 64-128-128-1 bf16, 200,003: 32.8 / 29.0 us; 64-32-1 bf16, 500,003: 44.1 / 34.4;
 // 256-128-128-128-1 bf16, 200,003: 76.2 / 61.5; rows that begin on a line, and fp32 networks: the same to 1 %.
+// (One set of vectors over and over, part of which the last cache keeps.  Out of memory, 16, 8 and 6 sets in
+// turn, a gigabyte together: 32.2 / 29.5, 40.3 / 36.3, 78.4 / 69.7.)
 __device__ __forceinline__ int first_unit(const SmallArgs &a, int w, int &end) {
   const int q = (int)blockIdx.x >> a.xcd_bits, x = (int)blockIdx.x - (q << a.xcd_bits), from = x * a.run;
   end = from + a.run < a.units ? from + a.run : a.units;

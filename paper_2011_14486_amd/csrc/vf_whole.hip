@@ -638,10 +638,11 @@ __global__ __launch_bounds__(256) void k_zero_u32(unsigned int *p, size_t n) {
 }  // namespace
 
 // Candidates per tile of a LAYER launch: 128 with 512 hidden units (64 with 1024), but 64 while all
-// ids of a decision make at most two tiles of 64 per compute unit, which two workgroups of 64 share
-// (20 layers of 4096 ids, lists of 128 / 64, beams of 6 and 8: 256-512-512-1 972 / 876 and 990 / 895 us,
-// 256-512-512-512-1 1151 / 974 and 1164 / 990); at most one with a single hidden layer, where the opening of
-// the tile is most of it and is repeated by twice as many (256-512-1: 828 / 842 and 835 / 851).
+// ids of a decision make at most two tiles of 64 per compute unit: two in five of them are valid, as a
+// rule, so that the lists make about one round of tiles of 64, where tiles of 128 leave every other unit
+// idle (20 layers of 4096 ids, lists of 128 / 64, beams of 6 and 8: 256-512-512-1 972 / 876 and 990 / 895
+// us, 256-512-512-512-1 1151 / 974 and 1164 / 990); at most one with a single hidden layer, where the
+// opening of the tile is most of it and is repeated by twice as many (256-512-1: 828 / 842 and 835 / 851).
 static int layer_tile(const vf_ctx *c) {
   int ncu = 256;
   (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
