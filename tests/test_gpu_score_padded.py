@@ -25,10 +25,10 @@ def score(vf, dims, w, raw, group=0):
 
 
 # one, two and four row tiles per wave; a filled-up layer in front of a full one and behind it; the widest
-# input of the smallest form; eight times the products and just above (the kernel for any width)
+# input of the smallest form; eight times the products and just above (the kernel for any width); the most LDS
 @pytest.mark.parametrize("dims", [[256, 256, 128, 1], [64, 32, 256, 1], [512, 160, 224, 1], [256, 288, 1], [192, 512, 480, 32, 1],
                                   [256, 544, 1024, 1], [64, 992, 1024, 1], [1024, 608, 1], [64, 160, 96, 1], [64, 288, 32, 1],
-                                  [96, 256, 1], [1024, 256, 1]])
+                                  [96, 256, 1], [1024, 256, 1], [1024, 1024, 1024, 1024, 1024, 1024, 992, 1]])
 @pytest.mark.parametrize("M,group", [(1, 0), (64, 0), (200, 128), (1025, 0)])
 def test_widths(vf, ovf, dims, M, group):
     rng = np.random.default_rng(dims + [M])

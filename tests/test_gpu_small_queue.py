@@ -54,7 +54,7 @@ def test_shares(vf, ovf, B, facs, dtype):
 @pytest.mark.parametrize("B,last", [(5, 8), (70, 8), (70, 99), (500, 99)])
 def test_mostly_valid(vf, ovf, B, last, dtype):
     """Spaces of root-level candidates of which all or seven in eight are valid: a wave takes its ids as they
-    come.  A batch as single problems, single problems as the checker, a beam's survivors valid."""
+    come.  A batch as single problems, single problems as the oracle, a beam's survivors valid."""
     sp = I.make_space([1, 2, 4], [1, 2, 4], [1, 2, 4, 5, 6, 7, 8, last], I.ALL_PERMS[:5], 2, 1, [I.ROOT], 1, 64)
     pipe = I.tiny_conv_relu()
     pipes = np.stack([pipe] * B)
