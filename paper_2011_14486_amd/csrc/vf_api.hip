@@ -47,7 +47,7 @@ void note_root_share(vf_ctx *c) {
   const vf_space &sp = c->space;
   int root = 0;
   for (int k = 0; k < sp.ncat; ++k) root += sp.cat[k] == VF_ROOT;
-  c->root_share.assign((size_t)c->S, 0.0f);
+  for (int j = 0; j < c->S; ++j) c->root_share[j] = 0.0f;
   if (!root) return;
   const double pairs = (double)root / (sp.ncat * sp.nsat), splits = (double)sp.nf[0] * sp.nf[1] * sp.nf[2];
   for (int j = 0; j < c->S; ++j) {

@@ -131,7 +131,7 @@ struct vf_ctx {
   int32_t noise_first = 0;
   std::vector<vf_stage> h_stages;  // host copy of the stage records
   bool beam_checked = false;       // all slots verified to hold the same pipeline
-  std::vector<float> root_share;   // [S] share of the ids that are root-level candidates (valid behind any prefix)
+  float root_share[4096] = {};     // [S] share of the ids that are root-level candidates (valid behind any prefix)
 
   vf_model model;
   vf_packed_model pm;
