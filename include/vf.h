@@ -199,7 +199,9 @@ int vf_argmin_step(vf_ctx *ctx, int stage, int commit, int32_t *best_cid_dev, fl
  * out_states_dev[batch][S] the committed states s_1..s_n so far (all stages),
  * out_cids_dev[batch][S] the chosen candidate ids, out_values_dev[batch][S] their
  * values; entries of stages not scheduled yet are zero states, -1 and +inf.
- * A few problems take one launch per layer, more of them two.  With a problem for most compute
+ * A few problems (all tiles of a decision at once on the compute units) take one launch in which as many
+ * workgroups as a decision has tiles share a problem: they exchange the tiles' minima, and one that waits in
+ * vain for a minimum works it out itself.  More problems take two launches per layer.  With a problem for most compute
  * units, and from 24 problems on decisions of few candidates, the layers run inside one launch (the
  * model's tile must fit the LDS): with fewer problems than half the compute units several workgroups
  * share a problem from the start, with more a workgroup that has finished its own problems helps
@@ -286,7 +288,8 @@ int vf_sync_status(vf_ctx *ctx);
  * launch of vf_greedy_schedule, in polling rounds (default 2^22, seconds); a helper's wait
  * for work starts over whenever a problem finishes anywhere, so a launch that is merely long
  * does not run it out.  A wait that reaches the bound gives up: the launch still ends, see
- * vf_greedy_schedule for what follows.  A bound of 0 makes every wait that cannot be
+ * vf_greedy_schedule for what follows (with a few problems nothing does: the launch goes on and
+ * decides the same).  A bound of 0 makes every wait that cannot be
  * satisfied at once give up; meant for tests of that path. */
 int vf_set_wait_limit(vf_ctx *ctx, unsigned int rounds);
 

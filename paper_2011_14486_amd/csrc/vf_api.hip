@@ -277,7 +277,7 @@ void vf_destroy(vf_ctx *c) {
   (void)hipStreamSynchronize(c->stream);
   free_pipeline(c);
   vfk_free_model(c);
-  void *ps[] = {c->d_space, c->d_err,  c->d_stat, c->d_wlist, c->d_team, c->d_pub, c->d_feat,   c->d_act[0], c->d_act[1],
+  void *ps[] = {c->d_space, c->d_err,  c->d_stat, c->d_wlist, c->d_team, c->d_chain, c->d_pub, c->d_feat,   c->d_act[0], c->d_act[1],
                 c->d_pval,  c->d_pidx, c->d_scores, c->d_tk_val, c->d_tk_idx};
   for (void *p : ps)
     if (p) (void)hipFree(p);
@@ -543,20 +543,18 @@ int vf_greedy_schedule(vf_ctx *c, int first, int last, vf_state *out_states, int
     }
     if (rc != VF_OK && (rc != VF_ENOMEM || c->n_sched != first)) return rc;
   }
-  if (decided) {
-    // nothing left to do
-  } else if (vfk_can_chain(c)) {
-    // a few problems: one launch per layer, each taking the decision of the layer before
-    rc = vfk_greedy_chain(c, first, last);
-    if (rc != VF_OK) return rc;
-    c->n_sched = last + 1;
-  } else {
+  if (!decided && vfk_can_chain(c)) {
+    // a few problems: all layers in one launch that also fills the caller's tables
+    rc = vfk_greedy_chain(c, first, last, reinterpret_cast<int32_t *>(out_states), out_cids, out_vals);
+    if (rc == VF_OK) c->n_sched = last + 1;
+    if (rc != VF_ENOMEM) return rc;
+  }
+  if (!decided)
     for (int i = first; i <= last; ++i) {
       rc = step(c, i, 1, nullptr, nullptr);
       if (rc != VF_OK) return rc;
       c->n_sched = i + 1;
     }
-  }
   rc = vfk_copy_tables(c, out_states, out_cids, out_vals, nullptr);
   return rc == VF_OK ? finish_prefix(c) : rc;
 }

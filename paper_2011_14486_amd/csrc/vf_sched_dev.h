@@ -228,7 +228,7 @@ __device__ void build_dec_from(Dec &d, vf_space &sp, const Tables &t, int b, int
 // The same context with one round of fetches and the rest read by the one thread that derives
 // (a chain of three dependent fetches, but no per-thread addresses that a long kernel would
 // have to keep or spill): the form the whole-schedule kernel uses.
-__device__ void build_dec(Dec &d, vf_space &sp, const Tables &t, int b, int stage) {
+[[maybe_unused]] __device__ void build_dec(Dec &d, vf_space &sp, const Tables &t, int b, int stage) {
   const int tid = threadIdx.x, nt = blockDim.x, S = t.S;
   const size_t row = (size_t)b * S;
   for (int i = tid; i < (int)(sizeof(vf_space) / 4); i += nt) ((int32_t *)&sp)[i] = t.space[i];

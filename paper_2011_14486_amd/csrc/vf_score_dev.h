@@ -173,38 +173,54 @@ __device__ __forceinline__ uint4 stream_load(__amdgpu_buffer_rsrc_t rs, int voff
 // 64..255).  Column 0 of the result plus the layer's bias is what the candidates'
 // accumulators start from.  wf: this wave's fragments of the whole stream; stat:
 // DecPack::stat; wide: 256 input rows.  Every wave of the workgroup calls it for its RT row tiles.
+//
+// Group q of stat (8 words) is k-step 0 or q + 2; the order of the k-steps is the same wherever this is done.
 template <int RT>
-__device__ __forceinline__ void fold_bias(__amdgpu_buffer_rsrc_t wf, const uint32_t *stat, bool wide, int w, int lane,
-                                          const float *bias_in, float *bias_out) {
-  floatx16 fa[RT];
+__device__ __forceinline__ void fold_zero(floatx16 (&fa)[RT]) {
 #pragma unroll
   for (int r = 0; r < RT; ++r)
 #pragma unroll
     for (int q = 0; q < 16; ++q) fa[r][q] = 0.0f;
+}
+template <int RT>
+__device__ __forceinline__ void fold_step(floatx16 (&fa)[RT], const uint4 (&a)[RT], const uint32_t *stat, int sk, int lane) {
+  const uint32_t *xb = stat + 8 * (sk == 0 ? 0 : sk - 2) + 4 * (lane >> 5);
+  uint4 bv;
+  bv.x = xb[0]; bv.y = xb[1]; bv.z = xb[2]; bv.w = xb[3];
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+    fa[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[r]), __builtin_bit_cast(bf16x8, bv), fa[r], 0, 0, 0);
+}
+template <int RT>
+__device__ __forceinline__ void fold_load(uint4 (&a)[RT], __amdgpu_buffer_rsrc_t wf, int sk, int lane) {
+#pragma unroll
+  for (int r = 0; r < RT; ++r) a[r] = stream_load(wf, 16 * lane, sk * RT + r);
+}
+// (the layer's bias first, then the stores: one behind the other they would wait for each other, since the
+// compiler cannot tell the two arrays apart)
+template <int RT>
+__device__ __forceinline__ void fold_bias(__amdgpu_buffer_rsrc_t wf, const uint32_t *stat, bool wide, int w, int lane,
+                                          const float *bias_in, float *bias_out) {
+  floatx16 fa[RT];
+  fold_zero<RT>(fa);
   const int n = wide ? 14 : 2;
 #pragma unroll 7
-  for (int q = 0; q < n; ++q) {
-    const int sk = q == 0 ? 0 : q + 2;  // k-step of the whole first layer: 0, 3, 4, 5, ...
+  for (int i = 0; i < n; ++i) {
+    const int sk = i == 0 ? 0 : i + 2;  // k-step of the whole first layer: 0, 3, 4, 5, ...
     uint4 a[RT];
-#pragma unroll
-    for (int r = 0; r < RT; ++r) a[r] = stream_load(wf, 16 * lane, sk * RT + r);
-    const uint32_t *xb = stat + 8 * q + 4 * (lane >> 5);
-    uint4 bv;
-    bv.x = xb[0]; bv.y = xb[1]; bv.z = xb[2]; bv.w = xb[3];
-#pragma unroll
-    for (int r = 0; r < RT; ++r)
-      fa[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[r]), __builtin_bit_cast(bf16x8, bv),
-                                                     fa[r], 0, 0, 0);
+    fold_load<RT>(a, wf, sk, lane);
+    fold_step<RT>(fa, a, stat, sk, lane);
   }
   if ((lane & 31) == 0) {
+    float b[RT][16];
 #pragma unroll
-    for (int r = 0; r < RT; ++r) {
-      const int mbase = (w + r * 8) * 32 + 4 * (lane >> 5);
+    for (int r = 0; r < RT; ++r)
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
+      for (int q = 0; q < 16; ++q) b[r][q] = bias_in[(w + r * 8) * 32 + 4 * (lane >> 5) + 8 * (q / 4) + q % 4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) bias_out[mbase + 8 * g + e] = bias_in[mbase + 8 * g + e] + fa[r][4 * g + e];
-    }
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) bias_out[(w + r * 8) * 32 + 4 * (lane >> 5) + 8 * (q / 4) + q % 4] = b[r][q] + fa[r][q];
   }
 }
 
