@@ -543,9 +543,10 @@ int vf_greedy_schedule(vf_ctx *c, int first, int last, vf_state *out_states, int
     }
     if (rc != VF_OK && (rc != VF_ENOMEM || c->n_sched != first)) return rc;
   }
-  if (!decided && vfk_can_chain(c)) {
+  const bool chain = !decided && vfk_can_chain(c);
+  if (chain || (!decided && vfk_small_can_chain(c))) {
     // a few problems: all layers in one launch that also fills the caller's tables
-    rc = vfk_greedy_chain(c, first, last, reinterpret_cast<int32_t *>(out_states), out_cids, out_vals);
+    rc = (chain ? vfk_greedy_chain : vfk_small_chain)(c, first, last, reinterpret_cast<int32_t *>(out_states), out_cids, out_vals);
     if (rc == VF_OK) c->n_sched = last + 1;
     if (rc != VF_ENOMEM) return rc;
   }

@@ -38,27 +38,14 @@ namespace {
 
 #include "vf_score_dev.h"
 
-struct ChainArgs {
-  Tables t;
-  int first, last;
-  int64_t M;
-  int nprob, group;            // workgroups per problem; grid = nprob * group
-  int ntiles;                  // tiles of a decision
-  unsigned long long *slots;   // [nprob][S][ntiles] first minimum of every tile, 0 = not there yet
-  unsigned int *claims;        // [nprob][S + 1] tiles claimed per stage; workgroups that have left
-  unsigned int wait_rounds;
-  uint32_t *decpack;           // [nprob] receives the context of stage last + 1, if there is one
-  int32_t *out_states, *out_cids;  // nullable: the caller's tables
-  float *out_vals;
-  unsigned long long *stat;    // nullable: [0] += ids pushed through the network, [1] += valid ones
-};
+#include "vf_chain_dev.h"
+
+__global__ __launch_bounds__(256) void k_chain_clear(uint4 *p, size_t n) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) p[i] = make_uint4(0u, 0u, 0u, 0u);
+}
 
 constexpr int CHAIN_XS = 56;  // elements between the columns of the input buffer (48 used)
-
-// Entry i of a state record in the 64 core features (i < 15).
-__device__ __forceinline__ int state_feature(int i) {
-  return i < 3 ? 17 + i : i == 3 ? 23 : i == 4 ? 26 : i == 5 ? 29 : i < 8 ? 26 + i : i < 12 ? 26 + i : 8 + i;
-}
 
 // NC ids per tile; hidden layers of 512 units (RT row tiles per wave), PD k-steps of weight fragments in
 // flight.  ONE: the network has a single hidden layer.
@@ -78,16 +65,9 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
   float *auxs = reinterpret_cast<float *>(okf + NC);              // [wl_off] biases
   uint32_t *wls = reinterpret_cast<uint32_t *>(auxs + ((md.wl_off + 3) & ~3));  // [dims[NH] / 2] output vector, bfloat16 pairs
   uint4 *heldw = reinterpret_cast<uint4 *>(wls + md.dims[1] / 2);  // [8][HELD][RT][64] weights of the folded first layer
-  __shared__ DecPack pks[2];     // the open decision's context and the next one's, in turn
-  __shared__ EvalTabs tabs;      // the open decision's quotient tables
-  __shared__ DecScratch ds;
-  __shared__ int32_t cf64[64], st16[16], sums[3];  // the last winner's rows, the sums behind it, alive
-  __shared__ int claim[2];       // a further tile of the open decision; one of the next
-  __shared__ int missing;        // >= 0: a tile whose minimum did not come
+  __shared__ ChainShared sh;
   __shared__ uint32_t digs[NC];  // the next tile's ids, taken apart
   __shared__ int shut;           // none of them can be valid
-  __shared__ int32_t win_c;      // the winner's digits, packed (they order like the ids); -1: none
-  __shared__ float win_v;
 
   int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -98,11 +78,9 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
   const size_t row = (size_t)p * S;
   unsigned long long *const slots = ca.slots + row * ntiles;
   unsigned int *const claims = ca.claims + (size_t)p * (S + 1);
-  constexpr int CLAIMER = 448;  // the thread that claims tiles (first of the wave that polls)
 
   // ---- once per workgroup
-  constexpr unsigned int NONE = 0xffffffffu;
-  unsigned int c_more = 0u, c_next = NONE;  // (the claimer's) a further tile of this decision, one of the next
+  unsigned int c_more = 0u, c_next = NO_CLAIM;  // (the claimer's) a further tile of this decision, one of the next
   for (int i = tid; i < (int)md.wl_off; i += 512) auxs[i] = md.aux[i];
   for (int i = tid; i < md.dims[NH] / 2; i += 512) wls[i] = pack_bf16(md.aux[md.wl_off + 2 * i], md.aux[md.wl_off + 2 * i + 1]);
   const __amdgpu_buffer_rsrc_t ws = stream_rsrc(md.w_stream + (size_t)w * md.wave_stride);
@@ -113,18 +91,7 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
   for (int j = 0; j < PD; ++j)
 #pragma unroll
     for (int r = 0; r < RT; ++r) ring[j][r] = stream_load(ws, 16 * lane, j * RT + r);
-  for (int i = tid; i < (int)(sizeof(vf_space) / 4); i += 512)
-    reinterpret_cast<int32_t *>(&pks[0].sp)[i] = reinterpret_cast<int32_t *>(&pks[1].sp)[i] = ca.t.space[i];
-  if (member == 0 && (ca.out_states || ca.out_cids || ca.out_vals)) {
-    // the layers that this call does not decide, as they are; the others follow one by one
-    for (int i = tid; i < S * 16; i += 512) {
-      const int j = i / 16;
-      if (j >= ca.first && j <= ca.last) continue;
-      if (ca.out_states) ca.out_states[row * 16 + i] = ca.t.states[row * 16 + i];
-      if ((i & 15) == 0 && ca.out_cids) ca.out_cids[row + j] = ca.t.cids[row + j];
-      if ((i & 15) == 0 && ca.out_vals) ca.out_vals[row + j] = ca.t.vals[row + j];
-    }
-  }
+  chain_begin(sh, ca, row, member, tid);
 
   int stage = ca.first - 1;  // the open decision's (none yet)
   int t = ntiles;
@@ -168,7 +135,7 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
     lane = tid & 63;
     if (t < ntiles) {
       // ---- a tile of the open decision
-      const DecPack &pk = pks[cur];
+      const DecPack &pk = sh.pks[cur];
       const int64_t n0 = (int64_t)t * NC, nend = n0 + NC < ca.M ? n0 + NC : ca.M;
       if (!ready) {
         if (w == 4) {
@@ -198,23 +165,23 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
             *reinterpret_cast<uint4 *>(xin + (size_t)lane * XS + 8 * w) = o;
           };
           if (w == 0) {
-            const bool valid = eval_digits<true>(pk.d, pk.sp, dg, &tabs, core);
+            const bool valid = eval_digits<true>(pk.d, pk.sp, dg, &sh.tabs, core);
             okf[lane] = inb && valid;
             put8(core + 16);
           } else if (w == 1) {
-            eval_digits<true>(pk.d, pk.sp, dg, &tabs, core);
+            eval_digits<true>(pk.d, pk.sp, dg, &sh.tabs, core);
             put8(core + 24);
           } else if (w == 2) {
-            eval_digits<true>(pk.d, pk.sp, dg, &tabs, core);
+            eval_digits<true>(pk.d, pk.sp, dg, &sh.tabs, core);
             put8(core + 32);
           } else if (w == 3) {
-            eval_digits<true>(pk.d, pk.sp, dg, &tabs, core);
+            eval_digits<true>(pk.d, pk.sp, dg, &sh.tabs, core);
             put8(core + 40);
           } else if (w == 4) {
-            eval_digits<true>(pk.d, pk.sp, dg, &tabs, core);
+            eval_digits<true>(pk.d, pk.sp, dg, &sh.tabs, core);
             put8(core + 48);
           } else {
-            eval_digits<true>(pk.d, pk.sp, dg, &tabs, core);
+            eval_digits<true>(pk.d, pk.sp, dg, &sh.tabs, core);
             *reinterpret_cast<uint4 *>(xin + (size_t)lane * XS + 40) =
                 make_uint4(0u, inb ? pack_bf16(0.0f, plog2_dev(core[59])) : 0u, 0u, 0u);
           }
@@ -263,7 +230,7 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
         for (int c = 0; c < CT; ++c)
           if (lane < 32) red[w * NC + c * 32 + lane] = dot[c];
       }
-      if (tid == CLAIMER) claim[0] = (int)c_more;
+      if (tid == CLAIMER) sh.claim[0] = (int)c_more;
       __syncthreads();
       if (w == 0) {
         float v = __builtin_inff();
@@ -294,123 +261,31 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
                              (unsigned long long)__float_as_uint(v) << 32 | (c >= 0 ? (uint32_t)c + 1u : 0xffffffffu),
                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
-      t = claim[0];
+      t = sh.claim[0];
       if (t < ntiles) __syncthreads();  // (the scan has read what the next tile writes)
       continue;
     }
 
     // ---- no tile left to claim: what is known of the next stage
     const int next = stage + 1;
-    DecPack &nk = pks[cur ^ 1];
-    const DecPack &pk = pks[cur];
+    DecPack &nk = sh.pks[cur ^ 1];
+    const DecPack &pk = sh.pks[cur];
     const bool opens = next < S;         // (behind the last stage there is no context to make)
     const bool decides = next <= ca.last;
-    if (tid == CLAIMER && decides && c_next == NONE) c_next = atomicAdd(&claims[next], 1u);
+    if (tid == CLAIMER && decides && c_next == NO_CLAIM) c_next = atomicAdd(&claims[next], 1u);
     uint4 ends[LATE ? 4 : 1][RT];  // k-steps 0 and 13..15 of the folded layer
     if (decides) {
 #pragma unroll
       for (int i = 0; i < (LATE ? 4 : 1); ++i) fold_load<RT>(ends[i], wf, i == 0 || !wide ? 0 : 12 + i, lane);
     }
-    if (stage < ca.first) {
-      // the call's first stage, from the tables
-      dec_fetch_rows(nk.d, nk.sp, ds, ca.t, p, next, -1);
-      __syncthreads();
-      dec_fetch_anchor(nk.d, ds, ca.t, p, next, -1);
-      if (tid >= 128 && tid < 128 + VF_STAT_WORDS) nk.stat[tid - 128] = stat_word(nk.d, tid - 128);
-      if (tid < 3) sums[tid] = ds.sc[tid < 2 ? 1 + tid : 0];
-      if (tid == CLAIMER) claim[1] = (int)c_next;
-      __syncthreads();
-    } else if (opens) {
-      // from the open context where it has them (its neighbour rows move on by one), else fetched before
-      if (tid < 128) {
-        nk.d.nb[48 + tid] = pk.d.nb[tid < 96 ? tid : tid + 64];
-      } else if (tid < 192) {
-        const int q = tid - 128;  // the same as pairs, normalised
-        nk.stat[40 + q] = pk.stat[q < 48 ? 16 + q : 48 + q];
-      } else if (tid < 208) {
-        nk.d.intr[tid - 192] = pk.d.nb[144 + tid - 192];
-      } else if (tid < 216) {
-        nk.stat[tid - 208] = pk.stat[88 + tid - 208];
-      } else if (tid < 220) {
-        nk.stat[tid - 208] = 0u;
-      } else if (w == 6) {
-        if (lane < 16) {
-          nk.d.nb[176 + lane] = pre;
-          const int32_t odd = __shfl_down(pre, 1);
-          if ((lane & 1) == 0) nk.stat[104 + lane / 2] = pack_bf16(plog2_dev(pre), plog2_dev(odd));
-        } else if (lane < 32) {
-          nk.d.srec[lane - 16] = pre;
-        } else if (lane < 34) {
-          ds.sc[lane - 29] = pre;
-        }
-      }
-      __syncthreads();
-      if (w == 5) {  // the anchor's rows (as dec_fetch_anchor)
-        const int a = nk.d.srec[8];
-        int32_t v = 0;
-        if (a >= 0 && a < next) {
-          const size_t ar = row + a;
-          if (lane < 16) v = a != stage ? ca.t.states[ar * 16 + lane] : 0;
-          else if (lane < 32) v = ca.t.stages[ar * 16 + lane - 16];
-          else if (lane < 36) v = a != stage ? ca.t.cf[ar * 64 + (lane == 32 ? 42 : lane == 33 ? 54 : lane == 34 ? 32 : 23)] : 0;
-        }
-        if (lane < 16) ds.ast[lane] = v;
-        else if (lane < 32) ds.arec[lane - 16] = v;
-        else if (lane < 36) ds.acf[lane - 32] = v;
-      }
-    }
+    chain_rows(sh, nk, pk, ca, p, row, stage, c_next, pre, tid, lane, w);
 
     if (stage >= ca.first) {
       // ---- the open decision's minima
-      if (w == 7) {
-        float v = __builtin_inff();
-        int32_t c = -1;
-        int miss = -1;
-        unsigned int rounds = 0;
-        bool drained = false;  // no unclaimed tile
-        for (int q0 = 0; q0 < ntiles && miss < 0; q0 += 256) {
-          unsigned long long word[4] = {0ull, 0ull, 0ull, 0ull};
-          for (;;) {
-            bool lack = false;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              const int q = q0 + 64 * k + lane;
-              if (q < ntiles && word[k] == 0ull)
-                word[k] = __hip_atomic_load(&slots[(size_t)stage * ntiles + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) lack = lack || (q0 + 64 * k + lane < ntiles && word[k] == 0ull);
-            if (__ballot(lack) == 0ull) break;
-            // a tile that nobody has claimed: one for this workgroup (some are not running yet)
-            if (!drained && (rounds & 7u) == 7u) {
-              int q = 0;
-              if (lane == 0) q = (int)atomicAdd(&claims[stage], 1u);
-              q = __builtin_amdgcn_readfirstlane(q);
-              if (q < ntiles) { miss = q; break; }
-              drained = true;
-            }
-            if (rounds++ >= ca.wait_rounds) {
-#pragma unroll
-              for (int k = 0; k < 4; ++k) {
-                const unsigned long long m = __ballot(q0 + 64 * k + lane < ntiles && word[k] == 0ull);
-                if (m != 0ull && miss < 0) miss = q0 + 64 * k + (int)__builtin_ctzll(m);
-              }
-              break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-          }
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const uint32_t dg = (uint32_t)word[k];
-            take_min(v, c, __uint_as_float((uint32_t)(word[k] >> 32)), dg == 0xffffffffu ? -1 : (int32_t)dg - 1);
-          }
-        }
-        wave_min(v, c);
-        if (lane == 0) { win_v = v; win_c = c; missing = miss; claim[1] = (int)c_next; }
-      }
+      if (w == 7) chain_poll(sh, ca, slots, claims, ntiles, stage, c_next, lane);
       __syncthreads();
-      if (missing >= 0) {
-        t = __builtin_amdgcn_readfirstlane(missing);
+      if (sh.missing >= 0) {
+        t = __builtin_amdgcn_readfirstlane(sh.missing);
         __syncthreads();  // (before the word is written again)
         continue;
       }
@@ -422,87 +297,29 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
           for (int r = 0; r < RT; ++r) asm volatile("" : "+v"(ends[i][r].x), "+v"(ends[i][r].y), "+v"(ends[i][r].z), "+v"(ends[i][r].w));
       }
       // ---- s_i := the winner: its rows, a share each by threads of four waves; the ids of the next tile
-      const int32_t c = win_c;
-      if (lane == 0 && w < 4) {
-        int32_t core[64];
-        const Digits dg = unpack_digits((uint32_t)(c >= 0 ? c : 0));
-        if (w == 0) {
-          const bool ok = eval_digits<true>(pk.d, pk.sp, dg, &tabs, core) && c >= 0;
-#pragma unroll
-          for (int k = 0; k < 32; ++k) cf64[k] = ok ? core[k] : 0;
-          sums[2] = ok ? pk.d.lvl_ok[0] : 0;
-          st16[15] = ok ? 1 : 0;
-        } else if (w == 1) {
-          const bool ok = eval_digits<true>(pk.d, pk.sp, dg, &tabs, core) && c >= 0;
-#pragma unroll
-          for (int k = 32; k < 42; ++k) cf64[k] = ok ? core[k] : 0;
-          sums[0] = ok ? (int32_t)sadd((uint32_t)pk.d.pm, (uint32_t)core[40]) : pk.d.pm;
-        } else if (w == 2) {
-          const bool ok = eval_digits<true>(pk.d, pk.sp, dg, &tabs, core) && c >= 0;
-#pragma unroll
-          for (int k = 42; k < 48; ++k) cf64[k] = ok ? core[k] : 0;
-        } else {
-          const bool ok = eval_digits<true>(pk.d, pk.sp, dg, &tabs, core) && c >= 0;
-#pragma unroll
-          for (int k = 48; k < 64; ++k) cf64[k] = ok ? core[k] : 0;
-          sums[1] = ok ? (int32_t)sadd((uint32_t)pk.d.pb, (uint32_t)core[50]) : pk.d.pb;
-        }
-      }
-      if (w == 4 && decides && claim[1] < ntiles) take_apart(claim[1], pk.sp);
+      chain_winner(sh, pk, lane, w);
+      if (w == 4 && decides && sh.claim[1] < ntiles) take_apart(sh.claim[1], pk.sp);
       __syncthreads();
-      // every workgroup writes the tables (it reads its anchors from there); one writes the caller's
-      const bool ok = st16[15] != 0;
-      const size_t at = row + stage;
-      if (tid >= 128 && tid < 192 && ok) ca.t.cf[at * 64 + tid - 128] = cf64[tid - 128];
-      if (tid >= 192 && tid < 208) {
-        const int i = tid - 192;
-        const int32_t v = i < 15 ? cf64[state_feature(i)] : st16[15];
-        if (ok) ca.t.states[at * 16 + i] = v;
-        if (member == 0 && ca.out_states) ca.out_states[at * 16 + i] = ok ? v : 0;
-      }
-      if (tid == 256) {
-        const int32_t id = ok ? (int32_t)id_of(pk.sp, unpack_digits((uint32_t)c)) : -1;
-        const float v = ok ? win_v : __builtin_inff();
-        ca.t.cids[at] = id;
-        ca.t.vals[at] = v;
-        if (member == 0 && ca.out_cids) ca.out_cids[at] = id;
-        if (member == 0 && ca.out_vals) ca.out_vals[at] = v;
-        if (!ok) ca.t.alive[p] = 0;
-      }
-      if (tid == 257 || tid == 258) ca.t.prefix[((size_t)p * (S + 1) + stage + 1) * 2 + tid - 257] = sums[tid - 257];
+      chain_tables(sh, pk, ca, p, row, stage, member, tid);
     }
     if (!opens) break;
 
     // ---- the next decision's context: the shared rows, so that the folded layer can begin
-    const bool fresh = stage >= ca.first && nk.d.srec[8] == stage;  // the anchor is the stage just decided
-    if (stage >= ca.first) {
-      if (tid < 15) st16[tid] = cf64[state_feature(tid)];
-      if (tid >= 64 && tid < 112) nk.d.nb[tid - 64] = cf64[tid - 64];
-      if (tid >= 320 && tid < 344) nk.stat[16 + tid - 320] = pack_bf16(plog2_dev(cf64[2 * (tid - 320)]), plog2_dev(cf64[2 * (tid - 320) + 1]));
-    }
-    if (tid >= 384 && tid < 388) {
-      const bool anchored = nk.d.srec[8] >= 0 && (fresh ? st16[15] : ds.ast[15]) == 1;
-      const int k = tid - 384;
-      const int32_t lo = k == 0 ? (fresh ? cf64[42] : ds.acf[0]) : k == 1 ? (fresh ? cf64[32] : ds.acf[2]) : k == 2 ? sums[0] : ds.sc[3];
-      const int32_t hi = k == 0 ? (fresh ? cf64[54] : ds.acf[1]) : k == 1 ? 0 : k == 2 ? sums[1] : ds.sc[4];
-      nk.stat[12 + k] = k < 2 && !anchored ? 0u : pack_bf16(plog2_dev(lo), plog2_dev(hi));
-    }
+    chain_shared_rows(sh, nk, ca, stage, tid);
     __syncthreads();
     if (!decides) {
       // (a schedule in pieces: the context is left for the call that goes on)
-      if (tid == 0)
-        dec_derive(nk.d, nk.sp, next, sums[2], fresh ? st16 : ds.ast, ds.arec, fresh ? cf64 : ds.acf, !fresh, sums[0], sums[1],
-                   ds.sc[3], ds.sc[4]);
+      if (tid == 0) chain_derive(sh, nk, ca, stage);
       __syncthreads();
       if (member == 0)
         for (int i = tid; i < VF_DECPACK_DWORDS; i += 512)
           ca.decpack[(size_t)p * VF_DECPACK_DWORDS + i] = reinterpret_cast<const uint32_t *>(&nk)[i];
       break;
     }
-    t = __builtin_amdgcn_readfirstlane(claim[1]);
+    t = __builtin_amdgcn_readfirstlane(sh.claim[1]);
     if (stage < ca.first && w == 4 && t < ntiles) take_apart(t, nk.sp);
     ready = t < ntiles;
-    c_next = NONE;
+    c_next = NO_CLAIM;
     // the folded layer; first by all waves but wave 0, which derives the rest of the context meanwhile, then by
     // wave 0, while the others make the quotient tables of it
     for (int ph = 0; ph < 2; ++ph) {
@@ -532,44 +349,34 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
 #pragma unroll
           for (int q = 0; q < 16; ++q) fa[r][q] = bv[r][q] + fa[r][q];
       } else if (ph == 0) {
-        if (lane == 0) {
-          if (fresh)
-            dec_derive(nk.d, nk.sp, next, sums[2], st16, ds.arec, cf64, false, sums[0], sums[1], ds.sc[3], ds.sc[4]);
-          else
-            dec_derive(nk.d, nk.sp, next, sums[2], ds.ast, ds.arec, ds.acf, true, sums[0], sums[1], ds.sc[3], ds.sc[4]);
-        }
+        if (lane == 0) chain_derive(sh, nk, ca, stage);
       } else {
-        fill_evaltabs(tabs, nk.d, nk.sp, 64);
+        fill_evaltabs(sh.tabs, nk.d, nk.sp, 64);
         if (w == 4 && t < ntiles) look_shut(t, nk);
       }
       __syncthreads();
     }
     cur ^= 1;
     stage = next;
-    // what the context behind this one takes from memory, for the end of this decision
-    if (w == 6 && stage + 1 < S) {
-      if (lane < 16) pre = stage + 4 < S ? ca.t.intr[(row + stage + 4) * 16 + lane] : 0;
-      else if (lane < 32) pre = ca.t.stages[(row + stage + 1) * 16 + lane - 16];
-      else if (lane < 34) pre = ca.t.suffix[(row + stage + 1) * 2 + lane - 32];
-    }
+    if (w == 6) pre = chain_prefetch(ca, row, stage, lane);
   }
-
-  // ---- the last workgroup of the problem to leave clears its words
-  __syncthreads();
-  if (tid == 0) missing = (int)(atomicAdd(&claims[S], 1u) + 1u);
-  __syncthreads();
-  if (missing == ca.group) {
-    for (size_t i = (size_t)ca.first * ntiles + tid; i < (size_t)(ca.last + 1) * ntiles; i += 512) slots[i] = 0ull;
-    for (int i = tid; i <= S; i += 512) claims[i] = 0u;
-  }
-}
-
-__global__ __launch_bounds__(256) void k_chain_clear(uint4 *p, size_t n) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = make_uint4(0u, 0u, 0u, 0u);
+  chain_leave(sh, ca, slots, claims, ntiles, tid);
 }
 
 }  // namespace
+
+// The words of a launch with `units` 16-byte units, zero.
+int vfk_chain_words(vf_ctx *c, size_t units) {
+  if (units <= c->chain_units) return VF_OK;
+  if (c->d_chain) { VF_HIP(c, hipStreamSynchronize(c->stream)); (void)hipFree(c->d_chain); c->d_chain = nullptr; }
+  c->chain_units = 0;
+  if (hipMalloc((void **)&c->d_chain, units * 16) != hipSuccess) { (void)hipGetLastError(); c->d_chain = nullptr; return VF_ENOMEM; }
+  hipLaunchKernelGGL(k_chain_clear, dim3((unsigned)((units + 255) / 256)), dim3(256), 0, c->stream,
+                     reinterpret_cast<uint4 *>(c->d_chain), units);
+  VF_HIP(c, hipGetLastError());
+  c->chain_units = units;
+  return VF_OK;
+}
 
 typedef void (*chain_kernel)(vf_fast_dev, int, NoiseArgs, ChainArgs);
 
@@ -609,29 +416,8 @@ int vfk_greedy_chain(vf_ctx *c, int first, int last, int32_t *out_states, int32_
   const chain_kernel kern = chain_shape(c, &fd, &ks, &NC, &smem);
   if (!kern || first > last) return VF_ESTATE;
   ChainArgs ca;
-  ca.t = tables_of(c);
-  ca.first = first; ca.last = last;
-  ca.M = c->M;
-  ca.nprob = c->B;
-  ca.ntiles = (int)((c->M + NC - 1) / NC);
-  ca.group = ca.ntiles;
-  const size_t nslots = (size_t)c->B * c->S * ca.ntiles, nclaims = (size_t)c->B * (c->S + 1);
-  const size_t want = (nslots * 8 + nclaims * 4 + 15) / 16;
-  if (want > c->chain_units) {
-    if (c->d_chain) { VF_HIP(c, hipStreamSynchronize(c->stream)); (void)hipFree(c->d_chain); c->d_chain = nullptr; }
-    c->chain_units = 0;
-    if (hipMalloc((void **)&c->d_chain, want * 16) != hipSuccess) { (void)hipGetLastError(); c->d_chain = nullptr; return VF_ENOMEM; }
-    hipLaunchKernelGGL(k_chain_clear, dim3((unsigned)((want + 255) / 256)), dim3(256), 0, c->stream,
-                       reinterpret_cast<uint4 *>(c->d_chain), want);
-    VF_HIP(c, hipGetLastError());
-    c->chain_units = want;
-  }
-  ca.slots = c->d_chain;
-  ca.claims = reinterpret_cast<unsigned int *>(c->d_chain + nslots);
-  ca.wait_rounds = c->wait_rounds;
-  ca.decpack = c->d_decpack;
-  ca.out_states = out_states; ca.out_cids = out_cids; ca.out_vals = out_vals;
-  ca.stat = c->profiling ? c->d_stat : nullptr;
+  const int rc = chain_args(c, first, last, (int)((c->M + NC - 1) / NC), out_states, out_cids, out_vals, &ca);
+  if (rc != VF_OK) return rc;
   NoiseArgs na;
   na.eps = c->noise_eps;
   na.k0 = (uint32_t)c->noise_seed; na.k1 = (uint32_t)(c->noise_seed >> 32);

@@ -251,6 +251,9 @@ int vfk_pack_small(vf_ctx *c, const float *weights_dev);
 bool vfk_small_generates(const vf_ctx *c);
 int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob, int64_t M, int64_t ld, int use_valid_row,
                     float *scores, int64_t ld_scores, int noise_stage, const vf_partbuf *parts, int *nparts_out, int *part_out);
+// and whole schedules of a few problems, as vfk_greedy_chain
+bool vfk_small_can_chain(const vf_ctx *c);
+int vfk_small_chain(vf_ctx *c, int first, int last, int32_t *out_states, int32_t *out_cids, float *out_vals);
 // Enumerate + featurize + score + partial argmin of one stage in a single kernel (bf16
 // MLPs of uniform hidden width whose input width is the space's F).
 bool vfk_can_fuse_step(const vf_ctx *c);
@@ -281,6 +284,7 @@ int vfk_step_fused(vf_ctx *c, int stage, int *nparts_out);
 // Algorithm 1 over stages first..last in one launch for a few problems (vf_chain.hip), the tables to the
 // caller's buffers included (nullable); VF_ESTATE if the model, the space or the batch does not take it.
 bool vfk_can_chain(const vf_ctx *c);
+int vfk_chain_words(vf_ctx *c, size_t units);
 int vfk_greedy_chain(vf_ctx *c, int first, int last, int32_t *out_states, int32_t *out_cids, float *out_vals);
 // Scores of every candidate of `stage` for all problems into d_scores [B][Mpad]; invalid
 // candidates and padding columns get +inf.

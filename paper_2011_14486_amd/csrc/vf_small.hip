@@ -22,6 +22,8 @@ namespace {
 
 #include "vf_score_dev.h"
 
+#include "vf_chain_dev.h"
+
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef int32_t intx2 __attribute__((ext_vector_type(2), aligned(4)));  // 8-byte loads and stores of 4-byte aligned pairs
 typedef float floatx2 __attribute__((ext_vector_type(2), aligned(4)));
@@ -75,10 +77,14 @@ struct SmallArgs {
   // (share c has the blocks c, c + nparts, ...: valid ids come in runs), one share at a time per wave
   const uint32_t *decpack;
   int block, nblocks;
+  // CHAINED: the schedule; a tile is `spw` sub-tiles in a row, one each for the first waves of a workgroup
+  ChainArgs ca;
+  int spw;
 };
 
-// What a kernel scores: given features, the valid ids that its waves collect, or ids as they come.
-enum { GIVEN = 0, COLLECTED = 1, IDS = 2 };
+// What a kernel scores: given features, the valid ids that its waves collect, ids as they come, or ids as they
+// come through a whole schedule (vf_chain_dev.h).
+enum { GIVEN = 0, COLLECTED = 1, IDS = 2, CHAINED = 3 };
 
 // GEN: the candidates are enumerated and featurized where they are scored (x is not used); scores of
 // ids that are not valid candidates read +inf.  Every wave keeps the context of its problem, looks its ids
@@ -102,9 +108,6 @@ __device__ __forceinline__ void load_wave_dec(WaveDec &wd, const uint32_t *decpa
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   fill_evaltabs_at(wd.tabs, wd.pk.d, wd.pk.sp, lane, 64);
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-}
-__device__ __forceinline__ bool eval_wave(const WaveDec &wd, uint32_t cid, int32_t *core) {
-  return eval_digits<true>(wd.pk.d, wd.pk.sp, digits_small(wd.pk.sp, cid), &wd.tabs, core);
 }
 // Goes on through the share's blocks (blk: the next one) until `want` valid ids are queued or there are
 // no more blocks; masked ids' scores are written.  All lanes call it.
@@ -135,6 +138,34 @@ __device__ __forceinline__ void drop_queue(WaveDec &wd, int &queued, int n, int 
 __device__ __forceinline__ int32_t pick(int g, int32_t a, int32_t b) { return g ? b : a; }
 __device__ __forceinline__ int32_t pick(int g, int32_t a, int32_t b, int32_t c, int32_t d) {
   return g & 2 ? (g & 1 ? d : c) : (g & 1 ? b : a);
+}
+
+__device__ __forceinline__ NoiseArgs noise_of(const SmallArgs &a, bool chain, int stage) {
+  NoiseArgs na = a.na;
+  if (chain) na.stage = stage;
+  return na;
+}
+// (CHAINED) The first minimum of a workgroup's tile from its waves' (v, c), to the other workgroups; on to the next tile.
+__device__ __forceinline__ int post_tile(ChainShared &sh, const ChainArgs &ca, unsigned long long *slots, float *tile_v, int32_t *tile_c,
+                                         int stage, int tile, float v, int32_t c, int lane, int w) {
+  wave_min(v, c);
+  if (lane == 0) {
+    tile_v[w] = v;
+    tile_c[w] = c;
+  }
+  __syncthreads();
+  if (w == 0) {
+    v = tile_v[lane & 7];
+    c = tile_c[lane & 7];
+    wave_min(v, c);
+    if (lane == 0)
+      __hip_atomic_store(&slots[(size_t)stage * ca.ntiles + tile],
+                         (unsigned long long)__float_as_uint(v) << 32 | (c >= 0 ? (uint32_t)c + 1u : 0xffffffffu), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+  }
+  const int t = __builtin_amdgcn_readfirstlane(sh.claim[0]);
+  if (t < ca.ntiles) __syncthreads();  // (before the next tile's minima)
+  return t;
 }
 
 __device__ __forceinline__ void stage_small(const SmallArgs &a, uint4 *wl, float *bl) {
@@ -194,7 +225,7 @@ __device__ __forceinline__ void load_raw(int32_t (&r)[ROWS][N], const int32_t *p
 // always under way.
 template <int CT, int NT, int MODE>
 __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
-  constexpr bool GEN = MODE != GIVEN, DIRECT = MODE == IDS;
+  constexpr bool GEN = MODE != GIVEN, DIRECT = MODE == IDS, CHAIN = MODE == CHAINED;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint4 *const wl = reinterpret_cast<uint4 *>(smem);
   float *const bl = reinterpret_cast<float *>(wl + a.md.nw);
@@ -232,12 +263,24 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
   };
   // (GEN: a unit is a share of a problem's ids)
   const int stride = ((int)gridDim.x >> a.xcd_bits) * 8;
-  int u_end, u = first_unit(a, w, u_end), sub = 0;
-  if (u >= u_end) return;
-  int p = u / a.nparts, part = u - p * a.nparts;
+  int u_end = 0, u = CHAIN ? 0 : first_unit(a, w, u_end), sub = 0;
+  if (!CHAIN && u >= u_end) return;
+  int p = CHAIN ? (int)blockIdx.x % a.ca.nprob : u / a.nparts, part = CHAIN ? 0 : u - p * a.nparts;
   int64_t n0 = GEN ? 0 : (int64_t)part * a.spp * 32 * CT;
   int blk = part, queued = 0;  // (GEN)
-  if constexpr (GEN) load_wave_dec(wd, a.decpack, p, lane);
+  // (CHAINED)
+  __shared__ ChainShared sh;
+  __shared__ float tile_v[8];
+  __shared__ int32_t tile_c[8];
+  const int member = CHAIN ? (int)blockIdx.x / a.ca.nprob : 0;
+  const size_t row = (size_t)p * a.ca.t.S;
+  unsigned long long *const slots = CHAIN ? a.ca.slots + row * a.ca.ntiles : nullptr;
+  unsigned int *const claims = CHAIN ? a.ca.claims + (size_t)p * (a.ca.t.S + 1) : nullptr;
+  int cur = 1, stage = a.ca.first - 1, tile = a.ca.ntiles;
+  unsigned int c_next = NO_CLAIM;
+  int32_t pre = 0;
+  if constexpr (CHAIN) chain_begin(sh, a.ca, row, member, threadIdx.x);
+  else if constexpr (GEN) load_wave_dec(wd, a.decpack, p, lane);
   else fetch(p, n0, 0);
   float v = __builtin_inff();
   int32_t vc = -1;
@@ -254,7 +297,17 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
       nn0 = (int64_t)npart * a.spp * 32 * CT;
     }
     int have = 0;  // (GEN) candidates of this sub-tile
-    if constexpr (GEN) {
+    if constexpr (CHAIN) {
+      while (tile >= a.ca.ntiles)
+        if (!chain_between(sh, a.ca, slots, claims, p, row, member, cur, stage, tile, c_next, pre, threadIdx.x)) {
+          chain_leave(sh, a.ca, slots, claims, a.ca.ntiles, threadIdx.x);
+          return;
+        }
+      n0 = ((int64_t)tile * a.spw + w) * (32 * CT);
+      have = w < a.spw && n0 < a.M ? (int)(a.M - n0 < 32 * CT ? a.M - n0 : 32 * CT) : 0;
+      nu = u;
+      if (threadIdx.x == CLAIMER) sh.claim[0] = a.ca.ntiles > a.ca.group ? (int)atomicAdd(&claims[stage], 1u) : a.ca.ntiles;
+    } else if constexpr (GEN) {
       if constexpr (DIRECT) {
         n0 = (int64_t)blk * (32 * CT);
         have = (int)(a.M - n0 < 32 * CT ? a.M - n0 : 32 * CT);
@@ -267,7 +320,7 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
       }
       nu = ends ? u + stride : u;
     }
-    const bool more = nu < u_end;
+    const bool more = CHAIN || nu < u_end;
     if (!more) { np = p; nn0 = n0; }
     // (the weights and biases that a sub-tile starts with are read afresh from LDS for every one: kept
     // across the sub-tiles they would fill the registers)
@@ -280,17 +333,22 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
     if constexpr (GEN) {
 #pragma unroll
       for (int c = 0; c < CT; ++c)
-        id[c] = !ok[c] ? 0u : DIRECT ? (uint32_t)n0 + CT * (lane & 31) + c : wd.queue[CT * (lane & 31) + c];
+        id[c] = !ok[c] ? 0u : DIRECT || CHAIN ? (uint32_t)n0 + CT * (lane & 31) + c : wd.queue[CT * (lane & 31) + c];
     }
     uint4 own[GEN ? 4 : 1][CT];  // (GEN) the candidates' rows 0..63, as the k-steps 0..3 want them
     // (GEN) no candidate in the share, or in the block
-    const bool closed = GEN && (DIRECT ? range_closed(wd.pk.d, wd.pk.sp, (uint32_t)n0, (uint32_t)(n0 + have)) : have == 0);
+    const DecPack &kc = CHAIN ? sh.pks[cur] : wd.pk;
+    const EvalTabs &tc = CHAIN ? sh.tabs : wd.tabs;
+    const bool closed = GEN && (DIRECT || CHAIN ? have == 0 || range_closed(kc.d, kc.sp, (uint32_t)n0, (uint32_t)(n0 + have)) : have == 0);
+    uint32_t dig[CT];  // (CHAINED) the digits of the ids
     if constexpr (GEN) {
       if (!closed) {
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
           int32_t core[64];
-          const bool valid = eval_wave(wd, id[c], core);  // (behind the last one too: core must be defined)
+          const Digits dg = digits_small(kc.sp, id[c]);
+          const bool valid = eval_digits<true>(kc.d, kc.sp, dg, &tc, core);  // (behind the last one too: core must be defined)
+          dig[c] = pack_digits(dg);
           ok[c] = ok[c] && valid;
 #pragma unroll
           for (int s = 0; s < 4; ++s) {
@@ -346,7 +404,7 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
         // rows 64..255, the same for all candidates of the decision (DecPack::stat holds them as pairs)
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-          const uint32_t *nb = wd.pk.stat + 16 + (ch * 32 - 64 + 16 * s + 8 * h) / 2;
+          const uint32_t *nb = kc.stat + 16 + (ch * 32 - 64 + 16 * s + 8 * h) / 2;
           const uint4 q = make_uint4(nb[0], nb[1], nb[2], nb[3]);
 #pragma unroll
           for (int c = 0; c < CT; ++c) in[s][c] = q;
@@ -460,9 +518,15 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
         for (int c = 0; c < CT; ++c) {
           float sc = s[c];
           const int32_t at_id = GEN ? (int32_t)id[c] : (int32_t)(n + c);
-          if (a.na.eps != 0.0f) sc = add_noise(a.na, sc, p, at_id);
-          if (ok[c] && sc < v) { v = sc; vc = at_id; }
+          if (a.na.eps != 0.0f) sc = add_noise(noise_of(a, CHAIN, stage), sc, p, at_id);
+          if (ok[c] && sc < v) { v = sc; vc = CHAIN ? (int32_t)dig[c] : at_id; }
         }
+      }
+      if constexpr (CHAIN) {
+        tile = post_tile(sh, a.ca, slots, tile_v, tile_c, stage, tile, v, vc, lane, w);
+        v = __builtin_inff();
+        vc = -1;
+        continue;
       }
       if (ends) {
         wave_min(v, vc);
@@ -498,7 +562,7 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
 // candidate's score does not depend on how many candidates the call has.
 template <int CT, int NT, int MODE>
 __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
-  constexpr bool GEN = MODE != GIVEN, DIRECT = MODE == IDS;
+  constexpr bool GEN = MODE != GIVEN, DIRECT = MODE == IDS, CHAIN = MODE == CHAINED;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint4 *const wl = reinterpret_cast<uint4 *>(smem);
   const floatx4 *const wf = reinterpret_cast<const floatx4 *>(smem);
@@ -527,12 +591,24 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
   };
   // (GEN: a unit is a share of a problem's ids)
   const int stride = ((int)gridDim.x >> a.xcd_bits) * 8;
-  int u_end, u = first_unit(a, w, u_end), sub = 0;
-  if (u >= u_end) return;
-  int p = u / a.nparts, part = u - p * a.nparts;
+  int u_end = 0, u = CHAIN ? 0 : first_unit(a, w, u_end), sub = 0;
+  if (!CHAIN && u >= u_end) return;
+  int p = CHAIN ? (int)blockIdx.x % a.ca.nprob : u / a.nparts, part = CHAIN ? 0 : u - p * a.nparts;
   int64_t n0 = GEN ? 0 : (int64_t)part * a.spp * 16 * CT;
   int blk = part, queued = 0;  // (GEN)
-  if constexpr (GEN) load_wave_dec(wd, a.decpack, p, lane);
+  // (CHAINED)
+  __shared__ ChainShared sh;
+  __shared__ float tile_v[8];
+  __shared__ int32_t tile_c[8];
+  const int member = CHAIN ? (int)blockIdx.x / a.ca.nprob : 0;
+  const size_t row = (size_t)p * a.ca.t.S;
+  unsigned long long *const slots = CHAIN ? a.ca.slots + row * a.ca.ntiles : nullptr;
+  unsigned int *const claims = CHAIN ? a.ca.claims + (size_t)p * (a.ca.t.S + 1) : nullptr;
+  int cur = 1, stage = a.ca.first - 1, tile = a.ca.ntiles;
+  unsigned int c_next = NO_CLAIM;
+  int32_t pre = 0;
+  if constexpr (CHAIN) chain_begin(sh, a.ca, row, member, threadIdx.x);
+  else if constexpr (GEN) load_wave_dec(wd, a.decpack, p, lane);
   else fetch(p, n0, 0);
   float v = __builtin_inff();
   int32_t vc = -1;
@@ -548,7 +624,17 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
       nn0 = (int64_t)npart * a.spp * 16 * CT;
     }
     int have = 0;  // (GEN) candidates of this sub-tile
-    if constexpr (GEN) {
+    if constexpr (CHAIN) {
+      while (tile >= a.ca.ntiles)
+        if (!chain_between(sh, a.ca, slots, claims, p, row, member, cur, stage, tile, c_next, pre, threadIdx.x)) {
+          chain_leave(sh, a.ca, slots, claims, a.ca.ntiles, threadIdx.x);
+          return;
+        }
+      n0 = ((int64_t)tile * a.spw + w) * (16 * CT);
+      have = w < a.spw && n0 < a.M ? (int)(a.M - n0 < 16 * CT ? a.M - n0 : 16 * CT) : 0;
+      nu = u;
+      if (threadIdx.x == CLAIMER) sh.claim[0] = a.ca.ntiles > a.ca.group ? (int)atomicAdd(&claims[stage], 1u) : a.ca.ntiles;
+    } else if constexpr (GEN) {
       if constexpr (DIRECT) {
         n0 = (int64_t)blk * (16 * CT);
         have = (int)(a.M - n0 < 16 * CT ? a.M - n0 : 16 * CT);
@@ -561,7 +647,7 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
       }
       nu = ends ? u + stride : u;
     }
-    const bool more = nu < u_end;
+    const bool more = CHAIN || nu < u_end;
     if (!more) { np = p; nn0 = n0; }
     // (the weights and biases that a sub-tile starts with are read afresh from LDS for every one: kept
     // across the sub-tiles they would fill the registers)
@@ -574,17 +660,22 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
     if constexpr (GEN) {
 #pragma unroll
       for (int c = 0; c < CT; ++c)
-        id[c] = !ok[c] ? 0u : DIRECT ? (uint32_t)n0 + CT * (lane & 15) + c : wd.queue[CT * (lane & 15) + c];
+        id[c] = !ok[c] ? 0u : DIRECT || CHAIN ? (uint32_t)n0 + CT * (lane & 15) + c : wd.queue[CT * (lane & 15) + c];
     }
     float own[GEN ? 4 : 1][4][CT];  // (GEN) the candidates' rows 0..63: group of 16, row of the lane group, column
     // (GEN) no candidate in the share, or in the block
-    const bool closed = GEN && (DIRECT ? range_closed(wd.pk.d, wd.pk.sp, (uint32_t)n0, (uint32_t)(n0 + have)) : have == 0);
+    const DecPack &kc = CHAIN ? sh.pks[cur] : wd.pk;
+    const EvalTabs &tc = CHAIN ? sh.tabs : wd.tabs;
+    const bool closed = GEN && (DIRECT || CHAIN ? have == 0 || range_closed(kc.d, kc.sp, (uint32_t)n0, (uint32_t)(n0 + have)) : have == 0);
+    uint32_t dig[CT];  // (CHAINED) the digits of the ids
     if constexpr (GEN) {
       if (!closed) {
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
           int32_t core[64];
-          const bool valid = eval_wave(wd, id[c], core);  // (behind the last one too: core must be defined)
+          const Digits dg = digits_small(kc.sp, id[c]);
+          const bool valid = eval_digits<true>(kc.d, kc.sp, dg, &tc, core);  // (behind the last one too: core must be defined)
+          dig[c] = pack_digits(dg);
           ok[c] = ok[c] && valid;
 #pragma unroll
           for (int g = 0; g < 4; ++g)
@@ -662,7 +753,7 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
         for (int g = 0; g < 2; ++g)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const float f = plog2_dev(wd.pk.d.nb[ch * 32 - 64 + 16 * g + 4 * q + e]);
+            const float f = plog2_dev(kc.d.nb[ch * 32 - 64 + 16 * g + 4 * q + e]);
 #pragma unroll
             for (int c = 0; c < CT; ++c) in[g][e][c] = f;
           }
@@ -768,9 +859,15 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
         const int32_t at_id = GEN ? (int32_t)id[c] : (int32_t)(n + c);
         if (a.scores && (GEN ? CT * (lane & 15) + c < have : n + c < a.M)) a.scores[(size_t)p * a.ld_scores + at_id] = s[c];
         float sc = s[c];
-        if (a.na.eps != 0.0f) sc = add_noise(a.na, sc, p, at_id);
-        if (ok[c] && sc < v) { v = sc; vc = at_id; }
+        if (a.na.eps != 0.0f) sc = add_noise(noise_of(a, CHAIN, stage), sc, p, at_id);
+        if (ok[c] && sc < v) { v = sc; vc = CHAIN ? (int32_t)dig[c] : at_id; }
       }
+    }
+    if constexpr (CHAIN) {
+      tile = post_tile(sh, a.ca, slots, tile_v, tile_c, stage, tile, v, vc, lane, w);
+      v = __builtin_inff();
+      vc = -1;
+      continue;
     }
     if (ends) {
       wave_min(v, vc);
@@ -870,6 +967,8 @@ bool vfk_small_generates(const vf_ctx *c) {
          (size_t)d.nw * 16 + (size_t)d.nbias * 4 <= GEN_LDS;
 }
 
+typedef void (*small_kernel)(SmallArgs);
+
 // Scores on the kernels above.  part_out: candidates per partial minimum, a divisor of 128.  x null: the
 // candidates of the decisions whose contexts d_decpack holds are generated (masked scores).
 int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob, int64_t M, int64_t ld, int use_valid_row,
@@ -931,7 +1030,6 @@ int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob,
   // (a kilobyte more: the last refill of a weight fragment reads behind the weights)
   size_t smem = (size_t)a.md.nw * 16 + (size_t)a.md.nbias * 4 + 1024;
   if (!x) smem = (smem + 15) / 16 * 16 + 8 * sizeof(WaveDec);
-  typedef void (*small_kernel)(SmallArgs);
 #define VF_SMALL(k, ct, mode, n1, n2, n3, n4) {k<ct, n1, mode>, k<ct, n2, mode>, k<ct, n3, mode>, k<ct, n4, mode>}
 #define VF_SMALL_ALL(mode)                                                                                  \
   {{VF_SMALL(k_small_bf16, 1, mode, 1, 2, 3, 4), VF_SMALL(k_small_bf16, 2, mode, 1, 2, 3, 4)},              \
@@ -947,5 +1045,52 @@ int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob,
   a.run = (int)((units + (1 << a.xcd_bits) - 1) >> a.xcd_bits);
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), smem, c->stream, a);
   VF_HIP(c, hipGetLastError());
+  return VF_OK;
+}
+
+// Whole schedules in one launch (CHAINED) while a decision's tiles are one round: a launch per step of a decision
+// costs more than the decision.  Launches per layer / one launch, 6000 ids, two layers: 64-128-128-1 fp32, one
+// problem 55.9 / 46.6 us, five 69.5 / 60.8, bf16 41.8 / 34.3, 64-96-32-1 bf16, ten problems 46.5 / 35.9; 20 layers of
+// 4096 ids, 256-96-64-1 bf16, one problem 393 / 264, 256-64-1, four 371 / 239.  What is left of a decision is a
+// chain of small steps (vf_chain.hip) and the products of one sub-tile per SIMD.
+// Sub-tiles per workgroup with which all tiles of a decision are on the compute units at once (one wave per SIMD
+// if that does), 0: there are too many.
+static int small_chain_spw(const vf_ctx *c) {
+  if (!vfk_small_generates(c) || c->M < 1) return 0;
+  int ncu = 256;
+  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
+  const int64_t subs = (c->M + (c->model.dtype == VF_BF16 ? 31 : 15)) / (c->model.dtype == VF_BF16 ? 32 : 16);
+  for (int spw = 4; spw <= 8; spw += 4)
+    if ((subs + spw - 1) / spw * c->B <= ncu) return spw;
+  return 0;
+}
+
+bool vfk_small_can_chain(const vf_ctx *c) { return small_chain_spw(c) != 0; }
+
+int vfk_small_chain(vf_ctx *c, int first, int last, int32_t *out_states, int32_t *out_cids, float *out_vals) {
+  const int spw = small_chain_spw(c);
+  if (spw == 0 || first > last) return VF_ESTATE;
+  const bool bf16 = c->model.dtype == VF_BF16;
+  const int base = bf16 ? 32 : 16;
+  SmallArgs a = {};
+  const int rc = chain_args(c, first, last, (int)((c->M + base * spw - 1) / (base * spw)), out_states, out_cids, out_vals, &a.ca);
+  if (rc != VF_OK) return rc;
+  a.md = c->pm.small;
+  a.M = c->M;
+  a.spp = 1;
+  a.spw = spw;
+  a.na.eps = c->noise_eps;
+  a.na.k0 = (uint32_t)c->noise_seed; a.na.k1 = (uint32_t)(c->noise_seed >> 32);
+  a.na.stage = first; a.na.first_rollout = c->noise_first;
+  const size_t smem = (size_t)a.md.nw * 16 + (size_t)a.md.nbias * 4 + 1024;
+  static constexpr small_kernel kerns[2][4] = {
+      {k_small_bf16<1, 1, CHAINED>, k_small_bf16<1, 2, CHAINED>, k_small_bf16<1, 3, CHAINED>, k_small_bf16<1, 4, CHAINED>},
+      {k_small_f32<1, 2, CHAINED>, k_small_f32<1, 4, CHAINED>, k_small_f32<1, 6, CHAINED>, k_small_f32<1, 8, CHAINED>}};
+  const small_kernel kern = kerns[bf16 ? 0 : 1][a.md.NT * base / 32 - 1];
+  vf_prof_scope prof(c, VF_PROF_SCORE);
+  VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+  hipLaunchKernelGGL(kern, dim3((unsigned)(c->B * a.ca.group)), dim3(512), smem, c->stream, a);
+  VF_HIP(c, hipGetLastError());
+  c->dec_stage = last + 1 < c->S ? last + 1 : -1;
   return VF_OK;
 }

@@ -1,4 +1,4 @@
-"""GPU: schedules of a few problems in one launch (vf_chain.hip) against the launches layer by layer, bit for bit."""
+"""GPU: schedules of a few problems in one launch (vf_chain.hip, vf_small.hip) against the launches layer by layer, bit for bit."""
 import numpy as np
 import pytest
 
@@ -26,10 +26,10 @@ def space(shape, F):
     return I.make_space([1, 2], [1], [4], perms, 1, 1, [I.ROOT, I.L2], 1, F)                                  # 8
 
 
-def context(vf, pipes, sp, dims):
+def context(vf, pipes, sp, dims, dtype=I.BF16):
     ctx = vf.vf_create(0)
     vf.vf_set_space(ctx, sp); vf.vf_set_pipeline(ctx, pipes)
-    vf.vf_set_model(ctx, I.model_record(I.MLP, dims, I.BF16), I.mlp_weights(dims, 3, bias_std=0.1))
+    vf.vf_set_model(ctx, I.model_record(I.MLP, dims, dtype), I.mlp_weights(dims, 3, bias_std=0.1))
     return ctx
 
 
@@ -107,3 +107,26 @@ def test_chain_in_a_graph(vf):
             vf.vf_reset_state(ctx)
             assert same([t.cpu().numpy() for t in vf.vf_greedy_schedule(ctx, last=9 + k)][1][:, :10 + k], ref[1][:, :10 + k])
         vf.vf_destroy(ctx)
+
+
+# small networks: one, four or eight waves of a workgroup have a sub-tile (32 ids in bf16, 16 in fp32), the last ones
+# none or part of one; 768 ids: 12 tiles of 64 in fp32 up to 21 problems, of 128 behind that
+@pytest.mark.parametrize("dims,dtype", [([64, 128, 128, 1], I.FP32), ([256, 40, 24, 1], I.FP32), ([64, 96, 32, 1], I.BF16),
+                                        ([256, 64, 1], I.BF16)])
+@pytest.mark.parametrize("shape,B", [("whole", 1), ("whole", 22), ("odd", 3), ("full", 2), ("one", 40)])
+@pytest.mark.parametrize("wait", [1 << 22, 0])
+def test_small_chain_equals_layer_by_layer(vf, dims, dtype, shape, B, wait):
+    pipes = np.stack([I.random_pipeline(7, 70 + b, max_hw=60, max_c=160) for b in range(B)])
+    pipes[B // 2, 2, 3] = 2
+    ctx = context(vf, pipes, space(shape, dims[0]), dims, dtype)
+    vf.vf_set_wait_limit(ctx, wait)
+    for eps in (0.0, 0.1):
+        vf.vf_set_noise(ctx, eps, 11, 2)
+        whole, launches = greedy_with_launches(vf, ctx)
+        assert launches == 1
+        assert same(whole, layer_by_layer(vf, ctx))
+    vf.vf_reset_state(ctx)
+    vf.vf_greedy_schedule(ctx, last=2)
+    best, value = (t.cpu().numpy() for t in vf.vf_argmin_step(ctx, 3, True))
+    assert np.array_equal(best, whole[1][:, 3]) and np.array_equal(value, whole[2][:, 3])
+    vf.vf_destroy(ctx)
