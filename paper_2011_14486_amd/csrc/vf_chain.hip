@@ -360,7 +360,7 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
     stage = next;
     if (w == 6) pre = chain_prefetch(ca, row, stage, lane);
   }
-  chain_leave(sh, ca, slots, claims, ntiles, tid);
+  chain_leave(sh, ca, slots, claims, p, ntiles, tid);
 }
 
 }  // namespace

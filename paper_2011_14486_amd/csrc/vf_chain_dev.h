@@ -210,7 +210,6 @@ __device__ __forceinline__ void chain_tables(const ChainShared &sh, const DecPac
     ca.t.vals[at] = v;
     if (member == 0 && ca.out_cids) ca.out_cids[at] = id;
     if (member == 0 && ca.out_vals) ca.out_vals[at] = v;
-    if (!ok) ca.t.alive[p] = 0;
   }
   if (tid == 257 || tid == 258) ca.t.prefix[((size_t)p * (ca.t.S + 1) + stage + 1) * 2 + tid - 257] = sh.sums[tid - 257];
 }
@@ -254,9 +253,10 @@ __device__ __forceinline__ int32_t chain_prefetch(const ChainArgs &ca, size_t ro
   return pre;
 }
 
-// The last workgroup of the problem to leave clears its words.
+// The last workgroup of the problem to leave clears its words, and marks a problem that found no winner: one
+// that only starts when others have gone on still needs the mark that the call began with.
 __device__ __forceinline__ void chain_leave(ChainShared &sh, const ChainArgs &ca, unsigned long long *slots, unsigned int *claims,
-                                            int ntiles, int tid) {
+                                            int p, int ntiles, int tid) {
   const int S = ca.t.S;
   __syncthreads();
   if (tid == 0) sh.missing = (int)(atomicAdd(&claims[S], 1u) + 1u);
@@ -264,6 +264,7 @@ __device__ __forceinline__ void chain_leave(ChainShared &sh, const ChainArgs &ca
   if (sh.missing == ca.group) {
     for (size_t i = (size_t)ca.first * ntiles + tid; i < (size_t)(ca.last + 1) * ntiles; i += 512) slots[i] = 0ull;
     for (int i = tid; i <= S; i += 512) claims[i] = 0u;
+    if (tid == 0 && sh.st16[15] == 0) ca.t.alive[p] = 0;
   }
 }
 

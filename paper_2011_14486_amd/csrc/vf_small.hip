@@ -300,7 +300,7 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
     if constexpr (CHAIN) {
       while (tile >= a.ca.ntiles)
         if (!chain_between(sh, a.ca, slots, claims, p, row, member, cur, stage, tile, c_next, pre, threadIdx.x)) {
-          chain_leave(sh, a.ca, slots, claims, a.ca.ntiles, threadIdx.x);
+          chain_leave(sh, a.ca, slots, claims, p, a.ca.ntiles, threadIdx.x);
           return;
         }
       n0 = ((int64_t)tile * a.spw + w) * (32 * CT);
@@ -627,7 +627,7 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
     if constexpr (CHAIN) {
       while (tile >= a.ca.ntiles)
         if (!chain_between(sh, a.ca, slots, claims, p, row, member, cur, stage, tile, c_next, pre, threadIdx.x)) {
-          chain_leave(sh, a.ca, slots, claims, a.ca.ntiles, threadIdx.x);
+          chain_leave(sh, a.ca, slots, claims, p, a.ca.ntiles, threadIdx.x);
           return;
         }
       n0 = ((int64_t)tile * a.spw + w) * (16 * CT);
