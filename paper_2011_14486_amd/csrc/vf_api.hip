@@ -111,7 +111,6 @@ void free_pipeline(vf_ctx *c) {
   c->d_alive = c->d_forced = nullptr;
   c->d_vals = nullptr;
   c->d_decpack = nullptr;
-  c->d_decpack2 = nullptr;
   c->dec_stage = -1;
   void *alt[] = {c->d_alt_states, c->d_alt_cf, c->d_alt_prefix, c->d_alt_cids, c->d_alt_vals, c->d_alt_alive,
                  c->d_sel_val,    c->d_sel_idx, c->d_sel_n};
@@ -333,8 +332,7 @@ int vf_set_pipeline(vf_ctx *c, const vf_stage *st, int S, int B) {
   if (rc == VF_OK) rc = dev_alloc(c, c->d_vals, n);
   if (rc == VF_OK) rc = dev_alloc(c, c->d_alive, (size_t)B);
   if (rc == VF_OK) rc = dev_alloc(c, c->d_forced, n);
-  if (rc == VF_OK) rc = dev_alloc(c, c->d_decpack, (size_t)2 * B * VF_DECPACK_DWORDS);
-  if (rc == VF_OK) c->d_decpack2 = c->d_decpack + (size_t)B * VF_DECPACK_DWORDS;
+  if (rc == VF_OK) rc = dev_alloc(c, c->d_decpack, (size_t)B * VF_DECPACK_DWORDS);
   if (rc != VF_OK) {
     free_pipeline(c);
     return rc;

@@ -4,6 +4,7 @@
 // slots' candidates (the LAYER form of k_whole: compact scores by list position and the first
 // minimum of every 64 entries), the choice of the B smallest of them (k_beam_select), and per
 // survivor its commit and the opening of its next decision (k_beam_advance).
+#include <type_traits>
 #include <utility>
 
 #include "vf_internal.h"
@@ -294,13 +295,15 @@ __global__ __launch_bounds__(SEL_THREADS) void k_beam_select(const float *scores
 // scorer.  The next context comes from the parent's rows in the old tables and the winner's rows in
 // LDS, so nothing waits for the copies.  A slot without a survivor is cleared; if the layer has none
 // at all the schedules end: every slot is carried over unchanged and marked dead.
-template <int RT>
-__global__ __launch_bounds__(512) void k_beam_advance(Tables t, AltTables nw, int stage, int open, uint32_t M, int64_t Mpad,
+// Two workgroups per slot: one goes on to the next decision, the other carries the parent's rows over.
+template <int RT, int AHEAD>
+__global__ __launch_bounds__(512) void k_beam_advance(Tables t, AltTables nw, int stage, int open, int64_t Mpad,
                                                       const float *sel_val, const int32_t *sel_idx, const int32_t *sel_n,
-                                                      const uint32_t *decpack_cur, uint32_t *decpack_next, vf_fast_dev md,
-                                                      uint32_t *pub, uint32_t *list) {
+                                                      vf_fast_dev md, const uint32_t *pub_cur, uint32_t *pub, uint32_t *list) {
   __shared__ AdvanceShared sh;
-  const int tid = threadIdx.x, lane = tid & 63, j = blockIdx.x, S = t.S;
+  const int tid = threadIdx.x, lane = tid & 63, width = (int)gridDim.x / 2, S = t.S;
+  const bool carries = (int)blockIdx.x >= width;
+  const int j = (int)blockIdx.x - (carries ? width : 0);
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nsel = sel_n[0];
   const size_t dst = (size_t)j * S;
@@ -308,9 +311,7 @@ __global__ __launch_bounds__(512) void k_beam_advance(Tables t, AltTables nw, in
   int32_t cid = -1;
   if (nsel == 0) src_slot = j;
   else if (j < nsel) { src_slot = sel_idx[j] / (int32_t)Mpad; cid = sel_idx[j] % (int32_t)Mpad; }
-  if (cid >= 0 && tid < VF_DECPACK_DWORDS)
-    reinterpret_cast<uint32_t *>(&sh.pk)[tid] = decpack_cur[(size_t)src_slot * VF_DECPACK_DWORDS + tid];
-  {
+  if (carries) {
     const int rows = nsel == 0 ? S : stage;  // committed rows to carry over
     const size_t src = (size_t)(src_slot < 0 ? 0 : src_slot) * S;
     const int32_t *const cf = t.cf + src * 64, *const states = t.states + src * 16, *const cids = t.cids + src;
@@ -334,14 +335,16 @@ __global__ __launch_bounds__(512) void k_beam_advance(Tables t, AltTables nw, in
       for (int i = tid; i <= stage; i += 512) { nci[i] = -1; nva[i] = __builtin_inff(); }
       for (int i = tid; i < (S + 1) * 2; i += 512) npre[i] = 0;
     }
+    return;
   }
   if (cid >= 0) {
+    fetch_opened(sh, pub_cur + (size_t)src_slot * VF_PUB_WORDS, tid);
     if (tid == 0) { sh.cid = cid; sh.val = sel_val[j]; }
     Tables tn = t;
     tn.states = nw.states; tn.cf = nw.cf; tn.prefix = nw.prefix; tn.cids = nw.cids; tn.alive = nw.alive; tn.vals = nw.vals;
-    advance_layer<RT>(sh, t, tn, src_slot, j, stage, open, M, md, pub + (size_t)j * VF_PUB_WORDS, list + (size_t)j * Mpad,
-                      decpack_next + (size_t)j * VF_DECPACK_DWORDS, tid, w, lane);
-    if (tid == 0) {
+    advance_layer<RT, AHEAD>(sh, t, tn, src_slot, j, stage, open, md, pub + (size_t)j * VF_PUB_WORDS, list + (size_t)j * Mpad,
+                             tid, w, lane);
+    if (tid == 256) {  // (the thread that advance_layer has mark the dead)
       nw.alive[j] = sh.sums[2] ? 1 : 0;
       if (!sh.sums[2]) t.err[0] = 1;  // cannot happen: only valid candidates have finite scores
     }
@@ -407,25 +410,29 @@ int vfk_beam_layers(vf_ctx *c, int first, int last) {
   if (rc != VF_OK) return rc;
   vf_fast_dev fd;
   vfk_fast_dev(c, true, &fd, nullptr, nullptr);
-  uint32_t *cur = c->d_decpack, *next = c->d_decpack2;
+  int ncu = 256;
+  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
+  const bool ahead = c->B <= ncu;  // (as in vfk_greedy_layers)
   for (int i = first; i <= last; ++i) {
     int nparts = 0;
     rc = vfk_layer_score(c, -1, c->d_scores, &nparts);
     if (rc != VF_OK) return rc;
     const uint32_t *list = reinterpret_cast<const uint32_t *>(c->d_wlist);
+    uint32_t *const pub = c->d_pub + (size_t)c->pub_set * c->B * VF_PUB_WORDS;
+    c->pub_set ^= 1;
     hipLaunchKernelGGL(k_beam_select, dim3(1), dim3(SEL_THREADS), 0, c->stream, c->d_scores, c->d_pval, c->d_pidx,
-                       (const uint32_t *)(c->d_pub + (size_t)c->B * VF_PUB_WORDS), nparts, list, c->d_pub, c->d_space, (int64_t)c->Mpad, c->B, c->d_sel_val, c->d_sel_idx, c->d_sel_n);
+                       (const uint32_t *)(c->d_pub + (size_t)2 * c->B * VF_PUB_WORDS), nparts, list, pub, c->d_space, (int64_t)c->Mpad, c->B, c->d_sel_val, c->d_sel_idx, c->d_sel_n);
     VF_HIP(c, hipGetLastError());
     {
       vf_prof_scope prof(c, VF_PROF_COMMIT);
-      hipLaunchKernelGGL((c->pm.fast_rt == 4 ? k_beam_advance<4> : k_beam_advance<2>), dim3((unsigned)c->B), dim3(512), 0,
-                         c->stream, tables_of(c), alt_of(c), i, (int)(i < last), (uint32_t)c->M, (int64_t)c->Mpad,
-                         c->d_sel_val, c->d_sel_idx, c->d_sel_n, cur, next, fd, c->d_pub,
+      hipLaunchKernelGGL((c->pm.fast_rt == 4 ? ahead ? k_beam_advance<4, 4> : k_beam_advance<4, 0> : ahead ? k_beam_advance<2, 14> : k_beam_advance<2, 0>),
+                         dim3((unsigned)c->B * 2), dim3(512), 0,
+                         c->stream, tables_of(c), alt_of(c), i, (int)(i < last), (int64_t)c->Mpad,
+                         c->d_sel_val, c->d_sel_idx, c->d_sel_n, fd, pub, c->d_pub + (size_t)c->pub_set * c->B * VF_PUB_WORDS,
                          reinterpret_cast<uint32_t *>(c->d_wlist));
       VF_HIP(c, hipGetLastError());
     }
-    c->dec_stage = -1;  // (the context of the next layer is in either buffer, or not built)
-    std::swap(cur, next);
+    c->dec_stage = -1;  // (the context of the next layer is among the opened decisions)
     vfk_beam_swap(c);
     c->n_sched = i + 1;
   }

@@ -297,7 +297,7 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
           for (int r = 0; r < RT; ++r) asm volatile("" : "+v"(ends[i][r].x), "+v"(ends[i][r].y), "+v"(ends[i][r].z), "+v"(ends[i][r].w));
       }
       // ---- s_i := the winner: its rows, a share each by threads of four waves; the ids of the next tile
-      chain_winner(sh, pk, lane, w);
+      winner_rows(sh, pk, sh.win_c, lane, w);
       if (w == 4 && decides && sh.claim[1] < ntiles) take_apart(sh.claim[1], pk.sp);
       __syncthreads();
       chain_tables(sh, pk, ca, p, row, stage, member, tid);
@@ -305,11 +305,11 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
     if (!opens) break;
 
     // ---- the next decision's context: the shared rows, so that the folded layer can begin
-    chain_shared_rows(sh, nk, ca, stage, tid);
+    next_shared_rows(sh, nk, stage >= ca.first, stage, tid);
     __syncthreads();
     if (!decides) {
       // (a schedule in pieces: the context is left for the call that goes on)
-      if (tid == 0) chain_derive(sh, nk, ca, stage);
+      if (tid == 0) next_derive(sh, nk, stage >= ca.first, stage);
       __syncthreads();
       if (member == 0)
         for (int i = tid; i < VF_DECPACK_DWORDS; i += 512)
@@ -349,7 +349,7 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
 #pragma unroll
           for (int q = 0; q < 16; ++q) fa[r][q] = bv[r][q] + fa[r][q];
       } else if (ph == 0) {
-        if (lane == 0) chain_derive(sh, nk, ca, stage);
+        if (lane == 0) next_derive(sh, nk, stage >= ca.first, stage);
       } else {
         fill_evaltabs(sh.tabs, nk.d, nk.sp, 64);
         if (w == 4 && t < ntiles) look_shut(t, nk);

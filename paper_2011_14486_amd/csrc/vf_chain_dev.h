@@ -20,11 +20,6 @@ struct ChainArgs {
   unsigned long long *stat;    // nullable: [0] += ids pushed through the network, [1] += valid ones
 };
 
-// Entry i of a state record in the 64 core features (i < 15).
-__device__ __forceinline__ int state_feature(int i) {
-  return i < 3 ? 17 + i : i == 3 ? 23 : i == 4 ? 26 : i == 5 ? 29 : i < 8 ? 26 + i : i < 12 ? 26 + i : 8 + i;
-}
-
 struct ChainShared {
   DecPack pks[2];     // the open decision's context and the next one's, in turn
   EvalTabs tabs;      // the open decision's quotient tables
@@ -66,7 +61,7 @@ __device__ __forceinline__ void chain_rows(ChainShared &sh, DecPack &nk, const D
     // the call's first stage, from the tables
     dec_fetch_rows(nk.d, nk.sp, ds, ca.t, p, next, -1);
     __syncthreads();
-    dec_fetch_anchor(nk.d, ds, ca.t, p, next, -1);
+    dec_fetch_anchor(nk.d, ds, ca.t, p, next, -1, tid);
     if (tid >= 128 && tid < 128 + VF_STAT_WORDS) nk.stat[tid - 128] = stat_word(nk.d, tid - 128);
     if (tid < 3) sh.sums[tid] = ds.sc[tid < 2 ? 1 + tid : 0];
     if (tid == CLAIMER) sh.claim[1] = (int)c_next;
@@ -161,36 +156,6 @@ __device__ __forceinline__ void chain_poll(ChainShared &sh, const ChainArgs &ca,
   if (lane == 0) { sh.win_v = v; sh.win_c = c; sh.missing = miss; sh.claim[1] = (int)c_next; }
 }
 
-// s_i := the winner: its rows, a share each by threads of four waves.
-__device__ __forceinline__ void chain_winner(ChainShared &sh, const DecPack &pk, int lane, int w) {
-  const int32_t c = sh.win_c;
-  if (lane == 0 && w < 4) {
-    int32_t core[64];
-    const Digits dg = unpack_digits((uint32_t)(c >= 0 ? c : 0));
-    if (w == 0) {
-      const bool ok = eval_digits<true>(pk.d, pk.sp, dg, &sh.tabs, core) && c >= 0;
-#pragma unroll
-      for (int k = 0; k < 32; ++k) sh.cf64[k] = ok ? core[k] : 0;
-      sh.sums[2] = ok ? pk.d.lvl_ok[0] : 0;
-      sh.st16[15] = ok ? 1 : 0;
-    } else if (w == 1) {
-      const bool ok = eval_digits<true>(pk.d, pk.sp, dg, &sh.tabs, core) && c >= 0;
-#pragma unroll
-      for (int k = 32; k < 42; ++k) sh.cf64[k] = ok ? core[k] : 0;
-      sh.sums[0] = ok ? (int32_t)sadd((uint32_t)pk.d.pm, (uint32_t)core[40]) : pk.d.pm;
-    } else if (w == 2) {
-      const bool ok = eval_digits<true>(pk.d, pk.sp, dg, &sh.tabs, core) && c >= 0;
-#pragma unroll
-      for (int k = 42; k < 48; ++k) sh.cf64[k] = ok ? core[k] : 0;
-    } else {
-      const bool ok = eval_digits<true>(pk.d, pk.sp, dg, &sh.tabs, core) && c >= 0;
-#pragma unroll
-      for (int k = 48; k < 64; ++k) sh.cf64[k] = ok ? core[k] : 0;
-      sh.sums[1] = ok ? (int32_t)sadd((uint32_t)pk.d.pb, (uint32_t)core[50]) : pk.d.pb;
-    }
-  }
-}
-
 // The winner to the tables: every workgroup writes them (it reads its anchors from there), one the caller's.
 __device__ __forceinline__ void chain_tables(const ChainShared &sh, const DecPack &pk, const ChainArgs &ca, int p, size_t row, int stage,
                                              int member, int tid) {
@@ -212,33 +177,6 @@ __device__ __forceinline__ void chain_tables(const ChainShared &sh, const DecPac
     if (member == 0 && ca.out_vals) ca.out_vals[at] = v;
   }
   if (tid == 257 || tid == 258) ca.t.prefix[((size_t)p * (ca.t.S + 1) + stage + 1) * 2 + tid - 257] = sh.sums[tid - 257];
-}
-
-// The rows of the next context that the winner decides, and with them all of its shared input rows.
-__device__ __forceinline__ void chain_shared_rows(ChainShared &sh, DecPack &nk, const ChainArgs &ca, int stage, int tid) {
-  const bool fresh = stage >= ca.first && nk.d.srec[8] == stage;  // the anchor is the stage just decided
-  if (stage >= ca.first) {
-    if (tid < 15) sh.st16[tid] = sh.cf64[state_feature(tid)];
-    if (tid >= 64 && tid < 112) nk.d.nb[tid - 64] = sh.cf64[tid - 64];
-    if (tid >= 320 && tid < 344) nk.stat[16 + tid - 320] = pack_bf16(plog2_dev(sh.cf64[2 * (tid - 320)]), plog2_dev(sh.cf64[2 * (tid - 320) + 1]));
-  }
-  if (tid >= 384 && tid < 388) {
-    const bool anchored = nk.d.srec[8] >= 0 && (fresh ? sh.st16[15] : sh.ds.ast[15]) == 1;
-    const int k = tid - 384;
-    const int32_t lo = k == 0 ? (fresh ? sh.cf64[42] : sh.ds.acf[0]) : k == 1 ? (fresh ? sh.cf64[32] : sh.ds.acf[2]) : k == 2 ? sh.sums[0] : sh.ds.sc[3];
-    const int32_t hi = k == 0 ? (fresh ? sh.cf64[54] : sh.ds.acf[1]) : k == 1 ? 0 : k == 2 ? sh.sums[1] : sh.ds.sc[4];
-    nk.stat[12 + k] = k < 2 && !anchored ? 0u : pack_bf16(plog2_dev(lo), plog2_dev(hi));
-  }
-}
-
-// One thread: the rest of the next context.
-__device__ __forceinline__ void chain_derive(const ChainShared &sh, DecPack &nk, const ChainArgs &ca, int stage) {
-  const bool fresh = stage >= ca.first && nk.d.srec[8] == stage;
-  if (fresh)
-    dec_derive(nk.d, nk.sp, stage + 1, sh.sums[2], sh.st16, sh.ds.arec, sh.cf64, false, sh.sums[0], sh.sums[1], sh.ds.sc[3], sh.ds.sc[4]);
-  else
-    dec_derive(nk.d, nk.sp, stage + 1, sh.sums[2], sh.ds.ast, sh.ds.arec, sh.ds.acf, true, sh.sums[0], sh.sums[1], sh.ds.sc[3],
-               sh.ds.sc[4]);
 }
 
 // One wave: what the context behind the open one takes from memory, for the end of this decision.
@@ -287,14 +225,14 @@ __device__ __forceinline__ void chain_leave(ChainShared &sh, const ChainArgs &ca
       __syncthreads();  // (before the word is written again)
       return true;
     }
-    chain_winner(sh, pk, lane, w);
+    winner_rows(sh, pk, sh.win_c, lane, w);
     __syncthreads();
     chain_tables(sh, pk, ca, p, row, stage, member, tid);
   }
   if (!opens) return false;
-  chain_shared_rows(sh, nk, ca, stage, tid);
+  next_shared_rows(sh, nk, stage >= ca.first, stage, tid);
   __syncthreads();
-  if (tid == 0) chain_derive(sh, nk, ca, stage);
+  if (tid == 0) next_derive(sh, nk, stage >= ca.first, stage);
   __syncthreads();
   if (!decides) {
     // (a schedule in pieces: the context is left for the call that goes on)

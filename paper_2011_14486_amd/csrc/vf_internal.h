@@ -16,7 +16,7 @@
 // size of one packed decision context (see vf_sched_dev.h)
 #define VF_DECPACK_DWORDS 428
 // size of one opened decision as it is left in memory for other workgroups (see vf_layer_dev.h)
-#define VF_PUB_WORDS 1649
+#define VF_PUB_WORDS 1652
 
 // Where the scorers put their per-workgroup (value, id) minima when the context's own
 // growable buffers must not be used (nullable everywhere it is taken): `cap` pairs.
@@ -97,7 +97,6 @@ struct vf_ctx {
   int32_t *d_forced = nullptr;  // [B][S] staging for vf_set_state
   uint32_t *d_decpack = nullptr; // [B][VF_DECPACK_DWORDS] decision context of stage dec_stage
   int dec_stage = -1;            // stage d_decpack was built for, -1: none
-  uint32_t *d_decpack2 = nullptr; // second context buffer (behind the first in the same allocation), for beam search
   unsigned long long *d_chain = nullptr; size_t chain_units = 0;  // words of vfk_greedy_chain (zero between launches), in 16 bytes
 
   // beam search: a second set of state tables (the survivors of a layer are written
@@ -150,7 +149,8 @@ struct vf_ctx {
   mutable int occ_blocks = 0;
   unsigned int wait_rounds = 1u << 22;  // bound of the waits between workgroups that share a problem
   int32_t *d_wlist = nullptr; size_t wlist_elems = 0;  // [B][Mpad] lists of valid candidates (packed digits)
-  uint32_t *d_pub = nullptr; size_t pub_elems = 0;     // [B][VF_PUB_WORDS] opened decisions of a single layer, number of minima
+  uint32_t *d_pub = nullptr; size_t pub_elems = 0;     // [2][B][VF_PUB_WORDS] opened decisions of a single layer, number of minima
+  int pub_set = 0;                                      // the set that the next layer is scored from
   mutable const void *layer_kern = nullptr;            // the scorer that vfk_layer_fits found to fit, and its LDS
   mutable size_t layer_smem = 0;
 

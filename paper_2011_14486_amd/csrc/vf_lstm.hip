@@ -10,6 +10,8 @@
 // step at every commit.  A candidate then costs one cell step on its own features plus
 // one step per stage still unscheduled; for those the input part of the gates does not
 // depend on the candidate either and comes from a per-problem table.
+#include <type_traits>
+
 #include "vf_internal.h"
 
 namespace {

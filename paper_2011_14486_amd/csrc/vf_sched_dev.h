@@ -84,17 +84,6 @@ __device__ void needed(const int32_t *srec, const int32_t *arec, const uint32_t 
   E[2] = (arec[0] == VF_CONV) ? (uint32_t)srec[3] : umin((uint32_t)srec[3], box[2]);
 }
 
-// What the decision for one stage has just produced, for a caller that builds the next
-// stage's context before those rows are in memory (they are in LDS): the stage's 64 committed
-// features, its state record, the running sums behind it, and whether the problem goes on.
-// stage < 0: nothing is overridden.
-struct FreshRows {
-  int stage;
-  const int32_t *cf;   // [64]
-  const int32_t *st;   // [16]
-  int32_t pm, pb, alive;
-};
-
 // One thread: what the decision context derives from the rows it was given - the regions and
 // instance counts per compute_at level from the anchor's committed loop structure, the levels
 // on offer, the anchor's context features, the running sums.  ast / arec: the anchor's state
@@ -148,9 +137,9 @@ __device__ __forceinline__ void dec_derive(Dec &d, const vf_space &sp, int stage
 // Cooperative set-up of the decision context for problem b, stage `stage`, in three steps with
 // a workgroup barrier between them: every word that comes from memory is fetched by a thread of
 // its own, in two rounds (the anchor's rows need the stage record first), and one thread then
-// works on LDS only.  Rows of stage `fresh` are left out of the fetches: dec_finish takes them
-// from fr (a caller that has just decided that stage can run the two fetch rounds before it
-// knows the winner).
+// works on LDS only.  Rows of stage `fresh` are left out of the fetches: next_shared_rows and
+// next_derive take them from LDS (a caller that decides that stage runs the two fetch rounds before
+// it knows the winner).
 struct DecScratch {
   int32_t sc[8];  // alive, prefix sums (2), suffix sums (2)
   int32_t ast[16], arec[16], acf[4];
@@ -185,8 +174,8 @@ __device__ void dec_fetch_rows(Dec &d, vf_space &sp, DecScratch &ds, const Table
   if (tid == 62 || tid == 63) ds.sc[tid - 59] = t.suffix[(row + stage) * 2 + (tid - 62)];
 }
 
-__device__ void dec_fetch_anchor(const Dec &d, DecScratch &ds, const Tables &t, int b, int stage, int fresh) {
-  const int tid = threadIdx.x, S = t.S;
+__device__ void dec_fetch_anchor(const Dec &d, DecScratch &ds, const Tables &t, int b, int stage, int fresh, int tid) {
+  const int S = t.S;
   const size_t row = (size_t)b * S;
   const int a = d.srec[8];
   const bool fetch = a >= 0 && a < stage && a != fresh;
@@ -198,31 +187,14 @@ __device__ void dec_fetch_anchor(const Dec &d, DecScratch &ds, const Tables &t, 
   }
 }
 
-__device__ void dec_finish(Dec &d, const vf_space &sp, DecScratch &ds, int stage, const FreshRows &fr) {
-  const int tid = threadIdx.x, nt = blockDim.x;
-  if (fr.stage >= 0) {
-    // the rows of the stage decided last, from the caller
-    const int k = stage - fr.stage;
-    if (k >= 1 && k <= 3)
-      for (int f = tid; f < 48; f += nt) d.nb[(k - 1) * 48 + f] = fr.cf[f];
-    if (d.srec[8] == fr.stage) {
-      if (tid < 16) ds.ast[tid] = fr.st[tid];
-      else if (tid >= 32 && tid < 36) ds.acf[tid - 32] = fr.cf[tid == 32 ? 42 : tid == 33 ? 54 : tid == 34 ? 32 : 23];
-    }
-    if (tid == 59) { ds.sc[0] = fr.alive; ds.sc[1] = fr.pm; ds.sc[2] = fr.pb; }
-    __syncthreads();
-  }
-  if (tid == 0) dec_derive(d, sp, stage, ds.sc[0], ds.ast, ds.arec, ds.acf, true, ds.sc[1], ds.sc[2], ds.sc[3], ds.sc[4]);
-  __syncthreads();
-}
-
-__device__ void build_dec_from(Dec &d, vf_space &sp, const Tables &t, int b, int stage, const FreshRows &fr) {
+__device__ void build_dec_from(Dec &d, vf_space &sp, const Tables &t, int b, int stage) {
   __shared__ DecScratch ds;
-  dec_fetch_rows(d, sp, ds, t, b, stage, fr.stage);
+  dec_fetch_rows(d, sp, ds, t, b, stage, -1);
   __syncthreads();
-  dec_fetch_anchor(d, ds, t, b, stage, fr.stage);
+  dec_fetch_anchor(d, ds, t, b, stage, -1, threadIdx.x);
   __syncthreads();
-  dec_finish(d, sp, ds, stage, fr);
+  if (threadIdx.x == 0) dec_derive(d, sp, stage, ds.sc[0], ds.ast, ds.arec, ds.acf, true, ds.sc[1], ds.sc[2], ds.sc[3], ds.sc[4]);
+  __syncthreads();
 }
 
 // The same context with one round of fetches and the rest read by the one thread that derives
@@ -568,9 +540,7 @@ __device__ __forceinline__ uint32_t stat_word(const Dec &d, int q) {
 
 // Builds the pack for (problem b, stage) in LDS (every thread of the block takes part).
 [[maybe_unused]] __device__ void fill_decpack(DecPack &pk, const Tables &t, int b, int stage) {
-  FreshRows none;
-  none.stage = -1; none.cf = nullptr; none.st = nullptr; none.pm = none.pb = none.alive = 0;
-  build_dec_from(pk.d, pk.sp, t, b, stage, none);  // (two rounds of fetches instead of three)
+  build_dec_from(pk.d, pk.sp, t, b, stage);  // (two rounds of fetches instead of three)
   for (int q = threadIdx.x; q < VF_STAT_WORDS; q += blockDim.x) pk.stat[q] = stat_word(pk.d, q);
   __syncthreads();
 }
@@ -620,59 +590,6 @@ __device__ __forceinline__ uint32_t stat_word(const Dec &d, int q) {
   }
 }
 
-// commit_winner for a caller that goes on to the next decision by itself: the winner's rows are
-// left in LDS (cf64, st16, and the values of a FreshRows record) for build_dec_from, and reach
-// the tables only if `store` - every workgroup of a launch works them out, one of them writes.
-// The running sums of the decision's own stage are taken from its context (d.pm, d.pb).
-[[maybe_unused]] __device__ __forceinline__ void commit_winner_fresh(const Tables &t, const Dec &d, const vf_space &sp, int b,
-                                                                   int stage, int32_t c, float v, uint32_t M,
-                                                                   const EvalTabs &tb, bool store, int32_t *cf64,
-                                                                   int32_t *st16, int32_t *sums3) {
-  const int S = t.S;
-  const size_t row = (size_t)b * S + stage;
-  int32_t *pre = t.prefix + ((size_t)b * (S + 1) + stage) * 2;
-  const int32_t pre_m = d.pm, pre_b = d.pb;
-  int32_t core[64];
-  bool ok = false;
-  if (c >= 0 && (uint32_t)c < M) ok = eval_digits<true>(d, sp, digits_small(sp, (uint32_t)c), &tb, core);
-  if (!ok) {
-#pragma unroll
-    for (int k = 0; k < 64; ++k) cf64[k] = 0;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) st16[k] = 0;
-    sums3[0] = pre_m; sums3[1] = pre_b; sums3[2] = 0;
-    if (store) {
-      t.alive[b] = 0;
-      t.cids[row] = -1;
-      t.vals[row] = __builtin_inff();
-      pre[2] = pre_m; pre[3] = pre_b;
-    }
-  } else {
-    int32_t st[16];
-    st[0] = core[17]; st[1] = core[18]; st[2] = core[19];
-    st[3] = core[23]; st[4] = core[26]; st[5] = core[29]; st[6] = core[32]; st[7] = core[33];
-    st[8] = core[34]; st[9] = core[35]; st[10] = core[36];
-    st[11] = core[37];
-    st[12] = core[20]; st[13] = core[21]; st[14] = core[22];
-    st[15] = 1;
-    const int32_t pm = (int32_t)sadd((uint32_t)pre_m, (uint32_t)core[40]), pb = (int32_t)sadd((uint32_t)pre_b, (uint32_t)core[50]);
-#pragma unroll
-    for (int k = 0; k < 64; ++k) cf64[k] = core[k];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) st16[k] = st[k];
-    sums3[0] = pm; sums3[1] = pb; sums3[2] = d.lvl_ok[0];
-    if (store) {
-#pragma unroll
-      for (int k = 0; k < 64; ++k) t.cf[row * 64 + k] = core[k];
-#pragma unroll
-      for (int k = 0; k < 16; ++k) t.states[row * 16 + k] = st[k];
-      t.cids[row] = c;
-      t.vals[row] = v;
-      pre[2] = pm; pre[3] = pb;
-    }
-  }
-}
-
 // The same as a real call, for kernels whose main loop should not carry the registers of
 // an inlined copy.  The table pointers that a commit touches come one by one, so that they
 // travel in registers: a structure would go through the stack (scratch memory, a round trip
@@ -687,6 +604,74 @@ __device__ __forceinline__ uint32_t stat_word(const Dec &d, int q) {
   t.vals = vals;
   t.S = S;
   commit_winner(t, d, sp, b, stage, c, v, M, false, &tb);
+}
+
+// ---- from a decision to the next, for a workgroup of 512 that has the decision's context (pk) and quotient tables in
+// LDS.  SH has cf64, st16, sums (the winner's rows, the sums behind it, alive), tabs and ds.
+
+// s_i := the candidate with the packed digits c (-1: none): its rows, a share each by threads of four waves.
+template <class SH>
+__device__ __forceinline__ void winner_rows(SH &sh, const DecPack &pk, int32_t c, int lane, int w) {
+  if (lane == 0 && w < 4) {
+    int32_t core[64];
+    const Digits dg = unpack_digits((uint32_t)(c >= 0 ? c : 0));
+    if (w == 0) {
+      const bool ok = eval_digits<true>(pk.d, pk.sp, dg, &sh.tabs, core) && c >= 0;
+#pragma unroll
+      for (int k = 0; k < 32; ++k) sh.cf64[k] = ok ? core[k] : 0;
+      sh.sums[2] = ok ? pk.d.lvl_ok[0] : 0;
+      sh.st16[15] = ok ? 1 : 0;
+    } else if (w == 1) {
+      const bool ok = eval_digits<true>(pk.d, pk.sp, dg, &sh.tabs, core) && c >= 0;
+#pragma unroll
+      for (int k = 32; k < 42; ++k) sh.cf64[k] = ok ? core[k] : 0;
+      sh.sums[0] = ok ? (int32_t)sadd((uint32_t)pk.d.pm, (uint32_t)core[40]) : pk.d.pm;
+    } else if (w == 2) {
+      const bool ok = eval_digits<true>(pk.d, pk.sp, dg, &sh.tabs, core) && c >= 0;
+#pragma unroll
+      for (int k = 42; k < 48; ++k) sh.cf64[k] = ok ? core[k] : 0;
+    } else {
+      const bool ok = eval_digits<true>(pk.d, pk.sp, dg, &sh.tabs, core) && c >= 0;
+#pragma unroll
+      for (int k = 48; k < 64; ++k) sh.cf64[k] = ok ? core[k] : 0;
+      sh.sums[1] = ok ? (int32_t)sadd((uint32_t)pk.d.pb, (uint32_t)core[50]) : pk.d.pb;
+    }
+  }
+}
+
+// Entry i of a state record in the 64 core features (i < 15).
+__device__ __forceinline__ int state_feature(int i) {
+  return i < 3 ? 17 + i : i == 3 ? 23 : i == 4 ? 26 : i == 5 ? 29 : i < 8 ? 26 + i : i < 12 ? 26 + i : 8 + i;
+}
+
+// The rows of the next context that the winner decides, and with them all of its shared input rows.
+// decided: `stage` has just been (otherwise there is none behind this context yet).
+template <class SH>
+__device__ __forceinline__ void next_shared_rows(SH &sh, DecPack &nk, bool decided, int stage, int tid) {
+  const bool fresh = decided && nk.d.srec[8] == stage;  // the anchor is the stage just decided
+  if (decided) {
+    if (tid < 15) sh.st16[tid] = sh.cf64[state_feature(tid)];
+    if (tid >= 64 && tid < 112) nk.d.nb[tid - 64] = sh.cf64[tid - 64];
+    if (tid >= 320 && tid < 344) nk.stat[16 + tid - 320] = pack_bf16(plog2_dev(sh.cf64[2 * (tid - 320)]), plog2_dev(sh.cf64[2 * (tid - 320) + 1]));
+  }
+  if (tid >= 384 && tid < 388) {
+    const bool anchored = nk.d.srec[8] >= 0 && (fresh ? sh.st16[15] : sh.ds.ast[15]) == 1;
+    const int k = tid - 384;
+    const int32_t lo = k == 0 ? (fresh ? sh.cf64[42] : sh.ds.acf[0]) : k == 1 ? (fresh ? sh.cf64[32] : sh.ds.acf[2]) : k == 2 ? sh.sums[0] : sh.ds.sc[3];
+    const int32_t hi = k == 0 ? (fresh ? sh.cf64[54] : sh.ds.acf[1]) : k == 1 ? 0 : k == 2 ? sh.sums[1] : sh.ds.sc[4];
+    nk.stat[12 + k] = k < 2 && !anchored ? 0u : pack_bf16(plog2_dev(lo), plog2_dev(hi));
+  }
+}
+
+// One thread: the rest of the next context.
+template <class SH>
+__device__ __forceinline__ void next_derive(const SH &sh, DecPack &nk, bool decided, int stage) {
+  const bool fresh = decided && nk.d.srec[8] == stage;
+  if (fresh)
+    dec_derive(nk.d, nk.sp, stage + 1, sh.sums[2], sh.st16, sh.ds.arec, sh.cf64, false, sh.sums[0], sh.sums[1], sh.ds.sc[3], sh.ds.sc[4]);
+  else
+    dec_derive(nk.d, nk.sp, stage + 1, sh.sums[2], sh.ds.ast, sh.ds.arec, sh.ds.acf, true, sh.sums[0], sh.sums[1], sh.ds.sc[3],
+               sh.ds.sc[4]);
 }
 
 // Builds the pack for (problem b, stage) in LDS and copies it to out[b].

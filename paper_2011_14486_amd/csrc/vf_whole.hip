@@ -20,6 +20,8 @@
 // one behind the first layer's activations, one behind the partial output dots.
 #include <stdlib.h>
 
+#include <type_traits>
+
 #include "vf_internal.h"
 
 namespace {
@@ -607,15 +609,15 @@ __global__ __launch_bounds__(512) void k_open_layer(vf_fast_dev md, const uint32
 // Between two LAYER launches of a greedy schedule: the decision of `stage` from the parts' minima,
 // committed, and (open) the next decision opened; one workgroup per problem.  One launch instead of
 // a commit and an opening that hands the context through memory.
-template <int RT>
-__global__ __launch_bounds__(512) void k_greedy_advance(Tables t, int stage, int open, uint32_t M, int64_t Mpad,
-                                                        vf_fast_dev md, uint32_t *decpack, uint32_t *pub, uint32_t *list,
+template <int RT, int AHEAD>
+__global__ __launch_bounds__(512) void k_greedy_advance(Tables t, int stage, int open, int64_t Mpad,
+                                                        vf_fast_dev md, uint32_t *pub, uint32_t *list,
                                                         float *pval, int32_t *pidx, int nparts) {
   __shared__ AdvanceShared sh;
   const int tid = threadIdx.x, lane = tid & 63, p = blockIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  uint32_t *const ctx = decpack + (size_t)p * VF_DECPACK_DWORDS;
-  if (tid < VF_DECPACK_DWORDS) reinterpret_cast<uint32_t *>(&sh.pk)[tid] = ctx[tid];
+  pub += (size_t)p * VF_PUB_WORDS;
+  fetch_opened(sh, pub, tid);
   pval += (size_t)p * nparts;
   pidx += (size_t)p * nparts;
   if (w == 7) {  // (the wave with the least to fetch)
@@ -625,8 +627,7 @@ __global__ __launch_bounds__(512) void k_greedy_advance(Tables t, int stage, int
     wave_min(v, c);
     if (lane == 0) { sh.cid = c; sh.val = v; }
   }
-  advance_layer<RT>(sh, t, t, p, p, stage, open, M, md, pub + (size_t)p * VF_PUB_WORDS, list + (size_t)p * Mpad, ctx, tid, w,
-                    lane);
+  advance_layer<RT, AHEAD>(sh, t, t, p, p, stage, open, md, pub, list + (size_t)p * Mpad, tid, w, lane);
   if (open) no_minima(pval, pidx, sh.os.ncand, nparts, tid);
 }
 
@@ -863,11 +864,12 @@ int vfk_layer_open(vf_ctx *c, int stage) {
   vf_fast_dev fd;
   vfk_fast_dev(c, true, &fd, nullptr, nullptr);
   int rc = grow_words(c, (void **)&c->d_wlist, c->wlist_elems, (size_t)c->B * c->Mpad);
-  if (rc == VF_OK) rc = grow_words(c, (void **)&c->d_pub, c->pub_elems, (size_t)c->B * VF_PUB_WORDS + 4);
+  if (rc == VF_OK) rc = grow_words(c, (void **)&c->d_pub, c->pub_elems, (size_t)2 * c->B * VF_PUB_WORDS + 4);
   const int nparts = layer_parts(c);
   if (rc == VF_OK) rc = vfk_ensure_parts(c, (size_t)nparts * c->B);
   if (rc == VF_OK) rc = vfk_prepare(c, stage);
   if (rc != VF_OK) return rc;
+  c->pub_set = 0;
   hipLaunchKernelGGL((c->pm.fast_rt == 4 ? k_open_layer<4> : k_open_layer<2>), dim3((unsigned)c->B), dim3(512), 0, c->stream,
                      fd, (const uint32_t *)c->d_decpack, c->d_pub, reinterpret_cast<uint32_t *>(c->d_wlist),
                      (int64_t)c->Mpad, c->d_pval, c->d_pidx, nparts);
@@ -888,11 +890,11 @@ int vfk_layer_score(vf_ctx *c, int noise_stage, float *scores, int *nparts_out) 
   WholeArgs wa = {};
   wa.t = tables_of(c);
   wa.list = reinterpret_cast<uint32_t *>(c->d_wlist); wa.Mpad = c->Mpad;
-  wa.pub = c->d_pub;
+  wa.pub = c->d_pub + (size_t)c->pub_set * c->B * VF_PUB_WORDS;
   wa.scores = scores;
   wa.pval = c->d_pval; wa.pidx = c->d_pidx;
   wa.nparts = layer_parts(c);
-  wa.n_minima = c->d_pub + (size_t)c->B * VF_PUB_WORDS;
+  wa.n_minima = c->d_pub + (size_t)2 * c->B * VF_PUB_WORDS;
   vf_prof_scope prof(c, VF_PROF_SCORE);
   VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
   hipLaunchKernelGGL(kern, dim3((unsigned)ncu), dim3(512), smem, c->stream, fd, ks, c->M, c->B,
@@ -904,17 +906,19 @@ int vfk_layer_score(vf_ctx *c, int noise_stage, float *scores, int *nparts_out) 
 
 // Algorithm 1 over stages first..last on lists of valid candidates, two launches per layer.
 int vfk_greedy_layers(vf_ctx *c, int first, int last) {
-  int rc = vfk_layer_open(c, first);
+  int rc = vfk_layer_open(c, first), ncu = 256;
+  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
   vf_fast_dev fd;
   vfk_fast_dev(c, true, &fd, nullptr, nullptr);
+  const bool ahead = c->B <= ncu;  // (a workgroup has its compute unit to itself)
   for (int i = first; i <= last && rc == VF_OK; ++i) {
     int nparts = 0;
     rc = vfk_layer_score(c, i, nullptr, &nparts);
     if (rc != VF_OK) return rc;
     vf_prof_scope prof(c, VF_PROF_COMMIT);
     c->dec_stage = -1;
-    hipLaunchKernelGGL((c->pm.fast_rt == 4 ? k_greedy_advance<4> : k_greedy_advance<2>), dim3((unsigned)c->B), dim3(512), 0,
-                       c->stream, tables_of(c), i, (int)(i < last), (uint32_t)c->M, (int64_t)c->Mpad, fd, c->d_decpack,
+    hipLaunchKernelGGL((c->pm.fast_rt == 4 ? ahead ? k_greedy_advance<4, 4> : k_greedy_advance<4, 0> : ahead ? k_greedy_advance<2, 14> : k_greedy_advance<2, 0>),
+                       dim3((unsigned)c->B), dim3(512), 0, c->stream, tables_of(c), i, (int)(i < last), (int64_t)c->Mpad, fd,
                        c->d_pub, reinterpret_cast<uint32_t *>(c->d_wlist), c->d_pval, c->d_pidx, nparts);
     VF_HIP(c, hipGetLastError());
     c->n_sched = i + 1;
