@@ -117,6 +117,30 @@ def test_beam_fused_bf16(vf, ovf, K, dims):
     vf.vf_destroy(ctx)
 
 
+# the choice on lists: survivors ranked (up to 256 scores below the cut), sorted (more), bisected (more than 1024 parts
+# or 2048 scores below it)
+@pytest.mark.parametrize("K", [20, 250, 300, 700])
+@pytest.mark.parametrize("same", [False, True])
+def test_beam_choice_on_lists(vf, ovf, K, same):
+    """Many slots; equal scores for all (zero weights), which the order of slots and ids decides."""
+    sp = I.make_space([1, 2, 3, 8], [1, 2, 5], [1, 4, 16], [(0, 1, 2), (2, 1, 0)], 2, 1, [I.ROOT, I.L1, I.L2, I.INLINE], 2, 64)
+    pipe = I.random_pipeline(3, 41)
+    dims = [64, 512, 1]
+    w = I.mlp_weights(dims, 3, bias_std=0.1)
+    if same:
+        w[:] = 0.0
+        w[-1] = 0.75   # the output's bias
+    model = I.model_record(I.MLP, dims, I.BF16)
+    ctx, run = make_ctx(vf, pipe, sp, model, w, K)
+    if same:
+        cids, vals, st, nb = run(len(pipe) - 1)
+        ref = ovf.beam(pipe, sp, K, model, w)
+        assert np.array_equal(ref["cids"], cids) and np.array_equal(ref["values"], vals) and ref["n_beams"] == nb
+    else:
+        check_beam(ovf, pipe, sp, model, w, run, K, TOL[1])
+    vf.vf_destroy(ctx)
+
+
 @pytest.mark.parametrize("K", [6, 24])
 def test_beam_fp32_tiny_config_with_ties(vf, ovf, K):
     """The tiny conv+ReLU config has candidates with identical features, hence exactly
