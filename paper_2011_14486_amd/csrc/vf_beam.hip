@@ -531,11 +531,11 @@ int vfk_beam_select(vf_ctx *c) {
   return VF_OK;
 }
 
-// With more than 64 tiles of 128 ids in a layer.  Below that the launches on id ranges are as fast
-// (256-512-512-1, whole search: 20 layers of 4096 ids, 2 slots 0.79 against 0.82 ms here, 4 slots 0.93
-// against 0.87, 64 slots 4.2 against 1.57; 100 layers of 16384 ids, 1 slot 4.2 either way, 8 slots 11.2
-// against 5.3, 64 slots 48.6 against 11.0).
-bool vfk_beam_lists(const vf_ctx *c) { return (c->M + 127) / 128 * c->B > 64 && vfk_layer_fits(c); }
+// All but single slots with short decisions, whose selection on id ranges is one pass of block minima
+// (256-512-512-1, whole search, on id ranges / lists: 20 layers, one slot, 63 ids 559 / 603 us, 405: 588 / 603, 768:
+// 552 / 530, 4096: 688 / 617; two slots, 63 ids 619 / 619, 405: 640 / 620, 768: 618 / 540, 4096: 779 / 637; four slots,
+// 63 ids 692 / 625; 256-1024-1024-1, one slot, 4096 ids 1017 / 911; 100 layers of 16384 ids, one slot 3203 / 3196).
+bool vfk_beam_lists(const vf_ctx *c) { return (c->B > 1 || c->M > 512) && vfk_layer_fits(c); }
 
 int vfk_beam_layers(vf_ctx *c, int first, int last) {
   int rc = vfk_scores_buffer(c);

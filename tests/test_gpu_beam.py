@@ -141,6 +141,21 @@ def test_beam_choice_on_lists(vf, ovf, K, same):
     vf.vf_destroy(ctx)
 
 
+# decisions of 8 and 96 ids; one slot with more than 512 of them
+@pytest.mark.parametrize("K,factors", [(2, [1, 2]), (5, [1, 2, 4]), (1, [1, 2, 3, 8])])
+def test_beam_lists_of_short_decisions(vf, ovf, K, factors):
+    sp = I.make_space(factors, factors[:2], factors[-2:], [(0, 1, 2), (2, 1, 0)][:len(factors) - 1], 1 if K == 2 else 2, 1,
+                      [I.ROOT] if K == 2 else [I.ROOT, I.L1] if K == 5 else [I.ROOT, I.L1, I.L2, I.INLINE], 1 if K > 1 else 3, 64)
+    assert ovf.dense_count(sp) == {2: 8, 5: 96, 1: 768}[K]
+    pipe = I.random_pipeline(4, 43)
+    dims = [64, 512, 512, 1]
+    w = I.mlp_weights(dims, 5, bias_std=0.1)
+    model = I.model_record(I.MLP, dims, I.BF16)
+    ctx, run = make_ctx(vf, pipe, sp, model, w, K)
+    check_beam(ovf, pipe, sp, model, w, run, K, TOL[1])
+    vf.vf_destroy(ctx)
+
+
 @pytest.mark.parametrize("K", [6, 24])
 def test_beam_fp32_tiny_config_with_ties(vf, ovf, K):
     """The tiny conv+ReLU config has candidates with identical features, hence exactly
