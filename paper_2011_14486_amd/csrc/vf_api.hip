@@ -438,7 +438,12 @@ static int score_call(vf_ctx *c, const void *x, int32_t x_kind, int64_t M, int64
   int nparts = 0, part = 0, rc;
   if (x_kind == VF_X_RAW_I32) {
     if (c->model.kind != VF_MLP || ld < M) return VF_EINVAL;
+    c->one_wanted = want_min && !parts && (group == 0 || group >= M);
+    c->one_done = false;
+    c->one_idx = best_idx; c->one_val = best_val;
     rc = vfk_score_mlp(c, (const int32_t *)x, 0, 1, M, ld, 0, scores, ld, &nparts, -1, parts, &part);
+    c->one_wanted = false;
+    if (c->one_done) return rc;
   } else if (x_kind == VF_X_SEQ_BF16) {
     if (c->model.kind != VF_LSTM || ld < 0 || ld > (1 << 20)) return VF_EINVAL;
     rc = vfk_score_lstm(c, (const uint16_t *)x, M, (int)ld, scores, &nparts, parts, &part);

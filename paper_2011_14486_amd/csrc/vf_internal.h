@@ -97,7 +97,11 @@ struct vf_ctx {
   int32_t *d_forced = nullptr;  // [B][S] staging for vf_set_state
   uint32_t *d_decpack = nullptr; // [B][VF_DECPACK_DWORDS] decision context of stage dec_stage
   int dec_stage = -1;            // stage d_decpack was built for, -1: none
-  unsigned long long *d_chain = nullptr; size_t chain_units = 0;  // words of vfk_greedy_chain (zero between launches), in 16 bytes
+  // one minimum over all vectors of a vf_score call, wanted from the scorer itself (small networks); whether it took it
+  bool one_wanted = false, one_done = false;
+  int32_t *one_idx = nullptr;
+  float *one_val = nullptr;
+  unsigned long long *d_chain = nullptr; size_t chain_units = 0;  // words that workgroups exchange (vfk_chain_words; zero between launches), in 16 bytes
 
   // beam search: a second set of state tables (the survivors of a layer are written
   // there, then the two sets swap), masked scores, selection scratch

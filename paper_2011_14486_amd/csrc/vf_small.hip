@@ -72,6 +72,10 @@ struct SmallArgs {
   int32_t *pidx;
   int nparts, units, spp;
   int xcd_bits, run;  // see first_unit
+  // GIVEN_ONE: the words of one_minimum; the results, nullable
+  unsigned long long *words;
+  int32_t *one_idx;
+  float *one_val;
   NoiseArgs na;
   // GEN: the decisions' contexts; the ids of a decision in blocks of `block`, dealt out to `nparts` shares
   // (share c has the blocks c, c + nparts, ...: valid ids come in runs), one share at a time per wave
@@ -83,8 +87,8 @@ struct SmallArgs {
 };
 
 // What a kernel scores: given features, the valid ids that its waves collect, ids as they come, or ids as they
-// come through a whole schedule (vf_chain_dev.h).
-enum { GIVEN = 0, COLLECTED = 1, IDS = 2, CHAINED = 3 };
+// come through a whole schedule (vf_chain_dev.h).  GIVEN_ONE: given features and one minimum over all of them.
+enum { GIVEN = 0, COLLECTED = 1, IDS = 2, CHAINED = 3, GIVEN_ONE = 4 };
 
 // GEN: the candidates are enumerated and featurized where they are scored (x is not used); scores of
 // ids that are not valid candidates read +inf.  Every wave keeps the context of its problem, looks its ids
@@ -168,6 +172,57 @@ __device__ __forceinline__ int post_tile(ChainShared &sh, const ChainArgs &ca, u
   return t;
 }
 
+// The first minimum over all candidates from the waves' (v, c), in the launch that scores them: every workgroup
+// leaves its own in a word past the caches (value and id; a word that is not zero is complete), and the last
+// workgroup waits for all of them, reduces them and leaves zeros for the next launch.  (The others wait for
+// nothing, so every word comes.  Counting the arrivals, so that nobody waits, costs 4 us with 256 workgroups: atomics on
+// one word.)  A launch of its own for it / this: 64-128-128-1 bf16, 200,003 vectors 29.5 / 26.1 us, 20,000: 14.5 / 11.7,
+// fp32, 192,000: 91.7 / 88.5; 64-32-1 bf16, 1,000,001: 49.3 / 45.4.
+__device__ __forceinline__ void one_minimum(unsigned long long *words, int32_t *one_idx, float *one_val, float v, int32_t c) {
+  __shared__ float wave_v[8];
+  __shared__ int32_t wave_c[8];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, last = (int)gridDim.x - 1;
+  wave_min(v, c);
+  if (lane == 0) { wave_v[w] = v; wave_c[w] = c; }
+  __syncthreads();
+  if (w != 0) return;
+  v = wave_v[lane & 7];
+  c = wave_c[lane & 7];
+  wave_min(v, c);
+  if ((int)blockIdx.x != last) {
+    if (lane == 0)
+      __hip_atomic_store(&words[blockIdx.x], (unsigned long long)__float_as_uint(v) << 32 | (c >= 0 ? (uint32_t)c + 1u : 0xffffffffu),
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  for (int q0 = 0; q0 < last; q0 += 256) {
+    unsigned long long word[4] = {0ull, 0ull, 0ull, 0ull};
+    for (;;) {
+      bool lack = false;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int q = q0 + 64 * k + lane;
+        if (q < last && word[k] == 0ull) word[k] = __hip_atomic_load(&words[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) lack = lack || (q0 + 64 * k + lane < last && word[k] == 0ull);
+      if (__ballot(lack) == 0ull) break;
+      __builtin_amdgcn_s_sleep(1);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t id = (uint32_t)word[k];
+      if (id != 0u) words[q0 + 64 * k + lane] = 0ull;
+      take_min(v, c, __uint_as_float((uint32_t)(word[k] >> 32)), id == 0u || id == 0xffffffffu ? -1 : (int32_t)id - 1);
+    }
+  }
+  wave_min(v, c);
+  if (lane == 0) {
+    if (one_idx) one_idx[0] = c;
+    if (one_val) one_val[0] = v;
+  }
+}
+
 __device__ __forceinline__ void stage_small(const SmallArgs &a, uint4 *wl, float *bl) {
 #pragma unroll 4
   for (int i = threadIdx.x; i < a.md.nw; i += 512) wl[i] = a.md.w[i];
@@ -225,7 +280,7 @@ __device__ __forceinline__ void load_raw(int32_t (&r)[ROWS][N], const int32_t *p
 // always under way.
 template <int CT, int NT, int MODE>
 __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
-  constexpr bool GEN = MODE != GIVEN, DIRECT = MODE == IDS, CHAIN = MODE == CHAINED;
+  constexpr bool ONE = MODE == GIVEN_ONE, GEN = MODE != GIVEN && !ONE, DIRECT = MODE == IDS, CHAIN = MODE == CHAINED;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint4 *const wl = reinterpret_cast<uint4 *>(smem);
   float *const bl = reinterpret_cast<float *>(wl + a.md.nw);
@@ -264,7 +319,8 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
   // (GEN: a unit is a share of a problem's ids)
   const int stride = ((int)gridDim.x >> a.xcd_bits) * 8;
   int u_end = 0, u = CHAIN ? 0 : first_unit(a, w, u_end), sub = 0;
-  if (!CHAIN && u >= u_end) return;
+  const bool idle = ONE && u >= u_end;
+  if (!CHAIN && !ONE && u >= u_end) return;
   int p = CHAIN ? (int)blockIdx.x % a.ca.nprob : u / a.nparts, part = CHAIN ? 0 : u - p * a.nparts;
   int64_t n0 = GEN ? 0 : (int64_t)part * a.spp * 32 * CT;
   int blk = part, queued = 0;  // (GEN)
@@ -281,10 +337,10 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
   int32_t pre = 0;
   if constexpr (CHAIN) chain_begin(sh, a.ca, row, member, threadIdx.x);
   else if constexpr (GEN) load_wave_dec(wd, a.decpack, p, lane);
-  else fetch(p, n0, 0);
+  else if (!idle) fetch(p, n0, 0);
   float v = __builtin_inff();
   int32_t vc = -1;
-  for (;;) {
+  for (; !idle;) {
     // the sub-tile after this one
     int nu = u, nsub = sub + 1, np = p, npart = part;
     int64_t nn0 = n0 + 32 * CT;
@@ -528,7 +584,7 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
         vc = -1;
         continue;
       }
-      if (ends) {
+      if (!ONE && ends) {
         wave_min(v, vc);
         if (lane == 0) {
           a.pval[u] = v;
@@ -551,6 +607,7 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
     }
     u = nu; sub = nsub; p = np; part = npart; n0 = nn0;
   }
+  if constexpr (ONE) one_minimum(a.words, a.one_idx, a.one_val, v, vc);
 }
 
 // 16 * CT candidates per sub-tile, lane l has columns CT (l % 16) + 0 .. CT - 1 and rows 4 (l / 16) + 0..3
@@ -562,7 +619,7 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
 // candidate's score does not depend on how many candidates the call has.
 template <int CT, int NT, int MODE>
 __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
-  constexpr bool GEN = MODE != GIVEN, DIRECT = MODE == IDS, CHAIN = MODE == CHAINED;
+  constexpr bool ONE = MODE == GIVEN_ONE, GEN = MODE != GIVEN && !ONE, DIRECT = MODE == IDS, CHAIN = MODE == CHAINED;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint4 *const wl = reinterpret_cast<uint4 *>(smem);
   const floatx4 *const wf = reinterpret_cast<const floatx4 *>(smem);
@@ -592,7 +649,8 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
   // (GEN: a unit is a share of a problem's ids)
   const int stride = ((int)gridDim.x >> a.xcd_bits) * 8;
   int u_end = 0, u = CHAIN ? 0 : first_unit(a, w, u_end), sub = 0;
-  if (!CHAIN && u >= u_end) return;
+  const bool idle = ONE && u >= u_end;
+  if (!CHAIN && !ONE && u >= u_end) return;
   int p = CHAIN ? (int)blockIdx.x % a.ca.nprob : u / a.nparts, part = CHAIN ? 0 : u - p * a.nparts;
   int64_t n0 = GEN ? 0 : (int64_t)part * a.spp * 16 * CT;
   int blk = part, queued = 0;  // (GEN)
@@ -609,10 +667,10 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
   int32_t pre = 0;
   if constexpr (CHAIN) chain_begin(sh, a.ca, row, member, threadIdx.x);
   else if constexpr (GEN) load_wave_dec(wd, a.decpack, p, lane);
-  else fetch(p, n0, 0);
+  else if (!idle) fetch(p, n0, 0);
   float v = __builtin_inff();
   int32_t vc = -1;
-  for (;;) {
+  for (; !idle;) {
     int nu = u, nsub = sub + 1, np = p, npart = part;
     int64_t nn0 = n0 + 16 * CT;
     bool ends = nsub >= a.spp || nn0 >= a.M;
@@ -869,7 +927,7 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
       vc = -1;
       continue;
     }
-    if (ends) {
+    if (!ONE && ends) {
       wave_min(v, vc);
       if (lane == 0) {
         a.pval[u] = v;
@@ -891,6 +949,7 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
     }
     u = nu; sub = nsub; p = np; part = npart; n0 = nn0;
   }
+  if constexpr (ONE) one_minimum(a.words, a.one_idx, a.one_val, v, vc);
 }
 
 }  // namespace
@@ -1019,6 +1078,13 @@ int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob,
     a.pval = c->d_pval; a.pidx = c->d_pidx;
   }
   if (units == 0) return VF_OK;
+  const int grid = units < ncu ? (int)units : ncu;
+  a.words = nullptr;
+  a.one_idx = nullptr; a.one_val = nullptr;
+  if (c->one_wanted && vfk_chain_words(c, ((size_t)grid * 8 + 15) / 16) == VF_OK) {
+    a.words = c->d_chain;
+    a.one_idx = c->one_idx; a.one_val = c->one_val;
+  }
   a.md = c->pm.small;
   a.x = x; a.prob_stride = prob_stride; a.M = M; a.ld = ld; a.use_valid_row = use_valid_row;
   a.scores = scores; a.ld_scores = ld_scores;
@@ -1034,17 +1100,17 @@ int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob,
 #define VF_SMALL_ALL(mode)                                                                                  \
   {{VF_SMALL(k_small_bf16, 1, mode, 1, 2, 3, 4), VF_SMALL(k_small_bf16, 2, mode, 1, 2, 3, 4)},              \
    {VF_SMALL(k_small_f32, 1, mode, 2, 4, 6, 8), VF_SMALL(k_small_f32, 2, mode, 2, 4, 6, 8)}}
-  static constexpr small_kernel kerns[3][2][2][4] = {VF_SMALL_ALL(GIVEN), VF_SMALL_ALL(COLLECTED), VF_SMALL_ALL(IDS)};
+  static constexpr small_kernel kerns[4][2][2][4] = {VF_SMALL_ALL(GIVEN), VF_SMALL_ALL(COLLECTED), VF_SMALL_ALL(IDS), VF_SMALL_ALL(GIVEN_ONE)};
 #undef VF_SMALL_ALL
 #undef VF_SMALL
-  const small_kernel kern = kerns[x ? GIVEN : ids ? IDS : COLLECTED][bf16 ? 0 : 1][ct - 1][a.md.NT * base / 32 - 1];
+  const small_kernel kern = kerns[a.words ? 3 : x ? GIVEN : ids ? IDS : COLLECTED][bf16 ? 0 : 1][ct - 1][a.md.NT * base / 32 - 1];
   vf_prof_scope prof(c, VF_PROF_SCORE);
   VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-  const int grid = units < ncu ? (int)units : ncu;
   a.xcd_bits = x && grid % 8 == 0 ? 3 : 0;
   a.run = (int)((units + (1 << a.xcd_bits) - 1) >> a.xcd_bits);
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), smem, c->stream, a);
   VF_HIP(c, hipGetLastError());
+  c->one_done = a.words != nullptr;
   return VF_OK;
 }
 

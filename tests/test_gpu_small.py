@@ -53,6 +53,35 @@ def test_scores_and_minima(vf, ovf, dims, dtype):
     vf.vf_destroy(ctx)
 
 
+# one minimum over all: one workgroup (with idle waves), a few, one per compute unit, several units per wave
+@pytest.mark.parametrize("dims,dtype", [([64, 128, 128, 1], I.FP32), ([64, 32, 1], I.BF16)])
+@pytest.mark.parametrize("M", [1, 40, 500, 8192, 70001])
+def test_one_minimum(vf, dims, dtype, M):
+    """The launch's own minimum is the first one of its scores, call after call, with equal scores, between
+    schedules that use the same words, and with only one of the two results wanted."""
+    import torch
+    ctx = vf.vf_create(0)
+    vf.vf_set_space(ctx, I.tiny_space())
+    vf.vf_set_pipeline(ctx, I.tiny_conv_relu()[None])
+    vf.vf_set_model(ctx, I.model_record(I.MLP, dims, dtype), I.mlp_weights(dims, 3, bias_std=0.1))
+    rng = np.random.default_rng(M)
+    first = None
+    for rep in range(3):
+        x = torch.from_numpy(rng.integers(0, 1 << 20, (64, M)).astype(np.int32)).cuda()
+        x[:, M // 2:] = x[:, :1] if rep == 1 else x[:, M // 2:]      # (half of the scores the same)
+        s, bi, bv = vf.vf_score(ctx, x)
+        s = s.cpu().numpy()
+        assert bi.tolist() == [int(np.argmin(s))] and bv.tolist() == [s.min()], rep
+        vf.vf_reset_state(ctx)
+        got = [t.cpu().numpy() for t in vf.vf_greedy_schedule(ctx)]
+        first = first or got
+        assert all(np.array_equal(a, b) for a, b in zip(first, got))
+    x[:] = 3
+    s, bi, bv = vf.vf_score(ctx, x)
+    assert bi.tolist() == [0] and bv[0] == s[0]
+    vf.vf_destroy(ctx)
+
+
 @pytest.mark.parametrize("dtype", [I.FP32, I.BF16])
 def test_extreme_weights(vf, dtype):
     """Infinite and NaN scores never win; a group without a finite score has no winner."""
