@@ -109,16 +109,16 @@ struct ListPlace {
                                                                 float rcp_perm, float rcp_vec) {
   return list_digits(os, list_place(pk, os, pos_r, k, rcp_perm, rcp_vec));
 }
-// The list, by a workgroup of 512: a thread takes four entries in a row and goes on from the first to the
+// The list, by `threads` threads (of them tid): a thread takes four entries in a row and goes on from the first to the
 // others by carrying (the divisions of an entry are most of its work).  The list
 // is 16-byte aligned and a multiple of four long; what lies behind the last entry is 0.
-__device__ __forceinline__ void write_list(const DecPack &pk, const OpenScratch &os, uint32_t *idlist, int tid) {
+__device__ __forceinline__ void write_list(const DecPack &pk, const OpenScratch &os, uint32_t *idlist, int tid, int threads = 512) {
   const float rcp_perm = 1.0f / (float)pk.sp.nperm, rcp_vec = 1.0f / (float)pk.sp.nvec;
   const int n = os.ncand, last = os.npairs - 1;
   int pos_r[12];
 #pragma unroll
   for (int j = 0; j < 12; ++j) pos_r[j] = j <= last ? os.pos[j] : 0x7fffffff;
-  for (int k = 4 * tid; k < n; k += 4 * 512) {
+  for (int k = 4 * tid; k < n; k += 4 * threads) {
     ListPlace at = list_place(pk, os, pos_r, k, rcp_perm, rcp_vec);
     int next = os.pos[at.q + 1];  // (behind the last pair: n)
     uint32_t e[4];
