@@ -40,35 +40,6 @@ __device__ __forceinline__ void swap_halves(uint32_t &a, uint32_t &b) {
   b = r[1];
 }
 
-// (value, id) ordering of the scan: smaller value first, then smaller id; id < 0 = none
-__device__ __forceinline__ void take_min(float &v, int32_t &c, float ov, int32_t oc) {
-  if (oc >= 0 && (ov < v || (ov == v && (c < 0 || oc < c)))) { v = ov; c = oc; }
-}
-// Minimum pair of a full wave, left in every lane.  Rows of 16 lanes reduce by data-parallel
-// lane shifts (lane i takes lane i - n; a lane without a source keeps its own pair), the four
-// row results are then read from lanes 15, 31, 47 and 63.  All 64 lanes must be active.
-__device__ __forceinline__ void wave_min(float &v, int32_t &c) {
-#define VF_ROW_SHR_MIN(ctrl)                                                                              \
-  {                                                                                                       \
-    const float ov = __int_as_float(                                                                      \
-        __builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), ctrl, 0xf, 0xf, false));        \
-    const int32_t oc = __builtin_amdgcn_update_dpp(c, c, ctrl, 0xf, 0xf, false);                          \
-    take_min(v, c, ov, oc);                                                                               \
-  }
-  VF_ROW_SHR_MIN(0x111)
-  VF_ROW_SHR_MIN(0x112)
-  VF_ROW_SHR_MIN(0x114)
-  VF_ROW_SHR_MIN(0x118)
-#undef VF_ROW_SHR_MIN
-  float rv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 15));
-  int32_t rc = __builtin_amdgcn_readlane(c, 15);
-  take_min(rv, rc, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 31)), __builtin_amdgcn_readlane(c, 31));
-  take_min(rv, rc, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 47)), __builtin_amdgcn_readlane(c, 47));
-  take_min(rv, rc, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63)), __builtin_amdgcn_readlane(c, 63));
-  v = rv;
-  c = rc;
-}
-
 // One cell of the recurrent network in fp32: gate pre-activations ai, af, ag, ao and the old cell
 // state give the new cell state (returned through c) and the new hidden value (returned).
 //   c' = sigma(af) c + sigma(ai) tanh(ag),   h' = sigma(ao) tanh(c')
