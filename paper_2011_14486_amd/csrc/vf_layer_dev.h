@@ -209,6 +209,8 @@ struct __attribute__((aligned(16))) AdvanceShared {
   int32_t cid;       // the decision: a candidate id, -1 = none
   float val;
 };
+static_assert(offsetof(AdvanceShared, next) % 16 == 0 && sizeof(DecPack) + sizeof(EvalTabs) + sizeof(AdvanceShared::pad) == VF_PUB_BIAS * 4,
+              "a decision in LDS lies as it is published");
 // The published decision (one 16-byte piece by each of the threads from 256 on).
 __device__ __forceinline__ void fetch_opened(AdvanceShared &s, const uint32_t *pub, int tid) {
   if (tid >= 256 && tid < 256 + VF_PUB_BIAS / 4) reinterpret_cast<uint4 *>(&s.pk)[tid - 256] = reinterpret_cast<const uint4 *>(pub)[tid - 256];

@@ -1014,6 +1014,11 @@ int vfk_pack_small(vf_ctx *c, const float *wdev) {
     VF_HIP(c, hipGetLastError());
     off += (size_t)K * N + N;
   }
+  // (one_minimum's words with the model, so that no vf_score call allocates them; it does without if they are refused)
+  int ncu = 256;
+  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
+  const int rc = vfk_chain_words(c, ((size_t)ncu * 8 + 15) / 16);
+  if (rc != VF_OK && rc != VF_ENOMEM) return rc;
   d.w = reinterpret_cast<const uint4 *>(buf);
   d.bias = bias;
   return VF_OK;
