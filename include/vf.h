@@ -284,12 +284,12 @@ int vf_profile_counts(vf_ctx *ctx, int64_t *scored_host, int64_t *valid_host);
  * state, the affected layers have been run again with the launches per layer before this
  * call returns, and the tables are complete (see vf_greedy_schedule). */
 int vf_sync_status(vf_ctx *ctx);
-/* Bound of the waits between the workgroups that share a problem inside a whole-schedule
- * launch of vf_greedy_schedule, in polling rounds (default 2^22, seconds); a helper's wait
+/* Bound of the waits between workgroups: those that share a problem inside a whole-schedule
+ * launch of vf_greedy_schedule, and those of a vf_score launch with one minimum, in polling rounds (default 2^22, seconds); a helper's wait
  * for work starts over whenever a problem finishes anywhere, so a launch that is merely long
  * does not run it out.  A wait that reaches the bound gives up: the launch still ends, see
- * vf_greedy_schedule for what follows (with a few problems nothing does: the launch goes on and
- * decides the same).  A bound of 0 makes every wait that cannot be
+ * vf_greedy_schedule for what follows (with a few problems, and in vf_score, nothing does: the launch goes on
+ * and decides the same).  A bound of 0 makes every wait that cannot be
  * satisfied at once give up; meant for tests of that path. */
 int vf_set_wait_limit(vf_ctx *ctx, unsigned int rounds);
 

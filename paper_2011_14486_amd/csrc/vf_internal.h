@@ -34,6 +34,8 @@ struct vf_small_dev {
   int nw = 0, nbias = 0, L = 0, NT = 0;  // NT: row tiles of every hidden layer
   int dims[8] = {0}, nt[8] = {0}, kst[8] = {0}, woff[8] = {0}, boff[8] = {0};
   int wl_off = 0;  // fp32: the output vector behind the biases
+  unsigned long long *words = nullptr;  // one minimum over all vectors: a counter and a word per workgroup, zero between launches
+  int nwords = 0;
 };
 
 struct vf_packed_model {

@@ -72,8 +72,9 @@ struct SmallArgs {
   int32_t *pidx;
   int nparts, units, spp;
   int xcd_bits, run;  // see first_unit
-  // GIVEN_ONE: the words of one_minimum; the results, nullable
+  // GIVEN_ONE: the words of one_minimum, the bound of its wait; the results, nullable
   unsigned long long *words;
+  unsigned int wait_rounds;
   int32_t *one_idx;
   float *one_val;
   NoiseArgs na;
@@ -176,9 +177,23 @@ __device__ __forceinline__ int post_tile(ChainShared &sh, const ChainArgs &ca, u
 // leaves its own in a word past the caches (value and id; a word that is not zero is complete), and the last
 // workgroup waits for all of them, reduces them and leaves zeros for the next launch.  (The others wait for
 // nothing, so every word comes.  Counting the arrivals, so that nobody waits, costs 4 us with 256 workgroups: atomics on
-// one word.)  A launch of its own for it / this: 64-128-128-1 bf16, 200,003 vectors 29.5 / 26.1 us, 20,000: 14.5 / 11.7,
-// fp32, 192,000: 91.7 / 88.5; 64-32-1 bf16, 1,000,001: 49.3 / 45.4.
-__device__ __forceinline__ void one_minimum(unsigned long long *words, int32_t *one_idx, float *one_val, float v, int32_t c) {
+// one word.)  A launch of its own for it / this: 64-128-128-1 bf16, 200,003 vectors 27.0 / 24.0 us, 20,000: 13.4 / 10.4,
+// fp32, 192,000: 91.0 / 88.6; 64-32-1 bf16, 1,000,000: 48.1 / 44.0.
+// The wait is bounded all the same: behind `wait_rounds` the last workgroup marks the words that are missing as
+// taken, leaves what it has in a word of its own and goes; those that find their word taken put theirs there all the
+// same, and the last of them (words[0] counts) does the reduction.  Words of workgroup b: words[1 + b].
+constexpr unsigned long long WORD_TAKEN = 0xfffffffeull;  // (ids are below 2^30)
+__device__ __forceinline__ unsigned long long word_of(float v, int32_t c) {
+  return (unsigned long long)__float_as_uint(v) << 32 | (c >= 0 ? (uint32_t)c + 1u : 0xffffffffu);
+}
+__device__ __forceinline__ void take_word(unsigned long long *words, int q, unsigned long long word, float &v, int32_t &c) {
+  const uint32_t id = (uint32_t)word;
+  if (id == 0u) return;
+  __hip_atomic_store(&words[1 + q], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  take_min(v, c, __uint_as_float((uint32_t)(word >> 32)), id == 0xffffffffu ? -1 : (int32_t)id - 1);
+}
+__device__ __forceinline__ void one_minimum(unsigned long long *words, unsigned int wait_rounds, int32_t *one_idx, float *one_val, float v,
+                                            int32_t c) {
   __shared__ float wave_v[8];
   __shared__ int32_t wave_c[8];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, last = (int)gridDim.x - 1;
@@ -189,32 +204,65 @@ __device__ __forceinline__ void one_minimum(unsigned long long *words, int32_t *
   v = wave_v[lane & 7];
   c = wave_c[lane & 7];
   wave_min(v, c);
+  int late = -1;       // lane 0: words still to come behind this workgroup's own; 0: the reduction is its
+  bool handed = true;  // and all that there is to reduce is in the words
   if ((int)blockIdx.x != last) {
-    if (lane == 0)
-      __hip_atomic_store(&words[blockIdx.x], (unsigned long long)__float_as_uint(v) << 32 | (c >= 0 ? (uint32_t)c + 1u : 0xffffffffu),
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return;
-  }
-  for (int q0 = 0; q0 < last; q0 += 256) {
-    unsigned long long word[4] = {0ull, 0ull, 0ull, 0ull};
-    for (;;) {
-      bool lack = false;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int q = q0 + 64 * k + lane;
-        if (q < last && word[k] == 0ull) word[k] = __hip_atomic_load(&words[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0) {
+      unsigned long long was = 0ull;
+      const unsigned long long mine = word_of(v, c);
+      if (!__hip_atomic_compare_exchange_strong(&words[1 + blockIdx.x], &was, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT) &&
+          was == WORD_TAKEN) {
+        __hip_atomic_store(&words[1 + blockIdx.x], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        late = (int)__hip_atomic_fetch_add(&words[0], ~0ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) - 1;
       }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) lack = lack || (q0 + 64 * k + lane < last && word[k] == 0ull);
-      if (__ballot(lack) == 0ull) break;
-      __builtin_amdgcn_s_sleep(1);
     }
+  } else {
+    unsigned int rounds = 0;
+    int q0 = 0;
+    for (bool all = true; q0 < last; q0 += 256) {
+      unsigned long long word[4] = {0ull, 0ull, 0ull, 0ull};
+      for (;;) {
+        bool lack = false;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const uint32_t id = (uint32_t)word[k];
-      if (id != 0u) words[q0 + 64 * k + lane] = 0ull;
-      take_min(v, c, __uint_as_float((uint32_t)(word[k] >> 32)), id == 0u || id == 0xffffffffu ? -1 : (int32_t)id - 1);
+        for (int k = 0; k < 4; ++k) {
+          const int q = q0 + 64 * k + lane;
+          if (q < last && word[k] == 0ull) word[k] = __hip_atomic_load(&words[1 + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) lack = lack || (q0 + 64 * k + lane < last && word[k] == 0ull);
+        all = __ballot(lack) == 0ull;
+        if (all || rounds++ >= wait_rounds) break;
+        __builtin_amdgcn_s_sleep(1);
+      }
+      if (!all) break;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) take_word(words, q0 + 64 * k + lane, word[k], v, c);
     }
+    handed = q0 < last;
+    if (!handed) late = 0;
+    else {
+      // (what has been taken so far is in v and c, and those words are zero again)
+      wave_min(v, c);
+      int n = 0;
+      for (int q = q0 + lane; q < last; q += 64) {
+        unsigned long long was = 0ull;
+        n += __hip_atomic_compare_exchange_strong(&words[1 + q], &was, WORD_TAKEN, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT) ? 1 : 0;
+      }
+      for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off);
+      if (lane == 0) {
+        __hip_atomic_store(&words[1 + last], word_of(v, c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        late = (int)__hip_atomic_fetch_add(&words[0], (unsigned long long)n, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + n;
+      }
+    }
+  }
+  if (__builtin_amdgcn_readfirstlane(late) != 0) return;
+  if (handed) {
+    v = __builtin_inff();
+    c = -1;
+    for (int q = lane; q <= last; q += 64)
+      take_word(words, q, __hip_atomic_load(&words[1 + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), v, c);
   }
   wave_min(v, c);
   if (lane == 0) {
@@ -607,7 +655,7 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
     }
     u = nu; sub = nsub; p = np; part = npart; n0 = nn0;
   }
-  if constexpr (ONE) one_minimum(a.words, a.one_idx, a.one_val, v, vc);
+  if constexpr (ONE) one_minimum(a.words, a.wait_rounds, a.one_idx, a.one_val, v, vc);
 }
 
 // 16 * CT candidates per sub-tile, lane l has columns CT (l % 16) + 0 .. CT - 1 and rows 4 (l / 16) + 0..3
@@ -949,7 +997,7 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
     }
     u = nu; sub = nsub; p = np; part = npart; n0 = nn0;
   }
-  if constexpr (ONE) one_minimum(a.words, a.one_idx, a.one_val, v, vc);
+  if constexpr (ONE) one_minimum(a.words, a.wait_rounds, a.one_idx, a.one_val, v, vc);
 }
 
 }  // namespace
@@ -990,9 +1038,19 @@ int vfk_pack_small(vf_ctx *c, const float *wdev) {
   d.nw = (int)nw;
   d.nbias = (int)nbias;
   void *buf = nullptr;
-  VF_HIP(c, hipMalloc(&buf, nw * 16 + nbias * 4 + 16));
+  // (and one_minimum's words: with the model, so that they stay where they are until there is another)
+  int ncu = 256;
+  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
+  const size_t words_at = nw * 16 + (nbias * 4 + 15) / 16 * 16;
+  const int nwords = 1 + ncu;
+  VF_HIP(c, hipMalloc(&buf, words_at + (size_t)nwords * 8));
   c->pm.small_buf = buf;
   float *bias = reinterpret_cast<float *>(reinterpret_cast<uint4 *>(buf) + nw);
+  d.words = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(buf) + words_at);
+  d.nwords = nwords;
+  hipLaunchKernelGGL(k_pad_f32, dim3((2 * nwords + 255) / 256), dim3(256), 0, c->stream, wdev, 0, 2 * nwords,
+                     reinterpret_cast<float *>(d.words));
+  VF_HIP(c, hipGetLastError());
   size_t off = 0;
   for (int l = 0; l < L; ++l) {
     const int K = m.dims[l], N = m.dims[l + 1];
@@ -1014,11 +1072,6 @@ int vfk_pack_small(vf_ctx *c, const float *wdev) {
     VF_HIP(c, hipGetLastError());
     off += (size_t)K * N + N;
   }
-  // (one_minimum's words with the model, so that no vf_score call allocates them; it does without if they are refused)
-  int ncu = 256;
-  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
-  const int rc = vfk_chain_words(c, ((size_t)ncu * 8 + 15) / 16);
-  if (rc != VF_OK && rc != VF_ENOMEM) return rc;
   d.w = reinterpret_cast<const uint4 *>(buf);
   d.bias = bias;
   return VF_OK;
@@ -1086,8 +1139,9 @@ int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob,
   const int grid = units < ncu ? (int)units : ncu;
   a.words = nullptr;
   a.one_idx = nullptr; a.one_val = nullptr;
-  if (c->one_wanted && vfk_chain_words(c, ((size_t)grid * 8 + 15) / 16) == VF_OK) {
-    a.words = c->d_chain;
+  if (c->one_wanted && grid < c->pm.small.nwords) {
+    a.words = c->pm.small.words;
+    a.wait_rounds = c->wait_rounds;
     a.one_idx = c->one_idx; a.one_val = c->one_val;
   }
   a.md = c->pm.small;

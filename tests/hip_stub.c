@@ -54,7 +54,10 @@ hipError_t hipMalloc(void **p, size_t n) {
   *p = calloc(1, n);
   return *p ? hipSuccess : err(hipErrorOutOfMemory);
 }
-hipError_t hipFree(void *p) { free(p); return hipSuccess; }
+static int frees;
+/* how many allocations have been given back */
+int stub_frees(void) { return frees; }
+hipError_t hipFree(void *p) { frees += p != NULL; free(p); return hipSuccess; }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned int f) { (void)f; *p = calloc(1, n); return hipSuccess; }
 hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t st) {

@@ -82,6 +82,55 @@ def test_one_minimum(vf, dims, dtype, M):
     vf.vf_destroy(ctx)
 
 
+# a bound of 0: the workgroup that would wait hands the reduction over, unless every other one happens to be there
+@pytest.mark.parametrize("dims,dtype", [([64, 128, 128, 1], I.FP32), ([64, 32, 1], I.BF16)])
+@pytest.mark.parametrize("M", [40, 8192, 70001])
+def test_one_minimum_handed_over(vf, dims, dtype, M):
+    """The same minimum, call after call and in a graph's replays, whether the wait is given up or not."""
+    import ctypes as C
+    import torch
+    from paper_2011_14486_amd.binding import lib
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        ctx = vf.vf_create(0, s)
+        vf.vf_set_space(ctx, I.tiny_space())
+        vf.vf_set_pipeline(ctx, I.random_pipeline(20, 5)[None])
+        vf.vf_set_model(ctx, I.model_record(I.MLP, dims, dtype), I.mlp_weights(dims, 3, bias_std=0.1))
+        rng = np.random.default_rng(M)
+        x = torch.from_numpy(rng.integers(0, 1 << 20, (64, M)).astype(np.int32)).cuda()
+        out = (ctx.empty((M,), torch.float32), ctx.empty((1,), torch.int32), ctx.empty((1,), torch.float32))
+
+        def score():
+            p = [C.c_void_p(t.data_ptr()) for t in (x, *out)]
+            assert lib().vf_score(ctx.handle, p[0], vf.VF_X_RAW_I32, M, M, 0, *p[1:]) == vf.VF_OK
+
+        def check():
+            s.synchronize()
+            sc = out[0].cpu().numpy()
+            assert out[1].tolist() == [int(np.argmin(sc))] and out[2].tolist() == [sc.min()]
+
+        for rep in range(12):
+            vf.vf_set_wait_limit(ctx, 1 if rep % 4 == 3 else 0)
+            x.copy_(torch.from_numpy(rng.integers(0, 1 << 20, (64, M)).astype(np.int32)))
+            score()
+            check()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            score()
+        vf.vf_set_wait_limit(ctx, 1 << 22)
+        for rep in range(4):
+            # (a schedule in between takes words of its own, and the first one makes them)
+            vf.vf_reset_state(ctx)
+            vf.vf_greedy_schedule(ctx)
+            for call in (g.replay, score):
+                x.copy_(torch.from_numpy(rng.integers(0, 1 << 20, (64, M)).astype(np.int32)))
+                for t in out:
+                    t.zero_()
+                call()
+                check()
+        vf.vf_destroy(ctx)
+
+
 @pytest.mark.parametrize("dtype", [I.FP32, I.BF16])
 def test_extreme_weights(vf, dtype):
     """Infinite and NaN scores never win; a group without a finite score has no winner."""
