@@ -365,9 +365,13 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
 
 }  // namespace
 
-// The words of a launch with `units` 16-byte units, zero.
+// The words of a launch with `units` 16-byte units, zero; VF_ENOMEM without memory for them.
 int vfk_chain_words(vf_ctx *c, size_t units) {
   if (units <= c->chain_units) return VF_OK;
+  // (not while the stream is captured: they would be cleared when the graph runs, and a call may come before)
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) (void)hipGetLastError();
+  if (capture != hipStreamCaptureStatusNone) return VF_ENOMEM;
   if (c->d_chain) { VF_HIP(c, hipStreamSynchronize(c->stream)); (void)hipFree(c->d_chain); c->d_chain = nullptr; }
   c->chain_units = 0;
   if (hipMalloc((void **)&c->d_chain, units * 16) != hipSuccess) { (void)hipGetLastError(); c->d_chain = nullptr; return VF_ENOMEM; }

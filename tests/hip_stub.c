@@ -17,6 +17,7 @@ static dim3 cfg_grid, cfg_block;
 static size_t cfg_shared;
 static hipStream_t cfg_stream;
 static char static_array[1 << 20];
+static int capturing;
 static char refused[100];
 static int refused_skip;
 
@@ -27,6 +28,8 @@ void stub_fail_launch(const char *name, int skip) {
   snprintf(refused, sizeof refused, "%s", name ? name : "");
   refused_skip = skip;
 }
+/* every stream is being captured from now on (0: none is) */
+void stub_capture(int on) { capturing = on; }
 /* the launches so far, one "kernel grid weights" a line */
 const char *stub_log(void) { return log_text; }
 void stub_clear(void) { log_len = 0; log_text[0] = 0; }
@@ -67,6 +70,11 @@ hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hip
 }
 hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t st) { (void)st; memset(d, v, n); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t s) { (void)s; return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *st) {
+  (void)s;
+  *st = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
 hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)static_array; return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned f) { (void)f; *e = NULL; return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t e) { (void)e; return hipSuccess; }

@@ -109,6 +109,35 @@ def test_chain_in_a_graph(vf):
         vf.vf_destroy(ctx)
 
 
+@pytest.mark.parametrize("dims,dtype", [([256, 512, 512, 1], I.BF16), ([64, 128, 128, 1], I.FP32)])
+def test_first_schedule_of_a_context_in_a_graph(vf, dims, dtype):
+    """Captured before the context has made its words, and called before the graph has run."""
+    import torch
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        pipes = I.resnet18_batch(2, seed=5)[:, :6]
+        ref = context(vf, pipes, space("whole", dims[0]), dims, dtype)
+        want = [t.cpu().numpy() for t in vf.vf_greedy_schedule(ref)]
+        vf.vf_destroy(ref)
+        ctx = vf.vf_create(0, s)
+        vf.vf_set_space(ctx, space("whole", dims[0])); vf.vf_set_pipeline(ctx, pipes)
+        vf.vf_set_model(ctx, I.model_record(I.MLP, dims, dtype), I.mlp_weights(dims, 3, bias_std=0.1))
+        out = (ctx.empty((2, 6, 16), torch.int32), ctx.empty((2, 6), torch.int32), ctx.empty((2, 6), torch.float32))
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s, capture_error_mode="relaxed"):
+            vf.vf_reset_state(ctx)
+            vf.vf_greedy_schedule(ctx, out=out)
+        for k in range(3):
+            vf.vf_reset_state(ctx)
+            assert same([t.cpu().numpy() for t in vf.vf_greedy_schedule(ctx)], want)
+            for t in out:
+                t.zero_()
+            g.replay()
+            s.synchronize()
+            assert same([t.cpu().numpy() for t in out], want)
+        vf.vf_destroy(ctx)
+
+
 # small networks: one, four or eight waves of a workgroup have a sub-tile (32 ids in bf16, 16 in fp32), the last ones
 # none or part of one; 768 ids: 12 tiles of 64 in fp32 up to 21 problems, of 128 behind that
 @pytest.mark.parametrize("dims,dtype", [([64, 128, 128, 1], I.FP32), ([256, 40, 24, 1], I.FP32), ([64, 96, 32, 1], I.BF16),
