@@ -34,8 +34,6 @@ struct vf_small_dev {
   int nw = 0, nbias = 0, L = 0, NT = 0;  // NT: row tiles of every hidden layer
   int dims[8] = {0}, nt[8] = {0}, kst[8] = {0}, woff[8] = {0}, boff[8] = {0};
   int wl_off = 0;  // fp32: the output vector behind the biases
-  unsigned long long *words = nullptr;  // one minimum over all vectors: a counter and a word per workgroup, zero between launches
-  int nwords = 0;
 };
 
 struct vf_packed_model {
@@ -67,6 +65,8 @@ struct vf_packed_model {
   int pad_rt = 0;
   vf_small_dev small;              // small.w null: not small enough
   void *small_buf = nullptr;
+  unsigned long long *small_words = nullptr;  // one minimum over all vectors: a counter and a word per workgroup, zero between launches
+  int small_nwords = 0;
   // recurrent network wired to the search: [W_ih | W_hh] transposed, bf16 values as fp32, [64+H][4H]
   float *w_seqT = nullptr;
   uint16_t *w_seq_wide = nullptr;  // both in MFMA order by tiles of 16 units: see k_pack_seq_wide

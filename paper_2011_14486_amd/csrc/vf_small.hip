@@ -72,24 +72,34 @@ struct SmallArgs {
   int32_t *pidx;
   int nparts, units, spp;
   int xcd_bits, run;  // see first_unit
-  // GIVEN_ONE: the words of one_minimum, the bound of its wait; the results, nullable
-  unsigned long long *words;
-  unsigned int wait_rounds;
-  int32_t *one_idx;
-  float *one_val;
   NoiseArgs na;
   // GEN: the decisions' contexts; the ids of a decision in blocks of `block`, dealt out to `nparts` shares
   // (share c has the blocks c, c + nparts, ...: valid ids come in runs), one share at a time per wave
   const uint32_t *decpack;
   int block, nblocks;
-  // CHAINED: the schedule; a tile is `spw` sub-tiles in a row, one each for the first waves of a workgroup
-  ChainArgs ca;
-  int spw;
 };
 
 // What a kernel scores: given features, the valid ids that its waves collect, ids as they come, or ids as they
 // come through a whole schedule (vf_chain_dev.h).  GIVEN_ONE: given features and one minimum over all of them.
 enum { GIVEN = 0, COLLECTED = 1, IDS = 2, CHAINED = 3, GIVEN_ONE = 4 };
+
+// What two of them need besides.  (In arguments of their own: in those of every form, 816 bytes instead of 584,
+// they cost scoring with a minimum per group 0.7 %, 192,000 vectors 64-128-128-1 fp32 89.8 / 89.2 us.)
+struct SmallOneArgs : SmallArgs {
+  unsigned long long *words;  // of one_minimum, and the bound of its wait
+  unsigned int wait_rounds;
+  int32_t *one_idx;           // the results, nullable
+  float *one_val;
+};
+struct SmallChainArgs : SmallArgs {
+  ChainArgs ca;
+  int spw;                    // a tile is `spw` sub-tiles in a row, one each for the first waves of a workgroup
+};
+template <int MODE> struct small_args { typedef SmallArgs type; };
+template <> struct small_args<GIVEN_ONE> { typedef SmallOneArgs type; };
+template <> struct small_args<CHAINED> { typedef SmallChainArgs type; };
+__device__ __forceinline__ ChainArgs chain_of(const SmallArgs &) { return ChainArgs(); }
+__device__ __forceinline__ const ChainArgs &chain_of(const SmallChainArgs &a) { return a.ca; }
 
 // GEN: the candidates are enumerated and featurized where they are scored (x is not used); scores of
 // ids that are not valid candidates read +inf.  Every wave keeps the context of its problem, looks its ids
@@ -178,7 +188,7 @@ __device__ __forceinline__ int post_tile(ChainShared &sh, const ChainArgs &ca, u
 // workgroup waits for all of them, reduces them and leaves zeros for the next launch.  (The others wait for
 // nothing, so every word comes.  Counting the arrivals, so that nobody waits, costs 4 us with 256 workgroups: atomics on
 // one word.)  A launch of its own for it / this: 64-128-128-1 bf16, 200,003 vectors 27.0 / 24.0 us, 20,000: 13.4 / 10.4,
-// fp32, 192,000: 91.0 / 88.6; 64-32-1 bf16, 1,000,000: 48.1 / 44.0.
+// fp32, 192,000: 90.7 / 87.4; 64-32-1 bf16, 1,000,000: 48.1 / 44.0.
 // The wait is bounded all the same: behind `wait_rounds` the last workgroup marks the words that are missing as
 // taken, leaves what it has in a word of its own and goes; those that find their word taken put theirs there all the
 // same, and the last of them (words[0] counts) does the reduction.  Words of workgroup b: words[1 + b].
@@ -327,12 +337,13 @@ __device__ __forceinline__ void load_raw(int32_t (&r)[ROWS][N], const int32_t *p
 // about the same; two waves per SIMD overlap one's with the other's, and the next 32 input rows are
 // always under way.
 template <int CT, int NT, int MODE>
-__global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
+__global__ __launch_bounds__(512) void k_small_bf16(typename small_args<MODE>::type a) {
   constexpr bool ONE = MODE == GIVEN_ONE, GEN = MODE != GIVEN && !ONE, DIRECT = MODE == IDS, CHAIN = MODE == CHAINED;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint4 *const wl = reinterpret_cast<uint4 *>(smem);
   float *const bl = reinterpret_cast<float *>(wl + a.md.nw);
   WaveDec &wd = reinterpret_cast<WaveDec *>(bl + (a.md.nbias + 3) / 4 * 4)[threadIdx.x >> 6];  // (GEN only)
+  const ChainArgs &ca = chain_of(a);
   const int lane = threadIdx.x & 63, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   stage_small(a, wl, bl);
@@ -369,21 +380,21 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
   int u_end = 0, u = CHAIN ? 0 : first_unit(a, w, u_end), sub = 0;
   const bool idle = ONE && u >= u_end;
   if (!CHAIN && !ONE && u >= u_end) return;
-  int p = CHAIN ? (int)blockIdx.x % a.ca.nprob : u / a.nparts, part = CHAIN ? 0 : u - p * a.nparts;
+  int p = CHAIN ? (int)blockIdx.x % ca.nprob : u / a.nparts, part = CHAIN ? 0 : u - p * a.nparts;
   int64_t n0 = GEN ? 0 : (int64_t)part * a.spp * 32 * CT;
   int blk = part, queued = 0;  // (GEN)
   // (CHAINED)
   __shared__ ChainShared sh;
   __shared__ float tile_v[8];
   __shared__ int32_t tile_c[8];
-  const int member = CHAIN ? (int)blockIdx.x / a.ca.nprob : 0;
-  const size_t row = (size_t)p * a.ca.t.S;
-  unsigned long long *const slots = CHAIN ? a.ca.slots + row * a.ca.ntiles : nullptr;
-  unsigned int *const claims = CHAIN ? a.ca.claims + (size_t)p * (a.ca.t.S + 1) : nullptr;
-  int cur = 1, stage = a.ca.first - 1, tile = a.ca.ntiles;
+  const int member = CHAIN ? (int)blockIdx.x / ca.nprob : 0;
+  const size_t row = (size_t)p * ca.t.S;
+  unsigned long long *const slots = CHAIN ? ca.slots + row * ca.ntiles : nullptr;
+  unsigned int *const claims = CHAIN ? ca.claims + (size_t)p * (ca.t.S + 1) : nullptr;
+  int cur = 1, stage = ca.first - 1, tile = ca.ntiles;
   unsigned int c_next = NO_CLAIM;
   int32_t pre = 0;
-  if constexpr (CHAIN) chain_begin(sh, a.ca, row, member, threadIdx.x);
+  if constexpr (CHAIN) chain_begin(sh, ca, row, member, threadIdx.x);
   else if constexpr (GEN) load_wave_dec(wd, a.decpack, p, lane);
   else if (!idle) fetch(p, n0, 0);
   float v = __builtin_inff();
@@ -402,15 +413,15 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
     }
     int have = 0;  // (GEN) candidates of this sub-tile
     if constexpr (CHAIN) {
-      while (tile >= a.ca.ntiles)
-        if (!chain_between(sh, a.ca, slots, claims, p, row, member, cur, stage, tile, c_next, pre, threadIdx.x)) {
-          chain_leave(sh, a.ca, slots, claims, p, a.ca.ntiles, threadIdx.x);
+      while (tile >= ca.ntiles)
+        if (!chain_between(sh, ca, slots, claims, p, row, member, cur, stage, tile, c_next, pre, threadIdx.x)) {
+          chain_leave(sh, ca, slots, claims, p, ca.ntiles, threadIdx.x);
           return;
         }
       n0 = ((int64_t)tile * a.spw + w) * (32 * CT);
       have = w < a.spw && n0 < a.M ? (int)(a.M - n0 < 32 * CT ? a.M - n0 : 32 * CT) : 0;
       nu = u;
-      if (threadIdx.x == CLAIMER) sh.claim[0] = a.ca.ntiles > a.ca.group ? (int)atomicAdd(&claims[stage], 1u) : a.ca.ntiles;
+      if (threadIdx.x == CLAIMER) sh.claim[0] = ca.ntiles > ca.group ? (int)atomicAdd(&claims[stage], 1u) : ca.ntiles;
     } else if constexpr (GEN) {
       if constexpr (DIRECT) {
         n0 = (int64_t)blk * (32 * CT);
@@ -627,7 +638,7 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
         }
       }
       if constexpr (CHAIN) {
-        tile = post_tile(sh, a.ca, slots, tile_v, tile_c, stage, tile, v, vc, lane, w);
+        tile = post_tile(sh, ca, slots, tile_v, tile_c, stage, tile, v, vc, lane, w);
         v = __builtin_inff();
         vc = -1;
         continue;
@@ -666,13 +677,14 @@ __global__ __launch_bounds__(512) void k_small_bf16(SmallArgs a) {
 // when two columns per lane had one sum each and 192,000 vectors took 88 instead of 90 us), and a
 // candidate's score does not depend on how many candidates the call has.
 template <int CT, int NT, int MODE>
-__global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
+__global__ __launch_bounds__(512) void k_small_f32(typename small_args<MODE>::type a) {
   constexpr bool ONE = MODE == GIVEN_ONE, GEN = MODE != GIVEN && !ONE, DIRECT = MODE == IDS, CHAIN = MODE == CHAINED;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint4 *const wl = reinterpret_cast<uint4 *>(smem);
   const floatx4 *const wf = reinterpret_cast<const floatx4 *>(smem);
   float *const bl = reinterpret_cast<float *>(wl + a.md.nw);
   WaveDec &wd = reinterpret_cast<WaveDec *>(bl + (a.md.nbias + 3) / 4 * 4)[threadIdx.x >> 6];  // (GEN only)
+  const ChainArgs &ca = chain_of(a);
   const int lane = threadIdx.x & 63, q = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   stage_small(a, wl, bl);
@@ -699,21 +711,21 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
   int u_end = 0, u = CHAIN ? 0 : first_unit(a, w, u_end), sub = 0;
   const bool idle = ONE && u >= u_end;
   if (!CHAIN && !ONE && u >= u_end) return;
-  int p = CHAIN ? (int)blockIdx.x % a.ca.nprob : u / a.nparts, part = CHAIN ? 0 : u - p * a.nparts;
+  int p = CHAIN ? (int)blockIdx.x % ca.nprob : u / a.nparts, part = CHAIN ? 0 : u - p * a.nparts;
   int64_t n0 = GEN ? 0 : (int64_t)part * a.spp * 16 * CT;
   int blk = part, queued = 0;  // (GEN)
   // (CHAINED)
   __shared__ ChainShared sh;
   __shared__ float tile_v[8];
   __shared__ int32_t tile_c[8];
-  const int member = CHAIN ? (int)blockIdx.x / a.ca.nprob : 0;
-  const size_t row = (size_t)p * a.ca.t.S;
-  unsigned long long *const slots = CHAIN ? a.ca.slots + row * a.ca.ntiles : nullptr;
-  unsigned int *const claims = CHAIN ? a.ca.claims + (size_t)p * (a.ca.t.S + 1) : nullptr;
-  int cur = 1, stage = a.ca.first - 1, tile = a.ca.ntiles;
+  const int member = CHAIN ? (int)blockIdx.x / ca.nprob : 0;
+  const size_t row = (size_t)p * ca.t.S;
+  unsigned long long *const slots = CHAIN ? ca.slots + row * ca.ntiles : nullptr;
+  unsigned int *const claims = CHAIN ? ca.claims + (size_t)p * (ca.t.S + 1) : nullptr;
+  int cur = 1, stage = ca.first - 1, tile = ca.ntiles;
   unsigned int c_next = NO_CLAIM;
   int32_t pre = 0;
-  if constexpr (CHAIN) chain_begin(sh, a.ca, row, member, threadIdx.x);
+  if constexpr (CHAIN) chain_begin(sh, ca, row, member, threadIdx.x);
   else if constexpr (GEN) load_wave_dec(wd, a.decpack, p, lane);
   else if (!idle) fetch(p, n0, 0);
   float v = __builtin_inff();
@@ -731,15 +743,15 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
     }
     int have = 0;  // (GEN) candidates of this sub-tile
     if constexpr (CHAIN) {
-      while (tile >= a.ca.ntiles)
-        if (!chain_between(sh, a.ca, slots, claims, p, row, member, cur, stage, tile, c_next, pre, threadIdx.x)) {
-          chain_leave(sh, a.ca, slots, claims, p, a.ca.ntiles, threadIdx.x);
+      while (tile >= ca.ntiles)
+        if (!chain_between(sh, ca, slots, claims, p, row, member, cur, stage, tile, c_next, pre, threadIdx.x)) {
+          chain_leave(sh, ca, slots, claims, p, ca.ntiles, threadIdx.x);
           return;
         }
       n0 = ((int64_t)tile * a.spw + w) * (16 * CT);
       have = w < a.spw && n0 < a.M ? (int)(a.M - n0 < 16 * CT ? a.M - n0 : 16 * CT) : 0;
       nu = u;
-      if (threadIdx.x == CLAIMER) sh.claim[0] = a.ca.ntiles > a.ca.group ? (int)atomicAdd(&claims[stage], 1u) : a.ca.ntiles;
+      if (threadIdx.x == CLAIMER) sh.claim[0] = ca.ntiles > ca.group ? (int)atomicAdd(&claims[stage], 1u) : ca.ntiles;
     } else if constexpr (GEN) {
       if constexpr (DIRECT) {
         n0 = (int64_t)blk * (16 * CT);
@@ -970,7 +982,7 @@ __global__ __launch_bounds__(512) void k_small_f32(SmallArgs a) {
       }
     }
     if constexpr (CHAIN) {
-      tile = post_tile(sh, a.ca, slots, tile_v, tile_c, stage, tile, v, vc, lane, w);
+      tile = post_tile(sh, ca, slots, tile_v, tile_c, stage, tile, v, vc, lane, w);
       v = __builtin_inff();
       vc = -1;
       continue;
@@ -1046,10 +1058,10 @@ int vfk_pack_small(vf_ctx *c, const float *wdev) {
   VF_HIP(c, hipMalloc(&buf, words_at + (size_t)nwords * 8));
   c->pm.small_buf = buf;
   float *bias = reinterpret_cast<float *>(reinterpret_cast<uint4 *>(buf) + nw);
-  d.words = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(buf) + words_at);
-  d.nwords = nwords;
+  c->pm.small_words = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(buf) + words_at);
+  c->pm.small_nwords = nwords;
   hipLaunchKernelGGL(k_pad_f32, dim3((2 * nwords + 255) / 256), dim3(256), 0, c->stream, wdev, 0, 2 * nwords,
-                     reinterpret_cast<float *>(d.words));
+                     reinterpret_cast<float *>(c->pm.small_words));
   VF_HIP(c, hipGetLastError());
   size_t off = 0;
   for (int l = 0; l < L; ++l) {
@@ -1083,8 +1095,6 @@ bool vfk_small_generates(const vf_ctx *c) {
   return c->has_model && d.w && c->model.kind == VF_MLP && c->model.dims[0] == c->space.F &&
          (size_t)d.nw * 16 + (size_t)d.nbias * 4 <= GEN_LDS;
 }
-
-typedef void (*small_kernel)(SmallArgs);
 
 // Scores on the kernels above.  part_out: candidates per partial minimum, a divisor of 128.  x null: the
 // candidates of the decisions whose contexts d_decpack holds are generated (masked scores).
@@ -1137,13 +1147,7 @@ int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob,
   }
   if (units == 0) return VF_OK;
   const int grid = units < ncu ? (int)units : ncu;
-  a.words = nullptr;
-  a.one_idx = nullptr; a.one_val = nullptr;
-  if (c->one_wanted && grid < c->pm.small.nwords) {
-    a.words = c->pm.small.words;
-    a.wait_rounds = c->wait_rounds;
-    a.one_idx = c->one_idx; a.one_val = c->one_val;
-  }
+  const bool one = c->one_wanted && grid < c->pm.small_nwords;
   a.md = c->pm.small;
   a.x = x; a.prob_stride = prob_stride; a.M = M; a.ld = ld; a.use_valid_row = use_valid_row;
   a.scores = scores; a.ld_scores = ld_scores;
@@ -1159,17 +1163,30 @@ int vfk_score_small(vf_ctx *c, const int32_t *x, int64_t prob_stride, int nprob,
 #define VF_SMALL_ALL(mode)                                                                                  \
   {{VF_SMALL(k_small_bf16, 1, mode, 1, 2, 3, 4), VF_SMALL(k_small_bf16, 2, mode, 1, 2, 3, 4)},              \
    {VF_SMALL(k_small_f32, 1, mode, 2, 4, 6, 8), VF_SMALL(k_small_f32, 2, mode, 2, 4, 6, 8)}}
-  static constexpr small_kernel kerns[4][2][2][4] = {VF_SMALL_ALL(GIVEN), VF_SMALL_ALL(COLLECTED), VF_SMALL_ALL(IDS), VF_SMALL_ALL(GIVEN_ONE)};
+  static constexpr void (*kerns[3][2][2][4])(SmallArgs) = {VF_SMALL_ALL(GIVEN), VF_SMALL_ALL(COLLECTED), VF_SMALL_ALL(IDS)};
+  static constexpr void (*one_kerns[2][2][4])(SmallOneArgs) = VF_SMALL_ALL(GIVEN_ONE);
 #undef VF_SMALL_ALL
 #undef VF_SMALL
-  const small_kernel kern = kerns[a.words ? 3 : x ? GIVEN : ids ? IDS : COLLECTED][bf16 ? 0 : 1][ct - 1][a.md.NT * base / 32 - 1];
-  vf_prof_scope prof(c, VF_PROF_SCORE);
-  VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+  const int dt = bf16 ? 0 : 1, rt = a.md.NT * base / 32 - 1;
   a.xcd_bits = x && grid % 8 == 0 ? 3 : 0;
   a.run = (int)((units + (1 << a.xcd_bits) - 1) >> a.xcd_bits);
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), smem, c->stream, a);
+  vf_prof_scope prof(c, VF_PROF_SCORE);
+  if (one) {
+    SmallOneArgs oa;
+    static_cast<SmallArgs &>(oa) = a;
+    oa.words = c->pm.small_words;
+    oa.wait_rounds = c->wait_rounds;
+    oa.one_idx = c->one_idx; oa.one_val = c->one_val;
+    const auto kern = one_kerns[dt][ct - 1][rt];
+    VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), smem, c->stream, oa);
+  } else {
+    const auto kern = kerns[x ? GIVEN : ids ? IDS : COLLECTED][dt][ct - 1][rt];
+    VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), smem, c->stream, a);
+  }
   VF_HIP(c, hipGetLastError());
-  c->one_done = a.words != nullptr;
+  c->one_done = one;
   return VF_OK;
 }
 
@@ -1197,7 +1214,7 @@ int vfk_small_chain(vf_ctx *c, int first, int last, int32_t *out_states, int32_t
   if (spw == 0 || first > last) return VF_ESTATE;
   const bool bf16 = c->model.dtype == VF_BF16;
   const int base = bf16 ? 32 : 16;
-  SmallArgs a = {};
+  SmallChainArgs a = {};
   const int rc = chain_args(c, first, last, (int)((c->M + base * spw - 1) / (base * spw)), out_states, out_cids, out_vals, &a.ca);
   if (rc != VF_OK) return rc;
   a.md = c->pm.small;
@@ -1208,10 +1225,10 @@ int vfk_small_chain(vf_ctx *c, int first, int last, int32_t *out_states, int32_t
   a.na.k0 = (uint32_t)c->noise_seed; a.na.k1 = (uint32_t)(c->noise_seed >> 32);
   a.na.stage = first; a.na.first_rollout = c->noise_first;
   const size_t smem = (size_t)a.md.nw * 16 + (size_t)a.md.nbias * 4 + 1024;
-  static constexpr small_kernel kerns[2][4] = {
+  static constexpr void (*kerns[2][4])(SmallChainArgs) = {
       {k_small_bf16<1, 1, CHAINED>, k_small_bf16<1, 2, CHAINED>, k_small_bf16<1, 3, CHAINED>, k_small_bf16<1, 4, CHAINED>},
       {k_small_f32<1, 2, CHAINED>, k_small_f32<1, 4, CHAINED>, k_small_f32<1, 6, CHAINED>, k_small_f32<1, 8, CHAINED>}};
-  const small_kernel kern = kerns[bf16 ? 0 : 1][a.md.NT * base / 32 - 1];
+  const auto kern = kerns[bf16 ? 0 : 1][a.md.NT * base / 32 - 1];
   vf_prof_scope prof(c, VF_PROF_SCORE);
   VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
   hipLaunchKernelGGL(kern, dim3((unsigned)(c->B * a.ca.group)), dim3(512), smem, c->stream, a);
