@@ -24,8 +24,9 @@
 // Every store to the tables is waited for by the next use of a register that a load in flight may still fill: loads
 // that are used behind them are waited for in front (the empty asm statements).
 //
-// Tiles are claimed (a counter per decision), and a claim is only made by a workgroup that is running, so
-// every wait ends whether or not all workgroups are resident at once; the waits are bounded all the same,
+// Tiles are claimed (a counter per decision), and a claim is only made by a workgroup that is running: one
+// for every decision, and those that are left over while it waits.  So every wait ends whether or not all workgroups
+// are resident at once; the waits are bounded all the same,
 // and a workgroup whose wait runs out scores the missing tile itself, with the same result.  The last
 // workgroup of a problem to leave clears the problem's words for the next launch.
 #include <type_traits>
@@ -80,7 +81,7 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
   unsigned int *const claims = ca.claims + (size_t)p * (S + 1);
 
   // ---- once per workgroup
-  unsigned int c_more = 0u, c_next = NO_CLAIM;  // (the claimer's) a further tile of this decision, one of the next
+  unsigned int c_next = NO_CLAIM;  // (the claimer's) a tile of the next decision
   for (int i = tid; i < (int)md.wl_off; i += 512) auxs[i] = md.aux[i];
   for (int i = tid; i < md.dims[NH] / 2; i += 512) wls[i] = pack_bf16(md.aux[md.wl_off + 2 * i], md.aux[md.wl_off + 2 * i + 1]);
   const __amdgpu_buffer_rsrc_t ws = stream_rsrc(md.w_stream + (size_t)w * md.wave_stride);
@@ -145,7 +146,6 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
         __syncthreads();
       }
       ready = false;
-      if (tid == CLAIMER) c_more = ntiles > ca.group ? atomicAdd(&claims[stage], 1u) : (unsigned int)ntiles;
       const bool closed = shut != 0;
       float dot[CT];
       if (!closed) {
@@ -230,7 +230,6 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
         for (int c = 0; c < CT; ++c)
           if (lane < 32) red[w * NC + c * 32 + lane] = dot[c];
       }
-      if (tid == CLAIMER) sh.claim[0] = (int)c_more;
       __syncthreads();
       if (w == 0) {
         float v = __builtin_inff();
@@ -257,13 +256,9 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
           }
         }
         if (lane == 0)
-          __hip_atomic_store(&slots[(size_t)stage * ntiles + t],
-                             (unsigned long long)__float_as_uint(v) << 32 | (c >= 0 ? (uint32_t)c + 1u : 0xffffffffu),
-                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(&slots[(size_t)stage * ntiles + t], word_of(v, c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
-      t = sh.claim[0];
-      if (t < ntiles) __syncthreads();  // (the scan has read what the next tile writes)
-      continue;
+      t = ntiles;
     }
 
     // ---- no tile left to claim: what is known of the next stage
@@ -298,7 +293,7 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
       }
       // ---- s_i := the winner: its rows, a share each by threads of four waves; the ids of the next tile
       winner_rows(sh, pk, sh.win_c, lane, w);
-      if (w == 4 && decides && sh.claim[1] < ntiles) take_apart(sh.claim[1], pk.sp);
+      if (w == 4 && decides && sh.claim < ntiles) take_apart(sh.claim, pk.sp);
       __syncthreads();
       chain_tables(sh, pk, ca, p, row, stage, member, tid);
     }
@@ -316,7 +311,7 @@ __global__ __launch_bounds__(512, 2) void k_chain(vf_fast_dev md, int ks, NoiseA
           ca.decpack[(size_t)p * VF_DECPACK_DWORDS + i] = reinterpret_cast<const uint32_t *>(&nk)[i];
       break;
     }
-    t = __builtin_amdgcn_readfirstlane(sh.claim[1]);
+    t = __builtin_amdgcn_readfirstlane(sh.claim);
     if (stage < ca.first && w == 4 && t < ntiles) take_apart(t, nk.sp);
     ready = t < ntiles;
     c_next = NO_CLAIM;
@@ -428,7 +423,7 @@ int vfk_greedy_chain(vf_ctx *c, int first, int last, int32_t *out_states, int32_
   na.stage = first; na.first_rollout = c->noise_first;
   vf_prof_scope prof(c, VF_PROF_SCORE);
   VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-  hipLaunchKernelGGL(kern, dim3((unsigned)(c->B * ca.group)), dim3(512), smem, c->stream, fd, ks, na, ca);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(c->B * ca.ntiles)), dim3(512), smem, c->stream, fd, ks, na, ca);
   VF_HIP(c, hipGetLastError());
   c->dec_stage = last + 1 < c->S ? last + 1 : -1;
   return VF_OK;

@@ -9,8 +9,7 @@ struct ChainArgs {
   Tables t;
   int first, last;
   int64_t M;
-  int nprob, group;            // workgroups per problem; grid = nprob * group
-  int ntiles;                  // tiles of a decision
+  int nprob, ntiles;           // tiles of a decision, as many workgroups per problem; grid = nprob * ntiles
   unsigned long long *slots;   // [nprob][S][ntiles] first minimum of every tile, 0 = not there yet
   unsigned int *claims;        // [nprob][S + 1] tiles claimed per stage; workgroups that have left
   unsigned int wait_rounds;
@@ -25,13 +24,18 @@ struct ChainShared {
   EvalTabs tabs;      // the open decision's quotient tables
   DecScratch ds;
   int32_t cf64[64], st16[16], sums[3];  // the last winner's rows, the sums behind it, alive
-  int claim[2];       // a further tile of the open decision; one of the next
+  int claim;          // a tile of the next decision
   int missing;        // >= 0: a tile whose minimum did not come
   int32_t win_c;      // the winner's digits, packed (they order like the ids); -1: none
   float win_v;
 };
 constexpr int CLAIMER = 448;  // the thread that claims tiles (first of the wave that polls)
 constexpr unsigned int NO_CLAIM = 0xffffffffu;
+
+// A first minimum as a word that is not zero.
+__device__ __forceinline__ unsigned long long word_of(float v, int32_t c) {
+  return (unsigned long long)__float_as_uint(v) << 32 | (c >= 0 ? (uint32_t)c + 1u : 0xffffffffu);
+}
 
 // Once per workgroup: the space; the layers that this call does not decide to the caller's tables, as they
 // are (the others follow one by one).
@@ -64,7 +68,7 @@ __device__ __forceinline__ void chain_rows(ChainShared &sh, DecPack &nk, const D
     dec_fetch_anchor(nk.d, ds, ca.t, p, next, -1, tid);
     if (tid >= 128 && tid < 128 + VF_STAT_WORDS) nk.stat[tid - 128] = stat_word(nk.d, tid - 128);
     if (tid < 3) sh.sums[tid] = ds.sc[tid < 2 ? 1 + tid : 0];
-    if (tid == CLAIMER) sh.claim[1] = (int)c_next;
+    if (tid == CLAIMER) sh.claim = (int)c_next;
     __syncthreads();
   } else if (next < ca.t.S) {
     // from the open context where it has them (its neighbour rows move on by one), else fetched before
@@ -153,7 +157,7 @@ __device__ __forceinline__ void chain_poll(ChainShared &sh, const ChainArgs &ca,
     }
   }
   wave_min(v, c);
-  if (lane == 0) { sh.win_v = v; sh.win_c = c; sh.missing = miss; sh.claim[1] = (int)c_next; }
+  if (lane == 0) { sh.win_v = v; sh.win_c = c; sh.missing = miss; sh.claim = (int)c_next; }
 }
 
 // The winner to the tables: every workgroup writes them (it reads its anchors from there), one the caller's.
@@ -199,7 +203,7 @@ __device__ __forceinline__ void chain_leave(ChainShared &sh, const ChainArgs &ca
   __syncthreads();
   if (tid == 0) sh.missing = (int)(atomicAdd(&claims[S], 1u) + 1u);
   __syncthreads();
-  if (sh.missing == ca.group) {
+  if (sh.missing == ntiles) {
     for (size_t i = (size_t)ca.first * ntiles + tid; i < (size_t)(ca.last + 1) * ntiles; i += 512) slots[i] = 0ull;
     for (int i = tid; i <= S; i += 512) claims[i] = 0u;
     if (tid == 0 && sh.st16[15] == 0) ca.t.alive[p] = 0;
@@ -242,7 +246,7 @@ __device__ __forceinline__ void chain_leave(ChainShared &sh, const ChainArgs &ca
     return false;
   }
   fill_evaltabs(sh.tabs, nk.d, nk.sp);
-  t = __builtin_amdgcn_readfirstlane(sh.claim[1]);
+  t = __builtin_amdgcn_readfirstlane(sh.claim);
   c_next = NO_CLAIM;
   cur ^= 1;
   stage = next;
@@ -254,8 +258,6 @@ __device__ __forceinline__ void chain_leave(ChainShared &sh, const ChainArgs &ca
 // The arguments of a launch over stages first..last; VF_ENOMEM without memory for its words.
 [[maybe_unused]] static int chain_args(vf_ctx *c, int first, int last, int ntiles, int32_t *out_states, int32_t *out_cids,
                                        float *out_vals, ChainArgs *ca) {
-  int ncu = 256;
-  (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
   const size_t nslots = (size_t)c->B * c->S * ntiles, nclaims = (size_t)c->B * (c->S + 1);
   const int rc = vfk_chain_words(c, (nslots * 8 + nclaims * 4 + 15) / 16);
   if (rc != VF_OK) return rc;
@@ -264,7 +266,6 @@ __device__ __forceinline__ void chain_leave(ChainShared &sh, const ChainArgs &ca
   ca->M = c->M;
   ca->nprob = c->B;
   ca->ntiles = ntiles;
-  ca->group = ntiles * c->B <= ncu ? ntiles : ncu / c->B;
   ca->slots = c->d_chain;
   ca->claims = reinterpret_cast<unsigned int *>(c->d_chain + nslots);
   ca->wait_rounds = c->wait_rounds;

@@ -160,9 +160,9 @@ __device__ __forceinline__ NoiseArgs noise_of(const SmallArgs &a, bool chain, in
   if (chain) na.stage = stage;
   return na;
 }
-// (CHAINED) The first minimum of a workgroup's tile from its waves' (v, c), to the other workgroups; on to the next tile.
-__device__ __forceinline__ int post_tile(ChainShared &sh, const ChainArgs &ca, unsigned long long *slots, float *tile_v, int32_t *tile_c,
-                                         int stage, int tile, float v, int32_t c, int lane, int w) {
+// (CHAINED) The first minimum of a workgroup's tile from its waves' (v, c), to the other workgroups.
+__device__ __forceinline__ void post_tile(const ChainArgs &ca, unsigned long long *slots, float *tile_v, int32_t *tile_c, int stage,
+                                          int tile, float v, int32_t c, int lane, int w) {
   wave_min(v, c);
   if (lane == 0) {
     tile_v[w] = v;
@@ -174,13 +174,8 @@ __device__ __forceinline__ int post_tile(ChainShared &sh, const ChainArgs &ca, u
     c = tile_c[lane & 7];
     wave_min(v, c);
     if (lane == 0)
-      __hip_atomic_store(&slots[(size_t)stage * ca.ntiles + tile],
-                         (unsigned long long)__float_as_uint(v) << 32 | (c >= 0 ? (uint32_t)c + 1u : 0xffffffffu), __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&slots[(size_t)stage * ca.ntiles + tile], word_of(v, c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  const int t = __builtin_amdgcn_readfirstlane(sh.claim[0]);
-  if (t < ca.ntiles) __syncthreads();  // (before the next tile's minima)
-  return t;
 }
 
 // The first minimum over all candidates from the waves' (v, c), in the launch that scores them: every workgroup
@@ -193,9 +188,6 @@ __device__ __forceinline__ int post_tile(ChainShared &sh, const ChainArgs &ca, u
 // taken, leaves what it has in a word of its own and goes; those that find their word taken put theirs there all the
 // same, and the last of them (words[0] counts) does the reduction.  Words of workgroup b: words[1 + b].
 constexpr unsigned long long WORD_TAKEN = 0xfffffffeull;  // (ids are below 2^30)
-__device__ __forceinline__ unsigned long long word_of(float v, int32_t c) {
-  return (unsigned long long)__float_as_uint(v) << 32 | (c >= 0 ? (uint32_t)c + 1u : 0xffffffffu);
-}
 __device__ __forceinline__ void take_word(unsigned long long *words, int q, unsigned long long word, float &v, int32_t &c) {
   const uint32_t id = (uint32_t)word;
   if (id == 0u) return;
@@ -421,7 +413,6 @@ __global__ __launch_bounds__(512) void k_small_bf16(typename small_args<MODE>::t
       n0 = ((int64_t)tile * a.spw + w) * (32 * CT);
       have = w < a.spw && n0 < a.M ? (int)(a.M - n0 < 32 * CT ? a.M - n0 : 32 * CT) : 0;
       nu = u;
-      if (threadIdx.x == CLAIMER) sh.claim[0] = ca.ntiles > ca.group ? (int)atomicAdd(&claims[stage], 1u) : ca.ntiles;
     } else if constexpr (GEN) {
       if constexpr (DIRECT) {
         n0 = (int64_t)blk * (32 * CT);
@@ -638,7 +629,8 @@ __global__ __launch_bounds__(512) void k_small_bf16(typename small_args<MODE>::t
         }
       }
       if constexpr (CHAIN) {
-        tile = post_tile(sh, ca, slots, tile_v, tile_c, stage, tile, v, vc, lane, w);
+        post_tile(ca, slots, tile_v, tile_c, stage, tile, v, vc, lane, w);
+        tile = ca.ntiles;
         v = __builtin_inff();
         vc = -1;
         continue;
@@ -751,7 +743,6 @@ __global__ __launch_bounds__(512) void k_small_f32(typename small_args<MODE>::ty
       n0 = ((int64_t)tile * a.spw + w) * (16 * CT);
       have = w < a.spw && n0 < a.M ? (int)(a.M - n0 < 16 * CT ? a.M - n0 : 16 * CT) : 0;
       nu = u;
-      if (threadIdx.x == CLAIMER) sh.claim[0] = ca.ntiles > ca.group ? (int)atomicAdd(&claims[stage], 1u) : ca.ntiles;
     } else if constexpr (GEN) {
       if constexpr (DIRECT) {
         n0 = (int64_t)blk * (16 * CT);
@@ -982,7 +973,8 @@ __global__ __launch_bounds__(512) void k_small_f32(typename small_args<MODE>::ty
       }
     }
     if constexpr (CHAIN) {
-      tile = post_tile(sh, ca, slots, tile_v, tile_c, stage, tile, v, vc, lane, w);
+      post_tile(ca, slots, tile_v, tile_c, stage, tile, v, vc, lane, w);
+      tile = ca.ntiles;
       v = __builtin_inff();
       vc = -1;
       continue;
@@ -1231,7 +1223,7 @@ int vfk_small_chain(vf_ctx *c, int first, int last, int32_t *out_states, int32_t
   const auto kern = kerns[bf16 ? 0 : 1][a.md.NT * base / 32 - 1];
   vf_prof_scope prof(c, VF_PROF_SCORE);
   VF_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-  hipLaunchKernelGGL(kern, dim3((unsigned)(c->B * a.ca.group)), dim3(512), smem, c->stream, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(c->B * a.ca.ntiles)), dim3(512), smem, c->stream, a);
   VF_HIP(c, hipGetLastError());
   c->dec_stage = last + 1 < c->S ? last + 1 : -1;
   return VF_OK;
