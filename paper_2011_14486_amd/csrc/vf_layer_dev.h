@@ -110,14 +110,21 @@ struct ListPlace {
   return list_digits(os, list_place(pk, os, pos_r, k, rcp_perm, rcp_vec));
 }
 // The list, by `threads` threads (of them tid): a thread takes four entries in a row and goes on from the first to the
-// others by carrying (the divisions of an entry are most of its work).  The list
-// is 16-byte aligned and a multiple of four long; what lies behind the last entry is 0.
+// others by carrying (the divisions of an entry are most of its work).  The list is 16-byte aligned and has room for a
+// multiple of four.  Where there is a thread for every entry it takes just that one: the carrying would be three more
+// steps behind the divisions (fours / this, 20 layers, 256-512-512-1: 24 problems of 768 ids 899 / 874 us, 200: 1000 / 992,
+// 22: 497 / 487; 256-1024-1024-1, 200 of 768: 2382 / 2360).  k_whole with 1024 units spills 20 registers with both
+// forms, 11 with single entries alone, and takes as long: 256 problems of 4096 ids 12.63 ms / 12.64.
 __device__ __forceinline__ void write_list(const DecPack &pk, const OpenScratch &os, uint32_t *idlist, int tid, int threads = 512) {
   const float rcp_perm = 1.0f / (float)pk.sp.nperm, rcp_vec = 1.0f / (float)pk.sp.nvec;
   const int n = os.ncand, last = os.npairs - 1;
   int pos_r[12];
 #pragma unroll
   for (int j = 0; j < 12; ++j) pos_r[j] = j <= last ? os.pos[j] : 0x7fffffff;
+  if (n <= threads) {
+    if (tid < n) idlist[tid] = list_entry(pk, os, pos_r, tid, rcp_perm, rcp_vec);
+    return;
+  }
   for (int k = 4 * tid; k < n; k += 4 * threads) {
     ListPlace at = list_place(pk, os, pos_r, k, rcp_perm, rcp_vec);
     int next = os.pos[at.q + 1];  // (behind the last pair: n)

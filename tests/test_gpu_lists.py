@@ -54,6 +54,38 @@ def test_batch_on_lists_equals_single_problems(vf, dims):
     vf.vf_destroy(many)
 
 
+# lists as long as a workgroup has threads, just shorter and just longer (all ids are valid): written by teams, by a
+# workgroup per problem, by several workgroups per problem or between two launches
+@pytest.mark.parametrize("n", [504, 512, 525, 1050])
+@pytest.mark.parametrize("B", [24, 33, 170])
+@pytest.mark.parametrize("dims", [[256, 512, 512, 1], [64, 1024, 1]])
+def test_lists_around_the_workgroup_size(vf, n, B, dims):
+    """Ids and values of every layer bit-identical to those of one problem alone, step by step."""
+    f = lambda k: list(range(1, k + 1))
+    nx, ny, nc, nperm, nvec = {504: (7, 8, 3, 3, 1), 512: (8, 8, 8, 1, 1), 525: (7, 5, 5, 3, 1), 1050: (7, 5, 5, 3, 2)}[n]
+    sp = I.make_space(f(nx), f(ny), f(nc), I.ALL_PERMS[:nperm], nvec, 1, [I.ROOT], 1, dims[0])
+    assert I.space_dense_count(sp) == n
+    pipes = I.resnet18_batch(B, seed=3)[:, :4].copy()
+    pipes[:, :, 1:4] = np.maximum(pipes[:, :, 1:4], 8)
+    w, model = I.mlp_weights(dims, 4, bias_std=0.1), I.model_record(I.MLP, dims, I.BF16)
+    many = context(vf, pipes, sp, model, w)
+    whole = [t.cpu().numpy() for t in vf.vf_greedy_schedule(many)]
+    vf.vf_sync_status(many)
+    vf.vf_reset_state(many)
+    assert vf.vf_enumerate(many, 0)[2].tolist() == [n] * B
+    for i in range(4):
+        vf.vf_argmin_step(many, i, True)
+    for a, b in zip(whole, vf.vf_greedy_schedule(many, first=4)):
+        assert np.array_equal(a, b.cpu().numpy())
+    vf.vf_destroy(many)
+    for b in range(0, B, 11):
+        one = context(vf, pipes[b], sp, model, w)
+        for i in range(4):
+            best, value = (t.cpu().numpy() for t in vf.vf_argmin_step(one, i, True))
+            assert best[0] == whole[1][b, i] and value[0] == whole[2][b, i]
+        vf.vf_destroy(one)
+
+
 @pytest.mark.parametrize("B", [385, 512])
 def test_second_round_of_long_decisions_in_one_launch(vf, B):
     """16384 ids, more problems than compute units: whole schedules in one launch (from three quarters
