@@ -98,9 +98,8 @@ def make_ctx(vf, pipe, sp, model, w, K):
 @pytest.mark.parametrize("K,dims", [(1, [256, 512, 512, 1]), (4, [256, 512, 512, 1]), (16, [256, 512, 512, 1]),
                                     (40, [256, 512, 512, 1]), (3, [256, 512, 512, 512, 512, 1])])
 def test_beam_fused_bf16(vf, ovf, K, dims):
-    """One slot and (three slots) a network of four hidden layers, whose biases do not fit next to a
-    list's tile: the scorer on id ranges and the selection passes; otherwise lists of valid
-    candidates."""
+    """Lists of valid candidates; (three slots) a network of four hidden layers, whose biases do not fit next to a
+    list's tile: the scorer on id ranges and the selection passes."""
     sp = I.make_space([1, 2, 3, 8], [1, 2, 5], [1, 4, 16], [(0, 1, 2), (2, 1, 0), (1, 0, 2)], 2, 2,
                       [I.ROOT, I.L1, I.L2, I.INLINE], 2, 256)
     pipe = I.random_pipeline(4, 41)
@@ -153,6 +152,89 @@ def test_beam_lists_of_short_decisions(vf, ovf, K, factors):
     model = I.model_record(I.MLP, dims, I.BF16)
     ctx, run = make_ctx(vf, pipe, sp, model, w, K)
     check_beam(ovf, pipe, sp, model, w, run, K, TOL[1])
+    vf.vf_destroy(ctx)
+
+
+# one slot with few ids: id ranges
+@pytest.mark.parametrize("dims", [[64, 512, 512, 1], [256, 1024, 1]])
+def test_beam_of_one_slot_with_short_decisions(vf, ovf, dims):
+    sp = I.make_space([1, 2, 4], [1, 2], [1, 4], [(0, 1, 2), (2, 1, 0)], 2, 1, [I.ROOT, I.L1, I.L2, I.INLINE], 2, dims[0])
+    assert ovf.dense_count(sp) == 384
+    pipe = I.random_pipeline(5, 43)
+    w, model = I.mlp_weights(dims, 5, bias_std=0.1), I.model_record(I.MLP, dims, I.BF16)
+    ctx, run = make_ctx(vf, pipe, sp, model, w, 1)
+    check_beam(ovf, pipe, sp, model, w, run, 1, TOL[1])
+    cids, vals, st, nb = run(4)
+    vf.vf_reset_state(ctx)
+    gs, gc, gv = (t.cpu().numpy() for t in vf.vf_greedy_schedule(ctx))
+    assert np.array_equal(gc, cids) and np.array_equal(gv, vals) and np.array_equal(gs, st)
+    vf.vf_destroy(ctx)
+
+
+@pytest.mark.parametrize("K", [2, 9, 300])
+def test_beam_on_lists_ends_on_the_way(vf, ovf, K):
+    """A layer without a valid candidate: the schedules so far are carried over as they are, by the workgroups that
+    copy rows, and the layers behind it change nothing."""
+    sp = I.make_space([1, 2, 4], [1, 2], [4, 8], [(0, 1, 2), (2, 1, 0)], 2, 1, [I.ROOT, I.L1], 2, 64)
+    pipe = I.random_pipeline(5, 43)
+    pipe[:, 3] = np.maximum(pipe[:, 3], 8)
+    pipe[2, 3] = 2                                # fewer channels than every channel factor
+    dims = [64, 512, 1]
+    w, model = I.mlp_weights(dims, 5, bias_std=0.1), I.model_record(I.MLP, dims, I.BF16)
+    ctx, run = make_ctx(vf, pipe, sp, model, w, K)
+    check_beam(ovf, pipe, sp, model, w, run, K, TOL[1])
+    before = run(1)
+    assert before[3] == K and (before[0][:, 1] >= 0).all()
+    for last in (2, 4):
+        for a, b in zip(before, run(last)):
+            assert np.array_equal(a, b)
+    vf.vf_destroy(ctx)
+
+
+# 1024 slots with 10 and with 33 parts each: more minima than the bins take in two and in eight rounds, and more than
+# they take at all
+@pytest.mark.parametrize("n", [588, 2100])
+@pytest.mark.parametrize("same", [False, True])
+def test_beam_choice_among_many_minima(vf, n, same):
+    """Every id is valid.  Equal scores: the first (slot, id) pairs.  Others: against the scores of all extensions of the
+    survivors before, which vf_score gives from their features."""
+    import torch
+    f = lambda k: list(range(1, k + 1))
+    nx, ny, nc, nperm, nvec = {588: (7, 7, 4, 3, 1), 2100: (7, 5, 5, 6, 2)}[n]
+    sp = I.make_space(f(nx), f(ny), f(nc), I.ALL_PERMS[:nperm], nvec, 1, [I.ROOT], 1, 64)
+    assert I.space_dense_count(sp) == n
+    K, dims = 1024, [64, 512, 1]
+    pipe = I.resnet18_shaped()[:3].copy()
+    pipe[:, 1:4] = np.maximum(pipe[:, 1:4], 8)
+    w = I.mlp_weights(dims, 3, bias_std=0.1)
+    if same:
+        w[:] = 0.0
+        w[-1] = 0.75
+    model = I.model_record(I.MLP, dims, I.BF16)
+    ctx, run = make_ctx(vf, pipe, sp, model, w, K)
+    cids, vals, st, nb = run(2)
+    assert nb == K
+    if same:
+        rows = [()]
+        for _ in range(3):
+            rows = [r + (i,) for r in rows[:K // n + 1] for i in range(n)][:K]
+        assert cids.tolist() == [list(r) for r in rows] and (vals == 0.75).all()
+        vf.vf_destroy(ctx)
+        return
+    prev, _, _, _ = run(1)
+    assert (prev[:, 1] >= 0).all()
+    vf.vf_set_state(ctx, np.ascontiguousarray(prev[:, :2]))
+    Mp = vf.vf_padded_count(ctx)
+    x = vf.vf_featurize(ctx, 2).permute(1, 0, 2).reshape(64, K * Mp).contiguous()
+    ref = vf.vf_score(ctx, x, want_min=False)[0].reshape(K, Mp)[:, :n].double().cpu().numpy()
+    at = {tuple(r): j for j, r in enumerate(prev[:, :2].tolist())}
+    pairs = [(at[tuple(r[:2])], r[2]) for r in cids.tolist()]
+    assert len(set(pairs)) == K and (np.diff(vals[:, 2]) >= 0).all()
+    scale, tol = np.sqrt(np.mean(ref ** 2)), TOL[1]
+    got = np.array([ref[p] for p in pairs])
+    assert np.abs(got - vals[:, 2]).max() <= tol * max(np.abs(got).max(), scale)
+    better = np.argwhere(ref < vals[:, 2].max() - 2 * tol * max(abs(vals[:, 2].max()), scale))
+    assert set(map(tuple, better.tolist())) <= set(pairs)
     vf.vf_destroy(ctx)
 
 
