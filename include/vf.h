@@ -199,9 +199,10 @@ int vf_argmin_step(vf_ctx *ctx, int stage, int commit, int32_t *best_cid_dev, fl
  * out_states_dev[batch][S] the committed states s_1..s_n so far (all stages),
  * out_cids_dev[batch][S] the chosen candidate ids, out_values_dev[batch][S] their
  * values; entries of stages not scheduled yet are zero states, -1 and +inf.
- * A few problems (all tiles of a decision at once on the compute units) take one launch in which as many
- * workgroups as a decision has tiles share a problem: they exchange the tiles' minima, and one that waits in
- * vain for a minimum works it out itself.  More problems take two launches per layer.  With a problem for most compute
+ * A few problems (all tiles of a decision at once on the compute units) take one launch if the network is small or
+ * its hidden layers are 512 wide in bf16: as many workgroups as a decision has tiles share a problem, they exchange
+ * the tiles' minima, and one that waits in vain for a minimum works it out itself.  More problems, and networks of
+ * other widths, take launches per layer: two where scoring makes the features.  With a problem for most compute
  * units, and from 24 problems on decisions of few candidates, the layers run inside one launch (the
  * model's tile must fit the LDS): with fewer problems than half the compute units several workgroups
  * share a problem from the start, with more a workgroup that has finished its own problems helps

@@ -15,7 +15,7 @@
 // four k-steps in registers and six in LDS for good), the ids of the next tile.
 //
 // What bounds it: the chain of small steps.  256-512-512-1, 20 layers of 4096 ids, one problem: 437 us with a launch
-// per layer, 286 here (two problems 442 -> 295, four, with tiles of 64, 445 -> 307; 100 layers of 16384 ids 2342 ->
+// per layer, 287 here (two problems 438 -> 293, four, with tiles of 64, 443 -> 304; 100 layers of 16384 ids 2342 ->
 // 1599).  A decision takes 13 us: the tile 6 (features 0.8, first layer 0.5, hidden layer 4 with 512 KB of weights
 // per compute unit at 55 bytes a cycle, output and scan 0.7), the minima 1.5, the winner 1.1, the context and the fold 2.6.  Tiles of
 // 32 ids as long as there are compute units for them: the products of a tile of 64 take as long as its weights.

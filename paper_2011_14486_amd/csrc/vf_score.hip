@@ -1404,14 +1404,14 @@ bool vfk_layer_pays(const vf_ctx *c) {
   const int NC = c->pm.fast_rt == 4 || narrow_step(c) ? 64 : 128;
   return (c->M + NC - 1) / NC * c->B > compute_units(c) && vfk_layer_fits(c);
 }
-// Whole schedules, which otherwise take one launch per layer on id ranges (the chain): the same line,
-// and already where the tiles of 64 ids outnumber the compute units if the network is deep enough
-// for the smaller share of ids that are scored to outweigh the second launch: three hidden layers of 512,
-// or two behind a folded first layer.  The lists' tiles are then of 64 as well (layer_tile).  20 layers
-// of 4096 ids of which 40 % are valid, chain / lists, 5 and 8 problems: 256-512-512-1 596 / 557 and 596 /
-// 561 us, 256-512-512-512-1 761 / 642 and 763 / 646, 64-512-512-512-1 713 / 613 and 717 / 639; but 256-512-1
-// (6 problems) 407 / 510, 64-512-512-1 549 / 557 and 554 / 573.  With every id valid, 5 and 8 problems,
-// 256-512-512-1: 744 / 742 and 737 / 736.
+// Whole schedules, which otherwise take two launches per layer on id ranges as well (scorer, k_commit_next; where
+// k_chain takes them their tiles do not outnumber the compute units): the same line, and already where the tiles of
+// 64 ids outnumber the compute units if the network is deep enough for the smaller share of ids that are scored
+// to outweigh the longer steps between two layers: three hidden layers of 512, or two behind a folded first
+// layer.  The lists' tiles are then of 64 as well (layer_tile).  20 layers of 4096 ids of which 40 % are valid,
+// ranges / lists, 5 and 8 problems: 256-512-512-1 553 / 497 and 554 / 503 us, 64-512-512-512-1 668 / 583 and 673 / 638,
+// 256-512-512-512-1 718 / 618 and (the line is late there) 725 / 766; but 256-512-1 364 / 427 and 364 / 429, 64-512-1
+// 333 / 422 and 334 / 424; 64-512-512-1 503 / 487 and 503 / 493 (early).
 bool vfk_greedy_layers_pay(const vf_ctx *c) {
   if (vfk_layer_pays(c)) return true;
   return vfk_can_fuse_step(c) && c->pm.fast_rt == 2 && c->model.n_layers >= (c->model.dims[0] > 64 ? 3 : 4) &&

@@ -722,9 +722,9 @@ static whole_kernel whole_launch_shape(const vf_ctx *c, vf_fast_dev *fd, int *ks
 // this is wanted).  With fewer problems, from 24 on, a fixed team per problem, as large as the compute
 // units and the tiles of a decision allow, at most 16.  That is for decisions of few candidates: where
 // all problems have more tiles than there are compute units the lists go first (vfk_layer_pays).
-// The line at 24 is older than the present launches per layer, which are faster there (256-512-512-1,
-// 20 layers, teams against launches per layer: 24 problems of 768 ids 0.89 / 0.61 ms, 42: 1.25 / 0.62,
-// 64 of 512 ids 1.21 / 0.64, 128 of 256 ids 1.20 / 0.64).
+// The line at 24 is older than the other ways of today, which are faster there (256-512-512-1, 20 layers, teams against
+// launches per layer: 24 problems of 768 ids 0.88 / 0.51 ms, 42: 1.25 / 0.51, 64 of 512 ids 1.21 / 0.51, 128 of 256 ids
+// 1.21 / 0.55; against k_chain: 24 of 512 ids 0.74 / 0.29, 32: 0.83 / 0.30, 64 of 256 ids 0.81 / 0.30).
 int vfk_whole_team(const vf_ctx *c) {
   if (!vfk_can_fuse_step(c)) return 0;
   {
@@ -757,7 +757,7 @@ int vfk_whole_team(const vf_ctx *c) {
   // (a mailbox names a problem in 23 bits, a layer's tiles are counted in 16)
   if (c->B >= (1 << 23) || (c->M + 63) / 64 > 65535) return 0;
   if (c->B > ncu / 2) return 1;
-  if (c->B < 24) return 0;  // a handful of problems: a launch per layer (16 of 768 ids: 0.44 against 0.74 ms)
+  if (c->B < 24) return 0;  // a handful of problems: k_chain, or launches per layer (16 of 768 ids: 0.29 against 0.74 ms)
   int maxw = 0;
   for (int l = 0; l < c->model.n_layers; ++l) if (c->model.dims[l] > maxw) maxw = c->model.dims[l];
   const int NC = maxw > 512 ? 64 : 128;

@@ -152,7 +152,7 @@ SAMPLED_LAYERS_100 = [0, 1, 2, 24, 25, 26, 49, 50, 51, 74, 75, 76, 97, 98, 99]
 
 
 def test_mobilenet_shaped_all_stages(vf, ovf):
-    """The 100-stage pipeline at its real candidate count, one pipeline (two launches per layer);
+    """The 100-stage pipeline at its real candidate count, one pipeline (one launch);
     the checker looks at every one of the 100 decisions."""
     pipe, sp = I.mobilenetv2_shaped(), I.mobilenetv2_space()
     dims = [256, 512, 512, 1]
@@ -292,8 +292,8 @@ def test_profile_counts_are_the_candidates_of_algorithm_1(vf, ovf):
 
 @pytest.mark.parametrize("B", [1, 3])
 def test_chained_layers_equal_layer_by_layer(vf, ovf, B):
-    """With a few problems vf_greedy_schedule launches once per layer and every launch also takes
-    the decision of the layer before it; vf_argmin_step scores and commits in two launches.  Both
+    """With a few problems vf_greedy_schedule takes one launch, whose workgroups exchange the minima
+    of a layer and go on to the next; vf_argmin_step scores and commits in two launches.  Both
     must give bit-identical tables: plain, with exploration noise, in two pieces from a committed
     prefix, and when one problem's schedule ends early; problem 0 is followed by the checker."""
     pipes = I.resnet18_batch(B, seed=9)
