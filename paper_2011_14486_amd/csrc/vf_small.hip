@@ -1052,9 +1052,8 @@ int vfk_pack_small(vf_ctx *c, const float *wdev) {
   float *bias = reinterpret_cast<float *>(reinterpret_cast<uint4 *>(buf) + nw);
   c->pm.small_words = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(buf) + words_at);
   c->pm.small_nwords = nwords;
-  hipLaunchKernelGGL(k_pad_f32, dim3((2 * nwords + 255) / 256), dim3(256), 0, c->stream, wdev, 0, 2 * nwords,
-                     reinterpret_cast<float *>(c->pm.small_words));
-  VF_HIP(c, hipGetLastError());
+  // (cleared as the padding of what lies in front of them)
+  const int tail = (int)(words_at / 4 + 2 * nwords - nw * 4 - nbias);
   size_t off = 0;
   for (int l = 0; l < L; ++l) {
     const int K = m.dims[l], N = m.dims[l + 1];
@@ -1068,11 +1067,11 @@ int vfk_pack_small(vf_ctx *c, const float *wdev) {
       hipLaunchKernelGGL(k_pack_small_f32, dim3((n + 255) / 256), dim3(256), 0, c->stream, W, N, K, d.nt[l], d.kst[l],
                          reinterpret_cast<float *>(reinterpret_cast<uint4 *>(buf) + d.woff[l]));
     else
-      hipLaunchKernelGGL(k_pad_f32, dim3((d.kst[l] * 16 + 255) / 256), dim3(256), 0, c->stream, W, K, d.kst[l] * 16,
+      hipLaunchKernelGGL(k_pad_f32, dim3((d.kst[l] * 16 + tail + 255) / 256), dim3(256), 0, c->stream, W, K, d.kst[l] * 16 + tail,
                          bias + d.wl_off);
     VF_HIP(c, hipGetLastError());
-    hipLaunchKernelGGL(k_pad_f32, dim3((d.nt[l] * unit + 255) / 256), dim3(256), 0, c->stream, b, N, d.nt[l] * unit,
-                       bias + d.boff[l]);
+    const int nb = d.nt[l] * unit + (bf16 && l == L - 1 ? tail : 0);
+    hipLaunchKernelGGL(k_pad_f32, dim3((nb + 255) / 256), dim3(256), 0, c->stream, b, N, nb, bias + d.boff[l]);
     VF_HIP(c, hipGetLastError());
     off += (size_t)K * N + N;
   }
